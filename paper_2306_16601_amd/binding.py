@@ -1,4 +1,5 @@
-"""ctypes binding of libspmm4x1.so: argument marshalling only.
+"""Binding of libspmm4x1.so: argument marshalling only (ctypes; the two launch calls through C,
+csrc/native_call.c).
 
 Every function has the name and the argument order of its C declaration in
 include/spmm.h; nothing of the method is computed here.  Host buffers are numpy
@@ -9,6 +10,7 @@ missing shared object is an error, there is no fallback path.
 from __future__ import annotations
 
 import ctypes
+import importlib.util
 import os
 from typing import Optional, Tuple
 
@@ -16,6 +18,7 @@ import numpy as np
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(HERE, "libspmm4x1.so")
+NATIVE_PATH = os.path.join(HERE, "_native_call.so")      # spmm_run / spmm_run_tiled, marshalled in C (csrc/native_call.c)
 
 SPMM_OK, SPMM_E_ARG, SPMM_E_UNSUPPORTED, SPMM_E_ALLOC, SPMM_E_DEVICE = range(5)
 SPMM_BLOCK_N4K1, SPMM_BLOCK_N1K4 = 0, 1
@@ -110,6 +113,7 @@ def lib() -> ctypes.CDLL:
         L.spmm_destroy.argtypes = [vp]
         L.spmm_status_string.restype = ctypes.c_char_p
         L.spmm_status_string.argtypes = [ci]
+        _load_native().bind(*[ctypes.cast(f, vp).value for f in (L.spmm_run, L.spmm_run_tiled, L.spmm_info)])
         _lib = L
     return _lib
 
@@ -306,10 +310,37 @@ def spmm_run_status(handle: int, X_dev, M: int, ldx: int, ep: Optional[spmm_epil
                               None if ep is None else ctypes.byref(ep), _dev_ptr(out_dev), int(ldo), st))
 
 
-def spmm_run(handle: int, X_dev, M: int, ldx: int, ep: spmm_epilogue_t, out_dev, ldo: int, stream=None) -> None:
-    """out = postops(W . X), asynchronous on `stream` (a raw hipStream_t value, None = default stream)."""
-    _check_extents(handle, X_dev, M, ldx, ep, out_dev, ldo, 0)
-    _check(spmm_run_status(handle, X_dev, M, ldx, ep, out_dev, ldo, stream), "spmm_run")
+_native = None
+
+
+def _load_native():
+    """The C entry points of one launch; raises if they have not been built."""
+    global _native
+    if _native is None:
+        if not os.path.exists(NATIVE_PATH):
+            raise ImportError(
+                "%s is missing: build it first (python -c 'import __graft_entry__ as g; g.build()')" % NATIVE_PATH)
+        spec = importlib.util.spec_from_file_location(__package__ + "._native_call", NATIVE_PATH)
+        m = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(m)
+        m.hooks(lib, _check_extents, _check)
+        _native = m
+    return _native
+
+
+if os.path.exists(NATIVE_PATH):
+    # a launch of a short batch is a few microseconds: its arguments are marshalled in C, the library is
+    # loaded by the first call
+    spmm_run, spmm_run_tiled = _load_native().spmm_run, _load_native().spmm_run_tiled
+else:
+    def spmm_run(handle: int, X_dev, M: int, ldx: int, ep: spmm_epilogue_t, out_dev, ldo: int, stream=None) -> None:
+        """out = postops(W . X), asynchronous on `stream` (a raw hipStream_t value, None = default stream)."""
+        _load_native().spmm_run(handle, X_dev, M, ldx, ep, out_dev, ldo, stream)
+
+    def spmm_run_tiled(handle: int, X_dev, M: int, ldx: int, ep: spmm_epilogue_t, out_dev, ldo: int, tiled: int,
+                       stream=None) -> None:
+        """spmm_run with X (SPMM_TILED_X) and / or a 1-byte output (SPMM_TILED_OUT) in token-tile-major order."""
+        _load_native().spmm_run_tiled(handle, X_dev, M, ldx, ep, out_dev, ldo, tiled, stream)
 
 
 def tile_major(X: np.ndarray) -> np.ndarray:
@@ -326,15 +357,6 @@ def from_tile_major(T: np.ndarray, M: int) -> np.ndarray:
     """Inverse of tile_major: [tiles, R, 32] -> row-major [R, M]."""
     tiles, R, w = T.shape
     return np.ascontiguousarray(T.transpose(1, 0, 2).reshape(R, tiles * w)[:, :M])
-
-
-def spmm_run_tiled(handle: int, X_dev, M: int, ldx: int, ep: spmm_epilogue_t, out_dev, ldo: int, tiled: int,
-                   stream=None) -> None:
-    """spmm_run with X (SPMM_TILED_X) and / or a 1-byte output (SPMM_TILED_OUT) in token-tile-major order."""
-    st = None if stream is None else int(stream)
-    _check_extents(handle, X_dev, M, ldx, ep, out_dev, ldo, int(tiled))
-    _check(int(lib().spmm_run_tiled(handle, _dev_ptr(X_dev), int(M), int(ldx), ctypes.byref(ep), _dev_ptr(out_dev),
-                                    int(ldo), int(tiled), st)), "spmm_run_tiled")
 
 
 def spmm_run_tiled_bound(handle: int, X_dev, M: int, ldx: int, ep: spmm_epilogue_t, out_dev, ldo: int, tiled: int,

@@ -8,12 +8,15 @@ from __future__ import annotations
 import os
 import shutil
 import subprocess
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libspmm4x1.so")
+NATIVE = os.path.join(HERE, "_native_call.so")      # CPython entry points of the launch calls (plain C, no GPU code)
+NATIVE_SOURCE = os.path.join(CSRC, "native_call.c")
 OBJDIR = os.path.join(HERE, "_build")
 
 HOST_SOURCES = ["api.cpp", "pack.cpp", "spmm_plan.hip", "spmm_peak.hip"]
@@ -67,16 +70,27 @@ def _run(cmd, verbose):
     r = subprocess.run(cmd, capture_output=True, text=True)
     err = "\n".join(l for l in r.stderr.splitlines() if "packed-fp32-ops" not in l)
     if r.returncode != 0:
-        raise RuntimeError("hipcc failed: " + " ".join(cmd) + "\n" + err)
+        raise RuntimeError("compiler failed: " + " ".join(cmd) + "\n" + err)
     if verbose and err.strip():
         print(err)
 
 
+def build_native(verbose: bool = False) -> str:
+    """Compile the CPython module that marshals the launch calls."""
+    tmp = NATIVE + ".tmp.%d" % os.getpid()
+    _run([os.environ.get("CC", "gcc"), "-O2", "-std=gnu11", "-shared", "-fPIC", "-Wall",
+          "-I", sysconfig.get_paths()["include"], "-I", os.path.join(ROOT, "include"), NATIVE_SOURCE, "-o", tmp], verbose)
+    os.replace(tmp, NATIVE)
+    return NATIVE
+
+
 def build(force: bool = True, verbose: bool = False, jobs: int | None = None) -> str:
     """Compile every source with hipcc (cross-compiles without a GPU) and link the library."""
-    deps = sources() + HEADERS
-    if not force and os.path.exists(LIB) and all(os.path.getmtime(LIB) >= os.path.getmtime(d) for d in deps):
+    deps = sources() + HEADERS + [NATIVE_SOURCE]
+    if not force and all(os.path.exists(b) and all(os.path.getmtime(b) >= os.path.getmtime(d) for d in deps)
+                         for b in (LIB, NATIVE)):
         return LIB
+    build_native(verbose)
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     if jobs is None:
         jobs = max(1, min(8, os.cpu_count() or 1))

@@ -384,3 +384,27 @@ def test_binding_refuses_buffers_smaller_than_the_call_touches():
             sp.spmm_run(h, X, 128, 128, ep, big[65:], 128)
     finally:
         sp.spmm_destroy(h)
+
+
+@pytest.mark.parametrize("args, kw, error", [
+    ((), {}, TypeError),                                                                   # nothing given
+    (("h", 16, 4, 4, "ep", 16), {}, TypeError),                                            # ldo missing
+    (("h", 16, 4, 4, "ep", 16, 4, None, None), {}, TypeError),                             # one too many
+    (("h", 16, 4, 4, "ep", 16, 4), {"ldo": 4}, TypeError),                                 # given twice
+    (("h", 16, 4, 4, "ep", 16, 4), {"tiled": 1}, TypeError),                               # not an argument of spmm_run
+    (("h", 16, 4, 4, 7, 16, 4), {}, TypeError),                                            # ep is no epilogue
+    (("h", 16, "4x", 4, "ep", 16, 4), {}, ValueError),
+    (("h", 16, 4, 4, "ep", 16, 4), {"stream": None}, sp.SpmmError),                        # host-only handle: the library refuses
+    (("h",), dict(X_dev=16, M=4, ldx=4, ep="ep", out_dev=16, ldo=4, stream=0), sp.SpmmError),
+    (("h", 16, 4.0, np.int64(4), None, 16, 4), {}, sp.SpmmError),                          # other number types; no epilogue
+    ((None, 16, 4, 4, "ep", 16, 4), {}, sp.SpmmError),
+])
+def test_arguments_of_the_launch_call(args, kw, error):
+    hh = sp.spmm_pack_host(np.ones((4, 4), dtype=np.int8))
+    put = {"h": hh, "ep": sp.make_epilogue(None, 1.0, 0, None, "none", "s32")}
+    sub = lambda v: put.get(v, v) if isinstance(v, str) else v      # noqa: E731
+    try:
+        with pytest.raises(error):
+            sp.spmm_run(*[sub(v) for v in args], **{k: sub(v) for k, v in kw.items()})
+    finally:
+        sp.spmm_destroy(hh)
