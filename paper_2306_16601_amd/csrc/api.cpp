@@ -55,11 +55,11 @@ void free_device(spmm_handle* h)
 
 bool aligned(const void* p, size_t a) { return (reinterpret_cast<uintptr_t>(p) % a) == 0; }
 
-spmm::Plan plan_for(const spmm_handle* h, int64_t M, bool aligned = true, int out_bytes = 1)
+spmm::Plan plan_for(const spmm_handle* h, int64_t M, int out_bytes, bool x_fast = true, bool out_fast = true)
 {
     const spmm::WeightDims w{h->ntiles, h->nseg, (int)h->bsr.K, h->nsteps, h->max_steps_per_segment,
                              h->max_steps_per_tile};
-    return spmm::make_plan(M, w, h->num_cus, h->force_tm, h->force_r, aligned, out_bytes);
+    return spmm::make_plan(M, w, h->num_cus, h->force_tm, h->force_r, out_bytes, x_fast, out_fast);
 }
 
 }  // namespace
@@ -194,7 +194,7 @@ spmm_status_t spmm_plan(const spmm_handle_t* h, int64_t M, spmm_out_t out_type, 
                         int32_t* rows_per_workgroup, int64_t* workgroups)
 {
     if (!h || M <= 0) return SPMM_E_ARG;
-    const spmm::Plan p = plan_for(h, M, true, (out_type == SPMM_OUT_S32 || out_type == SPMM_OUT_F32) ? 4 : 1);
+    const spmm::Plan p = plan_for(h, M, (out_type == SPMM_OUT_S32 || out_type == SPMM_OUT_F32) ? 4 : 1);
     if (token_tile) *token_tile = p.token_tile;
     if (rows_per_workgroup) *rows_per_workgroup = p.waves * p.row_tiles_per_wave * spmm::TILE_ROWS;
     if (workgroups) *workgroups = p.workgroups;
@@ -278,8 +278,9 @@ static spmm_status_t run_common(const spmm_handle_t* h, const uint8_t* X_dev, in
     a.kc = h->kc; a.nseg = h->nseg; a.ntiles = h->ntiles;
     a.corr_mul = 128 - ep->x_zero_point;
     a.x_scale = ep->x_scale;
-    // fast paths use 16-byte accesses and 32-bit offsets
-    a.x_vec_ok = aligned(X_dev, 16) && (ldx % 16 == 0) && (h->bsr.K * ldx < ((int64_t)1 << 31));
+    // fast paths use 16-byte accesses (at any address) and 32-bit offsets
+    a.x_last16 = (h->bsr.K - 1) * ldx + M - 16;
+    a.x_fast = a.x_last16 >= 0 && ldx < ((int64_t)1 << 31) / spmm::SEGMENT_ROWS;
     if (x_tiled) {
         // token-tile-major activations: [ceil(M / 32)][K][32] bytes, 16-byte aligned
         if (!aligned(X_dev, 16)) return SPMM_E_ARG;
@@ -287,10 +288,12 @@ static spmm_status_t run_common(const spmm_handle_t* h, const uint8_t* X_dev, in
         if (tiles * h->bsr.K * SPMM_X_TILE >= ((int64_t)1 << 31)) return SPMM_E_UNSUPPORTED;
         a.ldx = SPMM_X_TILE;
         a.x_tile_stride = (int)(h->bsr.K * SPMM_X_TILE);
-        a.x_vec_ok = 1;
+        a.x_fast = 1;
+        a.x_last16 = tiles * h->bsr.K * SPMM_X_TILE - 16;
     }
     const int64_t esz = quant ? 1 : 4;
-    a.out_vec_ok = aligned(out_dev, 16) && ((ldo * esz) % 16 == 0) && (h->bsr.N * ldo * esz < ((int64_t)1 << 31));
+    a.out_vec_ok = h->bsr.N * ldo * esz < ((int64_t)1 << 31);
+    a.out_aligned = a.out_vec_ok && aligned(out_dev, 16) && (ldo * esz) % 16 == 0;
     if (out_tiled) {
         // token-tile-major 1-byte output: [ceil(M / 32)][N][32] bytes, 16-byte aligned
         if (!quant) return SPMM_E_UNSUPPORTED;
@@ -299,13 +302,13 @@ static spmm_status_t run_common(const spmm_handle_t* h, const uint8_t* X_dev, in
         if (tiles * h->bsr.N * SPMM_X_TILE >= ((int64_t)1 << 31)) return SPMM_E_UNSUPPORTED;
         a.ldo = SPMM_X_TILE;
         a.out_tile_stride = (int)(h->bsr.N * SPMM_X_TILE);
-        a.out_vec_ok = 1;
+        a.out_vec_ok = a.out_aligned = 1;
     }
     if (ep->sum) {
         a.sum = ep->sum;
         a.ld_sum = ep->ld_sum;
-        a.out_vec_ok = a.out_vec_ok && aligned(ep->sum, 16) && (ep->ld_sum % 4 == 0) &&
-                       (h->bsr.N * ep->ld_sum * 4 < ((int64_t)1 << 31));
+        a.out_vec_ok = a.out_vec_ok && (h->bsr.N * ep->ld_sum * 4 < ((int64_t)1 << 31));
+        a.out_aligned = a.out_aligned && a.out_vec_ok;
     }
 
     if (a.out_vec_ok) {
@@ -316,7 +319,7 @@ static spmm_status_t run_common(const spmm_handle_t* h, const uint8_t* X_dev, in
         a.out_bytes = (uint32_t)extent;
     }
 
-    const spmm::Plan p = plan_for(h, M, a.x_vec_ok && a.out_vec_ok, (int)esz);
+    const spmm::Plan p = plan_for(h, M, (int)esz, a.x_fast, a.out_vec_ok);
     const int rc = spmm::launch_spmm(p, a, ot, (gelu ? SPMM_POST_GELU : SPMM_POST_NONE) | (ep->sum ? spmm::POST_SUM_BIT : 0),
                                      hip_stream);
     return rc == 0 ? SPMM_OK : SPMM_E_DEVICE;
@@ -358,7 +361,7 @@ spmm_status_t spmm_kernel_variant_tiled(const spmm_handle_t* h, int64_t M, spmm_
     if (out_type < SPMM_OUT_S32 || out_type > SPMM_OUT_U8) return SPMM_E_ARG;
     if (postop != SPMM_POST_NONE && postop != SPMM_POST_GELU && postop != SPMM_POST_TABLE) return SPMM_E_ARG;
     if (postop == SPMM_POST_TABLE) postop = SPMM_POST_GELU;   // same kernels
-    const spmm::Plan p = plan_for(h, M, true, (out_type == SPMM_OUT_S32 || out_type == SPMM_OUT_F32) ? 4 : 1);
+    const spmm::Plan p = plan_for(h, M, (out_type == SPMM_OUT_S32 || out_type == SPMM_OUT_F32) ? 4 : 1);
     const int post = (out_type == SPMM_OUT_S32) ? 0 : (int)postop;   // S32 output ignores the post-operator
     if (p.stream)
         std::snprintf(buf, (size_t)buflen, "void spmm::spmm_rowtile_mfma_stream<%d, %d, %d, %d>(spmm::KernelArgs)",

@@ -85,9 +85,10 @@ struct KernelArgs {
     int xcd_map;         // simple / short-batch kernels: how a workgroup id decodes, see decode_workgroup()
     int corr_mul;        // 128 - x_zero_point: the activations are multiplied as (x - 128)
     float x_scale, inv_out, inv_mid, out_zp_f;
-    int x_vec_ok;        // X base 16-byte aligned, ldx % 16 == 0 and K * ldx < 2^31 (tile-major: the whole X < 2^31 bytes)
-    int out_vec_ok;      // out base 16-byte aligned, row pitch a multiple of 16 bytes, whole output < 2^31 bytes
-                         // (and, with Sum, the same for the second operand)
+    int64_t x_last16;    // offset of the last 16 bytes of X: no 16-byte read goes beyond them (negative: X has fewer)
+    int x_fast;          // the rows of one segment lie within 2^31 bytes, and X has 16: 32-bit offsets
+    int out_vec_ok;      // whole output < 2^31 bytes (and, with Sum, the second operand too): 32-bit offsets
+    int out_aligned;     // out_vec_ok, out base 16-byte aligned and row pitch a multiple of 16 bytes
     int out_tile_stride; // 0: out row-major [N][ldo]; else 1-byte out token-tile-major [ceil(M/32)][N][32], ldo = 32 and this = 32 N
     int x_tile_stride;   // 0: X row-major [K][ldx]; else X token-tile-major [ceil(M/32)][K][32], ldx = 32 and this = 32 K
     uint32_t out_bytes;  // with out_vec_ok: bytes from out to the end of the last element the call may write (< 2^31)
@@ -119,11 +120,12 @@ struct WeightDims {
     int max_steps_per_segment, max_steps_per_tile;
 };
 bool plan_supported(int token_tile, int variant);
-// aligned: X and out take the 16-byte paths (base and row pitch aligned); if not, the automatic choice
-// avoids the 16-wave pipelined kernels, whose general paths are the slow bytewise ones
 // out_bytes: size of an output element (the plan gives 4-byte outputs workgroups with loader waves)
-Plan make_plan(int64_t M, const WeightDims& w, int num_cus, int force_tm, int variant, bool aligned = true,
-               int out_bytes = 1);
+// x_fast: see KernelArgs; an X without it takes the simple kernel, whatever was forced
+// out_fast: 32-bit offsets suffice for out; if not, the automatic choice avoids the 16-wave pipelined
+// kernels, whose general store path is slow for want of registers
+Plan make_plan(int64_t M, const WeightDims& w, int num_cus, int force_tm, int variant, int out_bytes = 1,
+               bool x_fast = true, bool out_fast = true);
 // Launches the SpMM kernel; returns a hipError_t value as int (0 = success).
 // postop: SPMM_POST_* value, plus POST_SUM_BIT when a.sum is to be added
 constexpr int POST_SUM_BIT = 4;   // (a bit no SPMM_POST_* value uses)

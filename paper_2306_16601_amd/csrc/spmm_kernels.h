@@ -55,6 +55,14 @@ typedef int v2i __attribute__((ext_vector_type(2)));
 typedef float v4f __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) v2i* lds_v2i_ptr;
 
+// The same vectors at any address: global memory takes 16-byte (and dword) accesses at byte alignment on
+// this hardware (LLVM's unaligned-access-mode, on for the HSA target), so an unpadded row pitch costs the
+// cache lines that a piece straddles and nothing else.
+struct __attribute__((packed)) v4i_any { v4i v; };
+struct __attribute__((packed)) v4f_any { v4f v; };
+struct __attribute__((packed)) u32_any { uint32_t v; };
+__device__ __forceinline__ v4i load16_any(const void* p) { return ((const v4i_any*)p)->v; }
+
 constexpr int FLIP = (int)0x80808080;   // x ^ 0x80 == x - 128 as a signed byte
 
 // GELU in its erf form, y * Phi(y) = 0.5 * y * erfc(-y / sqrt(2)), in binary32, branch-free.
@@ -140,10 +148,8 @@ __device__ __forceinline__ uint32_t quantise(const KernelArgs& a, const float y,
 
 // Generic post-operators + store for 4 consecutive tokens m0..m0+3 of output row n: any
 // alignment, any tail (the slow path of every kernel).
-// WIDE: 1-byte outputs of an unaligned matrix are written in the widest pieces the address
-// allows (dword, two halves, bytes) instead of bytes, and aligned 4-byte outputs go out at agent
-// scope (see out_resource); costs registers the 16-wave pipelined kernels do not have (the
-// host does not pick those for unaligned operands, and their full tiles take finish_tile_fast).
+// WIDE: 4-byte outputs whose 16-byte pieces are aligned go out at agent scope (see out_resource);
+// costs registers the 16-wave pipelined kernels do not have (their full tiles take finish_tile_fast).
 // OT: layout of a 1-byte output: 1 = token-tile-major, 0 = row-major, -1 = whichever the arguments say
 template <int OUT, int POST, bool WIDE = false, int OT = -1, typename Lut>
 __device__ __forceinline__ void finish4(const KernelArgs& a, const v4i acc, const float s, const float b,
@@ -152,9 +158,10 @@ __device__ __forceinline__ void finish4(const KernelArgs& a, const v4i acc, cons
     const int valid = a.M - m0;   // > 0 guaranteed by caller
     if constexpr (OUT == SPMM_OUT_S32) {
         int32_t* o = (int32_t*)a.out + (int64_t)n * a.ldo + m0;
-        if (a.out_vec_ok && valid >= 4) {
-            if constexpr (WIDE) store16_out<SCOPE_AGENT>(out_resource(a), 4u * ((uint32_t)n * (uint32_t)a.ldo + (uint32_t)m0), acc);
-            else *(v4i*)o = acc;
+        if (WIDE && a.out_aligned && valid >= 4) {
+            store16_out<SCOPE_AGENT>(out_resource(a), 4u * ((uint32_t)n * (uint32_t)a.ldo + (uint32_t)m0), acc);
+        } else if (valid >= 4) {
+            ((v4i_any*)o)->v = acc;
         } else {
             for (int r = 0; r < 4; ++r)
                 if (r < valid) o[r] = acc[r];
@@ -175,10 +182,11 @@ __device__ __forceinline__ void finish4(const KernelArgs& a, const v4i acc, cons
         }
         if constexpr (OUT == SPMM_OUT_F32) {
             float* o = (float*)a.out + (int64_t)n * a.ldo + m0;
-            if (a.out_vec_ok && valid >= 4) {
-                v4f v = {y[0], y[1], y[2], y[3]};
-                if constexpr (WIDE) store16_out<SCOPE_AGENT>(out_resource(a), 4u * ((uint32_t)n * (uint32_t)a.ldo + (uint32_t)m0), v);
-                else *(v4f*)o = v;
+            const v4f v = {y[0], y[1], y[2], y[3]};
+            if (WIDE && a.out_aligned && valid >= 4) {
+                store16_out<SCOPE_AGENT>(out_resource(a), 4u * ((uint32_t)n * (uint32_t)a.ldo + (uint32_t)m0), v);
+            } else if (valid >= 4) {
+                ((v4f_any*)o)->v = v;
             } else {
                 for (int r = 0; r < 4; ++r)
                     if (r < valid) o[r] = y[r];
@@ -192,11 +200,8 @@ __device__ __forceinline__ void finish4(const KernelArgs& a, const v4i acc, cons
             const bool ot = (OT == 1) || (OT == -1 && a.out_tile_stride != 0);
             uint8_t* o = (uint8_t*)a.out + (int64_t)n * a.ldo +
                          (ot ? (int64_t)(m0 >> 5) * a.out_tile_stride + (m0 & 31) : (int64_t)m0);
-            if (valid >= 4 && (a.out_vec_ok || (WIDE && ((uintptr_t)o & 3) == 0))) {
-                *(uint32_t*)o = q[0] | (q[1] << 8) | (q[2] << 16) | (q[3] << 24);
-            } else if (WIDE && valid >= 4 && ((uintptr_t)o & 1) == 0) {
-                *(uint16_t*)o = (uint16_t)(q[0] | (q[1] << 8));
-                *(uint16_t*)(o + 2) = (uint16_t)(q[2] | (q[3] << 8));
+            if (valid >= 4) {
+                ((u32_any*)o)->v = q[0] | (q[1] << 8) | (q[2] << 16) | (q[3] << 24);
             } else {
                 for (int r = 0; r < 4; ++r)
                     if (r < valid) o[r] = (uint8_t)q[r];
@@ -210,18 +215,6 @@ __device__ __forceinline__ void finish4(const KernelArgs& a, const v4i acc, cons
 // wait-count bookkeeping that no global load is outstanding, so the next phase's multiply
 // loop does not stall on the prefetches issued just before it.
 __device__ __forceinline__ void wait_global_loads() { __builtin_amdgcn_s_waitcnt(0x0F70); }
-
-// Byte mask of a 16-byte piece of which the first nv bytes are wanted (nv <= 0: none).
-__device__ __forceinline__ v4i piece_mask(const int nv)
-{
-    v4i m;
-#pragma unroll
-    for (int w = 0; w < 4; ++w) {
-        const int keep = nv - 4 * w;
-        m[w] = keep >= 4 ? -1 : (keep <= 0 ? 0 : (int)((1u << (8 * keep)) - 1u));
-    }
-    return m;
-}
 
 // Byte offset of token column `col` inside an activation row.  Row-major X: the column itself (rows
 // are ldx apart).  Token-tile-major X, [ceil(M / 32)][K][32] (the re-structured input of Section 3.2:
@@ -241,48 +234,58 @@ __device__ __forceinline__ int xcol(const KernelArgs& a, const int col)
     else return a.x_tile_stride ? (col >> 5) * a.x_tile_stride + (col & 31) : col;
 }
 
-// 16 bytes of activation row `krow` starting at token `col`; tokens >= M read as 0.
-// The general path (odd leading dimension or base, or the last, partial piece of a row) reads the
-// aligned dwords that hold the wanted bytes and shifts them into place: every dword read holds
-// at least one wanted byte, so nothing outside the pages of X is touched, and a piece costs at
-// most five loads (byte loads of 64 different rows cost a cache-line look-up each: a 13-token
-// tail made the whole launch three times longer).
+// 16-byte pieces of one segment's activation rows in the token tile that is cut by the end of the rows, at
+// any alignment.  Tokens from M on are never stored, so what their bytes hold does not matter: a piece
+// beyond the end reads the start of its row, a piece cut by it reads on into the next row.  Only where
+// those 16 bytes would leave the matrix (its last row; rows shorter than a piece) is the read moved back
+// to the last 16 bytes, and the loaded piece then shifted into place.  Segments with such rows are known
+// beforehand (`inside` is uniform): everywhere else nothing touches the loaded registers before they are
+// used, and the loads stay in flight.  Offsets are 32 bits from a uniform base (KernelArgs::x_fast); the
+// base lies 16 bytes before the segment so that a read moved back into the previous one is not negative.
 template <int XT = -1>
-__device__ __forceinline__ v4i load_x16(const KernelArgs& a, const int krow, const int col)
-{
-    const uint8_t* src = a.X + (int64_t)krow * a.ldx + xcol<XT>(a, col);
-    const int nbytes = min(16, a.M - col);
-    if (a.x_vec_ok && nbytes == 16) return *(const v4i*)src;
-    v4i v = {0, 0, 0, 0};
-    if (nbytes <= 0) return v;
-    const uintptr_t p = (uintptr_t)src;
-    const uint32_t sh = (uint32_t)(p & 3);
-    const uint32_t* q = (const uint32_t*)(p - sh);
-    const int span = (int)sh + nbytes;            // bytes from q[0] on that are wanted
-    uint32_t d[5];
-#pragma unroll
-    for (int i = 0; i < 5; ++i) d[i] = (4 * i < span) ? q[i] : 0u;
-#pragma unroll
-    for (int w = 0; w < 4; ++w) {
-        const uint32_t x = __builtin_amdgcn_alignbyte(d[w + 1], d[w], sh);
-        const int keep = nbytes - 4 * w;          // wanted bytes of this dword
-        const uint32_t mask = keep >= 4 ? 0xffffffffu : (keep <= 0 ? 0u : ((1u << (8 * keep)) - 1u));
-        v[w] = (int)(x & mask);
+struct RaggedPieces {
+    const KernelArgs& a;
+    const uint8_t* base;
+    uint32_t bias, limit;
+    bool inside;
+    __device__ __forceinline__ RaggedPieces(const KernelArgs& args, const int k0, const int last) : a(args)
+    {
+        bias = k0 > 0 ? 16 : 0;
+        base = a.X + ((int64_t)k0 * a.ldx - bias);
+        const int64_t left = a.x_last16 - ((int64_t)k0 * a.ldx - bias);      // >= 0
+        limit = left < 0x7fffffff ? (uint32_t)left : 0x7fffffffu;
+        inside = a.x_tile_stride != 0 || bias + (uint32_t)last * (uint32_t)a.ldx + (uint32_t)((a.M - 1) & ~15) <= limit;
     }
-    return v;
-}
-
-// The same, byte by byte: few registers (the 16-wave pipelined kernels have 128 and none to
-// spare for a path they take only with unaligned activations), slow.
-template <int XT = -1>
-__device__ __forceinline__ v4i load_x16_bytewise(const KernelArgs& a, const int krow, const int col)
+    __device__ __forceinline__ uint32_t offset(const int row, const int col) const
+    {
+        return bias + (uint32_t)row * (uint32_t)a.ldx + (uint32_t)xcol<XT>(a, col < a.M ? col : 0);
+    }
+    __device__ __forceinline__ v4i load(const int row, const int col) const
+    {
+        return load16_any(base + min(offset(row, col), limit));
+    }
+    __device__ __forceinline__ v4i shifted(v4i v, const int row, const int col) const
+    {
+        const uint32_t off = offset(row, col), back = off - min(off, limit);      // 0 .. 15
+        if (back & 8) v = (v4i){v[2], v[3], 0, 0};
+        if (back & 4) v = (v4i){v[1], v[2], v[3], 0};
+        v4i r;
+#pragma unroll
+        for (int w = 0; w < 4; ++w)
+            r[w] = (int)__builtin_amdgcn_alignbyte(w < 3 ? (uint32_t)v[w + 1] : 0u, (uint32_t)v[w], back & 3);
+        return r;
+    }
+};
+// The same for a row-major matrix whose segments exceed 32-bit offsets, or that holds less than 16 bytes
+// (only the simple kernel takes those, see make_plan): pieces that would leave the matrix byte by byte.
+__device__ __forceinline__ v4i load_x16_far(const KernelArgs& a, const int row, const int col)
 {
-    const uint8_t* src = a.X + (int64_t)krow * a.ldx + xcol<XT>(a, col);
-    if (a.x_vec_ok && col + 16 <= a.M) return *(const v4i*)src;
+    const int64_t off = (int64_t)row * a.ldx + (col < a.M ? col : 0);
+    if (off <= a.x_last16) return load16_any(a.X + off);
     v4i v = {0, 0, 0, 0};
 #pragma unroll
     for (int j = 0; j < 16; ++j)
-        if (col + j < a.M) v[j >> 2] |= (int)((uint32_t)src[j] << (8 * (j & 3)));
+        if (col + j < a.M) v[j >> 2] |= (int)((uint32_t)a.X[off + j] << (8 * (j & 3)));
     return v;
 }
 
@@ -354,8 +357,17 @@ struct LdsLut {
     __device__ __forceinline__ uint32_t operator()(uint32_t key) const { return lds[Geo<TM>::lut_addr(key)]; }
 };
 
-// Post-operators + store for one full token tile of one wave, everything in bounds and
-// aligned: lane (g, c) holds tokens tok0 + 16 i + 4 g + {0..3} of output row 16 * tile + c.
+// Whether full token tiles go through finish_tile_fast.  4-byte outputs in rows that are not 16-byte aligned
+// go through finish4: its plain stores leave the lines that a piece straddles to the L2 to merge (2304 x 768,
+// 4095 tokens in rows of 4095, binary32: 26.8 us with stores at agent scope, 19.9 us at the default scope).
+template <int OUT>
+__device__ __forceinline__ bool takes_fast_stores(const KernelArgs& a)
+{
+    return (OUT == SPMM_OUT_S8 || OUT == SPMM_OUT_U8) ? a.out_vec_ok : a.out_aligned;
+}
+
+// Post-operators + store for one full token tile of one wave, everything in bounds (4-byte outputs:
+// and aligned): lane (g, c) holds tokens tok0 + 16 i + 4 g + {0..3} of output row 16 * tile + c.
 // 4-byte outputs are stored straight from the accumulator layout (16 bytes per lane, 64-byte
 // runs per row); 1-byte outputs go through the LDS staging chunks.
 template <int TM, int OUT, int POST, int OT = -1>
@@ -390,7 +402,7 @@ __device__ __forceinline__ void finish_tile_fast(const KernelArgs& a, const v4i 
                     y[r] = __fmaf_rn((float)acc[i][r], scale, bias);
                     if constexpr ((POST & SPMM_POST_GELU) != 0) y[r] = gelu_f32(y[r]);
                 }
-                if constexpr ((POST & POST_SUM_BIT) != 0) y = y + *(const v4f*)(sp + 16 * i);
+                if constexpr ((POST & POST_SUM_BIT) != 0) y = y + ((const v4f_any*)(sp + 16 * i))->v;
                 store16_out<SCOPE_AGENT>(rs, 4u * off + 64u * i, y);
             }
         }
@@ -424,7 +436,7 @@ __device__ __forceinline__ void finish_tile_fast(const KernelArgs& a, const v4i 
 #pragma unroll
                 for (int r = 0; r < 4; ++r) y[r] = __fmaf_rn((float)acc[i][r], scale, bias);
                 if constexpr ((POST & POST_SUM_BIT) != 0) {
-                    if (sum_row_ok) y = y + *(const v4f*)(sp + 16 * i);
+                    if (sum_row_ok) y = y + ((const v4f_any*)(sp + 16 * i))->v;
                 }
                 uint32_t q[4];
 #pragma unroll
@@ -438,7 +450,7 @@ __device__ __forceinline__ void finish_tile_fast(const KernelArgs& a, const v4i 
                 if constexpr (OT == 1) {
                     store16_out<SCOPE_AGENT>(rs, off, v, half_step * h);
                 } else if constexpr (OT == 0) {
-                    *(v4i*)((uint8_t*)a.out + off + half_step * h) = v;
+                    ((v4i_any*)((uint8_t*)a.out + off + half_step * h))->v = v;
                 } else {
                     if (ot) store16_out<SCOPE_AGENT>(rs, off, v, half_step * h);
                     else store16_out<SCOPE_DEFAULT>(rs, off, v, half_step * h);
@@ -462,10 +474,6 @@ __global__ void __launch_bounds__(NW * 64) spmm_rowtile_mfma(const KernelArgs a)
     constexpr int STAGERS = ROWS_PER_PASS * PIECES;
     constexpr int XLOADS = SEGMENT_ROWS / ROWS_PER_PASS;            // 16-byte loads per staging thread and phase
     static_assert(STAGERS <= NTHREADS && STAGERS % 64 == 0, "staging threads must be whole waves of the workgroup");
-    // The 16-wave kernels with 5 and 6 step slots use all 128 registers: the four mask registers of
-    // the cut piece would spill in them, so there a token count that is not a multiple of 16 takes
-    // the bytewise path for its last tile.
-    constexpr bool MASKED_TAIL = !(NW == 16 && MAXS >= 5);
     __shared__ __attribute__((aligned(16))) uint8_t lds[G::LDS];
 
     const int tid = threadIdx.x;
@@ -510,46 +518,35 @@ __global__ void __launch_bounds__(NW * 64) spmm_rowtile_mfma(const KernelArgs a)
     const uint32_t x_lds0 = G::X0 + (uint32_t)x_row0 * G::STRIDE + x_piece * 16;
 
     // ---- global loads of half h of the activations of phase q into registers.  The common case
-    // (16-byte aligned rows, full token tile) is branch-free so that all loads are in flight
+    // (full token tile) is branch-free so that all loads are in flight
     // together; rows past the end of K are redirected to the last valid row (never multiplied).
     // Two halves (first issued at the start of the previous phase, second half-way through its
     // multiply) keep only XH prefetch registers live.
-    auto x_issue_to = [&](v4i (&xr)[XH], const int q, const int h) {
+    auto x_issue_to = [&](v4i (&xr)[XH], const int q, const int h) __attribute__((always_inline)) {
         const int j = q / a.nseg, seg = q - j * a.nseg;
         const int tok0 = (stream + j * S) * TM;
         const int k0 = seg * SEGMENT_ROWS;
         const int last = min(SEGMENT_ROWS, a.K - k0) - 1;
         if (!stager) return;
         if constexpr (XT == 0) {
-            if (a.x_vec_ok && tok0 + TM <= a.M) {
-                // fast path: K * ldx < 2 GiB (checked on the host), 32-bit offsets from a uniform base
+            if (tok0 + TM <= a.M) {
+                // 32-bit offsets from a uniform base (x_fast)
                 const uint8_t* src = a.X + (int64_t)k0 * a.ldx + tok0;
 #pragma unroll
                 for (int u = 0; u < XH; ++u) {
                     const int row = min(x_row0 + (h * XH + u) * ROWS_PER_PASS, last);
-                    xr[u] = *(const v4i*)(src + ((uint32_t)row * (uint32_t)a.ldx + (uint32_t)(x_piece * 16)));
-                }
-            } else if (a.x_vec_ok && (MASKED_TAIL || (a.M & 15) == 0)) {
-                // ragged last tile of an aligned matrix: a piece is whole, beyond the end, or cut by it.
-                // The cut one is read whole as well (an aligned 16-byte chunk that holds a wanted byte
-                // lies inside the row pitch) and masked: branch-free.  (Without MASKED_TAIL only token
-                // counts that are multiples of 16 come here: no piece is cut.)
-                const uint8_t* src = a.X + (int64_t)k0 * a.ldx;
-                const int col = tok0 + x_piece * 16;
-                const bool in = col < a.M;
-#pragma unroll
-                for (int u = 0; u < XH; ++u) {
-                    const int row = min(x_row0 + (h * XH + u) * ROWS_PER_PASS, last);
-                    const v4i v = *(const v4i*)(src + ((uint32_t)row * (uint32_t)a.ldx + (uint32_t)(in ? col : 0)));
-                    if constexpr (MASKED_TAIL) xr[u] = v & piece_mask(a.M - col);
-                    else xr[u] = in ? v : (v4i){0, 0, 0, 0};
+                    xr[u] = load16_any(src + ((uint32_t)row * (uint32_t)a.ldx + (uint32_t)(x_piece * 16)));
                 }
             } else {
+                // last, ragged token tile: still one branch-free load per piece
+                const RaggedPieces<0> tail(a, k0, last);
+                const int col = tok0 + x_piece * 16;
 #pragma unroll
-                for (int u = 0; u < XH; ++u) {
-                    const int row = min(x_row0 + (h * XH + u) * ROWS_PER_PASS, last);
-                    if constexpr (NW == 16) xr[u] = load_x16_bytewise<0>(a, k0 + row, tok0 + x_piece * 16);
-                    else xr[u] = load_x16<0>(a, k0 + row, tok0 + x_piece * 16);
+                for (int u = 0; u < XH; ++u) xr[u] = tail.load(min(x_row0 + (h * XH + u) * ROWS_PER_PASS, last), col);
+                if (!tail.inside) {
+#pragma unroll
+                    for (int u = 0; u < XH; ++u)
+                        xr[u] = tail.shifted(xr[u], min(x_row0 + (h * XH + u) * ROWS_PER_PASS, last), col);
                 }
             }
         } else {
@@ -630,9 +627,10 @@ __global__ void __launch_bounds__(NW * 64) spmm_rowtile_mfma(const KernelArgs a)
     auto finish = [&](const int q) {
         const int j = q / a.nseg;
         if (q - j * a.nseg != a.nseg - 1) return;
+        const bool fast_out = takes_fast_stores<OUT>(a);
         const int tok0 = (stream + j * S) * TM;
         if (have_tile) {
-            if (a.out_vec_ok && tok0 + TM <= a.M) {
+            if (fast_out && tok0 + TM <= a.M) {
                 finish_tile_fast<TM, OUT, POST, OTILED>(a, acc, scale, bias, tile, tok0, lane, wave, lds);
             } else if (n < a.N) {
                 const LdsLut<TM> lut{lds};
@@ -767,36 +765,29 @@ __global__ void __launch_bounds__((NW + LW) * 64) spmm_rowtile_mfma_fed(const Ke
         const uint32_t x_lds0 = G::X0 + (uint32_t)x_row0 * G::STRIDE + x_piece * 16;
         const uint32_t x_off = (uint32_t)xcol(a, x_piece * 16);
         v4i xr[XLOADS];
-        auto x_issue = [&](const int q) {
+        auto x_issue = [&](const int q) __attribute__((always_inline)) {
             const int j = q / a.nseg, seg = q - j * a.nseg;
             const int tok0 = (stream + j * S) * TM;
             const int k0 = seg * SEGMENT_ROWS;
             const int last = min(SEGMENT_ROWS, a.K - k0) - 1;   // rows past K repeat the last one (never multiplied)
             if (!stager) return;
-            if (a.x_vec_ok && tok0 + TM <= a.M) {
+            if (tok0 + TM <= a.M) {
                 const uint8_t* src = a.X + (int64_t)k0 * a.ldx + xcol(a, tok0);
 #pragma unroll
                 for (int u = 0; u < XLOADS; ++u) {
                     const int row = min(x_row0 + u * ROWS_PER_PASS, last);
-                    xr[u] = *(const v4i*)(src + ((uint32_t)row * (uint32_t)a.ldx + x_off));
-                }
-            } else if (a.x_vec_ok) {
-                // ragged last tile of an aligned matrix: a piece is whole, beyond the end, or cut by it;
-                // the cut one is read whole (it lies inside the row pitch) and masked
-                const uint8_t* src = a.X + (int64_t)k0 * a.ldx;
-                const int col = tok0 + x_piece * 16;
-                const bool in = col < a.M;
-                const v4i mask = piece_mask(a.M - col);
-#pragma unroll
-                for (int u = 0; u < XLOADS; ++u) {
-                    const int row = min(x_row0 + u * ROWS_PER_PASS, last);
-                    xr[u] = *(const v4i*)(src + ((uint32_t)row * (uint32_t)a.ldx + (uint32_t)xcol(a, in ? col : 0))) & mask;
+                    xr[u] = load16_any(src + ((uint32_t)row * (uint32_t)a.ldx + x_off));
                 }
             } else {
+                // last, ragged token tile: still one branch-free load per piece
+                const RaggedPieces<> tail(a, k0, last);
+                const int col = tok0 + x_piece * 16;
 #pragma unroll
-                for (int u = 0; u < XLOADS; ++u) {
-                    const int row = min(x_row0 + u * ROWS_PER_PASS, last);
-                    xr[u] = load_x16(a, k0 + row, tok0 + x_piece * 16);
+                for (int u = 0; u < XLOADS; ++u) xr[u] = tail.load(min(x_row0 + u * ROWS_PER_PASS, last), col);
+                if (!tail.inside) {
+#pragma unroll
+                    for (int u = 0; u < XLOADS; ++u)
+                        xr[u] = tail.shifted(xr[u], min(x_row0 + u * ROWS_PER_PASS, last), col);
                 }
             }
         };
@@ -868,9 +859,10 @@ __global__ void __launch_bounds__((NW + LW) * 64) spmm_rowtile_mfma_fed(const Ke
     auto finish = [&](const int q) {
         const int j = q / a.nseg;
         if (q - j * a.nseg != a.nseg - 1) return;
+        const bool fast_out = takes_fast_stores<OUT>(a);
         const int tok0 = (stream + j * S) * TM;
         if (have_tile) {
-            if (a.out_vec_ok && tok0 + TM <= a.M) {
+            if (fast_out && tok0 + TM <= a.M) {
                 finish_tile_fast<TM, OUT, POST>(a, acc, scale, bias, tile, tok0, lane, wave, lds);
             } else if (n < a.N) {
                 const LdsLut<TM> lut{lds};
@@ -979,33 +971,22 @@ __global__ void __launch_bounds__(NW * 64) spmm_rowtile_mfma_simple(const Kernel
     auto x_load = [&](const int seg) __attribute__((always_inline)) {
         const int k0 = seg * SEGMENT_ROWS;
         const int last = min(SEGMENT_ROWS, a.K - k0) - 1;      // rows past K repeat the last one (never multiplied)
-        if (a.x_vec_ok && tok0 + TM <= a.M) {
-            const uint8_t* src = a.X + (int64_t)k0 * a.ldx;
+        auto for_pieces = [&](auto&& f) __attribute__((always_inline)) {
 #pragma unroll
             for (int u = 0; u < XL; ++u) {
                 const int p = tid + u * NW * 64;
-                const int row = min(p / PIECES, last), piece = p % PIECES;
-                xs[u] = *(const v4i*)(src + ((uint32_t)row * (uint32_t)a.ldx + (uint32_t)xcol(a, tok0 + piece * 16)));
+                f(xs[u], min(p / PIECES, last), tok0 + (p % PIECES) * 16);
             }
-        } else if (a.x_vec_ok) {
-            // ragged last tile of an aligned matrix: whole pieces, none, or the cut one read whole
-            // and masked; branch-free
+        };
+        if (!a.x_fast) {
+            for_pieces([&](v4i& x, int row, int col) { x = load_x16_far(a, k0 + row, col); });
+        } else if (tok0 + TM <= a.M) {
             const uint8_t* src = a.X + (int64_t)k0 * a.ldx;
-#pragma unroll
-            for (int u = 0; u < XL; ++u) {
-                const int p = tid + u * NW * 64;
-                const int row = min(p / PIECES, last), col = tok0 + (p % PIECES) * 16;
-                const bool in = col < a.M;
-                const v4i v = *(const v4i*)(src + ((uint32_t)row * (uint32_t)a.ldx + (uint32_t)xcol(a, in ? col : 0)));
-                xs[u] = v & piece_mask(a.M - col);
-            }
+            for_pieces([&](v4i& x, int row, int col) { x = load16_any(src + ((uint32_t)row * (uint32_t)a.ldx + (uint32_t)xcol(a, col))); });
         } else {
-#pragma unroll
-            for (int u = 0; u < XL; ++u) {
-                const int p = tid + u * NW * 64;
-                const int row = min(p / PIECES, last), piece = p % PIECES;
-                xs[u] = load_x16(a, k0 + row, tok0 + piece * 16);
-            }
+            const RaggedPieces<> tail(a, k0, last);
+            for_pieces([&](v4i& x, int row, int col) { x = tail.load(row, col); });
+            if (!tail.inside) for_pieces([&](v4i& x, int row, int col) { x = tail.shifted(x, row, col); });
         }
     };
     auto x_store = [&]() __attribute__((always_inline)) {
@@ -1107,22 +1088,36 @@ __global__ void __launch_bounds__(NW * 64) spmm_rowtile_mfma_slab(const KernelAr
     // the slab: PIECES 16-byte pieces per thread and segment (rows past K repeat the last one; no
     // step refers to them)
     v4i xr[SEGS][PIECES];
-    const bool fast = a.x_vec_ok && tok0 + TM <= a.M;
+    const bool fast = tok0 + TM <= a.M;
+    auto for_pieces = [&](const int seg, auto&& f) __attribute__((always_inline)) {
+        const int k0 = seg * SEGMENT_ROWS, last = min(SEGMENT_ROWS, a.K - k0) - 1;
+#pragma unroll
+        for (int u = 0; u < PIECES; ++u) {
+            const int p = tid + u * NW * 64;
+            f(xr[seg][u], min(p / PIECES, last), tok0 + (p % PIECES) * 16);
+        }
+    };
+    auto tail_of = [&](const int seg) __attribute__((always_inline)) {
+        return RaggedPieces<>(a, seg * SEGMENT_ROWS, min(SEGMENT_ROWS, a.K - seg * SEGMENT_ROWS) - 1);
+    };
 #pragma unroll
     for (int seg = 0; seg < SEGS; ++seg) {
         if (seg < a.nseg) {
+            const uint8_t* src = a.X + (int64_t)(seg * SEGMENT_ROWS) * a.ldx;
+            if (__builtin_expect(fast, 1)) {
+                for_pieces(seg, [&](v4i& x, int row, int col) { x = load16_any(src + ((uint32_t)row * (uint32_t)a.ldx + (uint32_t)xcol(a, col))); });
+            } else {      // ragged last token tile
+                const RaggedPieces<> tail = tail_of(seg);
+                for_pieces(seg, [&](v4i& x, int row, int col) { x = tail.load(row, col); });
+            }
+        }
+    }
+    if (__builtin_expect(!fast, 0)) {
 #pragma unroll
-            for (int u = 0; u < PIECES; ++u) {
-                const int p = tid + u * NW * 64;
-                const int row = min(seg * SEGMENT_ROWS + p / PIECES, a.K - 1), col = tok0 + (p % PIECES) * 16;
-                if (fast) {
-                    xr[seg][u] = *(const v4i*)(a.X + ((uint32_t)row * (uint32_t)a.ldx + (uint32_t)xcol(a, col)));
-                } else if (a.x_vec_ok) {      // ragged last tile of an aligned matrix: whole chunks, masked
-                    const v4i v = *(const v4i*)(a.X + ((uint32_t)row * (uint32_t)a.ldx + (uint32_t)xcol(a, col < a.M ? col : 0)));
-                    xr[seg][u] = v & piece_mask(a.M - col);
-                } else {
-                    xr[seg][u] = load_x16(a, row, col);
-                }
+        for (int seg = 0; seg < SEGS; ++seg) {
+            if (seg < a.nseg) {
+                const RaggedPieces<> tail = tail_of(seg);
+                if (!tail.inside) for_pieces(seg, [&](v4i& x, int row, int col) { x = tail.shifted(x, row, col); });
             }
         }
     }
@@ -1259,22 +1254,24 @@ __global__ void __launch_bounds__(NW * 64) spmm_rowtile_mfma_stream(const Kernel
     const int nchunks = (s_end - s_begin + CH - 1) / CH;
 
     v4i xs[XL];
-    const bool fast = a.x_vec_ok && tok0 + TM <= a.M;
+    const bool fast = tok0 + TM <= a.M;
     auto x_load = [&](const int seg) __attribute__((always_inline)) {
         const int k0 = seg * SEGMENT_ROWS;
         const int last = min(SEGMENT_ROWS, a.K - k0) - 1;      // rows past K repeat the last one (never multiplied)
+        auto for_pieces = [&](auto&& f) __attribute__((always_inline)) {
 #pragma unroll
-        for (int u = 0; u < XL; ++u) {
-            const int p = tid + u * NW * 64;
-            const int row = k0 + min(p / PIECES, last), col = tok0 + (p % PIECES) * 16;
-            if (fast) {
-                xs[u] = *(const v4i*)(a.X + ((uint32_t)row * (uint32_t)a.ldx + (uint32_t)xcol(a, col)));
-            } else if (a.x_vec_ok) {          // ragged last tile of an aligned matrix: whole chunks, masked
-                const v4i v = *(const v4i*)(a.X + ((uint32_t)row * (uint32_t)a.ldx + (uint32_t)xcol(a, col < a.M ? col : 0)));
-                xs[u] = v & piece_mask(a.M - col);
-            } else {
-                xs[u] = load_x16(a, row, col);
+            for (int u = 0; u < XL; ++u) {
+                const int p = tid + u * NW * 64;
+                f(xs[u], min(p / PIECES, last), tok0 + (p % PIECES) * 16);
             }
+        };
+        if (fast) {
+            const uint8_t* src = a.X + (int64_t)k0 * a.ldx;
+            for_pieces([&](v4i& x, int row, int col) { x = load16_any(src + ((uint32_t)row * (uint32_t)a.ldx + (uint32_t)xcol(a, col))); });
+        } else {      // ragged last token tile
+            const RaggedPieces<> tail(a, k0, last);
+            for_pieces([&](v4i& x, int row, int col) { x = tail.load(row, col); });
+            if (!tail.inside) for_pieces([&](v4i& x, int row, int col) { x = tail.shifted(x, row, col); });
         }
     };
     auto x_store = [&]() __attribute__((always_inline)) {

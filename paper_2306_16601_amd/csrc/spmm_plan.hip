@@ -110,12 +110,17 @@ static double plan_cost(const Plan& p, int num_cus)
     return (double)rounds * ((double)per_stream * (p.token_tile * per_token + 16.0) + 48.0);
 }
 
-Plan make_plan(int64_t M, const WeightDims& w, int num_cus, int force_tm, int variant, bool aligned, int out_bytes)
+Plan make_plan(int64_t M, const WeightDims& w, int num_cus, int force_tm, int variant, int out_bytes, bool x_fast, bool out_fast)
 {
     const int ntiles = w.ntiles, nseg = w.nseg, max_steps_per_segment = w.max_steps_per_segment;
     Plan p{};
     const int max_steps = max_steps_per_segment <= 4 ? 4 : (max_steps_per_segment <= 6 ? max_steps_per_segment : 8);
     p.max_steps = max_steps;
+    if (!x_fast && !(force_tm && force_tm <= 64 && (variant == 101 || variant == 102))) {
+        // rows so far apart that a segment of them exceeds 32-bit offsets, or an X of less than 16 bytes
+        fill_simple(p, M, w, 1, 64);
+        return p;
+    }
     if (force_tm == 64 && variant == 112) {
         // (weights with more than 6 steps per segment run 8 compute waves, which exist with 128-token tiles)
         fill_pipelined(p, M, ntiles, num_cus, max_steps <= 6 ? 64 : 128, max_steps <= 6 ? 12 : 8);
@@ -149,7 +154,7 @@ Plan make_plan(int64_t M, const WeightDims& w, int num_cus, int force_tm, int va
     }
     // 16 waves have 128 registers each: at most 6 steps per segment; denser weights run with 8
     // waves, 256 registers and half as many rows per workgroup (token tile 128 only).
-    if (max_steps > 6 || variant == 8 || (!aligned && force_tm == 0 && variant == 0)) {
+    if (max_steps > 6 || variant == 8 || (!out_fast && force_tm == 0 && variant == 0)) {
         fill_pipelined(p, M, ntiles, num_cus, 128, 8);
     } else if (force_tm == 96 || variant == 16) {
         fill_pipelined(p, M, ntiles, num_cus, force_tm ? force_tm : 128, 16);

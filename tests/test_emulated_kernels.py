@@ -79,6 +79,21 @@ CASES = [
     (256, 3584, 64, 0.9, "s32", "none", 32, 104, "spmm_rowtile_mfma_stream<32", {"kind": "ragged"}),
     (192, 4096, 40, 0.8, "s8", "none", 16, 104, "spmm_rowtile_mfma_stream<16", {"kind": "ragged"}),
     (144, 5000, 70, 0.95, "s32", "none", 64, 104, "spmm_rowtile_mfma_stream<64", {"kind": "ragged"}),
+    # pitch = token count at every alignment, exactly sized operands: pieces cut by the end of a row, rows shorter than a
+    # piece, a last segment of one row, an X of less than 16 bytes (byte-wise, whatever kernel is asked for)
+    (256, 513, 135, 0.8, "s8", "gelu", 96, 16, "spmm_rowtile_mfma<96, 16", {}),
+    (256, 1024, 397, 0.8, "f32", "none", 128, 16, "spmm_rowtile_mfma<128, 16", {"cus": 2}),
+    (128, 1030, 7, 0.7, "u8", "none", 128, 8, "spmm_rowtile_mfma<128, 8", {}),
+    (400, 1025, 387, 0.9, "f32", "none", 128, 112, "spmm_rowtile_mfma_fed<128, 12", {"cus": 2}),
+    (200, 513, 3, 0.8, "s32", "none", 64, 112, "spmm_rowtile_mfma_fed<64, 12", {"cus": 2}),
+    (128, 1025, 65, 0.8, "s8", "none", 64, 101, "spmm_rowtile_mfma_simple<64", {}),
+    (128, 514, 5, 0.8, "f32", "none", 16, 101, "spmm_rowtile_mfma_simple<16", {}),
+    (16, 3, 5, 0.0, "s32", "none", 16, 101, "spmm_rowtile_mfma_simple<16", {}),
+    (16, 1, 11, 0.0, "s8", "none", 128, 16, "spmm_rowtile_mfma<128, 16", {}),
+    (128, 2561, 17, 0.9, "s8", "gelu", 16, 103, "spmm_rowtile_mfma_slab<16", {}),
+    (128, 2561, 3, 0.9, "s32", "none", 32, 103, "spmm_rowtile_mfma_slab<32", {}),
+    (128, 3585, 69, 0.9, "u8", "none", 32, 104, "spmm_rowtile_mfma_stream<32", {}),
+    (128, 3585, 6, 0.9, "f32", "none", 16, 104, "spmm_rowtile_mfma_stream<16", {}),
 ]
 
 
