@@ -2,6 +2,7 @@
 // ownership, device upload of the packed weight and kernel dispatch.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -17,40 +18,54 @@ struct spmm_handle {
     spmm::HostLayout hl;           // host copy of the row-tile union layout
     // device copy of the same
     bool on_device = false;
-    int kc = 0, nseg = 0, ntiles = 0, max_steps_per_tile = 0, max_steps_per_segment = 0;
+    int nseg = 0, ntiles = 0, max_steps_per_tile = 0, max_steps_per_segment = 0;
     int num_cus = 256;
     int64_t nsteps = 0;
-    uint8_t* d_vals = nullptr;
-    uint32_t* d_idx = nullptr;
-    int32_t* d_seg_ptr = nullptr;
-    int32_t* d_rowsum = nullptr;
+    uint8_t* d_weight = nullptr;   // rowsum, bounds and step records (spmm_internal.h)
+    int tile_steps = 0;
     int64_t device_bytes = 0;
     int force_tm = 0, force_r = 0;
 };
 
 namespace {
 
-template <typename T>
-hipError_t upload(T*& dst, const std::vector<T>& src, int64_t& total)
+// The packed weight in its device form (spmm_internal.h), in one allocation and one copy.
+hipError_t upload_weight(spmm_handle* h)
 {
-    // at least one zero step's worth, so that step index 0 is always readable
-    const size_t bytes = std::max<size_t>(src.size() * sizeof(T), spmm::STEP_VAL_BYTES);
-    hipError_t e = hipMalloc((void**)&dst, bytes);
+    const spmm::HostLayout& hl = h->hl;
+    const int64_t nt = hl.ntiles, ns = hl.nseg;
+    const bool strided = nt * hl.max_steps_per_tile <= hl.nsteps + hl.nsteps / 2;
+    h->tile_steps = strided ? hl.max_steps_per_tile : 0;
+    // (at least one record, so that a step index of 0 is always readable)
+    const int64_t records = std::max<int64_t>(1, strided ? nt * hl.max_steps_per_tile : hl.nsteps);
+    const int64_t at = spmm::records_offset(nt, ns), bytes = at + records * spmm::RECORD_BYTES;
+    std::vector<uint8_t> blob((size_t)bytes, 0);
+    std::memcpy(blob.data(), hl.rowsum.data(), hl.rowsum.size() * 4);
+    int32_t* bounds = (int32_t*)(blob.data() + spmm::bounds_offset(nt));
+    for (int64_t t = 0; t < nt; ++t) {
+        const int64_t shift = strided ? t * hl.max_steps_per_tile - hl.seg_ptr[(size_t)(t * ns)] : 0;
+        for (int64_t g = 0; g <= ns; ++g) {
+            bounds[t * (ns + 1) + g] = (int32_t)(hl.seg_ptr[(size_t)(t * ns + g)] + shift);
+            if (g == ns) continue;
+            for (int64_t s = hl.seg_ptr[(size_t)(t * ns + g)]; s < hl.seg_ptr[(size_t)(t * ns + g + 1)]; ++s) {
+                uint8_t* r = blob.data() + at + (s + shift) * spmm::RECORD_BYTES;
+                std::memcpy(r, &hl.vals[(size_t)s * spmm::STEP_VAL_BYTES], spmm::STEP_VAL_BYTES);
+                const uint32_t base = (uint32_t)(g * spmm::SEGMENT_ROWS) * 0x10001u;
+                for (int i = 0; i < spmm::STEP_IDX_DWORDS; ++i)
+                    ((uint32_t*)(r + spmm::STEP_VAL_BYTES))[i] = hl.idx[(size_t)s * spmm::STEP_IDX_DWORDS + i] + base;
+            }
+        }
+    }
+    hipError_t e = hipMalloc((void**)&h->d_weight, (size_t)bytes);
     if (e != hipSuccess) return e;
-    total += (int64_t)bytes;
-    if (src.size() * sizeof(T) < bytes) e = hipMemset(dst, 0, bytes);
-    if (e != hipSuccess) return e;
-    if (!src.empty()) e = hipMemcpy(dst, src.data(), src.size() * sizeof(T), hipMemcpyHostToDevice);
-    return e;
+    h->device_bytes = bytes;
+    return hipMemcpy(h->d_weight, blob.data(), (size_t)bytes, hipMemcpyHostToDevice);
 }
 
 void free_device(spmm_handle* h)
 {
-    if (h->d_vals) (void)hipFree(h->d_vals);
-    if (h->d_idx) (void)hipFree(h->d_idx);
-    if (h->d_seg_ptr) (void)hipFree(h->d_seg_ptr);
-    if (h->d_rowsum) (void)hipFree(h->d_rowsum);
-    h->d_vals = nullptr; h->d_idx = nullptr; h->d_seg_ptr = nullptr; h->d_rowsum = nullptr;
+    if (h->d_weight) (void)hipFree(h->d_weight);
+    h->d_weight = nullptr;
 }
 
 bool aligned(const void* p, size_t a) { return (reinterpret_cast<uintptr_t>(p) % a) == 0; }
@@ -92,7 +107,7 @@ static spmm_status_t pack_common(const int8_t* W_host, int64_t N, int64_t K, int
         return SPMM_E_ALLOC;
     }
     const spmm::HostLayout& hl = h->hl;
-    h->kc = hl.kc; h->nseg = hl.nseg; h->ntiles = hl.ntiles; h->nsteps = hl.nsteps;
+    h->nseg = hl.nseg; h->ntiles = hl.ntiles; h->nsteps = hl.nsteps;
     h->max_steps_per_tile = hl.max_steps_per_tile;
     h->max_steps_per_segment = hl.max_steps_per_segment;
 
@@ -103,10 +118,13 @@ static spmm_status_t pack_common(const int8_t* W_host, int64_t N, int64_t K, int
             if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, h->device) == hipSuccess && cus > 0)
                 h->num_cus = cus;
         }
-        if (e == hipSuccess) e = upload(h->d_vals, hl.vals, h->device_bytes);
-        if (e == hipSuccess) e = upload(h->d_idx, hl.idx, h->device_bytes);
-        if (e == hipSuccess) e = upload(h->d_seg_ptr, hl.seg_ptr, h->device_bytes);
-        if (e == hipSuccess) e = upload(h->d_rowsum, hl.rowsum, h->device_bytes);
+        if (e == hipSuccess) {
+            try {
+                e = upload_weight(h);
+            } catch (...) {
+                e = hipErrorOutOfMemory;
+            }
+        }
         if (e != hipSuccess) {
             free_device(h);
             delete h;
@@ -151,7 +169,7 @@ spmm_status_t spmm_layout_dims(const spmm_handle_t* h, int32_t* tile_rows, int32
     if (!h) return SPMM_E_ARG;
     if (tile_rows) *tile_rows = spmm::TILE_ROWS;
     if (step_k) *step_k = spmm::STEP_K;
-    if (segment_rows) *segment_rows = h->kc;
+    if (segment_rows) *segment_rows = spmm::SEGMENT_ROWS;
     if (n_tiles) *n_tiles = h->ntiles;
     if (n_segments) *n_segments = h->nseg;
     if (n_steps) *n_steps = h->nsteps;
@@ -261,65 +279,65 @@ static spmm_status_t run_common(const spmm_handle_t* h, const uint8_t* X_dev, in
     std::memset(&a, 0, sizeof(a));
     if (quant && gelu) {
         if (!ep->lut || !(ep->mid_scale > 0.0f)) return SPMM_E_ARG;
-        a.inv_mid = 1.0f / ep->mid_scale;
+        a.aux = ep->lut;
+        a.inv = 1.0f / ep->mid_scale;
     } else if (quant) {
         if (!(ep->out_scale > 0.0f)) return SPMM_E_ARG;
         const int lo = (ot == SPMM_OUT_U8) ? 0 : -128, hi = (ot == SPMM_OUT_U8) ? 255 : 127;
         if (ep->out_zero_point < lo || ep->out_zero_point > hi) return SPMM_E_ARG;
-        a.inv_out = 1.0f / ep->out_scale;
+        a.inv = 1.0f / ep->out_scale;
         a.out_zp_f = (float)ep->out_zero_point;
     }
 
-    a.vals = h->d_vals; a.idx = h->d_idx; a.seg_ptr = h->d_seg_ptr; a.rowsum = h->d_rowsum;
-    a.X = X_dev; a.out = out_dev;
-    a.w_scale = ep->w_scale; a.bias = ep->bias; a.lut = ep->lut;
-    a.ldx = ldx; a.ldo = ldo;
-    a.N = (int)h->bsr.N; a.K = (int)h->bsr.K; a.M = (int)M;
-    a.kc = h->kc; a.nseg = h->nseg; a.ntiles = h->ntiles;
-    a.corr_mul = 128 - ep->x_zero_point;
-    a.x_scale = ep->x_scale;
+    const int64_t N = h->bsr.N, K = h->bsr.K, esz = quant ? 1 : 4;
+    const int64_t tiles = (M + SPMM_X_TILE - 1) / SPMM_X_TILE, limit = (int64_t)1 << 31;
     // fast paths use 16-byte accesses (at any address) and 32-bit offsets
-    a.x_last16 = (h->bsr.K - 1) * ldx + M - 16;
-    a.x_fast = a.x_last16 >= 0 && ldx < ((int64_t)1 << 31) / spmm::SEGMENT_ROWS;
+    bool x_fast = (K - 1) * ldx + M >= 16 && ldx < limit / spmm::SEGMENT_ROWS;
+    bool out_fast = N * ldo * esz < limit, out_aligned = aligned(out_dev, 16) && (ldo * esz) % 16 == 0;
     if (x_tiled) {
         // token-tile-major activations: [ceil(M / 32)][K][32] bytes, 16-byte aligned
         if (!aligned(X_dev, 16)) return SPMM_E_ARG;
-        const int64_t tiles = (M + SPMM_X_TILE - 1) / SPMM_X_TILE;
-        if (tiles * h->bsr.K * SPMM_X_TILE >= ((int64_t)1 << 31)) return SPMM_E_UNSUPPORTED;
-        a.ldx = SPMM_X_TILE;
-        a.x_tile_stride = (int)(h->bsr.K * SPMM_X_TILE);
-        a.x_fast = 1;
-        a.x_last16 = tiles * h->bsr.K * SPMM_X_TILE - 16;
+        if (tiles * K * SPMM_X_TILE >= limit) return SPMM_E_UNSUPPORTED;
+        ldx = SPMM_X_TILE;
+        x_fast = true;
     }
-    const int64_t esz = quant ? 1 : 4;
-    a.out_vec_ok = h->bsr.N * ldo * esz < ((int64_t)1 << 31);
-    a.out_aligned = a.out_vec_ok && aligned(out_dev, 16) && (ldo * esz) % 16 == 0;
     if (out_tiled) {
         // token-tile-major 1-byte output: [ceil(M / 32)][N][32] bytes, 16-byte aligned
         if (!quant) return SPMM_E_UNSUPPORTED;
         if (!aligned(out_dev, 16)) return SPMM_E_ARG;
-        const int64_t tiles = (M + SPMM_X_TILE - 1) / SPMM_X_TILE;
-        if (tiles * h->bsr.N * SPMM_X_TILE >= ((int64_t)1 << 31)) return SPMM_E_UNSUPPORTED;
-        a.ldo = SPMM_X_TILE;
-        a.out_tile_stride = (int)(h->bsr.N * SPMM_X_TILE);
-        a.out_vec_ok = a.out_aligned = 1;
+        if (tiles * N * SPMM_X_TILE >= limit) return SPMM_E_UNSUPPORTED;
+        ldo = SPMM_X_TILE;
+        out_fast = out_aligned = true;
     }
+    int64_t ld_sum = 0;
     if (ep->sum) {
-        a.sum = ep->sum;
-        a.ld_sum = ep->ld_sum;
-        a.out_vec_ok = a.out_vec_ok && (h->bsr.N * ep->ld_sum * 4 < ((int64_t)1 << 31));
-        a.out_aligned = a.out_aligned && a.out_vec_ok;
+        a.aux = ep->sum;
+        ld_sum = ep->ld_sum;
+        out_fast = out_fast && N * ld_sum * 4 < limit;
     }
+    // the kernels take 40-bit pitches; the pitch of a single row is nothing
+    if (K == 1 && !x_tiled) ldx = M;
+    if (N == 1 && !out_tiled) ldo = M;
+    if (N == 1) ld_sum = M;
+    if ((ldx | ldo | ld_sum) >> 40) return SPMM_E_UNSUPPORTED;
+    a.X = X_dev;
+    a.weight = h->d_weight;
+    a.out = out_dev;
+    a.w_scale = ep->w_scale;
+    a.bias = ep->bias;
+    a.ldx = (uint32_t)ldx;
+    a.ldo = (uint32_t)ldo;
+    a.ld_sum = (uint32_t)ld_sum;
+    a.ld_high = (uint32_t)(ldx >> 32 & 0xff) | (uint32_t)(ldo >> 32 & 0xff) << 8 | (uint32_t)(ld_sum >> 32 & 0xff) << 16;
+    a.M = (int32_t)M;
+    a.N = (int32_t)N;
+    a.k_flags = (uint32_t)K | (uint32_t)ep->x_zero_point << 24 | (x_tiled ? spmm::ARG_X_TILED : 0) |
+                (out_tiled ? spmm::ARG_OUT_TILED : 0) | (x_fast ? spmm::ARG_X_FAST : 0) |
+                (out_fast ? spmm::ARG_OUT_FAST : 0) | (out_fast && out_aligned ? spmm::ARG_OUT_ALIGNED : 0);
+    a.x_scale = ep->x_scale;
+    a.tile_steps = (uint16_t)h->tile_steps;
 
-    if (a.out_vec_ok) {
-        // extent of the output (the fast paths store through a buffer resource of this size: the
-        // hardware drops a store that would leave it)
-        const int64_t tiles = (M + SPMM_X_TILE - 1) / SPMM_X_TILE;
-        const int64_t extent = out_tiled ? tiles * h->bsr.N * SPMM_X_TILE : ((h->bsr.N - 1) * ldo + M) * esz;
-        a.out_bytes = (uint32_t)extent;
-    }
-
-    const spmm::Plan p = plan_for(h, M, (int)esz, a.x_fast, a.out_vec_ok);
+    const spmm::Plan p = plan_for(h, M, (int)esz, x_fast, out_fast);
     const int rc = spmm::launch_spmm(p, a, ot, (gelu ? SPMM_POST_GELU : SPMM_POST_NONE) | (ep->sum ? spmm::POST_SUM_BIT : 0),
                                      hip_stream);
     return rc == 0 ? SPMM_OK : SPMM_E_DEVICE;

@@ -65,34 +65,51 @@ void bsr_permute_rows(const Bsr& b, const std::vector<int32_t>& row_order, Bsr& 
 // ---------------------------------------------------------------------------------------
 // Kernel launch interface (plan and dispatch in spmm_plan.hip, kernels in spmm_kernels.h).
 // ---------------------------------------------------------------------------------------
+// The packed weight on the device is one allocation (upload_weight in api.cpp):
+//     int32   rowsum[ntiles][16]
+//     int32   bounds[ntiles][nseg + 1]   first record of every segment of the tile, and one past its last
+//     (padding to 128 bytes)
+//     records                            one per step, RECORD_BYTES = 1152: vals[64][16], then 64 u16 k positions
+//                                        in the pairing of HostLayout::idx, relative to the whole weight
+// The records of a tile start at record tile * tile_steps where that costs at most half as many records again
+// as there are steps (tile_steps = the longest tile's steps): a kernel can then request its first weights
+// without reading bounds first.  Otherwise (tile_steps = 0) they lie back to back and bounds says where.
+constexpr int RECORD_BYTES = STEP_VAL_BYTES + 4 * STEP_IDX_DWORDS;
+constexpr int64_t bounds_offset(int64_t ntiles) { return ntiles * TILE_ROWS * 4; }
+constexpr int64_t records_offset(int64_t ntiles, int64_t nseg)
+{
+    return (bounds_offset(ntiles) + ntiles * (nseg + 1) * 4 + 127) & ~(int64_t)127;
+}
+
+// What a launch passes to a kernel.  96 bytes: the runtime writes the arguments of every launch through the
+// bus, and from 128 bytes on a launch takes 3.3 us of the host instead of 2.7 us (measured; this was a plain
+// 232-byte struct).  The kernels unpack it into an Args (spmm_kernels.h).
 struct KernelArgs {
-    const uint8_t* vals;
-    const uint32_t* idx;
-    const int32_t* seg_ptr;
-    const int32_t* rowsum;
     const uint8_t* X;
+    const uint8_t* weight;      // see above
     void* out;
     const float* w_scale;
     const float* bias;
-    const int8_t* lut;
-    const float* sum;    // Sum post-operator: [N][ld_sum] or nullptr
-    int64_t ldx, ldo, ld_sum;
-    int N, K, M;
-    int kc, nseg, ntiles;
-    int n_tok_tiles, n_row_groups;
-    int n_streams;       // persistent kernel: workgroups per row group, each walking token tiles j*n_streams + stream
-    int tiles_per_stream, tiles_extra;   // n_tok_tiles = tiles_per_stream * n_streams + tiles_extra
-    int xcd_map;         // simple / short-batch kernels: how a workgroup id decodes, see decode_workgroup()
-    int corr_mul;        // 128 - x_zero_point: the activations are multiplied as (x - 128)
-    float x_scale, inv_out, inv_mid, out_zp_f;
-    int64_t x_last16;    // offset of the last 16 bytes of X: no 16-byte read goes beyond them (negative: X has fewer)
-    int x_fast;          // the rows of one segment lie within 2^31 bytes, and X has 16: 32-bit offsets
-    int out_vec_ok;      // whole output < 2^31 bytes (and, with Sum, the second operand too): 32-bit offsets
-    int out_aligned;     // out_vec_ok, out base 16-byte aligned and row pitch a multiple of 16 bytes
-    int out_tile_stride; // 0: out row-major [N][ldo]; else 1-byte out token-tile-major [ceil(M/32)][N][32], ldo = 32 and this = 32 N
-    int x_tile_stride;   // 0: X row-major [K][ldx]; else X token-tile-major [ceil(M/32)][K][32], ldx = 32 and this = 32 K
-    uint32_t out_bytes;  // with out_vec_ok: bytes from out to the end of the last element the call may write (< 2^31)
+    const void* aux;            // the table of a table chain, or the second operand of Sum
+    uint32_t ldx, ldo, ld_sum;  // low 32 bits,
+    uint32_t ld_high;           // and bits 32 .. 39 of the three, 8 bits each
+    int32_t M, N;
+    uint32_t k_flags;           // K (17 bits), ARG_* flags, x_zero_point << 24
+    float x_scale, inv, out_zp_f;   // inv: 1 / out_scale, or 1 / mid_scale of a table chain
+    uint16_t n_streams;         // persistent kernels: workgroups per row group, each walking token tiles j * n_streams + stream
+    uint16_t tile_steps;
+    uint32_t tiles_per_stream;  // token tiles / n_streams, rounded down
 };
+static_assert(sizeof(KernelArgs) == 96, "kernel arguments");
+constexpr int ARG_K_BITS = 17;
+constexpr int GRID_Y_BITS = 15;                  // of the simple and short-batch kernels' grids: the rest goes into z
+constexpr uint32_t ARG_X_TILED = 1u << 17;      // X token-tile-major [ceil(M/32)][K][32], ldx = 32; else row-major [K][ldx]
+constexpr uint32_t ARG_OUT_TILED = 1u << 18;    // 1-byte out token-tile-major [ceil(M/32)][N][32], ldo = 32; else row-major [N][ldo]
+constexpr uint32_t ARG_X_FAST = 1u << 19;       // the rows of one segment lie within 2^31 bytes, and X has 16: 32-bit offsets
+constexpr uint32_t ARG_OUT_FAST = 1u << 20;     // whole output < 2^31 bytes (and, with Sum, the second operand too)
+constexpr uint32_t ARG_OUT_ALIGNED = 1u << 21;  // ARG_OUT_FAST, out base 16-byte aligned and row pitch a multiple of 16 bytes
+constexpr uint32_t ARG_XCD_MAP_2 = 1u << 22;    // how a workgroup id decodes, see the kernels
+constexpr uint32_t ARG_XCD_MAP_1 = 1u << 23;
 
 struct Plan {
     int token_tile;          // TM of the pipelined kernel (128 or 96), or 64 for the simple kernel

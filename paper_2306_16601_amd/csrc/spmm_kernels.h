@@ -50,6 +50,72 @@
 
 namespace spmm {
 
+// KernelArgs, unpacked: what the kernels work with (scalar registers; what a kernel does not use costs nothing)
+struct Args {
+    const uint8_t* records;     // step records of the packed weight
+    const int32_t* bounds;      // [ntiles][nseg + 1]
+    const int32_t* rowsum;
+    const uint8_t* X;
+    void* out;
+    const float* w_scale;
+    const float* bias;
+    const int8_t* lut;
+    const float* sum;           // Sum post-operator: [N][ld_sum]
+    int64_t ldx, ldo, ld_sum;
+    int64_t x_last16;           // offset of the last 16 bytes of X: no 16-byte read goes beyond them (negative: X has fewer)
+    int N, K, M, nseg, ntiles, tile_steps;
+    int n_streams, tiles_per_stream;
+    int xcd_map;
+    int corr_mul;               // 128 - x_zero_point: the activations are multiplied as (x - 128)
+    float x_scale, inv, out_zp_f;
+    bool x_fast, out_fast, out_aligned;
+    int x_tile_stride;          // token-tile-major X: bytes between tiles, 32 K; else 0
+    int out_tile_stride;        // token-tile-major output: 32 N; else 0
+    uint32_t out_bytes;         // with out_fast: bytes from out to the end of the last element the call may write
+};
+
+template <int OUT>
+__device__ __forceinline__ Args unpack(const KernelArgs& p)
+{
+    Args a;
+    a.M = p.M;
+    a.N = p.N;
+    a.K = (int)(p.k_flags & ((1u << ARG_K_BITS) - 1));
+    a.nseg = (a.K + SEGMENT_ROWS - 1) / SEGMENT_ROWS;
+    a.ntiles = (a.N + TILE_ROWS - 1) / TILE_ROWS;
+    a.tile_steps = p.tile_steps;
+    a.rowsum = (const int32_t*)p.weight;
+    a.bounds = (const int32_t*)(p.weight + bounds_offset(a.ntiles));
+    a.records = p.weight + records_offset(a.ntiles, a.nseg);
+    a.X = p.X;
+    a.out = p.out;
+    a.w_scale = p.w_scale;
+    a.bias = p.bias;
+    a.lut = (const int8_t*)p.aux;
+    a.sum = (const float*)p.aux;
+    a.ldx = (int64_t)((uint64_t)p.ldx | (uint64_t)(p.ld_high & 0xff) << 32);
+    a.ldo = (int64_t)((uint64_t)p.ldo | (uint64_t)(p.ld_high >> 8 & 0xff) << 32);
+    a.ld_sum = (int64_t)((uint64_t)p.ld_sum | (uint64_t)(p.ld_high >> 16 & 0xff) << 32);
+    const int tiles32 = (a.M + SPMM_X_TILE - 1) / SPMM_X_TILE;
+    const bool xt = p.k_flags & ARG_X_TILED, ot = p.k_flags & ARG_OUT_TILED;
+    a.x_tile_stride = xt ? a.K * SPMM_X_TILE : 0;
+    a.out_tile_stride = ot ? a.N * SPMM_X_TILE : 0;
+    a.x_last16 = xt ? (int64_t)tiles32 * a.x_tile_stride - 16 : (int64_t)(a.K - 1) * a.ldx + a.M - 16;
+    a.out_bytes = ot ? (uint32_t)tiles32 * (uint32_t)a.out_tile_stride
+                     : ((uint32_t)(a.N - 1) * p.ldo + (uint32_t)a.M) * (OUT == SPMM_OUT_S32 || OUT == SPMM_OUT_F32 ? 4u : 1u);
+    a.x_fast = p.k_flags & ARG_X_FAST;
+    a.out_fast = p.k_flags & ARG_OUT_FAST;
+    a.out_aligned = p.k_flags & ARG_OUT_ALIGNED;
+    a.xcd_map = (p.k_flags & ARG_XCD_MAP_2) ? 2 : (p.k_flags & ARG_XCD_MAP_1) ? 1 : 0;
+    a.corr_mul = 128 - (int)(p.k_flags >> 24);
+    a.x_scale = p.x_scale;
+    a.inv = p.inv;
+    a.out_zp_f = p.out_zp_f;
+    a.n_streams = p.n_streams;
+    a.tiles_per_stream = (int)p.tiles_per_stream;
+    return a;
+}
+
 typedef int v4i __attribute__((ext_vector_type(4)));
 typedef int v2i __attribute__((ext_vector_type(2)));
 typedef float v4f __attribute__((ext_vector_type(4)));
@@ -117,7 +183,7 @@ struct GlobalLut {
 // so they stay at the default scope and the L2 merges them.
 typedef unsigned int v4u __attribute__((ext_vector_type(4)));
 constexpr int SCOPE_DEFAULT = 0, SCOPE_AGENT = 16;   // cache-policy operand of the buffer stores: none / sc1
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t out_resource(const KernelArgs& a)
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t out_resource(const Args& a)
 {
     // raw buffer (stride 0), 32-bit data format
     return __builtin_amdgcn_make_buffer_rsrc(a.out, 0, (int)a.out_bytes, 0x00020000);
@@ -133,16 +199,16 @@ __device__ __forceinline__ void store16_out(const __amdgpu_buffer_rsrc_t rs, con
 
 // quantised code of one pre-activation y (Quantize post-operator / table look-up)
 template <int OUT, int POST, typename Lut>
-__device__ __forceinline__ uint32_t quantise(const KernelArgs& a, const float y, const Lut& lut)
+__device__ __forceinline__ uint32_t quantise(const Args& a, const float y, const Lut& lut)
 {
     if constexpr ((POST & SPMM_POST_GELU) != 0) {
         // key = sat_s8(rint(y / mid_scale)) + 128; v_cvt_pk_u8_f32 converts with saturation to [0, 255]
-        const float t = rintf(y * a.inv_mid) + 128.0f;
+        const float t = rintf(y * a.inv) + 128.0f;
         return lut(__builtin_amdgcn_cvt_pk_u8_f32(t, 0u, 0u));
     } else {
         const float lo = (OUT == SPMM_OUT_U8) ? 0.0f : -128.0f;
         const float hi = (OUT == SPMM_OUT_U8) ? 255.0f : 127.0f;
-        return (uint32_t)((int)fminf(hi, fmaxf(lo, rintf(y * a.inv_out) + a.out_zp_f))) & 0xffu;
+        return (uint32_t)((int)fminf(hi, fmaxf(lo, rintf(y * a.inv) + a.out_zp_f))) & 0xffu;
     }
 }
 
@@ -152,7 +218,7 @@ __device__ __forceinline__ uint32_t quantise(const KernelArgs& a, const float y,
 // costs registers the 16-wave pipelined kernels do not have (their full tiles take finish_tile_fast).
 // OT: layout of a 1-byte output: 1 = token-tile-major, 0 = row-major, -1 = whichever the arguments say
 template <int OUT, int POST, bool WIDE = false, int OT = -1, typename Lut>
-__device__ __forceinline__ void finish4(const KernelArgs& a, const v4i acc, const float s, const float b,
+__device__ __forceinline__ void finish4(const Args& a, const v4i acc, const float s, const float b,
                                         const int n, const int m0, const Lut& lut)
 {
     const int valid = a.M - m0;   // > 0 guaranteed by caller
@@ -210,6 +276,18 @@ __device__ __forceinline__ void finish4(const KernelArgs& a, const v4i acc, cons
     }
 }
 
+// One step's weight operand and this lane's pair of activation rows from the step records; `step` is the same
+// for the whole wave.  (The rows are positions in the whole weight; they are cut to the segment where they are
+// used, first_row / second_row, and not here, where it would mean waiting for the load.)
+__device__ __forceinline__ void load_step(const Args& a, const int step, const int lane, v4i& w, uint32_t& rows)
+{
+    const uint8_t* r = a.records + (int64_t)step * RECORD_BYTES;
+    w = *(const v4i*)(r + (uint32_t)lane * 16u);
+    rows = *(const uint32_t*)(r + (STEP_VAL_BYTES + 32u * (uint32_t)(lane >> 4) + 4u * (uint32_t)((lane & 15) >> 1)));
+}
+__device__ __forceinline__ uint32_t first_row(const uint32_t rows) { return rows & (SEGMENT_ROWS - 1); }
+__device__ __forceinline__ uint32_t second_row(const uint32_t rows) { return rows >> 16 & (SEGMENT_ROWS - 1); }
+
 // s_waitcnt vmcnt(0) only (expcnt / lgkmcnt fields left at their maxima).  Issued when the
 // prefetches started at the beginning of a phase have long landed: it tells the compiler's
 // wait-count bookkeeping that no global load is outstanding, so the next phase's multiply
@@ -226,7 +304,7 @@ __device__ __forceinline__ void wait_global_loads() { __builtin_amdgcn_s_waitcnt
 // The pipelined kernel is instantiated for both layouts: its 16-wave forms have no register to spare
 // for a choice at run time.
 template <int XT = -1>
-__device__ __forceinline__ int xcol(const KernelArgs& a, const int col)
+__device__ __forceinline__ int xcol(const Args& a, const int col)
 {
     // (the whole X is smaller than 2 GiB in this layout, checked on the host: the offset fits an int)
     if constexpr (XT == 0) return col;
@@ -244,11 +322,11 @@ __device__ __forceinline__ int xcol(const KernelArgs& a, const int col)
 // base lies 16 bytes before the segment so that a read moved back into the previous one is not negative.
 template <int XT = -1>
 struct RaggedPieces {
-    const KernelArgs& a;
+    const Args& a;
     const uint8_t* base;
     uint32_t bias, limit;
     bool inside;
-    __device__ __forceinline__ RaggedPieces(const KernelArgs& args, const int k0, const int last) : a(args)
+    __device__ __forceinline__ RaggedPieces(const Args& args, const int k0, const int last) : a(args)
     {
         bias = k0 > 0 ? 16 : 0;
         base = a.X + ((int64_t)k0 * a.ldx - bias);
@@ -278,7 +356,7 @@ struct RaggedPieces {
 };
 // The same for a row-major matrix whose segments exceed 32-bit offsets, or that holds less than 16 bytes
 // (only the simple kernel takes those, see make_plan): pieces that would leave the matrix byte by byte.
-__device__ __forceinline__ v4i load_x16_far(const KernelArgs& a, const int row, const int col)
+__device__ __forceinline__ v4i load_x16_far(const Args& a, const int row, const int col)
 {
     const int64_t off = (int64_t)row * a.ldx + (col < a.M ? col : 0);
     if (off <= a.x_last16) return load16_any(a.X + off);
@@ -361,9 +439,9 @@ struct LdsLut {
 // go through finish4: its plain stores leave the lines that a piece straddles to the L2 to merge (2304 x 768,
 // 4095 tokens in rows of 4095, binary32: 26.8 us with stores at agent scope, 19.9 us at the default scope).
 template <int OUT>
-__device__ __forceinline__ bool takes_fast_stores(const KernelArgs& a)
+__device__ __forceinline__ bool takes_fast_stores(const Args& a)
 {
-    return (OUT == SPMM_OUT_S8 || OUT == SPMM_OUT_U8) ? a.out_vec_ok : a.out_aligned;
+    return (OUT == SPMM_OUT_S8 || OUT == SPMM_OUT_U8) ? a.out_fast : a.out_aligned;
 }
 
 // Post-operators + store for one full token tile of one wave, everything in bounds (4-byte outputs:
@@ -371,7 +449,7 @@ __device__ __forceinline__ bool takes_fast_stores(const KernelArgs& a)
 // 4-byte outputs are stored straight from the accumulator layout (16 bytes per lane, 64-byte
 // runs per row); 1-byte outputs go through the LDS staging chunks.
 template <int TM, int OUT, int POST, int OT = -1>
-__device__ __forceinline__ void finish_tile_fast(const KernelArgs& a, const v4i (&acc)[Geo<TM>::PIECES],
+__device__ __forceinline__ void finish_tile_fast(const Args& a, const v4i (&acc)[Geo<TM>::PIECES],
                                                  const float scale, const float bias, const int tile,
                                                  const int tok0, int lane, const int wave, uint8_t* lds)
 {
@@ -461,8 +539,9 @@ __device__ __forceinline__ void finish_tile_fast(const KernelArgs& a, const v4i 
 }
 
 template <int TM, int NW, int MAXS, int OUT, int POST, int LAYOUT = 0>
-__global__ void __launch_bounds__(NW * 64) spmm_rowtile_mfma(const KernelArgs a)
+__global__ void __launch_bounds__(NW * 64) spmm_rowtile_mfma(const KernelArgs args)
 {
+    const Args a = unpack<OUT>(args);
     using G = Geo<TM>;
     // LAYOUT bit 0: activations token-tile-major; bit 1: (1-byte) outputs token-tile-major
     constexpr int XT = LAYOUT & 1, OTILED = (LAYOUT >> 1) & 1;
@@ -493,7 +572,7 @@ __global__ void __launch_bounds__(NW * 64) spmm_rowtile_mfma(const KernelArgs a)
     // that token tiles next to each other in memory, which share cache lines when the tile width is
     // not a multiple of the line, mostly run on the same XCD
     if (a.xcd_map == 1) stream = (stream & 7) * (S >> 3) + (stream >> 3);
-    const int n_my = a.tiles_per_stream + (stream < a.tiles_extra ? 1 : 0);   // token tiles of this stream (>= 1)
+    const int n_my = a.tiles_per_stream + (stream < (a.M + TM - 1) / TM - a.tiles_per_stream * S ? 1 : 0);   // token tiles of this stream (>= 1)
     const int total = n_my * a.nseg;                                          // phases
 
     const int tile = rg * NW + wave;
@@ -584,8 +663,7 @@ __global__ void __launch_bounds__(NW * 64) spmm_rowtile_mfma(const KernelArgs a)
 #pragma unroll
         for (int s = 0; s < MAXS; ++s) {
             const int step = (s < cnt) ? s0 + s : 0;
-            A[s] = *(const v4i*)(a.vals + (int64_t)step * STEP_VAL_BYTES + lane * 16);
-            I[s] = a.idx[(int64_t)step * STEP_IDX_DWORDS + 8 * g + (c >> 1)];
+            load_step(a, step, lane, A[s], I[s]);
         }
     };
     auto w_issue = [&](const int q, v4i (&A)[MAXS], uint32_t (&I)[MAXS], int& cnt) {
@@ -593,8 +671,8 @@ __global__ void __launch_bounds__(NW * 64) spmm_rowtile_mfma(const KernelArgs a)
         int s0 = 0;
         if (have_tile) {
             const int seg = q % a.nseg;
-            s0 = a.seg_ptr[tile * a.nseg + seg];
-            cnt = a.seg_ptr[tile * a.nseg + seg + 1] - s0;
+            s0 = a.bounds[tile * (a.nseg + 1) + seg];
+            cnt = a.bounds[tile * (a.nseg + 1) + seg + 1] - s0;
         }
         w_issue_at(s0, A, I, cnt);
     };
@@ -607,8 +685,8 @@ __global__ void __launch_bounds__(NW * 64) spmm_rowtile_mfma(const KernelArgs a)
         for (int s = 0; s < MAXS; ++s) {
             if (s < cnt) {
                 // this lane supplies the address of list slot 16g + c/2 (and + 8), token half c & 1
-                const uint32_t a0 = (I[s] & 0xffffu) * G::STRIDE + base;
-                const uint32_t a1 = (I[s] >> 16) * G::STRIDE + base;
+                const uint32_t a0 = first_row(I[s]) * G::STRIDE + base;
+                const uint32_t a1 = second_row(I[s]) * G::STRIDE + base;
 #pragma unroll
                 for (int i = 0; i < PIECES; ++i) {
                     const v2i x0 = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_v2i_ptr)(lds + a0 + 16 * i));
@@ -654,8 +732,8 @@ __global__ void __launch_bounds__(NW * 64) spmm_rowtile_mfma(const KernelArgs a)
         // of the activation loads covers)
         int w_s0 = 0;
         if (have_tile) {
-            w_s0 = a.seg_ptr[tile * a.nseg];
-            n0 = a.seg_ptr[tile * a.nseg + 1] - w_s0;
+            w_s0 = a.bounds[tile * (a.nseg + 1)];
+            n0 = a.bounds[tile * (a.nseg + 1) + 1] - w_s0;
         }
         x_issue_to(xr, 0, 0);
         x_issue_to(x2, 0, 1);
@@ -732,8 +810,9 @@ __global__ void __launch_bounds__(NW * 64) spmm_rowtile_mfma(const KernelArgs a)
 // Both kinds pass exactly 1 + phases barriers.
 // =======================================================================================
 template <int TM, int NW, int LW, int MAXS, int OUT, int POST>
-__global__ void __launch_bounds__((NW + LW) * 64) spmm_rowtile_mfma_fed(const KernelArgs a)
+__global__ void __launch_bounds__((NW + LW) * 64) spmm_rowtile_mfma_fed(const KernelArgs args)
 {
+    const Args a = unpack<OUT>(args);
     using G = Geo<TM>;
     constexpr int PIECES = G::PIECES;
     constexpr int LTHREADS = LW * 64;
@@ -753,7 +832,7 @@ __global__ void __launch_bounds__((NW + LW) * 64) spmm_rowtile_mfma_fed(const Ke
     int stream = (a.xcd_map == 2) ? blockIdx.y : blockIdx.x;
     const int rg = (a.xcd_map == 2) ? blockIdx.x : blockIdx.y;
     if (a.xcd_map == 1) stream = (stream & 7) * (S >> 3) + (stream >> 3);
-    const int n_my = a.tiles_per_stream + (stream < a.tiles_extra ? 1 : 0);
+    const int n_my = a.tiles_per_stream + (stream < (a.M + TM - 1) / TM - a.tiles_per_stream * S ? 1 : 0);
     const int total = n_my * a.nseg;                                          // phases
     constexpr bool TABLE = (POST & SPMM_POST_GELU) != 0 && (OUT == SPMM_OUT_S8 || OUT == SPMM_OUT_U8);
 
@@ -829,14 +908,13 @@ __global__ void __launch_bounds__((NW + LW) * 64) spmm_rowtile_mfma_fed(const Ke
         int s0 = 0;
         if (have_tile) {
             const int seg = q % a.nseg;
-            s0 = a.seg_ptr[tile * a.nseg + seg];
-            cnt = a.seg_ptr[tile * a.nseg + seg + 1] - s0;
+            s0 = a.bounds[tile * (a.nseg + 1) + seg];
+            cnt = a.bounds[tile * (a.nseg + 1) + seg + 1] - s0;
         }
 #pragma unroll
         for (int s = 0; s < MAXS; ++s) {
             const int step = (s < cnt) ? s0 + s : 0;           // unused slots re-read step 0
-            A[s] = *(const v4i*)(a.vals + (int64_t)step * STEP_VAL_BYTES + lane * 16);
-            I[s] = a.idx[(int64_t)step * STEP_IDX_DWORDS + 8 * g + (c >> 1)];
+            load_step(a, step, lane, A[s], I[s]);
         }
     };
     auto multiply = [&](const int q, const v4i (&A)[MAXS], const uint32_t (&I)[MAXS], const int cnt) {
@@ -844,8 +922,8 @@ __global__ void __launch_bounds__((NW + LW) * 64) spmm_rowtile_mfma_fed(const Ke
 #pragma unroll
         for (int s = 0; s < MAXS; ++s) {
             if (s < cnt) {
-                const uint32_t a0 = (I[s] & 0xffffu) * G::STRIDE + base;
-                const uint32_t a1 = (I[s] >> 16) * G::STRIDE + base;
+                const uint32_t a0 = first_row(I[s]) * G::STRIDE + base;
+                const uint32_t a1 = second_row(I[s]) * G::STRIDE + base;
 #pragma unroll
                 for (int i = 0; i < PIECES; ++i) {
                     const v2i x0 = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_v2i_ptr)(lds + a0 + 16 * i));
@@ -907,20 +985,24 @@ __global__ void __launch_bounds__((NW + LW) * 64) spmm_rowtile_mfma_fed(const Ke
 }
 
 // Workgroup id -> (token tile, row group) of the simple and short-batch kernels.  Ids go round the
-// 8 XCDs; map 1 keeps the workgroups of a token tile on one XCD, map 2 those of a row group (the
-// host picks the one that slices the larger operand over the L2s).  False: a padding workgroup.
-__device__ __forceinline__ bool decode_workgroup(const KernelArgs& a, const int b, int& tt, int& rg)
+// 8 XCDs, x fastest, and gridDim.x is a multiple of 8: with map 1 x is the token tile (its workgroups,
+// one per row group, share an XCD), with map 2 the row group (the host picks the one that slices the
+// larger operand over the L2s).  The other axis may exceed what one grid dimension holds: y and z.
+// False: a padding workgroup.
+template <int TM, int ROWS>
+__device__ __forceinline__ bool decode_workgroup(const Args& a, int& tt, int& rg)
 {
-    const int xcd = b & 7, local = b >> 3;
+    const int x = blockIdx.x, yz = (int)(blockIdx.y + (blockIdx.z << GRID_Y_BITS));
+    const int n_tok_tiles = (a.M + TM - 1) / TM, n_row_groups = (a.N + ROWS - 1) / ROWS;
     if (a.xcd_map == 2) {
-        rg = xcd + 8 * (local / a.n_tok_tiles);
-        tt = local % a.n_tok_tiles;
-        return rg < a.n_row_groups;
+        rg = x;
+        tt = yz;
+    } else {
+        // (an XCD takes consecutive token tiles: tiles narrower than a cache line share their lines)
+        tt = (x & 7) * ((n_tok_tiles + 7) >> 3) + (x >> 3);
+        rg = yz;
     }
-    // (an XCD takes consecutive token tiles: tiles narrower than a cache line share their lines)
-    tt = xcd * ((a.n_tok_tiles + 7) >> 3) + local / a.n_row_groups;
-    rg = local % a.n_row_groups;
-    return tt < a.n_tok_tiles;
+    return tt < n_tok_tiles && rg < n_row_groups;
 }
 
 // =======================================================================================
@@ -932,8 +1014,9 @@ __device__ __forceinline__ bool decode_workgroup(const KernelArgs& a, const int 
 // Different tilings must agree bit for bit because int32 accumulation is order-free.
 // =======================================================================================
 template <int TM, int NW, int R, int OUT, int POST>
-__global__ void __launch_bounds__(NW * 64) spmm_rowtile_mfma_simple(const KernelArgs a)
+__global__ void __launch_bounds__(NW * 64) spmm_rowtile_mfma_simple(const KernelArgs args)
 {
+    const Args a = unpack<OUT>(args);
     // row pitch in LDS: 80 / 48 / 48 bytes = 20 / 12 / 12 banks, so that 16 rows whose indices
     // differ mod 16 (the packer's order) start in 16 different groups of four banks
     constexpr int STRIDE = (TM == 16) ? 48 : TM + 16;
@@ -942,7 +1025,7 @@ __global__ void __launch_bounds__(NW * 64) spmm_rowtile_mfma_simple(const Kernel
     __shared__ __attribute__((aligned(16))) uint8_t lds[SEGMENT_ROWS * STRIDE];
 
     int tt, rg;
-    if (!decode_workgroup(a, blockIdx.x, tt, rg)) return;
+    if (!decode_workgroup<TM, NW * R * TILE_ROWS>(a, tt, rg)) return;
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -1005,13 +1088,14 @@ __global__ void __launch_bounds__(NW * 64) spmm_rowtile_mfma_simple(const Kernel
         for (int r = 0; r < R; ++r) {
             const int tile = (rg * NW + wave) * R + r;
             if (tile >= a.ntiles) continue;
-            const int s0 = a.seg_ptr[tile * a.nseg + seg];
-            const int s1 = a.seg_ptr[tile * a.nseg + seg + 1];
+            const int s0 = a.bounds[tile * (a.nseg + 1) + seg];
+            const int s1 = a.bounds[tile * (a.nseg + 1) + seg + 1];
             for (int s = s0; s < s1; ++s) {
-                const v4i w = *(const v4i*)(a.vals + (int64_t)s * STEP_VAL_BYTES + lane * 16);
-                const uint32_t ix = a.idx[(int64_t)s * STEP_IDX_DWORDS + 8 * g + (c >> 1)];
-                const uint32_t a0 = (ix & 0xffffu) * STRIDE + (c & 1) * 8;
-                const uint32_t a1 = (ix >> 16) * STRIDE + (c & 1) * 8;
+                v4i w;
+                uint32_t ix;
+                load_step(a, s, lane, w, ix);
+                const uint32_t a0 = first_row(ix) * STRIDE + (c & 1) * 8;
+                const uint32_t a1 = second_row(ix) * STRIDE + (c & 1) * 8;
 #pragma unroll
                 for (int i = 0; i < PIECES; ++i) {
                     const v2i x0 = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_v2i_ptr)(lds + a0 + 16 * i));
@@ -1061,8 +1145,9 @@ __global__ void __launch_bounds__(NW * 64) spmm_rowtile_mfma_simple(const Kernel
 // TM = 16: 16 bytes per row, up to SLAB_SEGMENTS segments (64 KB).  TM = 32: 48 bytes per row (the
 // pitch of the simple kernel's 32-token tile), up to SLAB_SEGMENTS_32 segments (144 KB).
 template <int TM, int NW, int OUT, int POST>
-__global__ void __launch_bounds__(NW * 64) spmm_rowtile_mfma_slab(const KernelArgs a)
+__global__ void __launch_bounds__(NW * 64) spmm_rowtile_mfma_slab(const KernelArgs args)
 {
+    const Args a = unpack<OUT>(args);
     static_assert(TM == 16 || TM == 32, "token tile of the short-batch kernel");
     constexpr int STRIDE = (TM == 16) ? 16 : 48, PIECES = TM / 16, CH = 8;
     constexpr int SEGS = (TM == 16) ? SLAB_SEGMENTS : SLAB_SEGMENTS_32;
@@ -1070,7 +1155,7 @@ __global__ void __launch_bounds__(NW * 64) spmm_rowtile_mfma_slab(const KernelAr
     __shared__ __attribute__((aligned(16))) uint8_t lds[SEGS * SEGMENT_ROWS * STRIDE];
 
     int tt, rg;
-    if (!decode_workgroup(a, blockIdx.x, tt, rg)) return;
+    if (!decode_workgroup<TM, NW * TILE_ROWS>(a, tt, rg)) return;
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -1083,7 +1168,7 @@ __global__ void __launch_bounds__(NW * 64) spmm_rowtile_mfma_slab(const KernelAr
 
     // lane q holds the first step of segment q of this row tile (q = nseg: one past the last step)
     int bounds = 0;
-    if (have_tile && lane <= a.nseg) bounds = a.seg_ptr[tile * a.nseg + lane];
+    if (have_tile && lane <= a.nseg) bounds = a.bounds[tile * (a.nseg + 1) + lane];
 
     // the slab: PIECES 16-byte pieces per thread and segment (rows past K repeat the last one; no
     // step refers to them)
@@ -1146,8 +1231,7 @@ __global__ void __launch_bounds__(NW * 64) spmm_rowtile_mfma_slab(const KernelAr
         for (int j = 0; j < CH; ++j) {
             int step = s_begin + chunk * CH + j;
             step = (step < s_end) ? step : 0;          // step 0 is always readable
-            A[j] = *(const v4i*)(a.vals + (int64_t)step * STEP_VAL_BYTES + lane * 16);
-            I[j] = a.idx[(int64_t)step * STEP_IDX_DWORDS + 8 * g + (c >> 1)];
+            load_step(a, step, lane, A[j], I[j]);
         }
     };
     w_load(0, A0, I0);
@@ -1179,8 +1263,8 @@ __global__ void __launch_bounds__(NW * 64) spmm_rowtile_mfma_slab(const KernelAr
                     seg_end = __builtin_amdgcn_readlane(bounds, seg + 1);
                 }
                 const uint32_t base = (uint32_t)seg * (SEGMENT_ROWS * STRIDE) + (c & 1) * 8;
-                const uint32_t a0 = (I[j] & 0xffffu) * STRIDE + base;
-                const uint32_t a1 = (I[j] >> 16) * STRIDE + base;
+                const uint32_t a0 = first_row(I[j]) * STRIDE + base;
+                const uint32_t a1 = second_row(I[j]) * STRIDE + base;
 #pragma unroll
                 for (int i = 0; i < PIECES; ++i) {
                     const v2i x0 = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_v2i_ptr)(lds + a0 + 16 * i));
@@ -1225,8 +1309,9 @@ __global__ void __launch_bounds__(NW * 64) spmm_rowtile_mfma_slab(const KernelAr
 // in the drain after it (waves without a row tile, or with fewer steps, only in the drain).
 // =======================================================================================
 template <int TM, int NW, int OUT, int POST>
-__global__ void __launch_bounds__(NW * 64) spmm_rowtile_mfma_stream(const KernelArgs a)
+__global__ void __launch_bounds__(NW * 64) spmm_rowtile_mfma_stream(const KernelArgs args)
 {
+    const Args a = unpack<OUT>(args);
     static_assert(TM == 64 || TM == 32 || TM == 16, "token tile of the streamed kernel");
     constexpr int STRIDE = (TM == 16) ? 16 : TM + 16, PIECES = TM / 16, CH = 8;
     constexpr int XL = SEGMENT_ROWS * PIECES / (NW * 64);
@@ -1234,7 +1319,7 @@ __global__ void __launch_bounds__(NW * 64) spmm_rowtile_mfma_stream(const Kernel
     __shared__ __attribute__((aligned(16))) uint8_t lds[SEGMENT_ROWS * STRIDE];
 
     int tt, rg;
-    if (!decode_workgroup(a, blockIdx.x, tt, rg)) return;
+    if (!decode_workgroup<TM, NW * TILE_ROWS>(a, tt, rg)) return;
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -1248,7 +1333,7 @@ __global__ void __launch_bounds__(NW * 64) spmm_rowtile_mfma_stream(const Kernel
 
     // first step of every segment of this row tile, and one past the last: in LDS-free form only
     // the current boundary is kept (a scalar), fetched when a segment is entered
-    const int32_t* const bounds = a.seg_ptr + (have_tile ? tile * nseg : 0);
+    const int32_t* const bounds = a.bounds + (have_tile ? tile * (nseg + 1) : 0);
     const int s_begin = have_tile ? bounds[0] : 0;
     const int s_end = have_tile ? bounds[nseg] : 0;
     const int nchunks = (s_end - s_begin + CH - 1) / CH;
@@ -1290,8 +1375,7 @@ __global__ void __launch_bounds__(NW * 64) spmm_rowtile_mfma_stream(const Kernel
         for (int j = 0; j < CH; ++j) {
             int step = s_begin + chunk * CH + j;
             step = (step < s_end) ? step : 0;          // step 0 is always readable
-            A[j] = *(const v4i*)(a.vals + (int64_t)step * STEP_VAL_BYTES + lane * 16);
-            I[j] = a.idx[(int64_t)step * STEP_IDX_DWORDS + 8 * g + (c >> 1)];
+            load_step(a, step, lane, A[j], I[j]);
         }
     };
     w_load(0, A0, I0);
@@ -1331,8 +1415,8 @@ __global__ void __launch_bounds__(NW * 64) spmm_rowtile_mfma_stream(const Kernel
             const int step = s_begin + chunk * CH + j;
             if (step < s_end) {
                 while (step >= seg_end && seg + 1 < nseg) advance();     // (also skips empty segments)
-                const uint32_t a0 = (I[j] & 0xffffu) * STRIDE + (c & 1) * 8;
-                const uint32_t a1 = (I[j] >> 16) * STRIDE + (c & 1) * 8;
+                const uint32_t a0 = first_row(I[j]) * STRIDE + (c & 1) * 8;
+                const uint32_t a1 = second_row(I[j]) * STRIDE + (c & 1) * 8;
 #pragma unroll
                 for (int i = 0; i < PIECES; ++i) {
                     const v2i x0 = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_v2i_ptr)(lds + a0 + 16 * i));

@@ -61,9 +61,9 @@ struct FedLaunch {
 }  // namespace
 
 void SPMM_CAT(SPMM_CAT(SPMM_CAT(SPMM_CAT(SPMM_CAT(launch_cfg_fed_, SPMM_CFG_FED_TM), _), SPMM_CFG_NW), _), SPMM_CFG_MAXS)(
-    spmm_out_t out_type, int postop, unsigned grid_x, unsigned grid_y, unsigned block, void* stream, const KernelArgs& a)
+    spmm_out_t out_type, int postop, const unsigned* grid, unsigned block, void* stream, const KernelArgs& a)
 {
-    dispatch_epilogue<FedLaunch<SPMM_CFG_FED_TM, SPMM_CFG_NW, SPMM_CFG_MAXS>>(out_type, postop, dim3(grid_x, grid_y),
+    dispatch_epilogue<FedLaunch<SPMM_CFG_FED_TM, SPMM_CFG_NW, SPMM_CFG_MAXS>>(out_type, postop, dim3(grid[0], grid[1], grid[2]),
                                                                                dim3(block), (hipStream_t)stream, a);
 }
 #elif defined(SPMM_CFG_STREAM)
@@ -77,10 +77,9 @@ struct StreamLaunch {
 };
 }  // namespace
 
-void SPMM_CAT(launch_cfg_stream, SPMM_CFG_STREAM)(spmm_out_t out_type, int postop, unsigned grid_x, unsigned grid_y,
-                                                  unsigned block, void* stream, const KernelArgs& a)
+void SPMM_CAT(launch_cfg_stream, SPMM_CFG_STREAM)(spmm_out_t out_type, int postop, const unsigned* grid, unsigned block, void* stream, const KernelArgs& a)
 {
-    dispatch_epilogue<StreamLaunch>(out_type, postop, dim3(grid_x, grid_y), dim3(block), (hipStream_t)stream, a);
+    dispatch_epilogue<StreamLaunch>(out_type, postop, dim3(grid[0], grid[1], grid[2]), dim3(block), (hipStream_t)stream, a);
 }
 #elif defined(SPMM_CFG_SLAB)
 namespace {
@@ -93,10 +92,10 @@ struct SlabLaunch {
 };
 }  // namespace
 
-void SPMM_CAT(launch_cfg_slab, SPMM_CFG_SLAB)(spmm_out_t out_type, int postop, unsigned grid_x, unsigned grid_y, unsigned block, void* stream,
+void SPMM_CAT(launch_cfg_slab, SPMM_CFG_SLAB)(spmm_out_t out_type, int postop, const unsigned* grid, unsigned block, void* stream,
                      const KernelArgs& a)
 {
-    dispatch_epilogue<SlabLaunch>(out_type, postop, dim3(grid_x, grid_y), dim3(block), (hipStream_t)stream, a);
+    dispatch_epilogue<SlabLaunch>(out_type, postop, dim3(grid[0], grid[1], grid[2]), dim3(block), (hipStream_t)stream, a);
 }
 #elif defined(SPMM_CFG_SIMPLE)
 #ifdef SPMM_CFG_SIMPLE_TM
@@ -117,11 +116,10 @@ struct SimpleLaunch {
 };
 }  // namespace
 
-void SPMM_CAT(SPMM_SIMPLE_NAME, SPMM_CFG_SIMPLE)(spmm_out_t out_type, int postop, unsigned grid_x,
-                                                   unsigned grid_y, unsigned block, void* stream,
+void SPMM_CAT(SPMM_SIMPLE_NAME, SPMM_CFG_SIMPLE)(spmm_out_t out_type, int postop, const unsigned* grid, unsigned block, void* stream,
                                                    const KernelArgs& a)
 {
-    dispatch_epilogue<SimpleLaunch<SPMM_CFG_SIMPLE>>(out_type, postop, dim3(grid_x, grid_y), dim3(block),
+    dispatch_epilogue<SimpleLaunch<SPMM_CFG_SIMPLE>>(out_type, postop, dim3(grid[0], grid[1], grid[2]), dim3(block),
                                                      (hipStream_t)stream, a);
 }
 #else
@@ -133,7 +131,7 @@ struct PipeLaunch {
     {
         // one instantiation per layout of the activations and of 1-byte outputs (row-major / token-tile-major):
         // the 16-wave forms have no register to spare for a choice at run time
-        const int layout = (a.x_tile_stride ? 1 : 0) | (a.out_tile_stride ? 2 : 0);
+        const int layout = ((a.k_flags & ARG_X_TILED) ? 1 : 0) | ((a.k_flags & ARG_OUT_TILED) ? 2 : 0);
         if constexpr (OUT == SPMM_OUT_S8 || OUT == SPMM_OUT_U8) {
             if (layout == 3) { hipLaunchKernelGGL((spmm_rowtile_mfma<TM, NW, MAXS, OUT, POST, 3>), grid, block, 0, st, a); return; }
             if (layout == 2) { hipLaunchKernelGGL((spmm_rowtile_mfma<TM, NW, MAXS, OUT, POST, 2>), grid, block, 0, st, a); return; }
@@ -145,9 +143,9 @@ struct PipeLaunch {
 }  // namespace
 
 void SPMM_CAT(SPMM_CAT(SPMM_CAT(SPMM_CAT(SPMM_CAT(launch_cfg_, SPMM_CFG_TM), _), SPMM_CFG_NW), _), SPMM_CFG_MAXS)(
-    spmm_out_t out_type, int postop, unsigned grid_x, unsigned grid_y, unsigned block, void* stream, const KernelArgs& a)
+    spmm_out_t out_type, int postop, const unsigned* grid, unsigned block, void* stream, const KernelArgs& a)
 {
-    dispatch_epilogue<PipeLaunch<SPMM_CFG_TM, SPMM_CFG_NW, SPMM_CFG_MAXS>>(out_type, postop, dim3(grid_x, grid_y),
+    dispatch_epilogue<PipeLaunch<SPMM_CFG_TM, SPMM_CFG_NW, SPMM_CFG_MAXS>>(out_type, postop, dim3(grid[0], grid[1], grid[2]),
                                                                             dim3(block), (hipStream_t)stream, a);
 }
 #endif

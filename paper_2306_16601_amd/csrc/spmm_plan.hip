@@ -7,7 +7,7 @@
 namespace spmm {
 
 #define SPMM_DECLARE_CFG(name) \
-    void name(spmm_out_t, int postop, unsigned grid_x, unsigned grid_y, unsigned block, void* stream, const KernelArgs&)
+    void name(spmm_out_t, int postop, const unsigned* grid, unsigned block, void* stream, const KernelArgs&)
 SPMM_DECLARE_CFG(launch_cfg_128_16_4);
 SPMM_DECLARE_CFG(launch_cfg_128_16_5);
 SPMM_DECLARE_CFG(launch_cfg_128_16_6);
@@ -237,64 +237,62 @@ Plan make_plan(int64_t M, const WeightDims& w, int num_cus, int force_tm, int va
 int launch_spmm(const Plan& plan, KernelArgs& a, spmm_out_t out_type, int postop, void* stream)
 {
     (void)hipGetLastError();   // an error left by an earlier, unrelated call is not this launch's
-    a.n_tok_tiles = plan.n_tok_tiles;
-    a.n_row_groups = plan.n_row_groups;
-    a.n_streams = plan.n_streams;
-    a.xcd_map = plan.xcd_map;
+    a.n_streams = (uint16_t)plan.n_streams;
+    a.k_flags |= plan.xcd_map == 2 ? ARG_XCD_MAP_2 : plan.xcd_map == 1 ? ARG_XCD_MAP_1 : 0;
     const unsigned block = (unsigned)(plan.waves + plan.loaders) * 64;
     if (plan.simple) {
-        const unsigned grid = (unsigned)plan.workgroups;
+        // x: the axis that goes round the XCDs (see decode_workgroup), y and z: the other one
+        const unsigned x = 8u * (((unsigned)(plan.xcd_map == 2 ? plan.n_row_groups : plan.n_tok_tiles) + 7) / 8);
+        const unsigned other = (unsigned)(plan.xcd_map == 2 ? plan.n_tok_tiles : plan.n_row_groups);
+        const unsigned y = other < (1u << GRID_Y_BITS) ? other : (1u << GRID_Y_BITS);
+        const unsigned grid[3] = {x, y, (other + y - 1) / y};
         const int key = plan.token_tile * 10 + plan.row_tiles_per_wave;
         if (plan.stream) {
-            if (a.kc != SEGMENT_ROWS) return (int)hipErrorInvalidValue;
-            if (key == 641) launch_cfg_stream64(out_type, postop, grid, 1, block, stream, a);
-            else if (key == 321) launch_cfg_stream32(out_type, postop, grid, 1, block, stream, a);
-            else if (key == 161) launch_cfg_stream16(out_type, postop, grid, 1, block, stream, a);
+            if (key == 641) launch_cfg_stream64(out_type, postop, grid, block, stream, a);
+            else if (key == 321) launch_cfg_stream32(out_type, postop, grid, block, stream, a);
+            else if (key == 161) launch_cfg_stream16(out_type, postop, grid, block, stream, a);
             else return (int)hipErrorInvalidValue;
         } else if (plan.slab) {
-            if (a.kc != SEGMENT_ROWS) return (int)hipErrorInvalidValue;
-            if (key == 161 && a.nseg <= SLAB_SEGMENTS) launch_cfg_slab16(out_type, postop, grid, 1, block, stream, a);
-            else if (key == 321 && a.nseg <= SLAB_SEGMENTS_32) launch_cfg_slab32(out_type, postop, grid, 1, block, stream, a);
+            if (key == 161) launch_cfg_slab16(out_type, postop, grid, block, stream, a);
+            else if (key == 321) launch_cfg_slab32(out_type, postop, grid, block, stream, a);
             else return (int)hipErrorInvalidValue;
-        } else if (key == 641) launch_cfg_simple_1(out_type, postop, grid, 1, block, stream, a);
-        else if (key == 642) launch_cfg_simple_2(out_type, postop, grid, 1, block, stream, a);
-        else if (key == 321) launch_cfg_simple32_1(out_type, postop, grid, 1, block, stream, a);
-        else if (key == 161) launch_cfg_simple16_1(out_type, postop, grid, 1, block, stream, a);
+        } else if (key == 641) launch_cfg_simple_1(out_type, postop, grid, block, stream, a);
+        else if (key == 642) launch_cfg_simple_2(out_type, postop, grid, block, stream, a);
+        else if (key == 321) launch_cfg_simple32_1(out_type, postop, grid, block, stream, a);
+        else if (key == 161) launch_cfg_simple16_1(out_type, postop, grid, block, stream, a);
         else return (int)hipErrorInvalidValue;
         return (int)hipGetLastError();
     }
-    if (a.kc != SEGMENT_ROWS) return (int)hipErrorInvalidValue;
     // 2-D grid: x = token-tile stream, y = row group
-    unsigned gx = (unsigned)plan.n_streams, gy = (unsigned)plan.n_row_groups;
-    if (plan.xcd_map == 2) { gx = (unsigned)plan.n_row_groups; gy = (unsigned)plan.n_streams; }
-    a.tiles_per_stream = plan.n_tok_tiles / plan.n_streams;
-    a.tiles_extra = plan.n_tok_tiles % plan.n_streams;
+    const unsigned S = (unsigned)plan.n_streams, rg = (unsigned)plan.n_row_groups;
+    const unsigned grid[3] = {plan.xcd_map == 2 ? rg : S, plan.xcd_map == 2 ? S : rg, 1};
+    a.tiles_per_stream = (uint32_t)(plan.n_tok_tiles / plan.n_streams);
     const int maxs = (plan.waves == 8 && plan.max_steps == 5) ? 6 : plan.max_steps;   // no 8-wave 5-step build
     if (plan.loaders) {
         switch (plan.token_tile * 10000 + plan.waves * 100 + maxs) {
-        case 1281204: launch_cfg_fed_128_12_4(out_type, postop, gx, gy, block, stream, a); break;
-        case 1281206: launch_cfg_fed_128_12_6(out_type, postop, gx, gy, block, stream, a); break;
-        case 1280804: launch_cfg_fed_128_8_4(out_type, postop, gx, gy, block, stream, a); break;
-        case 1280806: launch_cfg_fed_128_8_6(out_type, postop, gx, gy, block, stream, a); break;
-        case 1280808: launch_cfg_fed_128_8_8(out_type, postop, gx, gy, block, stream, a); break;
-        case 961204: launch_cfg_fed_96_12_4(out_type, postop, gx, gy, block, stream, a); break;
-        case 961206: launch_cfg_fed_96_12_6(out_type, postop, gx, gy, block, stream, a); break;
-        case 641204: launch_cfg_fed_64_12_4(out_type, postop, gx, gy, block, stream, a); break;
-        case 641206: launch_cfg_fed_64_12_6(out_type, postop, gx, gy, block, stream, a); break;
+        case 1281204: launch_cfg_fed_128_12_4(out_type, postop, grid, block, stream, a); break;
+        case 1281206: launch_cfg_fed_128_12_6(out_type, postop, grid, block, stream, a); break;
+        case 1280804: launch_cfg_fed_128_8_4(out_type, postop, grid, block, stream, a); break;
+        case 1280806: launch_cfg_fed_128_8_6(out_type, postop, grid, block, stream, a); break;
+        case 1280808: launch_cfg_fed_128_8_8(out_type, postop, grid, block, stream, a); break;
+        case 961204: launch_cfg_fed_96_12_4(out_type, postop, grid, block, stream, a); break;
+        case 961206: launch_cfg_fed_96_12_6(out_type, postop, grid, block, stream, a); break;
+        case 641204: launch_cfg_fed_64_12_4(out_type, postop, grid, block, stream, a); break;
+        case 641206: launch_cfg_fed_64_12_6(out_type, postop, grid, block, stream, a); break;
         default: return (int)hipErrorInvalidValue;
         }
         return (int)hipGetLastError();
     }
     switch (plan.token_tile * 10000 + plan.waves * 100 + maxs) {
-    case 1281604: launch_cfg_128_16_4(out_type, postop, gx, gy, block, stream, a); break;
-    case 1281605: launch_cfg_128_16_5(out_type, postop, gx, gy, block, stream, a); break;
-    case 1281606: launch_cfg_128_16_6(out_type, postop, gx, gy, block, stream, a); break;
-    case 1280804: launch_cfg_128_8_4(out_type, postop, gx, gy, block, stream, a); break;
-    case 1280806: launch_cfg_128_8_6(out_type, postop, gx, gy, block, stream, a); break;
-    case 1280808: launch_cfg_128_8_8(out_type, postop, gx, gy, block, stream, a); break;
-    case 961604: launch_cfg_96_16_4(out_type, postop, gx, gy, block, stream, a); break;
-    case 961605: launch_cfg_96_16_5(out_type, postop, gx, gy, block, stream, a); break;
-    case 961606: launch_cfg_96_16_6(out_type, postop, gx, gy, block, stream, a); break;
+    case 1281604: launch_cfg_128_16_4(out_type, postop, grid, block, stream, a); break;
+    case 1281605: launch_cfg_128_16_5(out_type, postop, grid, block, stream, a); break;
+    case 1281606: launch_cfg_128_16_6(out_type, postop, grid, block, stream, a); break;
+    case 1280804: launch_cfg_128_8_4(out_type, postop, grid, block, stream, a); break;
+    case 1280806: launch_cfg_128_8_6(out_type, postop, grid, block, stream, a); break;
+    case 1280808: launch_cfg_128_8_8(out_type, postop, grid, block, stream, a); break;
+    case 961604: launch_cfg_96_16_4(out_type, postop, grid, block, stream, a); break;
+    case 961605: launch_cfg_96_16_5(out_type, postop, grid, block, stream, a); break;
+    case 961606: launch_cfg_96_16_6(out_type, postop, grid, block, stream, a); break;
     default: return (int)hipErrorInvalidValue;
     }
     return (int)hipGetLastError();
