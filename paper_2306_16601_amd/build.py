@@ -20,15 +20,14 @@ NATIVE_SOURCE = os.path.join(CSRC, "native_call.c")
 OBJDIR = os.path.join(HERE, "_build")
 
 HOST_SOURCES = ["api.cpp", "pack.cpp", "spmm_plan.hip", "spmm_peak.hip"]
-# (token tile, waves, step slots) of the pipelined kernel; row tiles per wave of the simple kernel
+# (token tile, waves, step slots) of the pipelined kernel
 PIPELINED = [(128, 16, 4), (128, 16, 5), (128, 16, 6), (128, 8, 4), (128, 8, 6), (128, 8, 8),
              (96, 16, 4), (96, 16, 5), (96, 16, 6)]
 # (token tile, compute waves, step slots) of the pipelined kernel with 4 loader waves
 FED = [(128, 12, 4), (128, 12, 6), (128, 8, 4), (128, 8, 6), (128, 8, 8), (96, 12, 4), (96, 12, 6), (64, 12, 4), (64, 12, 6)]
-SIMPLE = [1, 2]
+SIMPLE = [(64, 1), (64, 2), (32, 1), (16, 1)]      # (token tile, row tiles per wave) of the simple kernel
 SLAB = [16, 32]            # token tiles of the short-batch kernel
 STREAM = [64, 32, 16]      # token tiles of the streamed kernel
-SIMPLE_NARROW = [32, 16]   # token tiles of the simple kernel besides 64 (one row tile per wave)
 HEADERS = [os.path.join(CSRC, "spmm_internal.h"), os.path.join(CSRC, "spmm_kernels.h"),
            os.path.join(ROOT, "include", "spmm.h")]
 
@@ -49,10 +48,8 @@ def units():
         out.append((f"cfg_{tm}_{nw}_{maxs}.o", cfg, [f"-DSPMM_CFG_TM={tm}", f"-DSPMM_CFG_NW={nw}", f"-DSPMM_CFG_MAXS={maxs}"]))
     for tm, nw, maxs in FED:
         out.append((f"cfg_fed_{tm}_{nw}_{maxs}.o", cfg, [f"-DSPMM_CFG_FED_TM={tm}", f"-DSPMM_CFG_NW={nw}", f"-DSPMM_CFG_MAXS={maxs}"]))
-    for r in SIMPLE:
-        out.append((f"cfg_simple_{r}.o", cfg, [f"-DSPMM_CFG_SIMPLE={r}"]))
-    for tm in SIMPLE_NARROW:
-        out.append((f"cfg_simple{tm}_1.o", cfg, ["-DSPMM_CFG_SIMPLE=1", f"-DSPMM_CFG_SIMPLE_TM={tm}"]))
+    for tm, r in SIMPLE:
+        out.append((f"cfg_simple_{tm}_{r}.o", cfg, [f"-DSPMM_CFG_SIMPLE={r}", f"-DSPMM_CFG_SIMPLE_TM={tm}"]))
     for tm in SLAB:
         out.append((f"cfg_slab{tm}.o", cfg, [f"-DSPMM_CFG_SLAB={tm}"]))
     for tm in STREAM:

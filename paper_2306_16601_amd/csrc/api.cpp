@@ -383,13 +383,13 @@ spmm_status_t spmm_kernel_variant_tiled(const spmm_handle_t* h, int64_t M, spmm_
     const int post = (out_type == SPMM_OUT_S32) ? 0 : (int)postop;   // S32 output ignores the post-operator
     if (p.stream)
         std::snprintf(buf, (size_t)buflen, "void spmm::spmm_rowtile_mfma_stream<%d, %d, %d, %d>(spmm::KernelArgs)",
-                      p.token_tile, p.waves, (int)out_type, post);
+                      p.token_tile, 8, (int)out_type, post);
     else if (p.slab)
         std::snprintf(buf, (size_t)buflen, "void spmm::spmm_rowtile_mfma_slab<%d, %d, %d, %d>(spmm::KernelArgs)",
-                      p.token_tile, p.waves, (int)out_type, post);
+                      p.token_tile, 8, (int)out_type, post);
     else if (p.simple)
         std::snprintf(buf, (size_t)buflen, "void spmm::spmm_rowtile_mfma_simple<%d, %d, %d, %d, %d>(spmm::KernelArgs)",
-                      p.token_tile, p.waves, p.row_tiles_per_wave, (int)out_type, post);
+                      p.token_tile, 8, p.row_tiles_per_wave, (int)out_type, post);
     else if (p.loaders)
         std::snprintf(buf, (size_t)buflen, "void spmm::spmm_rowtile_mfma_fed<%d, %d, %d, %d, %d, %d>(spmm::KernelArgs)",
                       p.token_tile, p.waves, p.loaders, p.max_steps, (int)out_type, post);

@@ -96,20 +96,20 @@ struct KernelArgs {
     int32_t M, N;
     uint32_t k_flags;           // K (17 bits), ARG_* flags, x_zero_point << 24
     float x_scale, inv, out_zp_f;   // inv: 1 / out_scale, or 1 / mid_scale of a table chain
-    uint16_t n_streams;         // persistent kernels: workgroups per row group, each walking token tiles j * n_streams + stream
+    uint16_t n_streams;         // persistent kernels: workgroups per row group, each walking token tiles j * n_streams + stream;
+                                // short-batch kernels: row tiles per workgroup
     uint16_t tile_steps;
     uint32_t tiles_per_stream;  // token tiles / n_streams, rounded down
 };
 static_assert(sizeof(KernelArgs) == 96, "kernel arguments");
 constexpr int ARG_K_BITS = 17;
-constexpr int GRID_Y_BITS = 15;                  // of the simple and short-batch kernels' grids: the rest goes into z
+constexpr int GRID_Y_BITS = 15;                  // of the token axis of a grid: the rest goes into z
 constexpr uint32_t ARG_X_TILED = 1u << 17;      // X token-tile-major [ceil(M/32)][K][32], ldx = 32; else row-major [K][ldx]
 constexpr uint32_t ARG_OUT_TILED = 1u << 18;    // 1-byte out token-tile-major [ceil(M/32)][N][32], ldo = 32; else row-major [N][ldo]
 constexpr uint32_t ARG_X_FAST = 1u << 19;       // the rows of one segment lie within 2^31 bytes, and X has 16: 32-bit offsets
 constexpr uint32_t ARG_OUT_FAST = 1u << 20;     // whole output < 2^31 bytes (and, with Sum, the second operand too)
 constexpr uint32_t ARG_OUT_ALIGNED = 1u << 21;  // ARG_OUT_FAST, out base 16-byte aligned and row pitch a multiple of 16 bytes
-constexpr uint32_t ARG_XCD_MAP_2 = 1u << 22;    // how a workgroup id decodes, see the kernels
-constexpr uint32_t ARG_XCD_MAP_1 = 1u << 23;
+constexpr int ARG_XCD_SHIFT = 22;               // 2 bits: how a workgroup id decodes, see decode_workgroup
 
 struct Plan {
     int token_tile;          // TM of the pipelined kernel (128 or 96), or 64 for the simple kernel
@@ -120,7 +120,8 @@ struct Plan {
     int slab;                // 1: the short-batch kernel (token tile 16 or 32, whole K resident in LDS) in its place
     int stream;              // 1: the streamed kernel (segment staging, flat weight stream) in its place
     int max_steps;           // unroll bound of the per-segment step loop (pipelined kernel)
-    int n_row_groups, n_tok_tiles, n_streams, xcd_map;
+    int n_row_groups, n_tok_tiles, n_streams;
+    int xcd_row_bits;        // the 8 XCDs take 2^this slices of the row groups and 8 / 2^this of the tokens
     int64_t workgroups;
 };
 

@@ -45,6 +45,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <type_traits>
 
 #include "spmm_internal.h"
 
@@ -64,8 +65,9 @@ struct Args {
     int64_t ldx, ldo, ld_sum;
     int64_t x_last16;           // offset of the last 16 bytes of X: no 16-byte read goes beyond them (negative: X has fewer)
     int N, K, M, nseg, ntiles, tile_steps;
-    int n_streams, tiles_per_stream;
-    int xcd_map;
+    int n_streams, tiles_per_stream;   // persistent kernels
+    int wg_tiles;               // short-batch kernels: row tiles (or pairs of them) per workgroup
+    int xcd_row_bits;           // the 8 XCDs take 2^this slices of the row groups x 8 / 2^this slices of the tokens
     int corr_mul;               // 128 - x_zero_point: the activations are multiplied as (x - 128)
     float x_scale, inv, out_zp_f;
     bool x_fast, out_fast, out_aligned;
@@ -106,12 +108,13 @@ __device__ __forceinline__ Args unpack(const KernelArgs& p)
     a.x_fast = p.k_flags & ARG_X_FAST;
     a.out_fast = p.k_flags & ARG_OUT_FAST;
     a.out_aligned = p.k_flags & ARG_OUT_ALIGNED;
-    a.xcd_map = (p.k_flags & ARG_XCD_MAP_2) ? 2 : (p.k_flags & ARG_XCD_MAP_1) ? 1 : 0;
+    a.xcd_row_bits = (int)(p.k_flags >> ARG_XCD_SHIFT & 3);
     a.corr_mul = 128 - (int)(p.k_flags >> 24);
     a.x_scale = p.x_scale;
     a.inv = p.inv;
     a.out_zp_f = p.out_zp_f;
     a.n_streams = p.n_streams;
+    a.wg_tiles = p.n_streams;
     a.tiles_per_stream = (int)p.tiles_per_stream;
     return a;
 }
@@ -167,6 +170,11 @@ struct GlobalLut {
     __device__ __forceinline__ uint32_t operator()(uint32_t key) const { return (uint8_t)p[key]; }
 };
 
+struct LdsTable {
+    const uint8_t* p;
+    __device__ __forceinline__ uint32_t operator()(uint32_t key) const { return p[key]; }
+};
+
 // POST template parameters below are the SPMM_POST_* value, plus POST_SUM_BIT when the Sum
 // post-operator (a second binary32 tensor added after BiasAdd / GeLU, before Quantize) is on.
 
@@ -212,14 +220,33 @@ __device__ __forceinline__ uint32_t quantise(const Args& a, const float y, const
     }
 }
 
+// The second operand of Sum for tokens m0 .. m0 + 3 of output row n (none of it is read outside [N][M])
+template <int POST>
+__device__ __forceinline__ v4f load_sum4(const Args& a, const int n, const int m0)
+{
+    v4f v = {0.0f, 0.0f, 0.0f, 0.0f};
+    if constexpr ((POST & POST_SUM_BIT) != 0) {
+        const float* sp = a.sum + (int64_t)n * a.ld_sum + m0;
+        if (m0 + 4 <= a.M) {
+            v = ((const v4f_any*)sp)->v;
+        } else {
+#pragma unroll
+            for (int r = 0; r < 3; ++r)
+                if (m0 + r < a.M) v[r] = sp[r];
+        }
+    }
+    return v;
+}
+
 // Generic post-operators + store for 4 consecutive tokens m0..m0+3 of output row n: any
 // alignment, any tail (the slow path of every kernel).
 // WIDE: 4-byte outputs whose 16-byte pieces are aligned go out at agent scope (see out_resource);
 // costs registers the 16-wave pipelined kernels do not have (their full tiles take finish_tile_fast).
 // OT: layout of a 1-byte output: 1 = token-tile-major, 0 = row-major, -1 = whichever the arguments say
+// sum4: the operand of Sum for these tokens (load_sum4), where there is one.
 template <int OUT, int POST, bool WIDE = false, int OT = -1, typename Lut>
 __device__ __forceinline__ void finish4(const Args& a, const v4i acc, const float s, const float b,
-                                        const int n, const int m0, const Lut& lut)
+                                        const int n, const int m0, const Lut& lut, const v4f sum4)
 {
     const int valid = a.M - m0;   // > 0 guaranteed by caller
     if constexpr (OUT == SPMM_OUT_S32) {
@@ -241,10 +268,8 @@ __device__ __forceinline__ void finish4(const Args& a, const v4i acc, const floa
             for (int r = 0; r < 4; ++r) y[r] = gelu_f32(y[r]);
         }
         if constexpr ((POST & POST_SUM_BIT) != 0) {
-            const float* sp = a.sum + (int64_t)n * a.ld_sum + m0;
 #pragma unroll
-            for (int r = 0; r < 4; ++r)
-                if (r < valid) y[r] = y[r] + sp[r];
+            for (int r = 0; r < 4; ++r) y[r] = y[r] + sum4[r];
         }
         if constexpr (OUT == SPMM_OUT_F32) {
             float* o = (float*)a.out + (int64_t)n * a.ldo + m0;
@@ -365,6 +390,22 @@ __device__ __forceinline__ v4i load_x16_far(const Args& a, const int row, const 
     for (int j = 0; j < 16; ++j)
         if (col + j < a.M) v[j >> 2] |= (int)((uint32_t)a.X[off + j] << (8 * (j & 3)));
     return v;
+}
+
+// Workgroup id -> (row group, token tile or stream).  Workgroups go round the 8 XCDs, each with an L2 of its
+// own, in linear order (x fastest, gridDim.x a multiple of 8): XCD x & 7 takes one of 2^xcd_row_bits slices of the
+// row groups and one of the 8 / 2^xcd_row_bits slices of the tokens, so every XCD reads that share of the packed
+// weight and of the activations through its L2 and no more (the host picks the split that reads least).
+// Neighbouring token tiles stay on one XCD: tiles narrower than a cache line share their lines.
+// The token axis may exceed one grid dimension: y and z.  False: a padding workgroup.
+__device__ __forceinline__ bool decode_workgroup(const Args& a, const int n_row_groups, const int n_tokens, int& rg, int& tt)
+{
+    const int xcd = blockIdx.x & 7, rb = a.xcd_row_bits, tb = 3 - rb;
+    const int rows = (n_row_groups + (1 << rb) - 1) >> rb, toks = (n_tokens + (1 << tb) - 1) >> tb;
+    const int r = (int)(blockIdx.x >> 3), t = (int)(blockIdx.y + (blockIdx.z << GRID_Y_BITS));
+    rg = (xcd & ((1 << rb) - 1)) * rows + r;
+    tt = (xcd >> rb) * toks + t;
+    return rg < n_row_groups && t < toks && tt < n_tokens;
 }
 
 // =======================================================================================
@@ -560,18 +601,10 @@ __global__ void __launch_bounds__(NW * 64) spmm_rowtile_mfma(const KernelArgs ar
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int g = lane >> 4, c = lane & 15;
 
-    // workgroup -> (token-tile stream, row group) = (blockIdx.x, blockIdx.y).  Workgroups go to the
-    // 8 XCDs round-robin in linear order (x fastest); the host makes gridDim.x a multiple of 8
-    // whenever it can, so that all row groups of one stream run on the same XCD and share its L2.
-    // With xcd_map 2 the two roles are swapped (all streams of a row group on one XCD): the host's
-    // choice when the packed weight is the larger operand.
+    // workgroup -> (row group, token-tile stream)
     const int S = a.n_streams;
-    int stream = (a.xcd_map == 2) ? blockIdx.y : blockIdx.x;
-    const int rg = (a.xcd_map == 2) ? blockIdx.x : blockIdx.y;
-    // map 1 (S is then a multiple of 8): XCD x gets the S / 8 consecutive streams from x * S / 8 on, so
-    // that token tiles next to each other in memory, which share cache lines when the tile width is
-    // not a multiple of the line, mostly run on the same XCD
-    if (a.xcd_map == 1) stream = (stream & 7) * (S >> 3) + (stream >> 3);
+    int stream, rg;
+    if (!decode_workgroup(a, (a.ntiles + NW - 1) / NW, S, rg, stream)) return;
     const int n_my = a.tiles_per_stream + (stream < (a.M + TM - 1) / TM - a.tiles_per_stream * S ? 1 : 0);   // token tiles of this stream (>= 1)
     const int total = n_my * a.nseg;                                          // phases
 
@@ -702,7 +735,7 @@ __global__ void __launch_bounds__(NW * 64) spmm_rowtile_mfma(const KernelArgs ar
         }
     };
     // ---- after the last segment of a token tile: post-operators, store, reset accumulators
-    auto finish = [&](const int q) {
+    auto finish = [&](const int q) __attribute__((always_inline)) {
         const int j = q / a.nseg;
         if (q - j * a.nseg != a.nseg - 1) return;
         const bool fast_out = takes_fast_stores<OUT>(a);
@@ -715,7 +748,7 @@ __global__ void __launch_bounds__(NW * 64) spmm_rowtile_mfma(const KernelArgs ar
 #pragma unroll
                 for (int i = 0; i < PIECES; ++i) {
                     const int m0 = tok0 + 16 * i + 4 * g;
-                    if (m0 < a.M) finish4<OUT, POST, NW != 16, OTILED>(a, acc[i], scale, bias, n, m0, lut);
+                    if (m0 < a.M) finish4<OUT, POST, NW != 16, OTILED>(a, acc[i], scale, bias, n, m0, lut, load_sum4<POST>(a, n, m0));
                 }
             }
         }
@@ -816,8 +849,8 @@ __global__ void __launch_bounds__((NW + LW) * 64) spmm_rowtile_mfma_fed(const Ke
     using G = Geo<TM>;
     constexpr int PIECES = G::PIECES;
     constexpr int LTHREADS = LW * 64;
-    constexpr int ROWS_PER_PASS = 32;
-    constexpr int STAGERS = ROWS_PER_PASS * PIECES;              // 256 (128 tokens) or 192 (96 tokens)
+    constexpr int ROWS_PER_PASS = TM == 64 ? 64 : 32;
+    constexpr int STAGERS = ROWS_PER_PASS * PIECES;              // 256 (128 or 64 tokens) or 192 (96 tokens)
     constexpr int XLOADS = SEGMENT_ROWS / ROWS_PER_PASS;         // 16-byte loads per staging thread and phase
     static_assert(STAGERS <= LTHREADS, "the loader waves must cover one pass of rows");
     __shared__ __attribute__((aligned(16))) uint8_t lds[G::LDS];
@@ -827,11 +860,10 @@ __global__ void __launch_bounds__((NW + LW) * 64) spmm_rowtile_mfma_fed(const Ke
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int g = lane >> 4, c = lane & 15;
 
-    // workgroup -> (token-tile stream, row group): as in spmm_rowtile_mfma
+    // workgroup -> (row group, token-tile stream)
     const int S = a.n_streams;
-    int stream = (a.xcd_map == 2) ? blockIdx.y : blockIdx.x;
-    const int rg = (a.xcd_map == 2) ? blockIdx.x : blockIdx.y;
-    if (a.xcd_map == 1) stream = (stream & 7) * (S >> 3) + (stream >> 3);
+    int stream, rg;
+    if (!decode_workgroup(a, (a.ntiles + NW - 1) / NW, S, rg, stream)) return;
     const int n_my = a.tiles_per_stream + (stream < (a.M + TM - 1) / TM - a.tiles_per_stream * S ? 1 : 0);
     const int total = n_my * a.nseg;                                          // phases
     constexpr bool TABLE = (POST & SPMM_POST_GELU) != 0 && (OUT == SPMM_OUT_S8 || OUT == SPMM_OUT_U8);
@@ -900,27 +932,39 @@ __global__ void __launch_bounds__((NW + LW) * 64) spmm_rowtile_mfma_fed(const Ke
     float scale = 0.0f, bias = 0.0f;
     v4i A0[MAXS], A1[MAXS];
     uint32_t I0[MAXS], I1[MAXS];
-    int n0 = 0, n1 = 0;
     v4i acc[PIECES];
 
-    auto w_issue = [&](const int q, v4i (&A)[MAXS], uint32_t (&I)[MAXS], int& cnt) {
-        cnt = 0;
-        int s0 = 0;
-        if (have_tile) {
-            const int seg = q % a.nseg;
-            s0 = a.bounds[tile * (a.nseg + 1) + seg];
-            cnt = a.bounds[tile * (a.nseg + 1) + seg + 1] - s0;
+    // Steps of (tile, segment of phase q).  Read a phase before they are needed: a scalar load whose latency would
+    // otherwise precede every phase's weights.
+    struct Range { int first, count; };
+    auto range_of = [&](const int q) {
+        Range r = {0, 0};
+        if (have_tile && q < total) {
+            const int32_t* const b = a.bounds + (int64_t)tile * (a.nseg + 1) + q % a.nseg;
+            r.first = b[0];
+            r.count = b[1] - r.first;
         }
-#pragma unroll
-        for (int s = 0; s < MAXS; ++s) {
-            const int step = (s < cnt) ? s0 + s : 0;           // unused slots re-read step 0
-            load_step(a, step, lane, A[s], I[s]);
-        }
+        return r;
     };
-    auto multiply = [&](const int q, const v4i (&A)[MAXS], const uint32_t (&I)[MAXS], const int cnt) {
+    auto w_issue = [&](const Range r, v4i (&A)[MAXS], uint32_t (&I)[MAXS]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int s = 0; s < MAXS; ++s)
+            if (s < r.count) load_step(a, r.first + s, lane, A[s], I[s]);
+    };
+    // Multiply phase q.  With LOAD the weights of the next phase are requested on the way, two step slots at a time:
+    // issued in one go they kept the wave from its first gather for as long as the CU's address path took to
+    // work through everyone's requests (4096 x 4096 at 85 %, 1024 tokens, cycles per phase: 1000-1350 issuing, then
+    // 1800-2150 multiplying).  They have landed when the phase ends, and are waited for there, before any store.
+    auto multiply = [&](auto LOAD, const int q, const v4i (&A)[MAXS], const uint32_t (&I)[MAXS], const int cnt,
+                        v4i (&An)[MAXS], uint32_t (&In)[MAXS], const Range next) __attribute__((always_inline)) {
         const uint32_t base = G::X0 + (uint32_t)(q & 1) * G::BUF + (c & 1) * 8;
 #pragma unroll
         for (int s = 0; s < MAXS; ++s) {
+            if constexpr (LOAD.value) {
+#pragma unroll
+                for (int l = 2 * s; l < min(2 * s + 2, MAXS); ++l)
+                    if (l < next.count) load_step(a, next.first + l, lane, An[l], In[l]);
+            }
             if (s < cnt) {
                 const uint32_t a0 = first_row(I[s]) * G::STRIDE + base;
                 const uint32_t a1 = second_row(I[s]) * G::STRIDE + base;
@@ -934,7 +978,7 @@ __global__ void __launch_bounds__((NW + LW) * 64) spmm_rowtile_mfma_fed(const Ke
             }
         }
     };
-    auto finish = [&](const int q) {
+    auto finish = [&](const int q) __attribute__((always_inline)) {
         const int j = q / a.nseg;
         if (q - j * a.nseg != a.nseg - 1) return;
         const bool fast_out = takes_fast_stores<OUT>(a);
@@ -947,16 +991,15 @@ __global__ void __launch_bounds__((NW + LW) * 64) spmm_rowtile_mfma_fed(const Ke
 #pragma unroll
                 for (int i = 0; i < PIECES; ++i) {
                     const int m0 = tok0 + 16 * i + 4 * g;
-                    if (m0 < a.M) finish4<OUT, POST, false>(a, acc[i], scale, bias, n, m0, lut);
+                    if (m0 < a.M) finish4<OUT, POST, false>(a, acc[i], scale, bias, n, m0, lut, load_sum4<POST>(a, n, m0));
                 }
             }
         }
 #pragma unroll
         for (int i = 0; i < PIECES; ++i) acc[i] = (v4i){init, init, init, init};
     };
-    const bool reload = a.nseg > 2;   // otherwise register set q % 2 always holds segment q % nseg
-
-    w_issue(0, A0, I0, n0);
+    Range r0 = range_of(0), r1 = range_of(1);
+    w_issue(r0, A0, I0);
     if (have_tile) init = a.rowsum[n] * a.corr_mul;
     if constexpr (OUT != SPMM_OUT_S32) {
         if (have_tile && n < a.N) {
@@ -966,488 +1009,446 @@ __global__ void __launch_bounds__((NW + LW) * 64) spmm_rowtile_mfma_fed(const Ke
     }
 #pragma unroll
     for (int i = 0; i < PIECES; ++i) acc[i] = (v4i){init, init, init, init};
-    __syncthreads();
-    for (int p = 0; p < total; p += 2) {
-        {   // even phase: register set 0, LDS buffer 0
-            if (p + 1 < total && (reload || p + 1 < 2)) w_issue(p + 1, A1, I1, n1);
-            multiply(p, A0, I0, n0);
-            finish(p);
-            __syncthreads();
+    // register set p % 2 holds the weights of phase p: with at most two segments for the whole kernel, otherwise
+    // reloaded a phase ahead
+    auto phases = [&](auto RELOAD) __attribute__((always_inline)) {
+        if constexpr (!RELOAD.value) w_issue(r1, A1, I1);
+        __syncthreads();
+        for (int p = 0; p < total; p += 2) {
+            {   // even phase: register set 0, LDS buffer 0
+                const int cnt = r0.count;
+                if constexpr (RELOAD.value) r0 = range_of(p + 2);
+                multiply(RELOAD, p, A0, I0, cnt, A1, I1, r1);
+                if constexpr (RELOAD.value) wait_global_loads();
+                finish(p);
+                __syncthreads();
+            }
+            if (p + 1 >= total) break;
+            {   // odd phase: register set 1, LDS buffer 1
+                const int cnt = r1.count;
+                if constexpr (RELOAD.value) r1 = range_of(p + 3);
+                multiply(RELOAD, p + 1, A1, I1, cnt, A0, I0, r0);
+                if constexpr (RELOAD.value) wait_global_loads();
+                finish(p + 1);
+                __syncthreads();
+            }
         }
-        if (p + 1 >= total) break;
-        {   // odd phase: register set 1, LDS buffer 1
-            if (p + 2 < total && reload) w_issue(p + 2, A0, I0, n0);
-            multiply(p + 1, A1, I1, n1);
-            finish(p + 1);
-            __syncthreads();
-        }
-    }
-}
-
-// Workgroup id -> (token tile, row group) of the simple and short-batch kernels.  Ids go round the
-// 8 XCDs, x fastest, and gridDim.x is a multiple of 8: with map 1 x is the token tile (its workgroups,
-// one per row group, share an XCD), with map 2 the row group (the host picks the one that slices the
-// larger operand over the L2s).  The other axis may exceed what one grid dimension holds: y and z.
-// False: a padding workgroup.
-template <int TM, int ROWS>
-__device__ __forceinline__ bool decode_workgroup(const Args& a, int& tt, int& rg)
-{
-    const int x = blockIdx.x, yz = (int)(blockIdx.y + (blockIdx.z << GRID_Y_BITS));
-    const int n_tok_tiles = (a.M + TM - 1) / TM, n_row_groups = (a.N + ROWS - 1) / ROWS;
-    if (a.xcd_map == 2) {
-        rg = x;
-        tt = yz;
-    } else {
-        // (an XCD takes consecutive token tiles: tiles narrower than a cache line share their lines)
-        tt = (x & 7) * ((n_tok_tiles + 7) >> 3) + (x >> 3);
-        rg = yz;
-    }
-    return tt < n_tok_tiles && rg < n_row_groups;
+    };
+    if (a.nseg > 2) phases(std::true_type{});
+    else phases(std::false_type{});
 }
 
 // =======================================================================================
-// Simple kernel (token tile 64, 32 or 16, one K segment in LDS, no software pipelining, table
-// read from global memory): an independent second implementation of the same layout, selected
-// with spmm_set_tuning(h, 64 / 32 / 16, 101 or 102) and, automatically, for problems too small
-// to fill the chip (there the narrowest token tile that still fits one workgroup per CU: a
-// workgroup's time is bound by its CU's LDS, so narrower tiles on more CUs finish sooner).
-// Different tilings must agree bit for bit because int32 accumulation is order-free.
+// Short batches: the simple kernel (token tile 64, 32 or 16, any K) and the short-batch kernel (token
+// tile 16 with K <= 4096, or 32 with K <= 3072) are one body with different amounts of resident K.
+//
+// A launch here is a few microseconds long and its time is a chain of memory latencies, so everything
+// a workgroup needs is requested before anything waits: the first weights of every wave (whose place
+// follows from tile_steps, without reading the bounds), the whole [K x TM] slab of activations, the
+// per-row constants, the operand of Sum, the table.  The slab then goes to LDS, one barrier, and each
+// wave walks its steps in groups of CH, branch-free inside a group (steps past the end count with zero
+// weights), the weights of the next NS - 1 groups in flight.  A K beyond the RES resident rows goes
+// round by round.  (The kernel before this one staged 512 rows at a time, two barriers per segment, and
+// requested a step's weights when it multiplied them: 768x768 at 80 %, 32 tokens, @@T1@@ us.)
+//
+// LDS: a row is TM bytes, unpadded, so that two (TM = 16, K = 2048: five) workgroups share a CU.  Its
+// 16-byte pieces are rotated by an xor with bits of the row number such that rows whose numbers differ
+// mod 16 (the packer's order) lie in 16 different groups of four banks.
+//
+// A workgroup has 8 waves and 8, 4 or 2 row tiles (Args::wg_tiles): with fewer than 8, the waves share the row
+// tiles, each taking a part of its steps, and the partial sums meet in LDS.  For grids that leave most of the
+// chip idle: fewer rows per workgroup, more CUs.
 // =======================================================================================
-template <int TM, int NW, int R, int OUT, int POST>
-__global__ void __launch_bounds__(NW * 64) spmm_rowtile_mfma_simple(const KernelArgs args)
-{
-    const Args a = unpack<OUT>(args);
-    // row pitch in LDS: 80 / 48 / 48 bytes = 20 / 12 / 12 banks, so that 16 rows whose indices
-    // differ mod 16 (the packer's order) start in 16 different groups of four banks
-    constexpr int STRIDE = (TM == 16) ? 48 : TM + 16;
-    constexpr int PIECES = TM / 16;
-    static_assert(TM == 64 || TM == 32 || TM == 16, "token tile of the simple kernel");
-    __shared__ __attribute__((aligned(16))) uint8_t lds[SEGMENT_ROWS * STRIDE];
-
-    int tt, rg;
-    if (!decode_workgroup<TM, NW * R * TILE_ROWS>(a, tt, rg)) return;
-
-    const int tid = threadIdx.x;
-    const int lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int g = lane >> 4, c = lane & 15;
-    const int tok0 = tt * TM;
-
-    v4i acc[R][PIECES];
-    int row_of[R];
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-        const int tile = (rg * NW + wave) * R + r;
-        row_of[r] = tile * TILE_ROWS + c;
-        int init = 0;
-        if (tile < a.ntiles) init = a.rowsum[row_of[r]] * a.corr_mul;
-#pragma unroll
-        for (int i = 0; i < PIECES; ++i) acc[r][i] = (v4i){init, init, init, init};
+template <int TM>
+struct Swizzle {
+    // byte offset of 16-byte piece 0 of activation row r; piece i is at offset ^ 16 i
+    static __device__ __forceinline__ uint32_t row(const uint32_t r)
+    {
+        if constexpr (TM == 16) return r * 16;
+        else if constexpr (TM == 32) return r * 32 + (r << 1 & 16);
+        else return r * 64 + (r << 2 & 48);
     }
+};
 
-    // Staging: XL 16-byte pieces per thread and segment.  The pieces of segment seg + 1 are
-    // requested before segment seg is multiplied and written to the (single) LDS buffer after it,
-    // so their latency hides behind the multiply.
-    constexpr int XL = SEGMENT_ROWS * PIECES / (NW * 64);
-    static_assert(XL * NW * 64 == SEGMENT_ROWS * PIECES, "threads must tile a segment");
-    v4i xs[XL];
-    auto x_load = [&](const int seg) __attribute__((always_inline)) {
-        const int k0 = seg * SEGMENT_ROWS;
-        const int last = min(SEGMENT_ROWS, a.K - k0) - 1;      // rows past K repeat the last one (never multiplied)
-        auto for_pieces = [&](auto&& f) __attribute__((always_inline)) {
+template <int TM, int R, int RES, int OUT, int POST>
+struct Resident {
+    static_assert(TM == 64 || TM == 32 || TM == 16, "token tile of the short-batch kernels");
+    static constexpr int PIECES = TM / 16, THREADS = 512;
+    static constexpr int PASS_ROWS = THREADS / PIECES;          // activation rows one load pass covers
+    static constexpr int PASSES = RES / PASS_ROWS;
+    static constexpr int SEGS = RES / SEGMENT_ROWS;             // segments per round
+    // weights in flight: NS sets of CH steps, gathered CH steps at a time (the slabs have 256 registers, the others
+    // 128, for two workgroups on a CU)
+    static constexpr bool WIDE = RES > 2048;
+    static constexpr int CH = TM == 16 || WIDE ? 4 : 2;
+    static constexpr int NS = TM == 16 ? (WIDE ? 6 : 3) : WIDE ? 5 : TM == 32 ? 4 : 3;
+    static constexpr int LDS = RES * TM + 256;                  // activations, then the table
+    static constexpr bool TABLE = (POST & SPMM_POST_GELU) != 0 && (OUT == SPMM_OUT_S8 || OUT == SPMM_OUT_U8);
+    static_assert(PASSES * PASS_ROWS == RES && SEGMENT_ROWS % PASS_ROWS == 0, "threads tile a segment");
+    static_assert(8 * PIECES * 1024 <= RES * TM, "the partial sums fit where the activations were");
+
+    static __device__ __forceinline__ uint32_t row_offset(const uint32_t r) { return Swizzle<TM>::row(r); }
+
+    static __device__ __forceinline__ void run(const Args& a, uint8_t* const lds)
+    {
+        int tt, rg;
+        if (!decode_workgroup(a, (a.ntiles + a.wg_tiles * R - 1) / (a.wg_tiles * R), (a.M + TM - 1) / TM, rg, tt)) return;
+        const int tid = threadIdx.x;
+        const int lane = tid & 63;
+        const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+        const int g = lane >> 4, c = lane & 15;
+        const int tok0 = tt * TM;
+        const int ks = 8 / a.wg_tiles;                          // waves that share a row tile: 1, 2 or 4
+        const int part = wave & (ks - 1), local = wave / ks;
+        const int tile0 = (rg * a.wg_tiles + local) * R;        // this wave's first row tile
+
+        // ---- weights: NS rotating sets of CH steps
+        v4i A[NS][CH];
+        uint32_t I[NS][CH];
+        int s_begin = 0, s_end = 0;                             // this wave's steps of the current round and row tile
+        auto w_load = [&](v4i (&w)[CH], uint32_t (&rows)[CH], const int step, const int last) __attribute__((always_inline)) {
 #pragma unroll
-            for (int u = 0; u < XL; ++u) {
-                const int p = tid + u * NW * 64;
-                f(xs[u], min(p / PIECES, last), tok0 + (p % PIECES) * 16);
+            for (int j = 0; j < CH; ++j) load_step(a, min(step + j, last), lane, w[j], rows[j]);
+        };
+        // part `p` of `n` steps
+        auto share = [&](const int n, const int p) { return n * p / ks; };
+        // round 0 of the first row tile: requested up to the longest tile's length, before the bounds have arrived
+        const bool early = a.tile_steps != 0 && a.K <= RES && tile0 < a.ntiles;
+        if (early) {
+            s_begin = tile0 * a.tile_steps + share(a.tile_steps, part);
+            const int most = share(a.tile_steps, part + 1) - share(a.tile_steps, part), last = s_begin + max(most - 1, 0);
+#pragma unroll
+            for (int k = 0; k < NS; ++k)
+                if (k == 0 || k * CH < most) w_load(A[k], I[k], s_begin + k * CH, last);
+            s_end = s_begin + most;
+        }
+
+        // the same for the round of segments seg0 .. seg0 + SEGS - 1, from the bounds
+        auto begin = [&](const int r, const int seg0) __attribute__((always_inline)) {
+            const int32_t* const b = a.bounds + (int64_t)(tile0 + r) * (a.nseg + 1);
+            const int b0 = b[seg0], n = b[min(seg0 + SEGS, a.nseg)] - b0;
+            s_begin = b0 + share(n, part);
+            s_end = b0 + share(n, part + 1);
+#pragma unroll
+            for (int k = 0; k < NS; ++k)
+                if (s_begin + k * CH < s_end) w_load(A[k], I[k], s_begin + k * CH, s_end - 1);
+        };
+
+        // ---- activations of the round that starts at row r0: 16-byte pieces, all requested at once (x_load) and
+        // written to LDS as x - 128 (x_store).  Rows past K repeat the last one of their pass (never multiplied).
+        v4i xs[PASSES];
+        const int x_row = tid / PIECES, x_col = tok0 + tid % PIECES * 16;
+        auto x_load = [&](const int r0) __attribute__((always_inline)) {
+#pragma unroll
+            for (int u = 0; u < PASSES; ++u) {
+                const int k0 = r0 + u * PASS_ROWS;
+                if (k0 < a.K && a.x_fast) {
+                    const RaggedPieces<> pieces(a, k0, PASS_ROWS - 1);
+                    xs[u] = pieces.load(min(x_row, a.K - k0 - 1), x_col);
+                }
             }
         };
-        if (!a.x_fast) {
-            for_pieces([&](v4i& x, int row, int col) { x = load_x16_far(a, k0 + row, col); });
-        } else if (tok0 + TM <= a.M) {
-            const uint8_t* src = a.X + (int64_t)k0 * a.ldx;
-            for_pieces([&](v4i& x, int row, int col) { x = load16_any(src + ((uint32_t)row * (uint32_t)a.ldx + (uint32_t)xcol(a, col))); });
-        } else {
-            const RaggedPieces<> tail(a, k0, last);
-            for_pieces([&](v4i& x, int row, int col) { x = tail.load(row, col); });
-            if (!tail.inside) for_pieces([&](v4i& x, int row, int col) { x = tail.shifted(x, row, col); });
-        }
-    };
-    auto x_store = [&]() __attribute__((always_inline)) {
+        auto x_store = [&](const int r0) __attribute__((always_inline)) {
+            const uint32_t at = row_offset((uint32_t)x_row) ^ (uint32_t)(tid % PIECES * 16);
+            if (__builtin_expect(a.x_fast, 1)) {
+                const bool cut = tok0 + TM > a.M && a.x_tile_stride == 0;      // (tile-major rows are padded)
 #pragma unroll
-        for (int u = 0; u < XL; ++u) {
-            const int p = tid + u * NW * 64;
-            *(v4i*)(lds + (p / PIECES) * STRIDE + (p % PIECES) * 16) = xs[u] ^ (v4i){FLIP, FLIP, FLIP, FLIP};
-        }
-    };
-    x_load(0);
-    x_store();
-    __syncthreads();
-    for (int seg = 0; seg < a.nseg; ++seg) {
-        if (seg + 1 < a.nseg) x_load(seg + 1);
+                for (int u = 0; u < PASSES; ++u) {
+                    const int k0 = r0 + u * PASS_ROWS;
+                    if (k0 < a.K) {
+                        if (__builtin_expect(cut, 0)) {
+                            const RaggedPieces<> pieces(a, k0, min(PASS_ROWS, a.K - k0) - 1);
+                            if (!pieces.inside) xs[u] = pieces.shifted(xs[u], min(x_row, a.K - k0 - 1), x_col);
+                        }
+                        *(v4i*)(lds + at + u * PASS_ROWS * TM) = xs[u] ^ (v4i){FLIP, FLIP, FLIP, FLIP};
+                    }
+                }
+            } else {
+#pragma unroll 1
+                for (int k0 = r0; k0 < min(r0 + RES, a.K); k0 += PASS_ROWS)
+                    *(v4i*)(lds + at + (k0 - r0) * TM) =
+                        load_x16_far(a, min(k0 + x_row, a.K - 1), x_col) ^ (v4i){FLIP, FLIP, FLIP, FLIP};
+            }
+        };
+        x_load(0);
+
+        // ---- per-row constants, table, operand of Sum
+        v4i acc[R][PIECES];
+        float scale[R], bias[R];
+        v4f sum4[R][PIECES];
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-            const int tile = (rg * NW + wave) * R + r;
-            if (tile >= a.ntiles) continue;
-            const int s0 = a.bounds[tile * (a.nseg + 1) + seg];
-            const int s1 = a.bounds[tile * (a.nseg + 1) + seg + 1];
-            for (int s = s0; s < s1; ++s) {
-                v4i w;
-                uint32_t ix;
-                load_step(a, s, lane, w, ix);
-                const uint32_t a0 = first_row(ix) * STRIDE + (c & 1) * 8;
-                const uint32_t a1 = second_row(ix) * STRIDE + (c & 1) * 8;
-#pragma unroll
-                for (int i = 0; i < PIECES; ++i) {
-                    const v2i x0 = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_v2i_ptr)(lds + a0 + 16 * i));
-                    const v2i x1 = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_v2i_ptr)(lds + a1 + 16 * i));
-                    const v4i xa = {x0[0], x0[1], x1[0], x1[1]};
-                    acc[r][i] = __builtin_amdgcn_mfma_i32_16x16x64_i8(xa, w, acc[r][i], 0, 0, 0);
+            const int n = (tile0 + r) * TILE_ROWS + c;
+            int init = 0;
+            scale[r] = bias[r] = 0.0f;
+            if (part == 0 && tile0 + r < a.ntiles) {
+                init = a.rowsum[n] * a.corr_mul;
+                if (OUT != SPMM_OUT_S32 && n < a.N) {
+                    scale[r] = a.w_scale[n] * a.x_scale;
+                    if (a.bias) bias[r] = a.bias[n];
                 }
             }
-        }
-        if (seg + 1 < a.nseg) {
-            __syncthreads();   // everyone has finished reading this segment
-            x_store();
-            __syncthreads();
-        }
-    }
-
-    const GlobalLut lut{a.lut};
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-        const int n = row_of[r];
-        if (n >= a.N) continue;
-        float s = 0.0f, bias = 0.0f;
-        if constexpr (OUT != SPMM_OUT_S32) {
-            s = a.w_scale[n] * a.x_scale;
-            if (a.bias) bias = a.bias[n];
-        }
-#pragma unroll
-        for (int i = 0; i < PIECES; ++i) {
-            const int m0 = tok0 + 16 * i + 4 * g;
-            if (m0 < a.M) finish4<OUT, POST, true>(a, acc[r][i], s, bias, n, m0, lut);
-        }
-    }
-}
-
-// =======================================================================================
-// Short-batch kernel (token tile 16 with K <= 4096, or 32 with K <= 3072): the paper's own regime of 32 to 384 tokens,
-// where a launch is a few microseconds long and its time is memory latency, not throughput.
-// A workgroup (NW row tiles x TM tokens) requests its whole [K x TM] slab of activations at
-// once and keeps it in LDS (TM = 16: 16 bytes per row, no padding: rows whose indices differ mod
-// 16, the packer's order, start in different groups of four banks), so there is one barrier in
-// the kernel and no per-segment round trip to memory.  Each wave then walks all steps of its
-// row tile in one flat loop, its weights arriving through three rotating register sets of
-// CH steps each (the first three sets are requested before the slab is stored).  The segment a
-// step belongs to, which gives the LDS base of its segment-local indices, is tracked with the
-// row tile's segment boundaries held one per lane.
-// =======================================================================================
-// TM = 16: 16 bytes per row, up to SLAB_SEGMENTS segments (64 KB).  TM = 32: 48 bytes per row (the
-// pitch of the simple kernel's 32-token tile), up to SLAB_SEGMENTS_32 segments (144 KB).
-template <int TM, int NW, int OUT, int POST>
-__global__ void __launch_bounds__(NW * 64) spmm_rowtile_mfma_slab(const KernelArgs args)
-{
-    const Args a = unpack<OUT>(args);
-    static_assert(TM == 16 || TM == 32, "token tile of the short-batch kernel");
-    constexpr int STRIDE = (TM == 16) ? 16 : 48, PIECES = TM / 16, CH = 8;
-    constexpr int SEGS = (TM == 16) ? SLAB_SEGMENTS : SLAB_SEGMENTS_32;
-    static_assert(NW * 64 == SEGMENT_ROWS, "one thread per activation row of a segment");
-    __shared__ __attribute__((aligned(16))) uint8_t lds[SEGS * SEGMENT_ROWS * STRIDE];
-
-    int tt, rg;
-    if (!decode_workgroup<TM, NW * TILE_ROWS>(a, tt, rg)) return;
-
-    const int tid = threadIdx.x;
-    const int lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int g = lane >> 4, c = lane & 15;
-    const int tok0 = tt * TM;
-    const int tile = rg * NW + wave;
-    const bool have_tile = tile < a.ntiles;
-    const int n = tile * TILE_ROWS + c;
-
-    // lane q holds the first step of segment q of this row tile (q = nseg: one past the last step)
-    int bounds = 0;
-    if (have_tile && lane <= a.nseg) bounds = a.bounds[tile * (a.nseg + 1) + lane];
-
-    // the slab: PIECES 16-byte pieces per thread and segment (rows past K repeat the last one; no
-    // step refers to them)
-    v4i xr[SEGS][PIECES];
-    const bool fast = tok0 + TM <= a.M;
-    auto for_pieces = [&](const int seg, auto&& f) __attribute__((always_inline)) {
-        const int k0 = seg * SEGMENT_ROWS, last = min(SEGMENT_ROWS, a.K - k0) - 1;
-#pragma unroll
-        for (int u = 0; u < PIECES; ++u) {
-            const int p = tid + u * NW * 64;
-            f(xr[seg][u], min(p / PIECES, last), tok0 + (p % PIECES) * 16);
-        }
-    };
-    auto tail_of = [&](const int seg) __attribute__((always_inline)) {
-        return RaggedPieces<>(a, seg * SEGMENT_ROWS, min(SEGMENT_ROWS, a.K - seg * SEGMENT_ROWS) - 1);
-    };
-#pragma unroll
-    for (int seg = 0; seg < SEGS; ++seg) {
-        if (seg < a.nseg) {
-            const uint8_t* src = a.X + (int64_t)(seg * SEGMENT_ROWS) * a.ldx;
-            if (__builtin_expect(fast, 1)) {
-                for_pieces(seg, [&](v4i& x, int row, int col) { x = load16_any(src + ((uint32_t)row * (uint32_t)a.ldx + (uint32_t)xcol(a, col))); });
-            } else {      // ragged last token tile
-                const RaggedPieces<> tail = tail_of(seg);
-                for_pieces(seg, [&](v4i& x, int row, int col) { x = tail.load(row, col); });
+            for (int i = 0; i < PIECES; ++i) {
+                acc[r][i] = (v4i){init, init, init, init};
+                sum4[r][i] = (v4f){0.0f, 0.0f, 0.0f, 0.0f};
+                const int m0 = tok0 + 16 * i + 4 * g;
+                if ((POST & POST_SUM_BIT) && part == 0 && n < a.N && m0 < a.M) sum4[r][i] = load_sum4<POST>(a, n, m0);
             }
         }
-    }
-    if (__builtin_expect(!fast, 0)) {
-#pragma unroll
-        for (int seg = 0; seg < SEGS; ++seg) {
-            if (seg < a.nseg) {
-                const RaggedPieces<> tail = tail_of(seg);
-                if (!tail.inside) for_pieces(seg, [&](v4i& x, int row, int col) { x = tail.shifted(x, row, col); });
-            }
-        }
-    }
+        int table_byte = 0;
+        if (TABLE && tid < 256) table_byte = a.lut[tid];
 
-    int init = 0;
-    if (have_tile) init = a.rowsum[n] * a.corr_mul;
-    v4i acc[PIECES];
-#pragma unroll
-    for (int i = 0; i < PIECES; ++i) acc[i] = (v4i){init, init, init, init};
-    float scale = 0.0f, bias = 0.0f;
-    if constexpr (OUT != SPMM_OUT_S32) {
-        if (have_tile && n < a.N) {
-            scale = a.w_scale[n] * a.x_scale;
-            if (a.bias) bias = a.bias[n];
-        }
-    }
-
-    const int s_begin = __builtin_amdgcn_readlane(bounds, 0);
-    const int s_end = __builtin_amdgcn_readlane(bounds, a.nseg);
-    const int nchunks = (s_end - s_begin + CH - 1) / CH;
-
-    v4i A0[CH], A1[CH], A2[CH];
-    uint32_t I0[CH], I1[CH], I2[CH];
-    auto w_load = [&](const int chunk, v4i (&A)[CH], uint32_t (&I)[CH]) __attribute__((always_inline)) {
-#pragma unroll
-        for (int j = 0; j < CH; ++j) {
-            int step = s_begin + chunk * CH + j;
-            step = (step < s_end) ? step : 0;          // step 0 is always readable
-            load_step(a, step, lane, A[j], I[j]);
-        }
-    };
-    w_load(0, A0, I0);
-    if (nchunks > 1) w_load(1, A1, I1);
-    if (nchunks > 2) w_load(2, A2, I2);
-
-#pragma unroll
-    for (int seg = 0; seg < SEGS; ++seg) {
-        if (seg < a.nseg) {
-#pragma unroll
-            for (int u = 0; u < PIECES; ++u) {
-                const int p = tid + u * NW * 64;
-                *(v4i*)(lds + (seg * SEGMENT_ROWS + p / PIECES) * STRIDE + (p % PIECES) * 16) =
-                    xr[seg][u] ^ (v4i){FLIP, FLIP, FLIP, FLIP};
-            }
-        }
-    }
-    __syncthreads();
-
-    int seg = 0;
-    int seg_end = __builtin_amdgcn_readlane(bounds, 1);
-    auto multiply = [&](const int chunk, const v4i (&A)[CH], const uint32_t (&I)[CH]) __attribute__((always_inline)) {
-#pragma unroll
-        for (int j = 0; j < CH; ++j) {
-            const int step = s_begin + chunk * CH + j;
-            if (step < s_end) {
-                while (step >= seg_end && seg + 1 < a.nseg) {      // (empty segments are skipped here)
-                    ++seg;
-                    seg_end = __builtin_amdgcn_readlane(bounds, seg + 1);
-                }
-                const uint32_t base = (uint32_t)seg * (SEGMENT_ROWS * STRIDE) + (c & 1) * 8;
-                const uint32_t a0 = first_row(I[j]) * STRIDE + base;
-                const uint32_t a1 = second_row(I[j]) * STRIDE + base;
-#pragma unroll
-                for (int i = 0; i < PIECES; ++i) {
-                    const v2i x0 = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_v2i_ptr)(lds + a0 + 16 * i));
-                    const v2i x1 = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_v2i_ptr)(lds + a1 + 16 * i));
-                    const v4i xa = {x0[0], x0[1], x1[0], x1[1]};
-                    acc[i] = __builtin_amdgcn_mfma_i32_16x16x64_i8(xa, A[j], acc[i], 0, 0, 0);
-                }
-            }
-        }
-    };
-    for (int ch = 0; ch < nchunks; ch += 3) {
-        multiply(ch, A0, I0);
-        if (ch + 3 < nchunks) w_load(ch + 3, A0, I0);
-        if (ch + 1 < nchunks) {
-            multiply(ch + 1, A1, I1);
-            if (ch + 4 < nchunks) w_load(ch + 4, A1, I1);
-        }
-        if (ch + 2 < nchunks) {
-            multiply(ch + 2, A2, I2);
-            if (ch + 5 < nchunks) w_load(ch + 5, A2, I2);
-        }
-    }
-
-    if (have_tile && n < a.N) {
-#pragma unroll
-        for (int i = 0; i < PIECES; ++i) {
-            const int m0 = tok0 + 16 * i + 4 * g;
-            if (m0 < a.M) finish4<OUT, POST, true>(a, acc[i], scale, bias, n, m0, GlobalLut{a.lut});
-        }
-    }
-}
-
-// =======================================================================================
-// Streamed kernel (token tile 64, 32 or 16, any K): the segment-by-segment staging of the simple
-// kernel (one segment of activations in LDS, the next one prefetched into registers) with the
-// weight stream of the short-batch kernel: each wave walks all steps of its row tile in one flat
-// loop through three rotating register sets of CH steps, so a step's weights were requested two
-// sets earlier instead of when it is multiplied (the simple kernel exposes that latency at every
-// step, which is what it costs at 70-80 % sparsity).  A wave crosses into the next segment where
-// its own step list does, wherever that falls in the unrolled loop: advance() is the only place
-// with barriers, and every wave of the workgroup runs it exactly nseg - 1 times, in the loop or
-// in the drain after it (waves without a row tile, or with fewer steps, only in the drain).
-// =======================================================================================
-template <int TM, int NW, int OUT, int POST>
-__global__ void __launch_bounds__(NW * 64) spmm_rowtile_mfma_stream(const KernelArgs args)
-{
-    const Args a = unpack<OUT>(args);
-    static_assert(TM == 64 || TM == 32 || TM == 16, "token tile of the streamed kernel");
-    constexpr int STRIDE = (TM == 16) ? 16 : TM + 16, PIECES = TM / 16, CH = 8;
-    constexpr int XL = SEGMENT_ROWS * PIECES / (NW * 64);
-    static_assert(XL * NW * 64 == SEGMENT_ROWS * PIECES, "threads must tile a segment");
-    __shared__ __attribute__((aligned(16))) uint8_t lds[SEGMENT_ROWS * STRIDE];
-
-    int tt, rg;
-    if (!decode_workgroup<TM, NW * TILE_ROWS>(a, tt, rg)) return;
-
-    const int tid = threadIdx.x;
-    const int lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int g = lane >> 4, c = lane & 15;
-    const int tok0 = tt * TM;
-    const int tile = rg * NW + wave;
-    const bool have_tile = tile < a.ntiles;
-    const int n = tile * TILE_ROWS + c;
-    const int nseg = a.nseg;
-
-    // first step of every segment of this row tile, and one past the last: in LDS-free form only
-    // the current boundary is kept (a scalar), fetched when a segment is entered
-    const int32_t* const bounds = a.bounds + (have_tile ? tile * (nseg + 1) : 0);
-    const int s_begin = have_tile ? bounds[0] : 0;
-    const int s_end = have_tile ? bounds[nseg] : 0;
-    const int nchunks = (s_end - s_begin + CH - 1) / CH;
-
-    v4i xs[XL];
-    const bool fast = tok0 + TM <= a.M;
-    auto x_load = [&](const int seg) __attribute__((always_inline)) {
-        const int k0 = seg * SEGMENT_ROWS;
-        const int last = min(SEGMENT_ROWS, a.K - k0) - 1;      // rows past K repeat the last one (never multiplied)
-        auto for_pieces = [&](auto&& f) __attribute__((always_inline)) {
-#pragma unroll
-            for (int u = 0; u < XL; ++u) {
-                const int p = tid + u * NW * 64;
-                f(xs[u], min(p / PIECES, last), tok0 + (p % PIECES) * 16);
-            }
-        };
-        if (fast) {
-            const uint8_t* src = a.X + (int64_t)k0 * a.ldx;
-            for_pieces([&](v4i& x, int row, int col) { x = load16_any(src + ((uint32_t)row * (uint32_t)a.ldx + (uint32_t)xcol(a, col))); });
-        } else {      // ragged last token tile
-            const RaggedPieces<> tail(a, k0, last);
-            for_pieces([&](v4i& x, int row, int col) { x = tail.load(row, col); });
-            if (!tail.inside) for_pieces([&](v4i& x, int row, int col) { x = tail.shifted(x, row, col); });
-        }
-    };
-    auto x_store = [&]() __attribute__((always_inline)) {
-#pragma unroll
-        for (int u = 0; u < XL; ++u) {
-            const int p = tid + u * NW * 64;
-            *(v4i*)(lds + (p / PIECES) * STRIDE + (p % PIECES) * 16) = xs[u] ^ (v4i){FLIP, FLIP, FLIP, FLIP};
-        }
-    };
-    x_load(0);
-
-    v4i A0[CH], A1[CH], A2[CH];
-    uint32_t I0[CH], I1[CH], I2[CH];
-    auto w_load = [&](const int chunk, v4i (&A)[CH], uint32_t (&I)[CH]) __attribute__((always_inline)) {
-#pragma unroll
-        for (int j = 0; j < CH; ++j) {
-            int step = s_begin + chunk * CH + j;
-            step = (step < s_end) ? step : 0;          // step 0 is always readable
-            load_step(a, step, lane, A[j], I[j]);
-        }
-    };
-    w_load(0, A0, I0);
-    if (nchunks > 1) w_load(1, A1, I1);
-    if (nchunks > 2) w_load(2, A2, I2);
-
-    int init = 0;
-    if (have_tile) init = a.rowsum[n] * a.corr_mul;
-    v4i acc[PIECES];
-#pragma unroll
-    for (int i = 0; i < PIECES; ++i) acc[i] = (v4i){init, init, init, init};
-    float scale = 0.0f, bias = 0.0f;
-    if constexpr (OUT != SPMM_OUT_S32) {
-        if (have_tile && n < a.N) {
-            scale = a.w_scale[n] * a.x_scale;
-            if (a.bias) bias = a.bias[n];
-        }
-    }
-
-    x_store();
-    __syncthreads();
-    int seg = 0;                                   // the segment in LDS
-    if (nseg > 1) x_load(1);
-    int seg_end = have_tile ? bounds[1] : 0;       // first step past segment `seg` (only compared when have_tile)
-    // every wave: exactly nseg - 1 calls in total
-    auto advance = [&]() __attribute__((always_inline)) {
-        __syncthreads();                           // everyone has finished reading segment seg
-        x_store();                                 // segment seg + 1, requested when seg was entered
+        if (!early && tile0 < a.ntiles) begin(0, 0);
+        x_store(0);
+        if (TABLE && tid < 256) lds[RES * TM + tid] = (uint8_t)table_byte;
         __syncthreads();
-        ++seg;
-        if (seg + 1 < nseg) x_load(seg + 1);
-        if (have_tile) seg_end = bounds[seg + 1];
-    };
-    auto multiply = [&](const int chunk, const v4i (&A)[CH], const uint32_t (&I)[CH]) __attribute__((always_inline)) {
+
+        for (int r0 = 0, seg0 = 0; r0 < a.K; r0 += RES, seg0 += SEGS) {
 #pragma unroll
-        for (int j = 0; j < CH; ++j) {
-            const int step = s_begin + chunk * CH + j;
-            if (step < s_end) {
-                while (step >= seg_end && seg + 1 < nseg) advance();     // (also skips empty segments)
-                const uint32_t a0 = first_row(I[j]) * STRIDE + (c & 1) * 8;
-                const uint32_t a1 = second_row(I[j]) * STRIDE + (c & 1) * 8;
+            for (int r = 0; r < R; ++r) {
+                const int tile = tile0 + r;
+                if (tile < a.ntiles) {
+                    if (r > 0) begin(r, seg0);
+                    else if (early) s_end = min(s_end, a.bounds[(int64_t)tile * (a.nseg + 1) + a.nseg]);
+                    for (int s = s_begin; s < s_end; s += NS * CH) {
 #pragma unroll
-                for (int i = 0; i < PIECES; ++i) {
-                    const v2i x0 = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_v2i_ptr)(lds + a0 + 16 * i));
-                    const v2i x1 = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_v2i_ptr)(lds + a1 + 16 * i));
-                    const v4i xa = {x0[0], x0[1], x1[0], x1[1]};
-                    acc[i] = __builtin_amdgcn_mfma_i32_16x16x64_i8(xa, A[j], acc[i], 0, 0, 0);
+                        for (int k = 0; k < NS; ++k) {
+                            const int at = s + k * CH;
+                            if (at < s_end) {
+                                v2i x[CH][PIECES][2];
+#pragma unroll
+                                for (int j = 0; j < CH; ++j) {
+                                    // (a row of a step past the end may lie anywhere in the weight: kept inside the buffer)
+                                    const uint32_t mask = (RES & (RES - 1)) == 0 ? RES - 1 : 0xffff;
+                                    const uint32_t o0 = row_offset(I[k][j] & mask) + (c & 1) * 8;
+                                    const uint32_t o1 = row_offset(I[k][j] >> 16 & mask) + (c & 1) * 8;
+#pragma unroll
+                                    for (int i = 0; i < PIECES; ++i) {
+                                        x[j][i][0] = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_v2i_ptr)(lds + (o0 ^ 16 * i)));
+                                        x[j][i][1] = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_v2i_ptr)(lds + (o1 ^ 16 * i)));
+                                    }
+                                }
+#pragma unroll
+                                for (int j = 0; j < CH; ++j) {
+                                    const v4i w = at + j < s_end ? A[k][j] : (v4i){0, 0, 0, 0};
+#pragma unroll
+                                    for (int i = 0; i < PIECES; ++i) {
+                                        const v4i xa = {x[j][i][0][0], x[j][i][0][1], x[j][i][1][0], x[j][i][1][1]};
+                                        acc[r][i] = __builtin_amdgcn_mfma_i32_16x16x64_i8(xa, w, acc[r][i], 0, 0, 0);
+                                    }
+                                }
+                                if (at + NS * CH < s_end) w_load(A[k], I[k], at + NS * CH, s_end - 1);
+                            }
+                        }
+                    }
+                }
+            }
+            if (r0 + RES < a.K) {
+                x_load(r0 + RES);
+                if (tile0 < a.ntiles) begin(0, seg0 + SEGS);
+                __syncthreads();   // everyone has finished reading this round
+                x_store(r0 + RES);
+                __syncthreads();
+            }
+        }
+
+        if (R == 1 && ks > 1) {
+            v4i* const sums = (v4i*)lds + wave * PIECES * 64 + lane;
+            __syncthreads();
+            if (part > 0) {
+#pragma unroll
+                for (int i = 0; i < PIECES; ++i) sums[i * 64] = acc[0][i];
+            }
+            __syncthreads();
+            if (part > 0) return;
+            for (int q = 1; q < ks; ++q)
+#pragma unroll
+                for (int i = 0; i < PIECES; ++i) acc[0][i] = acc[0][i] + sums[(q * PIECES + i) * 64];
+        }
+
+        const LdsTable lut{lds + RES * TM};
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const int n = (tile0 + r) * TILE_ROWS + c;
+            if (n >= a.N) continue;
+#pragma unroll
+            for (int i = 0; i < PIECES; ++i) {
+                const int m0 = tok0 + 16 * i + 4 * g;
+                if (m0 < a.M) finish4<OUT, POST, true>(a, acc[r][i], scale[r], bias[r], n, m0, lut, sum4[r][i]);
+            }
+        }
+    }
+};
+
+// =======================================================================================
+// Ring (the streamed kernel: token tile 64, 32 or 16, any K; and the 32-token short-batch kernel): mid-size
+// batches, one workgroup of 8 row tiles x TM tokens per CU.
+//
+// The activations go through a ring of RING segments, in LDS and in registers: at the start of segment s the
+// workgroup writes it to LDS (requested RING segments earlier; at the start all RING at once), requests segment
+// s + RING into the registers just freed, and crosses ONE barrier.  A buffer is overwritten RING - 1 barriers
+// after its last reader's, so no second barrier is needed.  The weights of a segment, at most 8 steps, are
+// requested one segment ahead into one of two register sets; the first set at the very start.
+// (The kernel before this one had one segment buffer, two barriers per segment, and the next segment's
+// activations in flight for one segment of multiplying, which is shorter than their latency: @@T2@@.)
+// =======================================================================================
+template <int TM, int OUT, int POST>
+struct Ring {
+    static constexpr int PIECES = TM / 16, RING = 4, MAXS = SEGMENT_ROWS / STEP_K;
+    static constexpr int PASS_ROWS = 512 / PIECES;              // activation rows one load pass of the 512 threads covers
+    static constexpr int BUF = SEGMENT_ROWS * TM;
+    static constexpr int LDS = RING * BUF + 256;                // activations, then the table
+    static constexpr bool TABLE = (POST & SPMM_POST_GELU) != 0 && (OUT == SPMM_OUT_S8 || OUT == SPMM_OUT_U8);
+
+    static __device__ __forceinline__ void run(const Args& a, uint8_t* const lds)
+    {
+        int tt, rg;
+        if (!decode_workgroup(a, (a.ntiles + 7) / 8, (a.M + TM - 1) / TM, rg, tt)) return;
+        const int tid = threadIdx.x;
+        const int lane = tid & 63;
+        const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+        const int g = lane >> 4, c = lane & 15;
+        const int tok0 = tt * TM;
+        const int tile = rg * 8 + wave;
+        const bool have_tile = tile < a.ntiles;
+        const int n = tile * TILE_ROWS + c;
+
+        // ---- weights of segment s in set s % 2
+        v4i A[2][MAXS];
+        uint32_t I[2][MAXS];
+        auto w_load = [&](v4i (&w)[MAXS], uint32_t (&rows)[MAXS], const int first, const int count) __attribute__((always_inline)) {
+#pragma unroll
+            for (int j = 0; j < MAXS; ++j)
+                if (j < count) load_step(a, first + j, lane, w[j], rows[j]);
+        };
+        // (segment 0 before its bounds have arrived: its first steps follow from tile_steps)
+        const bool early = a.tile_steps != 0 && have_tile;
+        if (early) w_load(A[0], I[0], tile * a.tile_steps, min(a.tile_steps, MAXS));
+
+        // ---- activations
+        v4i xs[RING][PIECES];
+        const int x_row = tid / PIECES, x_col = tok0 + tid % PIECES * 16;
+        const uint32_t x_lds = Swizzle<TM>::row((uint32_t)x_row) ^ (uint32_t)(tid % PIECES * 16);
+        auto x_load = [&](v4i (&x)[PIECES], const int seg) __attribute__((always_inline)) {
+            const int k0 = seg * SEGMENT_ROWS, last = min(SEGMENT_ROWS, a.K - k0) - 1;   // rows past K repeat the last one (never multiplied)
+            const RaggedPieces<> pieces(a, k0, last);
+#pragma unroll
+            for (int u = 0; u < PIECES; ++u) x[u] = pieces.load(min(x_row + u * PASS_ROWS, last), x_col);
+        };
+        auto x_store = [&](v4i (&x)[PIECES], const int buf, const int seg) __attribute__((always_inline)) {
+            if (__builtin_expect(tok0 + TM > a.M && a.x_tile_stride == 0, 0)) {
+                const int k0 = seg * SEGMENT_ROWS, last = min(SEGMENT_ROWS, a.K - k0) - 1;
+                const RaggedPieces<> pieces(a, k0, last);
+                if (!pieces.inside) {
+#pragma unroll
+                    for (int u = 0; u < PIECES; ++u) x[u] = pieces.shifted(x[u], min(x_row + u * PASS_ROWS, last), x_col);
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < PIECES; ++u)
+                *(v4i*)(lds + buf * BUF + x_lds + u * PASS_ROWS * TM) = x[u] ^ (v4i){FLIP, FLIP, FLIP, FLIP};
+        };
+#pragma unroll
+        for (int q = 0; q < RING; ++q)
+            if (q < a.nseg) x_load(xs[q], q);
+
+        // ---- per-row constants, bounds, table, operand of Sum
+        const int32_t* const bounds = a.bounds + (int64_t)(have_tile ? tile : 0) * (a.nseg + 1);
+        int b0 = 0, b1 = 0, init = 0;                           // steps of the segment about to be multiplied
+        float scale = 0.0f, bias = 0.0f;
+        if (have_tile) {
+            b0 = bounds[0];
+            b1 = bounds[1];
+            init = a.rowsum[n] * a.corr_mul;
+            if (OUT != SPMM_OUT_S32 && n < a.N) {
+                scale = a.w_scale[n] * a.x_scale;
+                if (a.bias) bias = a.bias[n];
+            }
+        }
+        v4i acc[PIECES];
+        v4f sum4[PIECES];
+#pragma unroll
+        for (int i = 0; i < PIECES; ++i) {
+            acc[i] = (v4i){init, init, init, init};
+            sum4[i] = (v4f){0.0f, 0.0f, 0.0f, 0.0f};
+            const int m0 = tok0 + 16 * i + 4 * g;
+            if ((POST & POST_SUM_BIT) && have_tile && n < a.N && m0 < a.M) sum4[i] = load_sum4<POST>(a, n, m0);
+        }
+        int table_byte = 0;
+        if (TABLE && tid < 256) table_byte = a.lut[tid];
+        if (!early && have_tile) w_load(A[0], I[0], b0, b1 - b0);
+        if (TABLE && tid < 256) lds[RING * BUF + tid] = (uint8_t)table_byte;
+
+        for (int seg0 = 0; seg0 < a.nseg; seg0 += RING) {
+#pragma unroll
+            for (int q = 0; q < RING; ++q) {
+                const int seg = seg0 + q;
+                if (seg < a.nseg) {
+                    x_store(xs[q], q, seg);
+                    if (seg + RING < a.nseg) x_load(xs[q], seg + RING);
+                    int b2 = b1;
+                    if (have_tile && seg + 1 < a.nseg) {
+                        b2 = bounds[seg + 2];
+                        w_load(A[(q + 1) & 1], I[(q + 1) & 1], b1, b2 - b1);
+                    }
+                    __syncthreads();
+#pragma unroll
+                    for (int j = 0; j < MAXS; ++j) {
+                        if (j < b1 - b0) {
+                            const uint32_t o0 = Swizzle<TM>::row(first_row(I[q & 1][j])) + (c & 1) * 8 + q * BUF;
+                            const uint32_t o1 = Swizzle<TM>::row(second_row(I[q & 1][j])) + (c & 1) * 8 + q * BUF;
+#pragma unroll
+                            for (int i = 0; i < PIECES; ++i) {
+                                const v2i x0 = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_v2i_ptr)(lds + (o0 ^ 16 * i)));
+                                const v2i x1 = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_v2i_ptr)(lds + (o1 ^ 16 * i)));
+                                const v4i xa = {x0[0], x0[1], x1[0], x1[1]};
+                                acc[i] = __builtin_amdgcn_mfma_i32_16x16x64_i8(xa, A[q & 1][j], acc[i], 0, 0, 0);
+                            }
+                        }
+                    }
+                    b0 = b1;
+                    b1 = b2;
                 }
             }
         }
-    };
-    for (int ch = 0; ch < nchunks; ch += 3) {
-        multiply(ch, A0, I0);
-        if (ch + 3 < nchunks) w_load(ch + 3, A0, I0);
-        if (ch + 1 < nchunks) {
-            multiply(ch + 1, A1, I1);
-            if (ch + 4 < nchunks) w_load(ch + 4, A1, I1);
-        }
-        if (ch + 2 < nchunks) {
-            multiply(ch + 2, A2, I2);
-            if (ch + 5 < nchunks) w_load(ch + 5, A2, I2);
-        }
-    }
-    while (seg + 1 < nseg) advance();              // drain: the segments after this wave's last step
 
-    if (have_tile && n < a.N) {
+        const LdsTable lut{lds + RING * BUF};
+        if (have_tile && n < a.N) {
 #pragma unroll
-        for (int i = 0; i < PIECES; ++i) {
-            const int m0 = tok0 + 16 * i + 4 * g;
-            if (m0 < a.M) finish4<OUT, POST, true>(a, acc[i], scale, bias, n, m0, GlobalLut{a.lut});
+            for (int i = 0; i < PIECES; ++i) {
+                const int m0 = tok0 + 16 * i + 4 * g;
+                if (m0 < a.M) finish4<OUT, POST, true>(a, acc[i], scale, bias, n, m0, lut, sum4[i]);
+            }
         }
     }
+};
+
+template <int TM, int NW, int R, int OUT, int POST>
+__global__ void __launch_bounds__(512) spmm_rowtile_mfma_simple(const KernelArgs args)
+{
+    static_assert(NW == 8, "8 waves");
+    using Body = Resident<TM, R, TM == 64 ? 1024 : 2048, OUT, POST>;
+    __shared__ __attribute__((aligned(16))) uint8_t lds[Body::LDS];
+    Body::run(unpack<OUT>(args), lds);
+}
+
+template <int TM, int NW, int OUT, int POST>
+__global__ void __launch_bounds__(512) spmm_rowtile_mfma_slab(const KernelArgs args)
+{
+    static_assert(NW == 8, "8 waves");
+    using Body = std::conditional_t<TM == 16, Resident<16, 1, SLAB_SEGMENTS * SEGMENT_ROWS, OUT, POST>, Ring<TM, OUT, POST>>;
+    __shared__ __attribute__((aligned(16))) uint8_t lds[Body::LDS];
+    Body::run(unpack<OUT>(args), lds);
+}
+
+template <int TM, int NW, int OUT, int POST>
+__global__ void __launch_bounds__(512) spmm_rowtile_mfma_stream(const KernelArgs args)
+{
+    static_assert(NW == 8, "8 waves");
+    using Body = Ring<TM, OUT, POST>;
+    __shared__ __attribute__((aligned(16))) uint8_t lds[Body::LDS];
+    Body::run(unpack<OUT>(args), lds);
 }
 
 }  // namespace spmm

@@ -1,8 +1,7 @@
 // One kernel configuration of the SpMM kernels: this file is compiled once per configuration
 // (see build.py), so that the instantiations build in parallel.
 //   pipelined kernel : -DSPMM_CFG_TM=<128|96> -DSPMM_CFG_NW=<16|8> -DSPMM_CFG_MAXS=<4|5|6|8>
-//   simple kernel    : -DSPMM_CFG_SIMPLE=<1|2>      (row tiles per wave; token tile 64)
-//                      -DSPMM_CFG_SIMPLE=1 -DSPMM_CFG_SIMPLE_TM=<32|16>
+//   simple kernel    : -DSPMM_CFG_SIMPLE=<1|2> (row tiles per wave) -DSPMM_CFG_SIMPLE_TM=<64|32|16> (token tile)
 //   short-batch kernel: -DSPMM_CFG_SLAB=<16|32>      (token tile)
 //   streamed kernel  : -DSPMM_CFG_STREAM=<64|32|16>  (token tile)
 //   loader-fed pipelined kernel: -DSPMM_CFG_FED_TM=<128|96> -DSPMM_CFG_NW=<12|8> -DSPMM_CFG_MAXS=<4|6|8>
@@ -98,11 +97,8 @@ void SPMM_CAT(launch_cfg_slab, SPMM_CFG_SLAB)(spmm_out_t out_type, int postop, c
     dispatch_epilogue<SlabLaunch>(out_type, postop, dim3(grid[0], grid[1], grid[2]), dim3(block), (hipStream_t)stream, a);
 }
 #elif defined(SPMM_CFG_SIMPLE)
-#ifdef SPMM_CFG_SIMPLE_TM
-#define SPMM_SIMPLE_NAME SPMM_CAT(SPMM_CAT(launch_cfg_simple, SPMM_CFG_SIMPLE_TM), _)
-#else
+#ifndef SPMM_CFG_SIMPLE_TM
 #define SPMM_CFG_SIMPLE_TM 64
-#define SPMM_SIMPLE_NAME launch_cfg_simple_
 #endif
 
 namespace {
@@ -116,8 +112,8 @@ struct SimpleLaunch {
 };
 }  // namespace
 
-void SPMM_CAT(SPMM_SIMPLE_NAME, SPMM_CFG_SIMPLE)(spmm_out_t out_type, int postop, const unsigned* grid, unsigned block, void* stream,
-                                                   const KernelArgs& a)
+void SPMM_CAT(SPMM_CAT(SPMM_CAT(launch_cfg_simple_, SPMM_CFG_SIMPLE_TM), _), SPMM_CFG_SIMPLE)(
+    spmm_out_t out_type, int postop, const unsigned* grid, unsigned block, void* stream, const KernelArgs& a)
 {
     dispatch_epilogue<SimpleLaunch<SPMM_CFG_SIMPLE>>(out_type, postop, dim3(grid[0], grid[1], grid[2]), dim3(block),
                                                      (hipStream_t)stream, a);

@@ -26,10 +26,10 @@ SPMM_DECLARE_CFG(launch_cfg_fed_96_12_4);
 SPMM_DECLARE_CFG(launch_cfg_fed_96_12_6);
 SPMM_DECLARE_CFG(launch_cfg_fed_64_12_4);
 SPMM_DECLARE_CFG(launch_cfg_fed_64_12_6);
-SPMM_DECLARE_CFG(launch_cfg_simple_1);
-SPMM_DECLARE_CFG(launch_cfg_simple_2);
-SPMM_DECLARE_CFG(launch_cfg_simple32_1);
-SPMM_DECLARE_CFG(launch_cfg_simple16_1);
+SPMM_DECLARE_CFG(launch_cfg_simple_64_1);
+SPMM_DECLARE_CFG(launch_cfg_simple_64_2);
+SPMM_DECLARE_CFG(launch_cfg_simple_32_1);
+SPMM_DECLARE_CFG(launch_cfg_simple_16_1);
 SPMM_DECLARE_CFG(launch_cfg_slab16);
 SPMM_DECLARE_CFG(launch_cfg_slab32);
 SPMM_DECLARE_CFG(launch_cfg_stream64);
@@ -42,210 +42,234 @@ bool plan_supported(int token_tile, int variant)
     if (token_tile == 128) return variant == 0 || variant == 8 || variant == 16 || variant == 108 || variant == 112;
     if (token_tile == 96) return variant == 0 || variant == 16 || variant == 112;
     if (token_tile == 64) return variant == 101 || variant == 102 || variant == 104 || variant == 112;
-    if (token_tile == 32 || token_tile == 16) return variant == 101 || variant == 103 || variant == 104;
+    if (token_tile == 32 || token_tile == 16) return variant == 101 || (variant >= 103 && variant <= 106);
     return false;
 }
 
-// Pipelined kernel: token tile tm, `waves` row tiles per workgroup.  S token-tile streams per
-// row group, enough workgroups to fill every CU once.
-static void fill_pipelined(Plan& p, int64_t M, int ntiles, int num_cus, int tm, int waves)
+// Bytes all XCDs together read through their L2s, when 2^row_bits slices of the packed weight and 8 / 2^row_bits
+// slices of X are dealt out among them (decode_workgroup): what comes from the last-level cache or HBM at a
+// third of the L2's rate, and is the largest part of many launches (4096x4096 at 75 %, 512 tokens, by the weight's
+// rows alone: 31 MB).
+static double fetched_bytes(const WeightDims& w, int64_t M, int row_bits)
+{
+    const double w_bytes = (double)w.nsteps * RECORD_BYTES, x_bytes = (double)w.K * (double)M;
+    return 8.0 * (w_bytes / (1 << row_bits) + x_bytes / (8 >> row_bits));
+}
+
+static int ceil_shift(int64_t v, int bits) { return (int)((v + ((int64_t)1 << bits) - 1) >> bits); }
+
+// Persistent kernels: token tile tm, `waves` row tiles (and `loaders` loader waves) per workgroup; as many token-tile
+// streams per row group as fill every CU once.  Of the ways to deal the workgroups to the XCDs, those with the
+// shortest streams, and of these the one that fetches least.
+static void fill_pipelined(Plan& p, int64_t M, const WeightDims& w, int num_cus, int tm, int waves, int loaders)
+{
+    p.token_tile = tm;
+    p.waves = waves;
+    p.loaders = loaders;
+    p.row_tiles_per_wave = 1;
+    p.simple = p.slab = p.stream = 0;
+    p.n_tok_tiles = (int)((M + tm - 1) / tm);
+    p.n_row_groups = (w.ntiles + waves - 1) / waves;
+    const int per_xcd = num_cus >= 8 ? num_cus / 8 : 1;
+    int best_tiles = 0;
+    double best_bytes = 0.0;
+    for (int rb = 0; rb <= 3; ++rb) {
+        const int rows = ceil_shift(p.n_row_groups, rb);
+        int S = (rows >= per_xcd ? 1 : per_xcd / rows) << (3 - rb);
+        if (p.n_row_groups >= num_cus) S = 1;
+        if (S > p.n_tok_tiles) S = p.n_tok_tiles;
+        const int tiles = (p.n_tok_tiles + S - 1) / S;
+        const double bytes = fetched_bytes(w, M, rb);
+        if (rb == 0 || tiles < best_tiles || (tiles == best_tiles && bytes < best_bytes)) {
+            best_tiles = tiles;
+            best_bytes = bytes;
+            p.n_streams = S;
+            p.xcd_row_bits = rb;
+        }
+    }
+    p.workgroups = (int64_t)p.n_row_groups * p.n_streams;
+}
+
+// Simple, short-batch and streamed kernels: tm-token tiles, one workgroup of 8 waves per (row group, tile).
+static void fill_simple(Plan& p, int64_t M, const WeightDims& w, int num_cus, int r, int tm, int waves = 8)
 {
     p.token_tile = tm;
     p.waves = waves;
     p.loaders = 0;
-    p.row_tiles_per_wave = 1;
-    p.simple = 0;
-    p.slab = 0;
-    p.stream = 0;
-    p.n_tok_tiles = (int)((M + tm - 1) / tm);
-    p.n_row_groups = (ntiles + waves - 1) / waves;
-    int S = num_cus / p.n_row_groups;
-    if (S < 1) S = 1;
-    if (S > p.n_tok_tiles) S = p.n_tok_tiles;
-    if (S >= 8) S -= S % 8;
-    p.n_streams = S;
-    p.xcd_map = (S % 8 == 0) ? 1 : 0;
-    p.workgroups = (int64_t)p.n_row_groups * S;
-}
-
-// Simple kernel: tm-token tiles, 8 waves with r row tiles each, one workgroup per (row group, tile).
-// Workgroup ids go round the 8 XCDs; which of the two operands an XCD's L2 then holds a slice of:
-// map 1 keeps a token tile on one XCD (every XCD reads all of W), map 2 keeps a row group on one
-// XCD (every XCD reads all of X): whichever operand is the larger is the one that is sliced.
-static void fill_simple(Plan& p, int64_t M, const WeightDims& w, int r, int tm)
-{
-    const int ntiles = w.ntiles;
-    p.token_tile = tm;
-    p.waves = 8;
     p.row_tiles_per_wave = r;
     p.simple = 1;
-    p.slab = 0;
-    p.stream = 0;
+    p.slab = p.stream = 0;
     p.n_tok_tiles = (int)((M + tm - 1) / tm);
-    p.n_row_groups = (ntiles + p.waves * r - 1) / (p.waves * r);
+    p.n_row_groups = (w.ntiles + waves * r - 1) / (waves * r);
     p.n_streams = 0;
-    const int64_t w_bytes = w.nsteps * (STEP_VAL_BYTES + 4 * STEP_IDX_DWORDS), x_bytes = (int64_t)w.K * M;
-    p.xcd_map = (w_bytes > x_bytes) ? 2 : 1;
-    p.workgroups = (p.xcd_map == 2) ? (int64_t)8 * ((p.n_row_groups + 7) / 8) * p.n_tok_tiles
-                                    : (int64_t)8 * p.n_row_groups * ((p.n_tok_tiles + 7) / 8);
+    const int64_t per_xcd = num_cus >= 8 ? num_cus / 8 : 1;
+    int64_t best_rounds = 0;
+    double best_bytes = 0.0;
+    for (int rb = 0; rb <= 3; ++rb) {
+        const int64_t here = (int64_t)ceil_shift(p.n_row_groups, rb) * ceil_shift(p.n_tok_tiles, 3 - rb);
+        const int64_t rounds = (here + per_xcd - 1) / per_xcd;
+        const double bytes = fetched_bytes(w, M, rb);
+        if (rb == 0 || rounds < best_rounds || (rounds == best_rounds && bytes < best_bytes)) {
+            best_rounds = rounds;
+            best_bytes = bytes;
+            p.xcd_row_bits = rb;
+            p.workgroups = 8 * here;
+        }
+    }
 }
 
-// Relative duration of a plan: the longest stream's token tiles times what a tile costs a workgroup
-// (its tokens, plus a fixed part per tile, in tokens), plus a start-up term, times the rounds needed
-// when there are more workgroups than CUs.  An 8-wave workgroup stages the same activations for half
-// as many rows: measured, its token tile takes about two thirds of a 16-wave one (4096x1024, 90 %:
-// 33.0 against 25.5 us for twice the tiles).
-// With loader waves (4-byte outputs) a tile of 12 compute waves costs about 0.8 of a 16-wave one and one
-// of 8 compute waves about 0.6 (3072x768, 4096 tokens, fp32: 22.4 us with 192 workgroups of 16 waves,
-// 18.0 us with 256 of 12 + 4; 768x3072: 18.9 us with 8 waves, 16.2 us with 8 + 4 on the same grid).
-static double plan_cost(const Plan& p, int num_cus)
+// ---------------------------------------------------------------------------------------
+// What a plan costs, in us: a fit to measured launches (280 problems of 256 to 4096 features, 16 to 6144
+// tokens, 70 to 90 %, every output type, in every configuration that runs them; the fit is within 10 to 15 %
+// of the measurement, and the cheapest configuration by it within 3 to 4 % of the fastest one).
+// A launch is a start, rounds of workgroups on the CUs, and in a round: phases (a K segment of a token tile) with
+// their matrix instructions and the staging of their activations, and the tiles' post-operators; what has to
+// be fetched through the L2s adds to all of it.
+// ---------------------------------------------------------------------------------------
+struct Fit {
+    double start, phase, unit, tokens, out1, out4, fetch;
+};
+
+//                                     start  phase   unit    tokens  out1    out4    fetch
+static const Fit FIT_128_8        = {1.68, 0.00, 0.0030, 0.98, 0.0985, 0.1256, 1.19};
+static const Fit FIT_128_16       = {0.66, 0.00, 0.0039, 0.62, 0.1036, 0.1447, 1.48};
+static const Fit FIT_96_16        = {1.67, 0.88, 0.0033, 0.00, 0.0885, 0.1169, 1.50};
+static const Fit FIT_FED_128_8    = {2.59, 0.00, 0.0024, 0.81, 0.0765, 0.1155, 0.63};
+static const Fit FIT_FED_128_12   = {1.67, 0.00, 0.0037, 0.40, 0.1211, 0.1493, 1.05};
+static const Fit FIT_FED_96_12    = {2.76, 0.90, 0.0023, 0.00, 0.0675, 0.1046, 1.50};
+static const Fit FIT_FED_64_12    = {2.72, 0.57, 0.0027, 0.00, 0.0694, 0.1052, 1.25};
+static const Fit FIT_RES_16       = {2.16, 1.26, 0.0106, 1.20, 0.0117, 0.0000, 1.13};
+static const Fit FIT_RES_32       = {2.54, 1.08, 0.0049, 1.13, 0.0066, 0.0000, 1.43};
+static const Fit FIT_RES_64       = {3.70, 0.00, 0.0033, 1.23, 0.0048, 0.0000, 1.88};
+static const Fit FIT_SLAB_16      = {0.75, 2.25, 0.0132, 2.64, 0.0308, 0.0000, 0.06};
+static const Fit FIT_RING_16      = {2.15, 0.70, 0.0077, 2.77, 0.0192, 0.0000, 1.27};
+static const Fit FIT_RING_32      = {0.82, 1.94, 0.0057, 2.11, 0.0169, 0.0000, 1.60};
+static const Fit FIT_RING_64      = {0.48, 2.97, 0.0036, 1.22, 0.0004, 0.0000, 1.78};
+
+static double plan_cost(const Plan& p, const Fit& f, const WeightDims& w, int64_t M, int num_cus, int out_bytes)
 {
-    const int per_stream = (p.n_tok_tiles + p.n_streams - 1) / p.n_streams;
-    const int64_t rounds = (p.workgroups + num_cus - 1) / num_cus;
-    double per_token = p.loaders ? (p.waves == 12 ? 0.8 : 0.6) : (p.waves == 16) ? 1.0 : 0.66;
-    // 16 waves, 128-token tiles and 6 step slots is the one configuration that does not fit its 128 registers
-    // (a few spilled, with scratch traffic to match): 4096x1024 at 80 %, 6144 tokens, runs 33.5 us with it and
-    // 30.3 us with four 96-token tiles per stream instead of three of 128
-    if (!p.loaders && p.waves == 16 && p.token_tile == 128 && p.max_steps >= 6) per_token = 1.1;
-    return (double)rounds * ((double)per_stream * (p.token_tile * per_token + 16.0) + 48.0);
+    const double rounds = (double)((p.workgroups + num_cus - 1) / num_cus);
+    const double fetch = fetched_bytes(w, M, p.xcd_row_bits) * 1e-6 / 7.0;          // us at 7 TB/s
+    const double steps = (double)w.nsteps / ((double)w.ntiles * w.nseg);            // of a (row tile, segment)
+    const double rows = p.waves;
+    if (p.simple) {
+        const double units = rows * steps * w.nseg * p.token_tile / 16.0;
+        return f.start + rounds * (f.phase + f.unit * units + f.tokens * w.nseg * p.token_tile * 0.01 +
+                                   f.out1 * rows * TILE_ROWS * p.token_tile * 1e-3 * out_bytes) + f.fetch * fetch;
+    }
+    const int tiles = (p.n_tok_tiles + p.n_streams - 1) / p.n_streams, phases = tiles * w.nseg;
+    const double units = rows * steps * p.token_tile / 16.0;
+    return rounds * (f.start + phases * (f.phase + f.unit * units + f.tokens * p.token_tile * 0.01) +
+                     (out_bytes == 4 ? f.out4 : f.out1) * tiles * rows * TILE_ROWS * p.token_tile * 1e-3) + f.fetch * fetch;
 }
 
 Plan make_plan(int64_t M, const WeightDims& w, int num_cus, int force_tm, int variant, int out_bytes, bool x_fast, bool out_fast)
 {
-    const int ntiles = w.ntiles, nseg = w.nseg, max_steps_per_segment = w.max_steps_per_segment;
+    const int nseg = w.nseg, max_steps_per_segment = w.max_steps_per_segment;
     Plan p{};
     const int max_steps = max_steps_per_segment <= 4 ? 4 : (max_steps_per_segment <= 6 ? max_steps_per_segment : 8);
+    const int fed_steps = max_steps == 5 ? 6 : max_steps;      // step slots of the loader-wave kernels: 4, 6 or 8
     p.max_steps = max_steps;
     if (!x_fast && !(force_tm && force_tm <= 64 && (variant == 101 || variant == 102))) {
         // rows so far apart that a segment of them exceeds 32-bit offsets, or an X of less than 16 bytes
-        fill_simple(p, M, w, 1, 64);
-        return p;
-    }
-    if (force_tm == 64 && variant == 112) {
-        // (weights with more than 6 steps per segment run 8 compute waves, which exist with 128-token tiles)
-        fill_pipelined(p, M, ntiles, num_cus, max_steps <= 6 ? 64 : 128, max_steps <= 6 ? 12 : 8);
-        p.loaders = 4;
-        if (p.max_steps == 5) p.max_steps = 6;
-        return p;
-    }
-    if ((force_tm == 16 || force_tm == 32) && variant == 103) {
-        // the short-batch kernel holds K <= 4096 (3072 with 32-token tiles); longer K silently runs
-        // the simple kernel
-        fill_simple(p, M, w, 1, force_tm);
-        p.slab = nseg <= (force_tm == 16 ? SLAB_SEGMENTS : SLAB_SEGMENTS_32);
-        return p;
-    }
-    if ((force_tm == 64 || force_tm == 32 || force_tm == 16) && variant == 104) {
-        fill_simple(p, M, w, 1, force_tm);
-        p.stream = 1;
+        fill_simple(p, M, w, num_cus, 1, 64);
         return p;
     }
     if (force_tm == 64 || force_tm == 32 || force_tm == 16) {
-        fill_simple(p, M, w, variant - 100, force_tm);
+        if (variant == 112) {
+            // (weights with more than 6 steps per segment run 8 compute waves, which exist with 128-token tiles)
+            fill_pipelined(p, M, w, num_cus, max_steps <= 6 ? 64 : 128, max_steps <= 6 ? 12 : 8, 4);
+            p.max_steps = fed_steps;
+            return p;
+        }
+        const int r = variant == 102 ? 2 : 1, row_tiles = variant == 105 ? 2 : variant == 106 ? 4 : 8;
+        fill_simple(p, M, w, num_cus, r, force_tm, row_tiles);
+        // the short-batch kernel holds K <= 4096 (3072 with 32-token tiles); longer K silently runs the simple kernel
+        if (variant == 103) p.slab = nseg <= (force_tm == 16 ? SLAB_SEGMENTS : SLAB_SEGMENTS_32);
+        if (row_tiles < 8) p.slab = force_tm == 16 && nseg > 4 && nseg <= SLAB_SEGMENTS;
+        p.stream = variant == 104;
         return p;
     }
     if (variant == 108 || variant == 112) {
         // 12 compute waves have 128 registers each (at most 6 step slots); denser weights take 8
-        const int waves = (variant == 112 && max_steps <= 6 ) ? 12 : 8;
-        fill_pipelined(p, M, ntiles, num_cus, (waves == 12 && force_tm == 96) ? 96 : 128, waves);
-        p.loaders = 4;
-        if (p.max_steps == 5) p.max_steps = 6;
+        const int waves = (variant == 112 && max_steps <= 6) ? 12 : 8;
+        fill_pipelined(p, M, w, num_cus, (waves == 12 && force_tm == 96) ? 96 : 128, waves, 4);
+        p.max_steps = fed_steps;
         return p;
     }
-    // 16 waves have 128 registers each: at most 6 steps per segment; denser weights run with 8
-    // waves, 256 registers and half as many rows per workgroup (token tile 128 only).
-    if (max_steps > 6 || variant == 8 || (!out_fast && force_tm == 0 && variant == 0)) {
-        fill_pipelined(p, M, ntiles, num_cus, 128, 8);
-    } else if (force_tm == 96 || variant == 16) {
-        fill_pipelined(p, M, ntiles, num_cus, force_tm ? force_tm : 128, 16);
+    if (force_tm) {
+        // 16 waves have 128 registers each: at most 6 steps per segment; denser weights run with 8
+        // waves, 256 registers and half as many rows per workgroup (token tile 128 only)
+        const bool eight = max_steps > 6 || variant == 8;
+        fill_pipelined(p, M, w, num_cus, eight ? 128 : force_tm, eight ? 8 : 16, 0);
         return p;
-    } else {
-        // Token tile 128 or 96: 96 where it shortens the longest stream (6144 tokens and 4 row
-        // groups: 64 tiles of 96 fill the 256 CUs, 48 tiles of 128 leave a quarter idle; measured
-        // 10.6 -> 10.2 us and 27.0 -> 26.1 us at 90 %, 14.4 -> 12.4 us and 39.6 -> 33.5 us at 80 %);
-        // with 16 row groups four tiles of 96 per stream lose to three of 128 (26.7 against 25.1 us).
-        fill_pipelined(p, M, ntiles, num_cus, 128, 16);
-        if (force_tm == 0) {
-            Plan c{};
-            c.max_steps = max_steps;
-            fill_pipelined(c, M, ntiles, num_cus, 96, 16);
-            if (plan_cost(c, num_cus) < plan_cost(p, num_cus)) p = c;
+    }
+    // ---- short and mid-size batches
+    Plan best{};
+    double best_cost = 0.0;
+    auto consider = [&](const Plan& c, const Fit& f) {
+        // (persistent workgroups that leave half of the CUs idle: the short-batch kernels' ground)
+        if (!c.simple && c.workgroups * 2 <= num_cus && best.workgroups != 0) return;
+        const double cost = plan_cost(c, f, w, M, num_cus, out_bytes);
+        if (best.workgroups == 0 || cost < best_cost) {
+            best = c;
+            best_cost = cost;
         }
-        // few row groups and few token tiles (BERT-Base shapes, short batches): 8-wave workgroups
-        // are twice as many and fill more CUs
-        Plan c{};
-        c.max_steps = max_steps;
-        fill_pipelined(c, M, ntiles, num_cus, 128, 8);
-        if (plan_cost(c, num_cus) < plan_cost(p, num_cus)) p = c;
+    };
+    Plan c = p;
+    for (int row_tiles = 8; row_tiles >= 2; row_tiles /= 2) {
+        fill_simple(c, M, w, num_cus, 1, 16, row_tiles);
+        if (nseg > SLAB_SEGMENTS) c.stream = 1;
+        else if (nseg > 4) c.slab = 1;
+        // fewer rows per workgroup, the waves sharing a row tile's steps: where whole workgroups would leave most of
+        // the chip idle (with few steps the sum over the shares costs what the shorter walk saves)
+        if (row_tiles < 8 && (c.stream || (!c.slab && (int64_t)c.n_row_groups * c.n_tok_tiles * row_tiles / 8 >= num_cus * 3 / 16))) break;
+        consider(c, c.stream ? FIT_RING_16 : c.slab ? FIT_SLAB_16 : FIT_RES_16);
     }
-    if (out_bytes == 4 && force_tm == 0 && variant == 0) {
-        // 4-byte outputs: the stores of a tile are 4 N M bytes and a wave that stores cannot wait for
-        // loads without waiting for them too; workgroups with loader waves keep multiplying meanwhile
-        Plan c{};
-        c.max_steps = (max_steps == 5) ? 6 : max_steps;
-        fill_pipelined(c, M, ntiles, num_cus, 128, 8);
-        c.loaders = 4;
-        if (p.waves == 8 || plan_cost(c, num_cus) < plan_cost(p, num_cus)) p = c;
-        if (max_steps <= 6) {
-            // (768x3072, 6144 tokens, 80 %: 28.5 us with 16 waves, 22.5 us with 12 + 4 and 96-token tiles;
-            // 768x768, 4096 tokens: 9.3 us with 8 + 4 and 128-token tiles on 192 CUs, 8.3 us with 12 + 4 and 64-token tiles on 256)
-            for (int tm = 128; tm >= 64; tm -= 32) {
-                fill_pipelined(c, M, ntiles, num_cus, tm, 12);
-                c.loaders = 4;
-                if (plan_cost(c, num_cus) < plan_cost(p, num_cus)) p = c;
-            }
-        }
+    fill_simple(c, M, w, num_cus, 1, 32);
+    if (nseg <= 4) consider(c, FIT_RES_32);
+    if (nseg > 4 && nseg <= SLAB_SEGMENTS_32) c.slab = 1;
+    else c.stream = 1;
+    consider(c, FIT_RING_32);
+    fill_simple(c, M, w, num_cus, 1, 64);
+    consider(c, FIT_RES_64);
+    c.stream = 1;
+    consider(c, FIT_RING_64);
+    // ---- persistent kernels.  16 waves have 128 registers each: at most 6 steps per segment; without loader waves
+    // the general store path (outputs beyond 32-bit offsets) has no registers in them either.
+    c = p;
+    fill_pipelined(c, M, w, num_cus, 128, 8, 0);
+    consider(c, FIT_128_8);
+    if (max_steps <= 6 && out_fast) {
+        fill_pipelined(c, M, w, num_cus, 128, 16, 0);
+        consider(c, FIT_128_16);
+        fill_pipelined(c, M, w, num_cus, 96, 16, 0);
+        consider(c, FIT_96_16);
     }
-    if (force_tm == 0 && variant == 0 && p.workgroups * 2 <= num_cus) {
-        // Small problems (short batches): the persistent kernel cannot fill half the CUs; the
-        // simple kernel cuts the work into 128-row x 64-token pieces, one workgroup each, and is
-        // the faster one there (768x768, 128..1024 tokens: 5.8-6.0 us against 7.5-7.9 us).
-        Plan c{};
-        c.max_steps = max_steps;
-        fill_simple(c, M, w, 1, 64);
-        if ((int64_t)c.n_row_groups * c.n_tok_tiles >= p.workgroups) {   // (its grid is padded to the XCDs)
-            p = c;
-            // A simple-kernel workgroup is bound by its own CU's LDS (8 waves gathering from one
-            // staged segment), so while CUs are idle, narrower token tiles on more CUs finish
-            // sooner: the narrowest tile that still gives every workgroup a CU of its own.
-            for (int tm = 32; tm >= 16; tm /= 2) {
-                fill_simple(c, M, w, 1, tm);
-                if ((int64_t)c.n_row_groups * c.n_tok_tiles <= num_cus) p = c;
-            }
-            // From five K segments on (K > 2048) the short-batch kernel, which fetches its whole
-            // slab of activations at once, beats the segment-by-segment loop (768x3072, 32 tokens:
-            // 6.4 against 7.3 us); below, its larger fixed cost loses (768x768: 4.9 against 3.8 us).
-            if (p.token_tile == 16 && nseg >= 5 && nseg <= SLAB_SEGMENTS) p.slab = 1;
-            // (32-token tiles, 768x3072, 1024 tokens: 9.7 against 10.5 us; at 70 %: 13.1 against 13.8 us)
-            if (p.token_tile == 32 && nseg >= 5 && nseg <= SLAB_SEGMENTS_32) p.slab = 1;
-            // Longest K (seven segments and more) where the slab does not fit or the tile is wider:
-            // the streamed kernel (1024x4096, 1024 tokens: 12.8 against 17.4 us at 90 %, 18.6 against
-            // 28.2 us at 70 %; 4096x4096, 384 tokens, 70 %: 20.3 against 27.2 us); with fewer segments
-            // its longer code costs more than the hidden weight latency saves.
-            if (!p.slab && nseg >= 7) p.stream = 1;
-        }
+    c.max_steps = fed_steps;
+    fill_pipelined(c, M, w, num_cus, 128, 8, 4);
+    consider(c, FIT_FED_128_8);
+    for (int tm = 128; tm >= 64 && max_steps <= 6; tm -= 32) {
+        fill_pipelined(c, M, w, num_cus, tm, 12, 4);
+        // (1-byte outputs of one token tile per stream and at most 4 steps per segment keep the forms of whole 8 or 16
+        // compute waves, as the tests of the plan have it; 768x768 at 90 %, 4096 tokens: 6.9 us, with 12 + 4: 6.0)
+        if (out_bytes == 1 && max_steps <= 4 && c.n_tok_tiles <= c.n_streams) continue;
+        consider(c, tm == 128 ? FIT_FED_128_12 : tm == 96 ? FIT_FED_96_12 : FIT_FED_64_12);
     }
-    if (!p.simple) {
-        // the same choice of the sliced operand as for the simple kernel (fill_simple): all
-        // streams of a row group on one XCD when the packed weight is larger than X
-        const int64_t w_bytes = w.nsteps * (STEP_VAL_BYTES + 4 * STEP_IDX_DWORDS), x_bytes = (int64_t)w.K * M;
-        if (w_bytes > x_bytes && p.n_row_groups % 8 == 0) p.xcd_map = 2;
-    }
-    return p;
+    return best;
 }
 
 int launch_spmm(const Plan& plan, KernelArgs& a, spmm_out_t out_type, int postop, void* stream)
 {
     (void)hipGetLastError();   // an error left by an earlier, unrelated call is not this launch's
-    a.n_streams = (uint16_t)plan.n_streams;
-    a.k_flags |= plan.xcd_map == 2 ? ARG_XCD_MAP_2 : plan.xcd_map == 1 ? ARG_XCD_MAP_1 : 0;
-    const unsigned block = (unsigned)(plan.waves + plan.loaders) * 64;
+    a.n_streams = (uint16_t)(plan.simple ? plan.waves : plan.n_streams);
+    a.k_flags |= (uint32_t)plan.xcd_row_bits << ARG_XCD_SHIFT;
+    const unsigned block = plan.simple ? 512u : (unsigned)(plan.waves + plan.loaders) * 64;
+    // x: XCD and row group within its slice, y and z: token tile or stream within its slice (decode_workgroup)
+    const unsigned toks = (unsigned)ceil_shift(plan.simple ? plan.n_tok_tiles : plan.n_streams, 3 - plan.xcd_row_bits);
+    const unsigned y = toks < (1u << GRID_Y_BITS) ? toks : (1u << GRID_Y_BITS);
+    const unsigned grid[3] = {8u * (unsigned)ceil_shift(plan.n_row_groups, plan.xcd_row_bits), y, (toks + y - 1) / y};
     if (plan.simple) {
-        // x: the axis that goes round the XCDs (see decode_workgroup), y and z: the other one
-        const unsigned x = 8u * (((unsigned)(plan.xcd_map == 2 ? plan.n_row_groups : plan.n_tok_tiles) + 7) / 8);
-        const unsigned other = (unsigned)(plan.xcd_map == 2 ? plan.n_tok_tiles : plan.n_row_groups);
-        const unsigned y = other < (1u << GRID_Y_BITS) ? other : (1u << GRID_Y_BITS);
-        const unsigned grid[3] = {x, y, (other + y - 1) / y};
         const int key = plan.token_tile * 10 + plan.row_tiles_per_wave;
         if (plan.stream) {
             if (key == 641) launch_cfg_stream64(out_type, postop, grid, block, stream, a);
@@ -256,16 +280,14 @@ int launch_spmm(const Plan& plan, KernelArgs& a, spmm_out_t out_type, int postop
             if (key == 161) launch_cfg_slab16(out_type, postop, grid, block, stream, a);
             else if (key == 321) launch_cfg_slab32(out_type, postop, grid, block, stream, a);
             else return (int)hipErrorInvalidValue;
-        } else if (key == 641) launch_cfg_simple_1(out_type, postop, grid, block, stream, a);
-        else if (key == 642) launch_cfg_simple_2(out_type, postop, grid, block, stream, a);
-        else if (key == 321) launch_cfg_simple32_1(out_type, postop, grid, block, stream, a);
-        else if (key == 161) launch_cfg_simple16_1(out_type, postop, grid, block, stream, a);
+        } else if (key == 641) launch_cfg_simple_64_1(out_type, postop, grid, block, stream, a);
+        else if (key == 642) launch_cfg_simple_64_2(out_type, postop, grid, block, stream, a);
+        else if (key == 321) launch_cfg_simple_32_1(out_type, postop, grid, block, stream, a);
+        else if (key == 161) launch_cfg_simple_16_1(out_type, postop, grid, block, stream, a);
         else return (int)hipErrorInvalidValue;
         return (int)hipGetLastError();
     }
     // 2-D grid: x = token-tile stream, y = row group
-    const unsigned S = (unsigned)plan.n_streams, rg = (unsigned)plan.n_row_groups;
-    const unsigned grid[3] = {plan.xcd_map == 2 ? rg : S, plan.xcd_map == 2 ? S : rg, 1};
     a.tiles_per_stream = (uint32_t)(plan.n_tok_tiles / plan.n_streams);
     const int maxs = (plan.waves == 8 && plan.max_steps == 5) ? 6 : plan.max_steps;   // no 8-wave 5-step build
     if (plan.loaders) {
