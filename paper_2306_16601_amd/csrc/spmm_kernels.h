@@ -1386,12 +1386,13 @@ struct Ring {
                 const int seg = seg0 + q;
                 if (seg < a.nseg) {
                     x_store(xs[q], q, seg);
-                    if (seg + RING < a.nseg) x_load(xs[q], seg + RING);
                     int b2 = b1;
                     if (have_tile && seg + 1 < a.nseg) {
                         b2 = bounds[seg + 2];
                         w_load(A[(q + 1) & 1], I[(q + 1) & 1], b1, b2 - b1);
                     }
+                    // (behind the weights: loads complete in order, and those are needed first)
+                    if (seg + RING < a.nseg) x_load(xs[q], seg + RING);
                     __syncthreads();
 #pragma unroll
                     for (int j = 0; j < MAXS; ++j) {

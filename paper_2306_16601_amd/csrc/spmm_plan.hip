@@ -130,21 +130,29 @@ struct Fit {
     double start, phase, unit, tokens, out1, out4, fetch;
 };
 
+// persistent kernels: {up to two K segments (weights stay in registers), more (reloaded every phase)}
 //                                     start  phase   unit    tokens  out1    out4    fetch
-static const Fit FIT_128_8        = {1.68, 0.00, 0.0030, 0.98, 0.0985, 0.1256, 1.19};
-static const Fit FIT_128_16       = {0.66, 0.00, 0.0039, 0.62, 0.1036, 0.1447, 1.48};
-static const Fit FIT_96_16        = {1.67, 0.88, 0.0033, 0.00, 0.0885, 0.1169, 1.50};
-static const Fit FIT_FED_128_8    = {2.59, 0.00, 0.0024, 0.81, 0.0765, 0.1155, 0.63};
-static const Fit FIT_FED_128_12   = {1.67, 0.00, 0.0037, 0.40, 0.1211, 0.1493, 1.05};
-static const Fit FIT_FED_96_12    = {2.76, 0.90, 0.0023, 0.00, 0.0675, 0.1046, 1.50};
-static const Fit FIT_FED_64_12    = {2.72, 0.57, 0.0027, 0.00, 0.0694, 0.1052, 1.25};
-static const Fit FIT_RES_16       = {2.16, 1.26, 0.0106, 1.20, 0.0117, 0.0000, 1.13};
-static const Fit FIT_RES_32       = {2.54, 1.08, 0.0049, 1.13, 0.0066, 0.0000, 1.43};
-static const Fit FIT_RES_64       = {3.70, 0.00, 0.0033, 1.23, 0.0048, 0.0000, 1.88};
-static const Fit FIT_SLAB_16      = {0.75, 2.25, 0.0132, 2.64, 0.0308, 0.0000, 0.06};
-static const Fit FIT_RING_16      = {2.15, 0.70, 0.0077, 2.77, 0.0192, 0.0000, 1.27};
-static const Fit FIT_RING_32      = {0.82, 1.94, 0.0057, 2.11, 0.0169, 0.0000, 1.60};
-static const Fit FIT_RING_64      = {0.48, 2.97, 0.0036, 1.22, 0.0004, 0.0000, 1.78};
+static const Fit FIT_128_8[2]      = {{2.36, 0.00, 0.0027, 0.93, 0.0564, 0.0937, 1.57},
+                                     {1.55, 0.00, 0.0032, 0.90, 0.1313, 0.1594, 0.96}};
+static const Fit FIT_128_16[2]     = {{1.79, 0.00, 0.0036, 1.03, 0.0564, 0.0937, 1.57},
+                                     {1.42, 0.00, 0.0045, 0.21, 0.1313, 0.1594, 0.96}};
+static const Fit FIT_96_16[2]      = {{2.22, 1.20, 0.0027, 0.00, 0.0564, 0.0937, 1.57},
+                                     {1.31, 0.55, 0.0041, 0.00, 0.1313, 0.1594, 0.96}};
+static const Fit FIT_FED_128_8[2]  = {{2.69, 0.00, 0.0028, 0.78, 0.0515, 0.0884, 1.23},
+                                     {2.77, 0.00, 0.0022, 0.70, 0.1156, 0.1499, 0.76}};
+static const Fit FIT_FED_128_12[2] = {{2.48, 0.00, 0.0058, 0.39, 0.0515, 0.0884, 1.23},
+                                     {2.56, 0.00, 0.0031, 0.52, 0.1156, 0.1499, 0.76}};
+static const Fit FIT_FED_96_12[2]  = {{2.76, 0.90, 0.0034, 0.00, 0.0515, 0.0884, 1.23},
+                                     {2.48, 0.82, 0.0028, 0.00, 0.1156, 0.1499, 0.76}};
+static const Fit FIT_FED_64_12[2]  = {{2.88, 0.56, 0.0030, 0.00, 0.0515, 0.0884, 1.23},
+                                     {2.39, 0.52, 0.0033, 0.00, 0.1156, 0.1499, 0.76}};
+static const Fit FIT_RES_16        = {2.18, 1.27, 0.0107, 1.20, 0.0091, 0.0000, 1.18};
+static const Fit FIT_RES_32        = {2.56, 1.07, 0.0049, 1.16, 0.0067, 0.0000, 1.37};
+static const Fit FIT_RES_64        = {3.71, 0.00, 0.0039, 1.15, 0.0054, 0.0000, 1.70};
+static const Fit FIT_SLAB_16       = {0.83, 2.22, 0.0133, 2.73, 0.0271, 0.0000, 0.00};
+static const Fit FIT_RING_16       = {2.24, 0.68, 0.0082, 2.70, 0.0208, 0.0000, 1.04};
+static const Fit FIT_RING_32       = {0.90, 1.96, 0.0062, 2.06, 0.0130, 0.0000, 1.29};
+static const Fit FIT_RING_64       = {0.52, 2.99, 0.0039, 1.18, 0.0008, 0.0000, 1.53};
 
 static double plan_cost(const Plan& p, const Fit& f, const WeightDims& w, int64_t M, int num_cus, int out_bytes)
 {
@@ -205,13 +213,14 @@ Plan make_plan(int64_t M, const WeightDims& w, int num_cus, int force_tm, int va
         return p;
     }
     // ---- short and mid-size batches
+    const int reload = nseg > 2;
     Plan best{};
     double best_cost = 0.0;
     auto consider = [&](const Plan& c, const Fit& f) {
         // (persistent workgroups that leave half of the CUs idle: the short-batch kernels' ground)
         if (!c.simple && c.workgroups * 2 <= num_cus && best.workgroups != 0) return;
         const double cost = plan_cost(c, f, w, M, num_cus, out_bytes);
-        if (best.workgroups == 0 || cost < best_cost) {
+        if (best.workgroups == 0 || cost < 0.98 * best_cost) {
             best = c;
             best_cost = cost;
         }
@@ -226,35 +235,36 @@ Plan make_plan(int64_t M, const WeightDims& w, int num_cus, int force_tm, int va
         if (row_tiles < 8 && (c.stream || (!c.slab && (int64_t)c.n_row_groups * c.n_tok_tiles * row_tiles / 8 >= num_cus * 3 / 16))) break;
         consider(c, c.stream ? FIT_RING_16 : c.slab ? FIT_SLAB_16 : FIT_RES_16);
     }
+    // (the simple kernel where its resident rows hold all of K, the ring beyond)
     fill_simple(c, M, w, num_cus, 1, 32);
     if (nseg <= 4) consider(c, FIT_RES_32);
     if (nseg > 4 && nseg <= SLAB_SEGMENTS_32) c.slab = 1;
     else c.stream = 1;
     consider(c, FIT_RING_32);
     fill_simple(c, M, w, num_cus, 1, 64);
-    consider(c, FIT_RES_64);
+    if (nseg <= 2) consider(c, FIT_RES_64);
     c.stream = 1;
     consider(c, FIT_RING_64);
     // ---- persistent kernels.  16 waves have 128 registers each: at most 6 steps per segment; without loader waves
     // the general store path (outputs beyond 32-bit offsets) has no registers in them either.
     c = p;
-    fill_pipelined(c, M, w, num_cus, 128, 8, 0);
-    consider(c, FIT_128_8);
     if (max_steps <= 6 && out_fast) {
         fill_pipelined(c, M, w, num_cus, 128, 16, 0);
-        consider(c, FIT_128_16);
+        consider(c, FIT_128_16[reload]);
         fill_pipelined(c, M, w, num_cus, 96, 16, 0);
-        consider(c, FIT_96_16);
+        consider(c, FIT_96_16[reload]);
     }
+    fill_pipelined(c, M, w, num_cus, 128, 8, 0);
+    consider(c, FIT_128_8[reload]);
     c.max_steps = fed_steps;
     fill_pipelined(c, M, w, num_cus, 128, 8, 4);
-    consider(c, FIT_FED_128_8);
+    consider(c, FIT_FED_128_8[reload]);
     for (int tm = 128; tm >= 64 && max_steps <= 6; tm -= 32) {
         fill_pipelined(c, M, w, num_cus, tm, 12, 4);
         // (1-byte outputs of one token tile per stream and at most 4 steps per segment keep the forms of whole 8 or 16
         // compute waves, as the tests of the plan have it; 768x768 at 90 %, 4096 tokens: 6.9 us, with 12 + 4: 6.0)
         if (out_bytes == 1 && max_steps <= 4 && c.n_tok_tiles <= c.n_streams) continue;
-        consider(c, tm == 128 ? FIT_FED_128_12 : tm == 96 ? FIT_FED_96_12 : FIT_FED_64_12);
+        consider(c, (tm == 128 ? FIT_FED_128_12 : tm == 96 ? FIT_FED_96_12 : FIT_FED_64_12)[reload]);
     }
     return best;
 }
