@@ -6,6 +6,7 @@
 #include <cmath>
 #include <cstdio>
 #include <cstring>
+#include <memory>
 #include <new>
 
 #include "spmm_internal.h"
@@ -33,33 +34,18 @@ namespace {
 hipError_t upload_weight(spmm_handle* h)
 {
     const spmm::HostLayout& hl = h->hl;
-    const int64_t nt = hl.ntiles, ns = hl.nseg;
+    const int64_t nt = hl.ntiles;
     const bool strided = nt * hl.max_steps_per_tile <= hl.nsteps + hl.nsteps / 2;
     h->tile_steps = strided ? hl.max_steps_per_tile : 0;
     // (at least one record, so that a step index of 0 is always readable)
     const int64_t records = std::max<int64_t>(1, strided ? nt * hl.max_steps_per_tile : hl.nsteps);
-    const int64_t at = spmm::records_offset(nt, ns), bytes = at + records * spmm::RECORD_BYTES;
-    std::vector<uint8_t> blob((size_t)bytes, 0);
-    std::memcpy(blob.data(), hl.rowsum.data(), hl.rowsum.size() * 4);
-    int32_t* bounds = (int32_t*)(blob.data() + spmm::bounds_offset(nt));
-    for (int64_t t = 0; t < nt; ++t) {
-        const int64_t shift = strided ? t * hl.max_steps_per_tile - hl.seg_ptr[(size_t)(t * ns)] : 0;
-        for (int64_t g = 0; g <= ns; ++g) {
-            bounds[t * (ns + 1) + g] = (int32_t)(hl.seg_ptr[(size_t)(t * ns + g)] + shift);
-            if (g == ns) continue;
-            for (int64_t s = hl.seg_ptr[(size_t)(t * ns + g)]; s < hl.seg_ptr[(size_t)(t * ns + g + 1)]; ++s) {
-                uint8_t* r = blob.data() + at + (s + shift) * spmm::RECORD_BYTES;
-                std::memcpy(r, &hl.vals[(size_t)s * spmm::STEP_VAL_BYTES], spmm::STEP_VAL_BYTES);
-                const uint32_t base = (uint32_t)(g * spmm::SEGMENT_ROWS) * 0x10001u;
-                for (int i = 0; i < spmm::STEP_IDX_DWORDS; ++i)
-                    ((uint32_t*)(r + spmm::STEP_VAL_BYTES))[i] = hl.idx[(size_t)s * spmm::STEP_IDX_DWORDS + i] + base;
-            }
-        }
-    }
+    const int64_t bytes = spmm::records_offset(nt, hl.nseg) + records * spmm::RECORD_BYTES;
+    std::unique_ptr<uint8_t[]> form(new uint8_t[(size_t)bytes]);
+    spmm::device_form(hl, h->tile_steps, records, form.get());
     hipError_t e = hipMalloc((void**)&h->d_weight, (size_t)bytes);
     if (e != hipSuccess) return e;
     h->device_bytes = bytes;
-    return hipMemcpy(h->d_weight, blob.data(), (size_t)bytes, hipMemcpyHostToDevice);
+    return hipMemcpy(h->d_weight, form.get(), (size_t)bytes, hipMemcpyHostToDevice);
 }
 
 void free_device(spmm_handle* h)

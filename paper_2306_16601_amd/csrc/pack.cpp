@@ -7,107 +7,171 @@
 // after Algorithm 1).  Here that instruction is the 16x16x64 int8 matrix op, so the unit
 // of padding is 64 listed k positions per 16-row tile.
 #include <algorithm>
+#include <atomic>
 #include <cstring>
+#include <exception>
+#include <thread>
 
 #include "spmm_internal.h"
 
 namespace spmm {
+
+namespace {
+
+// f(begin, end) over [0, n) in at most 8 threads, each with at least `grain` items; the first exception of a
+// thread is rethrown here.  (Packing a model's weights is what its load waits for; row tiles are independent.)
+template <typename F>
+void parallel_for(int64_t n, int64_t grain, const F& f)
+{
+    const int64_t hw = std::max<int64_t>(1, std::thread::hardware_concurrency());
+    const int64_t parts = std::max<int64_t>(1, std::min<int64_t>({8, hw, n / std::max<int64_t>(1, grain)}));
+    if (parts == 1) {
+        f((int64_t)0, n);
+        return;
+    }
+    std::vector<std::exception_ptr> failed((size_t)parts);
+    std::vector<std::thread> threads;
+    threads.reserve((size_t)parts - 1);
+    auto part = [&](int64_t i) {
+        try {
+            f(n * i / parts, n * (i + 1) / parts);
+        } catch (...) {
+            failed[(size_t)i] = std::current_exception();
+        }
+    };
+    int64_t started = 1;
+    try {
+        for (; started < parts; ++started) threads.emplace_back(part, started);
+    } catch (...) {      // no more threads to be had: the rest of the work is done here
+    }
+    part(0);
+    for (int64_t i = started; i < parts; ++i) part(i);
+    for (std::thread& t : threads) t.join();
+    for (const std::exception_ptr& e : failed)
+        if (e) std::rethrow_exception(e);
+}
+
+inline uint64_t load8(const int8_t* p)
+{
+    uint64_t v;
+    std::memcpy(&v, p, 8);
+    return v;
+}
+
+// bit i: byte i is not zero
+inline uint64_t nonzero_bytes(uint64_t v)
+{
+    const uint64_t high = (((v & 0x7f7f7f7f7f7f7f7full) + 0x7f7f7f7f7f7f7f7full) | v) & 0x8080808080808080ull;
+    return (high >> 7) * 0x0102040810204080ull >> 56;
+}
+
+// The blocks of block-row br, at most K of them, to index / vals (4 bytes per block, as one dword); returns how many
+int64_t blocks_of_row(const int8_t* W, int64_t N, int64_t K, int64_t ldw, spmm_block_t block, int64_t br, int32_t* index,
+                      uint32_t* vals)
+{
+    int64_t n = 0;
+    if (block == SPMM_BLOCK_N4K1) {
+        const int rows = (int)std::min<int64_t>(4, N - br * 4);
+        const int8_t* r[4];
+        for (int i = 0; i < 4; ++i) r[i] = W + (br * 4 + std::min(i, rows - 1)) * ldw;     // (missing rows: the last one again)
+        const uint32_t keep = rows == 4 ? 0xffffffffu : (1u << (8 * rows)) - 1u;
+        auto add = [&](int64_t k) {
+            index[n] = (int32_t)k;
+            vals[n++] = ((uint32_t)(uint8_t)r[0][k] | (uint32_t)(uint8_t)r[1][k] << 8 | (uint32_t)(uint8_t)r[2][k] << 16 |
+                         (uint32_t)(uint8_t)r[3][k] << 24) & keep;
+        };
+        int64_t k = 0;
+        for (; k + 64 <= K; k += 64) {      // 64 positions at a time: few mispredicted loop ends
+            uint64_t m = 0;
+            for (int i = 0; i < 8; ++i) {
+                const int64_t at = k + 8 * i;
+                m |= nonzero_bytes(load8(r[0] + at) | load8(r[1] + at) | load8(r[2] + at) | load8(r[3] + at)) << (8 * i);
+            }
+            for (; m; m &= m - 1) add(k + __builtin_ctzll(m));
+        }
+        for (; k < K; ++k)
+            if (r[0][k] | r[1][k] | r[2][k] | r[3][k]) add(k);
+    } else {
+        const int8_t* r = W + br * ldw;
+        for (int64_t c = 0; c * 4 < K; ++c) {
+            uint32_t v = 0;
+            std::memcpy(&v, r + 4 * c, (size_t)std::min<int64_t>(4, K - 4 * c));
+            if (v) {
+                index[n] = (int32_t)c;
+                vals[n++] = v;
+            }
+        }
+    }
+    return n;
+}
+
+}  // namespace
 
 void bsr_from_dense(const int8_t* W, int64_t N, int64_t K, int64_t ldw, spmm_block_t block, Bsr& out)
 {
     out.N = N;
     out.K = K;
     out.block = block;
-    out.row_ptr.clear();
-    out.index.clear();
-    out.vals.clear();
-    if (block == SPMM_BLOCK_N4K1) {
-        out.block_rows = (N + 3) / 4;
-        out.row_ptr.reserve(out.block_rows + 1);
-        out.row_ptr.push_back(0);
-        for (int64_t br = 0; br < out.block_rows; ++br) {
-            const int64_t n0 = br * 4;
-            const int rows = (int)std::min<int64_t>(4, N - n0);
-            for (int64_t k = 0; k < K; ++k) {
-                int8_t v[4] = {0, 0, 0, 0};
-                bool any = false;
-                for (int i = 0; i < rows; ++i) {
-                    v[i] = W[(n0 + i) * ldw + k];
-                    any |= (v[i] != 0);
-                }
-                if (any) {
-                    out.index.push_back((int32_t)k);
-                    out.vals.insert(out.vals.end(), v, v + 4);
-                }
-            }
-            out.row_ptr.push_back((int64_t)out.index.size());
+    out.block_rows = (block == SPMM_BLOCK_N4K1) ? (N + 3) / 4 : N;
+    out.row_ptr.assign((size_t)out.block_rows + 1, 0);
+    // every thread collects its block-rows, then the pieces are put together
+    struct Piece { int64_t first; std::vector<int32_t> index; std::vector<uint32_t> vals; };
+    std::vector<Piece> pieces(8);
+    std::atomic<int> used{0};
+    const int64_t rows_per_block_row = (block == SPMM_BLOCK_N4K1) ? 4 : 1;
+    parallel_for(out.block_rows, std::max<int64_t>(1, 131072 / (K * rows_per_block_row)), [&](int64_t begin, int64_t end) {
+        Piece& p = pieces[(size_t)used.fetch_add(1)];
+        p.first = begin;
+        p.index.reserve((size_t)((end - begin) * K / 3));
+        p.vals.reserve((size_t)((end - begin) * K / 3));
+        std::vector<int32_t> index((size_t)K);
+        std::vector<uint32_t> vals((size_t)K);
+        for (int64_t br = begin; br < end; ++br) {
+            const int64_t n = blocks_of_row(W, N, K, ldw, block, br, index.data(), vals.data());
+            p.index.insert(p.index.end(), index.begin(), index.begin() + n);
+            p.vals.insert(p.vals.end(), vals.begin(), vals.begin() + n);
+            out.row_ptr[(size_t)br + 1] = (int64_t)p.index.size();      // within the piece, for now
         }
-    } else {
-        out.block_rows = N;
-        const int64_t kblocks = (K + 3) / 4;
-        out.row_ptr.reserve(N + 1);
-        out.row_ptr.push_back(0);
-        for (int64_t n = 0; n < N; ++n) {
-            for (int64_t c = 0; c < kblocks; ++c) {
-                const int cols = (int)std::min<int64_t>(4, K - 4 * c);
-                int8_t v[4] = {0, 0, 0, 0};
-                bool any = false;
-                for (int j = 0; j < cols; ++j) {
-                    v[j] = W[n * ldw + 4 * c + j];
-                    any |= (v[j] != 0);
-                }
-                if (any) {
-                    out.index.push_back((int32_t)c);
-                    out.vals.insert(out.vals.end(), v, v + 4);
-                }
-            }
-            out.row_ptr.push_back((int64_t)out.index.size());
-        }
+    });
+    pieces.resize((size_t)used.load());
+    std::sort(pieces.begin(), pieces.end(), [](const Piece& x, const Piece& y) { return x.first < y.first; });
+    int64_t total = 0;
+    for (size_t i = 0; i < pieces.size(); ++i) {
+        const int64_t end = i + 1 < pieces.size() ? pieces[i + 1].first : out.block_rows;
+        for (int64_t br = pieces[i].first; br < end; ++br) out.row_ptr[(size_t)br + 1] += total;
+        total += (int64_t)pieces[i].index.size();
+    }
+    out.index.resize((size_t)total);
+    out.vals.resize((size_t)total * 4);
+    int64_t at = 0;
+    for (const Piece& p : pieces) {
+        if (p.index.empty()) continue;
+        std::memcpy(&out.index[(size_t)at], p.index.data(), p.index.size() * sizeof(int32_t));
+        std::memcpy(&out.vals[(size_t)at * 4], p.vals.data(), p.vals.size() * 4);
+        at += (int64_t)p.index.size();
     }
 }
 
 void bsr_to_dense(const Bsr& b, int8_t* W, int64_t ldw)
 {
-    for (int64_t n = 0; n < b.N; ++n) std::memset(W + n * ldw, 0, (size_t)b.K);
-    for (int64_t br = 0; br < b.block_rows; ++br) {
-        for (int64_t e = b.row_ptr[br]; e < b.row_ptr[br + 1]; ++e) {
-            const int8_t* v = &b.vals[(size_t)e * 4];
-            if (b.block == SPMM_BLOCK_N4K1) {
-                const int64_t k = b.index[e];
-                for (int i = 0; i < 4 && br * 4 + i < b.N; ++i) W[(br * 4 + i) * ldw + k] = v[i];
-            } else {
-                const int64_t k0 = (int64_t)b.index[e] * 4;
-                for (int j = 0; j < 4 && k0 + j < b.K; ++j) W[br * ldw + k0 + j] = v[j];
+    const bool n4 = b.block == SPMM_BLOCK_N4K1;
+    parallel_for(b.block_rows, std::max<int64_t>(1, 262144 / (b.K * (n4 ? 4 : 1))), [&](int64_t begin, int64_t end) {
+        for (int64_t br = begin; br < end; ++br) {
+            const int rows = n4 ? (int)std::min<int64_t>(4, b.N - br * 4) : 1;
+            int8_t* const w = W + br * (n4 ? 4 : 1) * ldw;
+            for (int i = 0; i < rows; ++i) std::memset(w + i * ldw, 0, (size_t)b.K);
+            for (int64_t e = b.row_ptr[(size_t)br]; e < b.row_ptr[(size_t)br + 1]; ++e) {
+                const int8_t* v = &b.vals[(size_t)e * 4];
+                if (n4) {
+                    const int64_t k = b.index[(size_t)e];
+                    for (int i = 0; i < rows; ++i) w[i * ldw + k] = v[i];
+                } else {
+                    const int64_t k0 = (int64_t)b.index[(size_t)e] * 4;
+                    std::memcpy(w + k0, v, (size_t)std::min<int64_t>(4, b.K - k0));
+                }
             }
         }
-    }
-}
-
-// Expand the block-rows that intersect row tile `tile` into a dense 16 x K scratch.
-static void expand_tile(const Bsr& b, int64_t tile, std::vector<int8_t>& buf)
-{
-    std::fill(buf.begin(), buf.end(), (int8_t)0);
-    const int64_t K = b.K;
-    const int64_t n0 = tile * TILE_ROWS;
-    if (b.block == SPMM_BLOCK_N4K1) {
-        for (int q = 0; q < TILE_ROWS / 4; ++q) {
-            const int64_t br = n0 / 4 + q;
-            if (br >= b.block_rows) break;
-            for (int64_t e = b.row_ptr[br]; e < b.row_ptr[br + 1]; ++e) {
-                const int64_t k = b.index[e];
-                for (int i = 0; i < 4; ++i) buf[(size_t)(q * 4 + i) * K + k] = b.vals[(size_t)e * 4 + i];
-            }
-        }
-    } else {
-        for (int r = 0; r < TILE_ROWS; ++r) {
-            const int64_t n = n0 + r;
-            if (n >= b.N) break;
-            for (int64_t e = b.row_ptr[n]; e < b.row_ptr[n + 1]; ++e) {
-                const int64_t k0 = (int64_t)b.index[e] * 4;
-                for (int j = 0; j < 4 && k0 + j < K; ++j) buf[(size_t)r * K + k0 + j] = b.vals[(size_t)e * 4 + j];
-            }
-        }
-    }
+    });
 }
 
 // Order the listed k of one (row tile, segment) inside its steps so that the transposing
@@ -122,41 +186,43 @@ static void expand_tile(const Bsr& b, int64_t tile, std::vector<int8_t>& buf)
 // whenever the counts allow it; padding slots (zero weights) are pointed at a row of a
 // residue the half-read still lacks instead of all hitting row 0.
 // slot_k[s*64 + 16*g + t] = segment-local k or -1 (padding); slot_row = row actually read.
-static void arrange_for_lds_banks(const std::vector<int32_t>& list, int rows_in_segment, int nsteps,
-                                  std::vector<int32_t>& slot_k, std::vector<int32_t>& slot_row)
+static void arrange_for_lds_banks(const int32_t* list, int n_listed, int rows_in_segment, int nsteps, int32_t* slot_k,
+                                  int32_t* slot_row)
 {
-    const int H = 4 * nsteps;   // half-reads
-    slot_k.assign((size_t)nsteps * STEP_K, -1);
-    slot_row.assign((size_t)nsteps * STEP_K, 0);
+    constexpr int MAXH = 4 * SEGMENT_ROWS / STEP_K;     // half-reads of the longest list
+    const int H = 4 * nsteps;
     if (nsteps == 0) return;
-    std::vector<std::vector<int32_t>> by_res(16);
-    for (int32_t k : list) by_res[k & 15].push_back(k);
+    // entries by residue
+    int32_t by_res[16][SEGMENT_ROWS / 16];
+    int n_res[16] = {0};
+    for (int i = 0; i < n_listed; ++i) by_res[list[i] & 15][n_res[list[i] & 15]++] = list[i];
     int order[16];
     for (int r = 0; r < 16; ++r) order[r] = r;
-    std::stable_sort(order, order + 16, [&](int x, int y) { return by_res[x].size() > by_res[y].size(); });
+    std::stable_sort(order, order + 16, [&](int x, int y) { return n_res[x] > n_res[y]; });
 
     // Largest residue class first; each class is spread over the least-filled half-reads, one
     // entry per half-read, so that no half-read runs out of room while others still have
     // holes.  Only a class with more than H entries is forced to double up somewhere.
-    std::vector<std::vector<int32_t>> hr((size_t)H);
-    std::vector<uint32_t> mask((size_t)H, 0);
-    std::vector<int> by_load((size_t)H);
+    int32_t hr[MAXH][16];
+    int load[MAXH] = {0}, by_load[MAXH];
+    uint32_t mask[MAXH] = {0};
     for (int oi = 0; oi < 16; ++oi) {
         const int r = order[oi];
-        size_t next = 0;
-        while (next < by_res[r].size()) {
-            for (int h = 0; h < H; ++h) by_load[h] = h;
-            std::stable_sort(by_load.begin(), by_load.end(),
-                             [&](int x, int y) { return hr[x].size() < hr[y].size(); });
+        int next = 0;
+        while (next < n_res[r]) {
+            int count[18] = {0};                        // half-reads by load (at most 16), stable
+            for (int h = 0; h < H; ++h) ++count[load[h] + 1];
+            for (int l = 1; l < 18; ++l) count[l] += count[l - 1];
+            for (int h = 0; h < H; ++h) by_load[count[load[h]]++] = h;
             bool placed = false;
-            for (int i = 0; i < H && next < by_res[r].size(); ++i) {
+            for (int i = 0; i < H && next < n_res[r]; ++i) {
                 const int h = by_load[i];
-                if (hr[h].size() >= 16) break;
-                hr[h].push_back(by_res[r][next++]);
+                if (load[h] >= 16) break;
+                hr[h][load[h]++] = by_res[r][next++];
                 mask[h] |= 1u << r;
                 placed = true;
             }
-            if (!placed) break;   // cannot happen: 16 * H slots >= list.size()
+            if (!placed) break;   // cannot happen: 16 * H slots >= n_listed
         }
     }
     for (int h = 0; h < H; ++h) {
@@ -164,8 +230,8 @@ static void arrange_for_lds_banks(const std::vector<int32_t>& list, int rows_in_
         int next_res = 0;
         for (int j = 0; j < 16; ++j) {
             const int g = 2 * pair + j / 8, t = 8 * instr + j % 8;
-            const size_t slot = (size_t)s * STEP_K + 16 * g + t;
-            if (j < (int)hr[h].size()) {
+            const int slot = s * STEP_K + 16 * g + t;
+            if (j < load[h]) {
                 slot_k[slot] = hr[h][j];
                 slot_row[slot] = hr[h][j];
             } else {
@@ -175,6 +241,7 @@ static void arrange_for_lds_banks(const std::vector<int32_t>& list, int rows_in_
                     if (next_res < rows_in_segment) row = next_res;
                     mask[h] |= 1u << next_res;
                 }
+                slot_k[slot] = -1;
                 slot_row[slot] = row;
             }
         }
@@ -305,60 +372,139 @@ void bsr_permute_rows(const Bsr& b, const std::vector<int32_t>& row_order, Bsr& 
 void layout_from_bsr(const Bsr& b, int kc, HostLayout& out)
 {
     const int64_t N = b.N, K = b.K;
-    out.kc = kc;
+    const bool n4 = b.block == SPMM_BLOCK_N4K1;
+    out.kc = kc;                                            // SEGMENT_ROWS
     out.nseg = (int)((K + kc - 1) / kc);
     out.ntiles = (int)((N + TILE_ROWS - 1) / TILE_ROWS);
-    out.vals.clear();
-    out.idx.clear();
-    out.seg_ptr.assign(1, 0);
     out.rowsum.assign((size_t)out.ntiles * TILE_ROWS, 0);
     out.max_steps_per_tile = 0;
     out.max_steps_per_segment = 0;
+    const int nseg = out.nseg, seg_words = kc / 64;
+    const int units = n4 ? TILE_ROWS / 4 : TILE_ROWS;       // block-rows of a tile
+    const int64_t grain = std::max<int64_t>(1, 262144 / (K * TILE_ROWS));
 
-    std::vector<int8_t> buf((size_t)TILE_ROWS * K);
-    std::vector<int32_t> list, slot_k, slot_row;
-    for (int64_t tile = 0; tile < out.ntiles; ++tile) {
-        expand_tile(b, tile, buf);
-        for (int r = 0; r < TILE_ROWS; ++r) {
-            int32_t s = 0;
-            for (int64_t k = 0; k < K; ++k) s += buf[(size_t)r * K + k];
-            out.rowsum[(size_t)tile * TILE_ROWS + r] = s;
-        }
-        int steps_this_tile = 0;
-        for (int seg = 0; seg < out.nseg; ++seg) {
-            const int64_t k_lo = (int64_t)seg * kc, k_hi = std::min<int64_t>(K, k_lo + kc);
-            list.clear();
-            for (int64_t k = k_lo; k < k_hi; ++k) {
-                bool any = false;
-                for (int r = 0; r < TILE_ROWS; ++r) any |= (buf[(size_t)r * K + k] != 0);
-                if (any) list.push_back((int32_t)(k - k_lo));
-            }
-            const int nsteps = (int)((list.size() + STEP_K - 1) / STEP_K);
-            arrange_for_lds_banks(list, (int)(k_hi - k_lo), nsteps, slot_k, slot_row);
-            for (int s = 0; s < nsteps; ++s) {
-                const size_t vbase = out.vals.size(), ibase = out.idx.size();
-                out.vals.resize(vbase + STEP_VAL_BYTES, 0);
-                out.idx.resize(ibase + STEP_IDX_DWORDS, 0);
-                const int32_t* sk = &slot_k[(size_t)s * STEP_K];     // segment-local k, -1 = padding
-                const int32_t* sr = &slot_row[(size_t)s * STEP_K];   // activation row the slot reads
-                for (int lane = 0; lane < 64; ++lane) {
-                    const int g = lane / 16, r = lane % 16;
-                    for (int t = 0; t < 16; ++t) {
-                        const int32_t kl = sk[16 * g + t];
-                        if (kl >= 0) out.vals[vbase + (size_t)lane * 16 + t] = (uint8_t)buf[(size_t)r * K + k_lo + kl];
+    // ---- the union of every tile's k lists, one bit per k; rows past N and block-rows past the end have none
+    std::vector<uint64_t> listed((size_t)out.ntiles * nseg * seg_words, 0);
+    std::vector<int32_t> steps((size_t)out.ntiles * nseg);
+    parallel_for(out.ntiles, grain, [&](int64_t begin, int64_t end) {
+        for (int64_t tile = begin; tile < end; ++tile) {
+            uint64_t* const bits = &listed[(size_t)(tile * nseg) * seg_words];
+            int32_t* const sum = &out.rowsum[(size_t)tile * TILE_ROWS];
+            for (int q = 0; q < units && tile * units + q < b.block_rows; ++q) {
+                const int64_t br = tile * units + q;
+                for (int64_t e = b.row_ptr[(size_t)br]; e < b.row_ptr[(size_t)br + 1]; ++e) {
+                    const int8_t* v = &b.vals[(size_t)e * 4];
+                    if (n4) {
+                        const int32_t k = b.index[(size_t)e];
+                        bits[k >> 6] |= (uint64_t)1 << (k & 63);
+                        for (int i = 0; i < 4; ++i) sum[4 * q + i] += v[i];
+                    } else {
+                        for (int j = 0; j < 4; ++j) {
+                            const int32_t k = b.index[(size_t)e] * 4 + j;
+                            if (v[j]) bits[k >> 6] |= (uint64_t)1 << (k & 63);
+                            sum[q] += v[j];
+                        }
                     }
                 }
-                for (int g = 0; g < 4; ++g)
-                    for (int t = 0; t < 8; ++t)
-                        out.idx[ibase + 8 * g + t] = (uint32_t)sr[16 * g + t] | ((uint32_t)sr[16 * g + 8 + t] << 16);
             }
-            steps_this_tile += nsteps;
-            out.max_steps_per_segment = std::max(out.max_steps_per_segment, nsteps);
-            out.seg_ptr.push_back(out.seg_ptr.back() + nsteps);
+            for (int seg = 0; seg < nseg; ++seg) {
+                int n = 0;
+                for (int w = 0; w < seg_words; ++w) n += __builtin_popcountll(bits[seg * seg_words + w]);
+                steps[(size_t)(tile * nseg + seg)] = (n + STEP_K - 1) / STEP_K;
+            }
+        }
+    });
+    out.seg_ptr.assign((size_t)out.ntiles * nseg + 1, 0);
+    for (int64_t tile = 0; tile < out.ntiles; ++tile) {
+        int steps_this_tile = 0;
+        for (int seg = 0; seg < nseg; ++seg) {
+            const size_t i = (size_t)(tile * nseg + seg);
+            steps_this_tile += steps[i];
+            out.max_steps_per_segment = std::max(out.max_steps_per_segment, steps[i]);
+            out.seg_ptr[i + 1] = out.seg_ptr[i] + steps[i];
         }
         out.max_steps_per_tile = std::max(out.max_steps_per_tile, steps_this_tile);
     }
     out.nsteps = out.seg_ptr.back();
+    out.vals.assign((size_t)out.nsteps * STEP_VAL_BYTES, 0);
+    out.idx.assign((size_t)out.nsteps * STEP_IDX_DWORDS, 0);
+
+    // ---- the steps: listed k dealt to slots, every block's values scattered to their lanes
+    parallel_for(out.ntiles, grain, [&](int64_t begin, int64_t end) {
+        std::vector<int32_t> place((size_t)K);              // k -> 64 * step + slot, for the k listed in this tile
+        int32_t list[SEGMENT_ROWS], slot_k[SEGMENT_ROWS], slot_row[SEGMENT_ROWS];
+        for (int64_t tile = begin; tile < end; ++tile) {
+            for (int seg = 0; seg < nseg; ++seg) {
+                const size_t i = (size_t)(tile * nseg + seg);
+                const int k_lo = seg * kc, rows = (int)std::min<int64_t>(kc, K - k_lo);
+                int n = 0;
+                for (int w = 0; w < seg_words; ++w)
+                    for (uint64_t m = listed[i * seg_words + w]; m; m &= m - 1) list[n++] = 64 * w + __builtin_ctzll(m);
+                arrange_for_lds_banks(list, n, rows, steps[i], slot_k, slot_row);
+                for (int s = 0; s < steps[i]; ++s) {
+                    const int32_t* sk = slot_k + s * STEP_K;     // segment-local k, -1 = padding
+                    const int32_t* sr = slot_row + s * STEP_K;   // activation row the slot reads
+                    const int32_t step = out.seg_ptr[i] + s;
+                    for (int t = 0; t < STEP_K; ++t)
+                        if (sk[t] >= 0) place[(size_t)(k_lo + sk[t])] = (s + out.seg_ptr[i] - out.seg_ptr[(size_t)(tile * nseg)]) * STEP_K + t;
+                    uint32_t* const ix = &out.idx[(size_t)step * STEP_IDX_DWORDS];
+                    for (int g = 0; g < 4; ++g)
+                        for (int t = 0; t < 8; ++t) ix[8 * g + t] = (uint32_t)sr[16 * g + t] | ((uint32_t)sr[16 * g + 8 + t] << 16);
+                }
+            }
+            if (out.seg_ptr[(size_t)(tile * nseg)] == out.seg_ptr[(size_t)((tile + 1) * nseg)]) continue;
+            // vals[step][lane = 16 g + row][t] of slot 16 g + t
+            uint8_t* const vals = &out.vals[(size_t)out.seg_ptr[(size_t)(tile * nseg)] * STEP_VAL_BYTES];
+            auto lane_bytes = [&](int32_t k) {              // of row 0; row r is 16 r bytes on
+                const int32_t p = place[(size_t)k], slot = p & (STEP_K - 1);
+                return vals + (size_t)(p / STEP_K) * STEP_VAL_BYTES + (size_t)(slot & ~15) * 16 + (slot & 15);
+            };
+            for (int q = 0; q < units && tile * units + q < b.block_rows; ++q) {
+                const int64_t br = tile * units + q;
+                for (int64_t e = b.row_ptr[(size_t)br]; e < b.row_ptr[(size_t)br + 1]; ++e) {
+                    uint32_t v;
+                    std::memcpy(&v, &b.vals[(size_t)e * 4], 4);
+                    const int32_t at = b.index[(size_t)e];
+                    if (n4) {
+                        uint8_t* const to = lane_bytes(at) + 4 * q * 16;
+                        for (int j = 0; j < 4; ++j) to[16 * j] = (uint8_t)(v >> (8 * j));
+                    } else {
+                        for (int j = 0; j < 4; ++j)
+                            if (v >> (8 * j) & 0xff) *(lane_bytes(at * 4 + j) + q * 16) = (uint8_t)(v >> (8 * j));
+                    }
+                }
+            }
+        }
+    });
+}
+
+void device_form(const HostLayout& hl, int tile_steps, int64_t records, uint8_t* out)
+{
+    const int64_t nt = hl.ntiles, ns = hl.nseg, at = records_offset(nt, ns);
+    std::memset(out, 0, (size_t)at);
+    std::memcpy(out, hl.rowsum.data(), hl.rowsum.size() * 4);
+    int32_t* const bounds = (int32_t*)(out + bounds_offset(nt));
+    uint8_t* const rec = out + at;
+    if (nt * tile_steps == 0 && hl.nsteps == 0) std::memset(rec, 0, (size_t)records * RECORD_BYTES);
+    parallel_for(nt, std::max<int64_t>(1, 262144 / std::max<int64_t>(1, records * RECORD_BYTES / nt)), [&](int64_t begin, int64_t end) {
+        for (int64_t t = begin; t < end; ++t) {
+            const int64_t first = hl.seg_ptr[(size_t)(t * ns)], past = hl.seg_ptr[(size_t)((t + 1) * ns)];
+            const int64_t shift = tile_steps ? t * tile_steps - first : 0;
+            for (int64_t g = 0; g <= ns; ++g) bounds[t * (ns + 1) + g] = (int32_t)(hl.seg_ptr[(size_t)(t * ns + g)] + shift);
+            for (int64_t g = 0; g < ns; ++g) {
+                const uint32_t base = (uint32_t)(g * SEGMENT_ROWS) * 0x10001u;      // the rows of the whole weight
+                for (int64_t s = hl.seg_ptr[(size_t)(t * ns + g)]; s < hl.seg_ptr[(size_t)(t * ns + g + 1)]; ++s) {
+                    uint8_t* const r = rec + (s + shift) * RECORD_BYTES;
+                    std::memcpy(r, &hl.vals[(size_t)s * STEP_VAL_BYTES], STEP_VAL_BYTES);
+                    for (int i = 0; i < STEP_IDX_DWORDS; ++i) {
+                        const uint32_t v = hl.idx[(size_t)s * STEP_IDX_DWORDS + i] + base;
+                        std::memcpy(r + STEP_VAL_BYTES + 4 * i, &v, 4);
+                    }
+                }
+            }
+            if (tile_steps) std::memset(rec + (past + shift) * RECORD_BYTES, 0, (size_t)(tile_steps - (past - first)) * RECORD_BYTES);
+        }
+    });
 }
 
 }  // namespace spmm

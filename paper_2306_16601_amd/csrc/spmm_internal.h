@@ -65,7 +65,7 @@ void bsr_permute_rows(const Bsr& b, const std::vector<int32_t>& row_order, Bsr& 
 // ---------------------------------------------------------------------------------------
 // Kernel launch interface (plan and dispatch in spmm_plan.hip, kernels in spmm_kernels.h).
 // ---------------------------------------------------------------------------------------
-// The packed weight on the device is one allocation (upload_weight in api.cpp):
+// The packed weight on the device is one allocation (device_form in pack.cpp):
 //     int32   rowsum[ntiles][16]
 //     int32   bounds[ntiles][nseg + 1]   first record of every segment of the tile, and one past its last
 //     (padding to 128 bytes)
@@ -80,6 +80,9 @@ constexpr int64_t records_offset(int64_t ntiles, int64_t nseg)
 {
     return (bounds_offset(ntiles) + ntiles * (nseg + 1) * 4 + 127) & ~(int64_t)127;
 }
+
+// the packed weight in that form (tile_steps as above; `records` of them, at least one)
+void device_form(const HostLayout& hl, int tile_steps, int64_t records, uint8_t* out);
 
 // What a launch passes to a kernel.  96 bytes: the runtime writes the arguments of every launch through the
 // bus, and from 128 bytes on a launch takes 3.3 us of the host instead of 2.7 us (measured; this was a plain

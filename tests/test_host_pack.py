@@ -408,3 +408,20 @@ def test_arguments_of_the_launch_call(args, kw, error):
             sp.spmm_run(*[sub(v) for v in args], **{k: sub(v) for k, v in kw.items()})
     finally:
         sp.spmm_destroy(hh)
+
+
+@pytest.mark.parametrize("orient,N,K,s", [("n4k1", 1030, 777, 0.8), ("n1k4", 1030, 777, 0.8), ("n4k1", 2050, 64, 0.5),
+                                          ("n1k4", 515, 1999, 0.9), ("n4k1", 9, 65536, 0.99)])
+def test_packing_in_several_threads(orient, N, K, s):
+    """Weights large enough to be packed in several threads, with partial block-rows, tiles and words at every end."""
+    W = wl.sparse_weight(N, K, s, orient, jitter=0.2, keys=(91, N, K))
+    W[-1] = 0
+    h = sp.spmm_pack_host(W, orient)
+    try:
+        assert np.array_equal(sp.spmm_unpack(h), W)
+        nz = wl.realised_block_sparsity(W, orient)[0]
+        assert sp.spmm_info(h)[:3] == (N, K, nz)
+        X = wl.activations(K, 3, keys=(91, N, K))
+        assert np.array_equal(decode_layout_acc(h, X), W.astype(np.int64) @ X.astype(np.int64))
+    finally:
+        sp.spmm_destroy(h)
