@@ -272,7 +272,7 @@ static spmm_status_t run_common(const spmm_handle_t* h, const uint8_t* X_dev, in
         const int lo = (ot == SPMM_OUT_U8) ? 0 : -128, hi = (ot == SPMM_OUT_U8) ? 255 : 127;
         if (ep->out_zero_point < lo || ep->out_zero_point > hi) return SPMM_E_ARG;
         a.inv = 1.0f / ep->out_scale;
-        a.out_zp_f = (float)ep->out_zero_point;
+        a.out_zp_f = (float)(ep->out_zero_point - lo);
     }
 
     const int64_t N = h->bsr.N, K = h->bsr.K, esz = quant ? 1 : 4;

@@ -98,7 +98,7 @@ struct KernelArgs {
     uint32_t ld_high;           // and bits 32 .. 39 of the three, 8 bits each
     int32_t M, N;
     uint32_t k_flags;           // K (17 bits), ARG_* flags, x_zero_point << 24
-    float x_scale, inv, out_zp_f;   // inv: 1 / out_scale, or 1 / mid_scale of a table chain
+    float x_scale, inv, out_zp_f;   // inv: 1 / out_scale, or 1 / mid_scale of a table chain; out_zp_f: zero point - smallest code
     uint16_t n_streams;         // persistent kernels: workgroups per row group, each walking token tiles j * n_streams + stream;
                                 // short-batch kernels: row tiles per workgroup
     uint16_t tile_steps;

@@ -205,18 +205,25 @@ __device__ __forceinline__ void store16_out(const __amdgpu_buffer_rsrc_t rs, con
     __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, v), rs, (int)byte_off, (int)uniform_off, SCOPE);
 }
 
-// quantised code of one pre-activation y (Quantize post-operator / table look-up)
+// Quantised codes of four pre-activations (Quantize post-operator / table look-up), packed.
+// v_cvt_pk_u8_f32 converts with saturation to [0, 255] and puts the byte in its place, in one instruction: signed
+// codes go through it with 128 added (KernelArgs::out_zp_f) and taken off the whole word.  (Clamping, converting and
+// packing one by one is 3.5 instructions more per value, and the post-operators of a 96-token tile keep the vector units
+// of a CU busy for as long as half a segment of multiplying does.)
 template <int OUT, int POST, typename Lut>
-__device__ __forceinline__ uint32_t quantise(const Args& a, const float y, const Lut& lut)
+__device__ __forceinline__ uint32_t quantise4(const Args& a, const float (&y)[4], const Lut& lut)
 {
     if constexpr ((POST & SPMM_POST_GELU) != 0) {
-        // key = sat_s8(rint(y / mid_scale)) + 128; v_cvt_pk_u8_f32 converts with saturation to [0, 255]
-        const float t = rintf(y * a.inv) + 128.0f;
-        return lut(__builtin_amdgcn_cvt_pk_u8_f32(t, 0u, 0u));
+        uint32_t q[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r)     // key = sat_s8(rint(y / mid_scale)) + 128
+            q[r] = lut(__builtin_amdgcn_cvt_pk_u8_f32(rintf(y[r] * a.inv) + 128.0f, 0u, 0u));
+        return (q[0] | (q[1] << 8)) | ((q[2] | (q[3] << 8)) << 16);   // (two shift-or pairs, then one more)
     } else {
-        const float lo = (OUT == SPMM_OUT_U8) ? 0.0f : -128.0f;
-        const float hi = (OUT == SPMM_OUT_U8) ? 255.0f : 127.0f;
-        return (uint32_t)((int)fminf(hi, fmaxf(lo, rintf(y * a.inv) + a.out_zp_f))) & 0xffu;
+        uint32_t q = 0;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) q = __builtin_amdgcn_cvt_pk_u8_f32(rintf(y[r] * a.inv) + a.out_zp_f, r, q);
+        return OUT == SPMM_OUT_U8 ? q : q ^ (uint32_t)FLIP;
     }
 }
 
@@ -283,19 +290,17 @@ __device__ __forceinline__ void finish4(const Args& a, const v4i acc, const floa
                     if (r < valid) o[r] = y[r];
             }
         } else {
-            uint32_t q[4];
-#pragma unroll
-            for (int r = 0; r < 4; ++r) q[r] = quantise<OUT, POST>(a, y[r], lut);
+            const uint32_t q = quantise4<OUT, POST>(a, y, lut);
             // (token-tile-major output, [M / 32][N][32]: rows 32 bytes apart, a column's tile out_tile_stride
             // = 32 N bytes after the previous one; four consecutive tokens from a multiple of 4 share a tile)
             const bool ot = (OT == 1) || (OT == -1 && a.out_tile_stride != 0);
             uint8_t* o = (uint8_t*)a.out + (int64_t)n * a.ldo +
                          (ot ? (int64_t)(m0 >> 5) * a.out_tile_stride + (m0 & 31) : (int64_t)m0);
             if (valid >= 4) {
-                ((u32_any*)o)->v = q[0] | (q[1] << 8) | (q[2] << 16) | (q[3] << 24);
+                ((u32_any*)o)->v = q;
             } else {
                 for (int r = 0; r < 4; ++r)
-                    if (r < valid) o[r] = (uint8_t)q[r];
+                    if (r < valid) o[r] = (uint8_t)(q >> 8 * r);
             }
         }
     }
@@ -551,18 +556,17 @@ __device__ __forceinline__ void finish_tile_fast(const Args& a, const v4i (&acc)
             for (int j = 0; j < 4; ++j) {
                 const int i = 4 * h + j;
                 if (i >= G::PIECES) continue;   // (a 96-token tile ends after piece 5)
-                v4f y;
+                float y[4];
 #pragma unroll
                 for (int r = 0; r < 4; ++r) y[r] = __fmaf_rn((float)acc[i][r], scale, bias);
                 if constexpr ((POST & POST_SUM_BIT) != 0) {
-                    if (sum_row_ok) y = y + ((const v4f_any*)(sp + 16 * i))->v;
-                }
-                uint32_t q[4];
+                    if (sum_row_ok) {
+                        const v4f t = ((const v4f_any*)(sp + 16 * i))->v;
 #pragma unroll
-                for (int r = 0; r < 4; ++r) q[r] = quantise<OUT, POST>(a, y[r], lut);
-                // (two shift-or pairs, then one more: three instructions)
-                const uint32_t word = (q[0] | (q[1] << 8)) | ((q[2] | (q[3] << 8)) << 16);
-                *(uint32_t*)(lds + wbase + (uint32_t)(j ^ wsw) * G::STRIDE) = word;
+                        for (int r = 0; r < 4; ++r) y[r] = y[r] + t[r];
+                    }
+                }
+                *(uint32_t*)(lds + wbase + (uint32_t)(j ^ wsw) * G::STRIDE) = quantise4<OUT, POST>(a, y, lut);
             }
             const v4i v = *(const v4i*)(lds + raddr);   // same wave: LDS operations complete in order
             if (orow < a.N && 4 * h + rj < G::PIECES) {
@@ -629,15 +633,22 @@ __global__ void __launch_bounds__(NW * 64) spmm_rowtile_mfma(const KernelArgs ar
     const int x_row0 = tid / PIECES, x_piece = tid % PIECES;
     const uint32_t x_lds0 = G::X0 + (uint32_t)x_row0 * G::STRIDE + x_piece * 16;
 
-    // ---- global loads of half h of the activations of phase q into registers.  The common case
+    // Where a phase is, in scalar registers and stepped from one phase to the next: worked out from its number, it took a
+    // division at every use, on the vector units and by every wave (2048 x 2048 at 75 %, 4096 tokens: 21.4 -> 20.6 us).
+    struct Phase { int seg, tok0; };
+    auto after = [&](Phase f) __attribute__((always_inline)) {
+        if (++f.seg == a.nseg) { f.seg = 0; f.tok0 += S * TM; }
+        return f;
+    };
+    Phase cur = {0, stream * TM}, nxt_phase = after(cur);
+
+    // ---- global loads of half h of the activations of a phase into registers.  The common case
     // (full token tile) is branch-free so that all loads are in flight
     // together; rows past the end of K are redirected to the last valid row (never multiplied).
     // Two halves (first issued at the start of the previous phase, second half-way through its
     // multiply) keep only XH prefetch registers live.
-    auto x_issue_to = [&](v4i (&xr)[XH], const int q, const int h) __attribute__((always_inline)) {
-        const int j = q / a.nseg, seg = q - j * a.nseg;
-        const int tok0 = (stream + j * S) * TM;
-        const int k0 = seg * SEGMENT_ROWS;
+    auto x_issue_to = [&](v4i (&xr)[XH], const Phase f, const int h) __attribute__((always_inline)) {
+        const int tok0 = f.tok0, k0 = f.seg * SEGMENT_ROWS;
         const int last = min(SEGMENT_ROWS, a.K - k0) - 1;
         if (!stager) return;
         if constexpr (XT == 0) {
@@ -688,7 +699,7 @@ __global__ void __launch_bounds__(NW * 64) spmm_rowtile_mfma(const KernelArgs ar
         for (int u = 0; u < XH; ++u)
             *(v4i*)(buf + u * ROWS_PER_PASS * G::STRIDE) = xr[u] ^ (v4i){FLIP, FLIP, FLIP, FLIP};
     };
-    auto x_issue = [&](const int q, const int h) { x_issue_to(xr, q, h); };
+    auto x_issue = [&](const int h) { x_issue_to(xr, nxt_phase, h); };
     auto x_commit = [&](const int q, const int h) { x_commit_from(xr, q, h); };
     // ---- compressed weights + activation-row indices of (tile, segment of phase q).  Loads are
     // unconditional (slots past the segment's step count re-read step 0 and are never used).
@@ -699,11 +710,10 @@ __global__ void __launch_bounds__(NW * 64) spmm_rowtile_mfma(const KernelArgs ar
             load_step(a, step, lane, A[s], I[s]);
         }
     };
-    auto w_issue = [&](const int q, v4i (&A)[MAXS], uint32_t (&I)[MAXS], int& cnt) {
+    auto w_issue = [&](const int seg, v4i (&A)[MAXS], uint32_t (&I)[MAXS], int& cnt) {
         cnt = 0;
         int s0 = 0;
         if (have_tile) {
-            const int seg = q % a.nseg;
             s0 = a.bounds[tile * (a.nseg + 1) + seg];
             cnt = a.bounds[tile * (a.nseg + 1) + seg + 1] - s0;
         }
@@ -730,16 +740,15 @@ __global__ void __launch_bounds__(NW * 64) spmm_rowtile_mfma(const KernelArgs ar
             }
             if (s == MAXS / 2 - 1 && nxt) {
                 x_commit(q + 1, 0);
-                x_issue(q + 1, 1);
+                x_issue(1);
             }
         }
     };
     // ---- after the last segment of a token tile: post-operators, store, reset accumulators
-    auto finish = [&](const int q) __attribute__((always_inline)) {
-        const int j = q / a.nseg;
-        if (q - j * a.nseg != a.nseg - 1) return;
+    auto finish = [&]() __attribute__((always_inline)) {
+        if (cur.seg != a.nseg - 1) return;
         const bool fast_out = takes_fast_stores<OUT>(a);
-        const int tok0 = (stream + j * S) * TM;
+        const int tok0 = cur.tok0;
         if (have_tile) {
             if (fast_out && tok0 + TM <= a.M) {
                 finish_tile_fast<TM, OUT, POST, OTILED>(a, acc, scale, bias, tile, tok0, lane, wave, lds);
@@ -768,8 +777,8 @@ __global__ void __launch_bounds__(NW * 64) spmm_rowtile_mfma(const KernelArgs ar
             w_s0 = a.bounds[tile * (a.nseg + 1)];
             n0 = a.bounds[tile * (a.nseg + 1) + 1] - w_s0;
         }
-        x_issue_to(xr, 0, 0);
-        x_issue_to(x2, 0, 1);
+        x_issue_to(xr, cur, 0);
+        x_issue_to(x2, cur, 1);
         w_issue_at(w_s0, A0, I0, n0);
         if (have_tile) init = a.rowsum[n] * a.corr_mul;
         if constexpr (OUT != SPMM_OUT_S32) {
@@ -797,26 +806,30 @@ __global__ void __launch_bounds__(NW * 64) spmm_rowtile_mfma(const KernelArgs ar
         {   // even phase: register set 0, LDS buffer 0
             const bool nxt = p + 1 < total;
             if (nxt) {
-                x_issue(p + 1, 0);
-                if (reload || p + 1 < 2) w_issue(p + 1, A1, I1, n1);
+                x_issue(0);
+                if (reload || p + 1 < 2) w_issue(nxt_phase.seg, A1, I1, n1);
             }
             multiply(p, nxt, A0, I0, n0);
             if (nxt) x_commit(p + 1, 1);
             wait_global_loads();   // before the output stores: they must not be waited for
-            finish(p);
+            finish();
+            cur = nxt_phase;
+            nxt_phase = after(cur);
             __syncthreads();
         }
         if (p + 1 >= total) break;
         {   // odd phase: register set 1, LDS buffer 1
             const bool nxt = p + 2 < total;
             if (nxt) {
-                x_issue(p + 2, 0);
-                if (reload) w_issue(p + 2, A0, I0, n0);
+                x_issue(0);
+                if (reload) w_issue(nxt_phase.seg, A0, I0, n0);
             }
             multiply(p + 1, nxt, A1, I1, n1);
             if (nxt) x_commit(p + 2, 1);
             wait_global_loads();
-            finish(p + 1);
+            finish();
+            cur = nxt_phase;
+            nxt_phase = after(cur);
             __syncthreads();
         }
     }
@@ -866,6 +879,13 @@ __global__ void __launch_bounds__((NW + LW) * 64) spmm_rowtile_mfma_fed(const Ke
     if (!decode_workgroup(a, (a.ntiles + NW - 1) / NW, S, rg, stream)) return;
     const int n_my = a.tiles_per_stream + (stream < (a.M + TM - 1) / TM - a.tiles_per_stream * S ? 1 : 0);
     const int total = n_my * a.nseg;                                          // phases
+    // where a phase is (see spmm_rowtile_mfma)
+    struct Phase { int seg, tok0; };
+    auto after = [&](Phase f) __attribute__((always_inline)) {
+        if (++f.seg == a.nseg) { f.seg = 0; f.tok0 += S * TM; }
+        return f;
+    };
+    Phase cur = {0, stream * TM};
     constexpr bool TABLE = (POST & SPMM_POST_GELU) != 0 && (OUT == SPMM_OUT_S8 || OUT == SPMM_OUT_U8);
 
     if (wave >= NW) {
@@ -876,19 +896,18 @@ __global__ void __launch_bounds__((NW + LW) * 64) spmm_rowtile_mfma_fed(const Ke
         const uint32_t x_lds0 = G::X0 + (uint32_t)x_row0 * G::STRIDE + x_piece * 16;
         const uint32_t x_off = (uint32_t)xcol(a, x_piece * 16);
         v4i xr[XLOADS];
-        auto x_issue = [&](const int q) __attribute__((always_inline)) {
-            const int j = q / a.nseg, seg = q - j * a.nseg;
-            const int tok0 = (stream + j * S) * TM;
-            const int k0 = seg * SEGMENT_ROWS;
+        auto x_issue = [&]() __attribute__((always_inline)) {   // (and steps to the next phase)
+            const int tok0 = cur.tok0, k0 = cur.seg * SEGMENT_ROWS;
+            cur = after(cur);
             const int last = min(SEGMENT_ROWS, a.K - k0) - 1;   // rows past K repeat the last one (never multiplied)
             if (!stager) return;
             if (tok0 + TM <= a.M) {
                 const uint8_t* src = a.X + (int64_t)k0 * a.ldx + xcol(a, tok0);
+                const uint32_t ldx = (uint32_t)a.ldx;
+                const uint32_t first = (uint32_t)x_row0 * ldx + x_off, end = (uint32_t)last * ldx + x_off;
 #pragma unroll
-                for (int u = 0; u < XLOADS; ++u) {
-                    const int row = min(x_row0 + u * ROWS_PER_PASS, last);
-                    xr[u] = load16_any(src + ((uint32_t)row * (uint32_t)a.ldx + x_off));
-                }
+                for (int u = 0; u < XLOADS; ++u)
+                    xr[u] = load16_any(src + min(first + (uint32_t)(u * ROWS_PER_PASS) * ldx, end));
             } else {
                 // last, ragged token tile: still one branch-free load per piece
                 const RaggedPieces<> tail(a, k0, last);
@@ -909,16 +928,16 @@ __global__ void __launch_bounds__((NW + LW) * 64) spmm_rowtile_mfma_fed(const Ke
             for (int u = 0; u < XLOADS; ++u)
                 *(v4i*)(buf + u * ROWS_PER_PASS * G::STRIDE) = xr[u] ^ (v4i){FLIP, FLIP, FLIP, FLIP};
         };
-        x_issue(0);
+        x_issue();
         int table_byte = 0;
         if constexpr (TABLE) table_byte = a.lut[ltid];          // LTHREADS == 256 entries
         x_commit(0);
         if constexpr (TABLE) lds[G::lut_addr(ltid)] = (uint8_t)table_byte;
-        if (1 < total) x_issue(1);
+        if (1 < total) x_issue();
         __syncthreads();
         for (int p = 0; p < total; ++p) {
             if (p + 1 < total) x_commit(p + 1);
-            if (p + 2 < total) x_issue(p + 2);
+            if (p + 2 < total) x_issue();
             __syncthreads();
         }
         return;
@@ -937,13 +956,15 @@ __global__ void __launch_bounds__((NW + LW) * 64) spmm_rowtile_mfma_fed(const Ke
     // Steps of (tile, segment of phase q).  Read a phase before they are needed: a scalar load whose latency would
     // otherwise precede every phase's weights.
     struct Range { int first, count; };
-    auto range_of = [&](const int q) {
+    int w_seg = 0;                                            // of the next phase whose range will be read
+    auto next_range = [&](const int q) {                      // (phase q's)
         Range r = {0, 0};
         if (have_tile && q < total) {
-            const int32_t* const b = a.bounds + (int64_t)tile * (a.nseg + 1) + q % a.nseg;
+            const int32_t* const b = a.bounds + (int64_t)tile * (a.nseg + 1) + w_seg;
             r.first = b[0];
             r.count = b[1] - r.first;
         }
+        if (++w_seg == a.nseg) w_seg = 0;
         return r;
     };
     auto w_issue = [&](const Range r, v4i (&A)[MAXS], uint32_t (&I)[MAXS]) __attribute__((always_inline)) {
@@ -978,11 +999,12 @@ __global__ void __launch_bounds__((NW + LW) * 64) spmm_rowtile_mfma_fed(const Ke
             }
         }
     };
-    auto finish = [&](const int q) __attribute__((always_inline)) {
-        const int j = q / a.nseg;
-        if (q - j * a.nseg != a.nseg - 1) return;
+    auto finish = [&]() __attribute__((always_inline)) {        // (and steps to the next phase)
+        const Phase at = cur;
+        cur = after(cur);
+        if (at.seg != a.nseg - 1) return;
         const bool fast_out = takes_fast_stores<OUT>(a);
-        const int tok0 = (stream + j * S) * TM;
+        const int tok0 = at.tok0;
         if (have_tile) {
             if (fast_out && tok0 + TM <= a.M) {
                 finish_tile_fast<TM, OUT, POST>(a, acc, scale, bias, tile, tok0, lane, wave, lds);
@@ -998,8 +1020,11 @@ __global__ void __launch_bounds__((NW + LW) * 64) spmm_rowtile_mfma_fed(const Ke
 #pragma unroll
         for (int i = 0; i < PIECES; ++i) acc[i] = (v4i){init, init, init, init};
     };
-    Range r0 = range_of(0), r1 = range_of(1);
-    w_issue(r0, A0, I0);
+    Range r0 = next_range(0), r1 = next_range(1);
+    // (the first weights lie where tile_steps says: requested without waiting for the bounds)
+    Range early = r0;
+    if (a.tile_steps && have_tile) early = {tile * a.tile_steps, a.tile_steps};
+    w_issue(early, A0, I0);
     if (have_tile) init = a.rowsum[n] * a.corr_mul;
     if constexpr (OUT != SPMM_OUT_S32) {
         if (have_tile && n < a.N) {
@@ -1017,19 +1042,19 @@ __global__ void __launch_bounds__((NW + LW) * 64) spmm_rowtile_mfma_fed(const Ke
         for (int p = 0; p < total; p += 2) {
             {   // even phase: register set 0, LDS buffer 0
                 const int cnt = r0.count;
-                if constexpr (RELOAD.value) r0 = range_of(p + 2);
+                if constexpr (RELOAD.value) r0 = next_range(p + 2);
                 multiply(RELOAD, p, A0, I0, cnt, A1, I1, r1);
                 if constexpr (RELOAD.value) wait_global_loads();
-                finish(p);
+                finish();
                 __syncthreads();
             }
             if (p + 1 >= total) break;
             {   // odd phase: register set 1, LDS buffer 1
                 const int cnt = r1.count;
-                if constexpr (RELOAD.value) r1 = range_of(p + 3);
+                if constexpr (RELOAD.value) r1 = next_range(p + 3);
                 multiply(RELOAD, p + 1, A1, I1, cnt, A0, I0, r0);
                 if constexpr (RELOAD.value) wait_global_loads();
-                finish(p + 1);
+                finish();
                 __syncthreads();
             }
         }
