@@ -167,11 +167,9 @@ spmm_status_t spmm_layout_export(const spmm_handle_t *h, uint8_t *vals_host, uin
  *   X_dev   device, uint8 [K][ldx], ldx >= M
  *   out_dev device, [N][ldo] of the element type of ep->out_type, ldo >= M (in elements)
  *   M > 0
- * Any alignment, any leading dimension >= M and any token count work.  The fast paths need X_dev
- * and out_dev (and sum) 16-byte aligned with row pitches that are multiples of 16 bytes; M itself
- * may be anything then (a ragged last token tile costs only that tile).  Unaligned operands are
- * read through aligned dwords and written in the widest aligned pieces, which is noticeably
- * slower for short batches and several times slower for long ones: pad the pitches.
+ * Any alignment, any leading dimension >= M and any token count work, and all of them take the same kernels and
+ * 16-byte accesses: an unaligned row costs the cache lines its pieces straddle.  Only rows more than 4 MiB apart, an X
+ * of less than 16 bytes and outputs of 2 GiB and more take general paths.
  * The current HIP device must be the one the handle was packed on (SPMM_E_ARG otherwise).
  * Errors: SPMM_E_ARG (also: missing w_scale / lut, non-positive scales, zero point out
  * of range, ld_sum < M), SPMM_E_UNSUPPORTED (Sum with S32 output or with the table chain),
@@ -209,9 +207,8 @@ spmm_status_t spmm_make_gelu_lut(float mid_scale, float out_scale, int32_t out_z
 
 /* Kernel configuration chosen for a problem (reporting / tuning aid, Section 3.2 notes
  * that the tile size is tunable offline).  Writes the token-tile width, rows per
- * workgroup and the launch grid spmm_run would use for M tokens with 16-byte aligned operands
- * (unaligned operands may take a different kernel: their general paths need registers that the
- * widest configurations do not have). */
+ * workgroup and the launch grid spmm_run would use for M tokens (outputs of 2 GiB and more may take
+ * a different kernel: the widest configurations have no registers for their general store path). */
 spmm_status_t spmm_plan(const spmm_handle_t *h, int64_t M, spmm_out_t out_type,
                         int32_t *token_tile, int32_t *rows_per_workgroup, int64_t *workgroups);
 
@@ -222,21 +219,17 @@ spmm_status_t spmm_plan(const spmm_handle_t *h, int64_t M, spmm_out_t out_type,
  *                   denser weights silently use 8).
  *   token_tile  96: the same kernel on 96-token tiles, variant 0 or 16 (16 waves; denser
  *                   weights silently use token tile 128 with 8 waves).
- *   token_tile  64: variant 101 / 102 = the simple, unpipelined kernel with 1 / 2 row tiles
- *                   per wave (an independent second implementation for cross-checks, and the
- *                   automatic choice for problems too small to fill the chip).
- *   token_tile 32, 16: variant 101 = the simple kernel on narrower token tiles (what the
- *                   automatic choice takes for short batches: more, smaller workgroups).
- *   token_tile 16, 32: variant 103 = the short-batch kernel, which keeps a workgroup's whole
- *                   [K x token_tile] slab of activations in LDS (K <= 4096 with 16-token tiles,
- *                   K <= 3072 with 32; a longer K silently runs variant 101).  The automatic
- *                   choice for short batches with 2048 < K <= 4096:
- *                   Section 4.3 measures the kernels at 32 tokens and the models at sequence
- *                   lengths of 16 to 384.
- *   token_tile 64, 32, 16: variant 104 = the streamed kernel: the simple kernel's segment by
- *                   segment staging with the weights arriving through rotating register sets
- *                   (the automatic choice for short batches from seven K segments on, K > 3072,
- *                   where the short-batch kernel does not apply).
+ *   token_tile 128, 96, 64: variant 112 = the pipelined kernel with 12 waves and 4 more that only stage
+ *                   activations; 128: variant 108 = with 8 + 4 (what denser weights silently use).
+ *   token_tile 64, 32, 16: variant 101 = the simple kernel, the K slab of activations of a token tile
+ *                   in LDS at once (64: variant 102 = 2 row tiles per wave): small problems.
+ *   token_tile 32, 16: variant 105 / 106 = the same with 2 / 4 row tiles per workgroup instead of 8, whose
+ *                   waves share a row tile's steps (problems that would leave most CUs idle).
+ *   token_tile 16, 32: variant 103 = the short-batch kernel (K <= 4096 with 16-token tiles,
+ *                   K <= 3072 with 32; a longer K silently runs variant 101).  Section 4.3 measures the
+ *                   kernels at 32 tokens and the models at sequence lengths of 16 to 384.
+ *   token_tile 64, 32, 16: variant 104 = the streamed kernel: a ring of four K segments of activations,
+ *                   the weights a segment ahead (mid-size batches, short ones with the longest K).
  * Unsupported values return SPMM_E_UNSUPPORTED and change nothing.  Not thread-safe against
  * concurrent spmm_run on the same handle. */
 spmm_status_t spmm_set_tuning(spmm_handle_t *h, int32_t token_tile, int32_t variant);

@@ -115,13 +115,13 @@ constexpr uint32_t ARG_OUT_ALIGNED = 1u << 21;  // ARG_OUT_FAST, out base 16-byt
 constexpr int ARG_XCD_SHIFT = 22;               // 2 bits: how a workgroup id decodes, see decode_workgroup
 
 struct Plan {
-    int token_tile;          // TM of the pipelined kernel (128 or 96), or 64 for the simple kernel
-    int row_tiles_per_wave;  // 1 (pipelined) or 1 / 2 (simple kernel)
-    int waves;               // NW: waves that own a row tile
+    int token_tile;          // TM: 128, 96 or (with loaders) 64 for the persistent kernels, 64, 32 or 16 for the others
+    int row_tiles_per_wave;  // 1, or 2 (simple kernel)
+    int waves;               // waves that own a row tile; short-batch kernels: row tiles (or pairs) per workgroup of 8 waves
     int loaders;             // pipelined kernel: extra waves that only stage activations (0 or 4)
     int simple;              // 1: simple kernel
-    int slab;                // 1: the short-batch kernel (token tile 16 or 32, whole K resident in LDS) in its place
-    int stream;              // 1: the streamed kernel (segment staging, flat weight stream) in its place
+    int slab;                // 1: the short-batch kernel (token tile 16: K <= 4096 resident in LDS; 32: the ring) in its place
+    int stream;              // 1: the streamed kernel (a ring of segments) in its place
     int max_steps;           // unroll bound of the per-segment step loop (pipelined kernel)
     int n_row_groups, n_tok_tiles, n_streams;
     int xcd_row_bits;        // the 8 XCDs take 2^this slices of the row groups and 8 / 2^this of the tokens
@@ -129,11 +129,13 @@ struct Plan {
 };
 
 // variant: 0 = automatic, 8 / 16 = waves per workgroup (pipelined, token tile 128 or 96),
-// 108 / 112 = pipelined with 8 / 12 compute waves and 4 loader waves (token tile 128; 112 also 96),
+// 108 / 112 = pipelined with 8 / 12 compute waves and 4 loader waves (token tile 128; 112 also 96 and 64),
 // 101 / 102 = simple kernel with 1 / 2 row tiles per wave (token tile 64; 101 also 32 and 16),
-// 103 = short-batch kernel (token tile 16 or 32), 104 = streamed kernel (token tile 64, 32 or 16)
+// 103 = short-batch kernel (token tile 16 or 32), 104 = streamed kernel (token tile 64, 32 or 16),
+// 105 / 106 = simple or, from 5 segments on with 16-token tiles, short-batch kernel with 2 / 4 row tiles per workgroup,
+// whose waves share a row tile's steps (token tile 32 or 16)
 constexpr int SLAB_SEGMENTS = 8;      // K segments the short-batch kernel keeps in LDS, token tile 16
-constexpr int SLAB_SEGMENTS_32 = 6;   // and token tile 32
+constexpr int SLAB_SEGMENTS_32 = 6;   // K segments it takes with token tile 32
 // what the plan needs to know of a packed weight
 struct WeightDims {
     int ntiles, nseg, K;
@@ -141,7 +143,7 @@ struct WeightDims {
     int max_steps_per_segment, max_steps_per_tile;
 };
 bool plan_supported(int token_tile, int variant);
-// out_bytes: size of an output element (the plan gives 4-byte outputs workgroups with loader waves)
+// out_bytes: size of an output element
 // x_fast: see KernelArgs; an X without it takes the simple kernel, whatever was forced
 // out_fast: 32-bit offsets suffice for out; if not, the automatic choice avoids the 16-wave pipelined
 // kernels, whose general store path is slow for want of registers

@@ -22,14 +22,15 @@
 //    workgroup decomposition: a workgroup owns a group of row tiles and walks over token
 //    tiles, so the compressed weights it needs stay in registers.
 //
-// Four kernels share the layout and the inner step (two transposing LDS reads, one matrix
-// instruction per 16 tokens); the host's plan (spmm_plan.hip) picks one by shape:
+// Five kernels share the layout and the inner step (two transposing LDS reads, one matrix
+// instruction per 16 tokens); the host's plan (spmm_plan.hip) picks one by its estimate of their times:
 //   spmm_rowtile_mfma         persistent, software-pipelined: long batches
-//   spmm_rowtile_mfma_simple  one workgroup per 128 rows x 16/32/64 tokens, segment by segment:
-//                             small problems, and the independent cross-check of the others
-//   spmm_rowtile_mfma_slab    the same decomposition with the whole K slab of activations in
-//                             LDS and the weights streamed: short batches, 2048 < K <= 4096
-//   spmm_rowtile_mfma_stream  segment staging with the streamed weights: short batches, longest K
+//   spmm_rowtile_mfma_fed     the same with waves that only stage activations: long batches with 4-byte
+//                             outputs, or with weights that do not stay in registers
+//   spmm_rowtile_mfma_simple  one workgroup per 32 to 128 rows x 16/32/64 tokens, the whole K slab (up to
+//                             2048 rows at a time) in LDS at once: small problems
+//   spmm_rowtile_mfma_slab    the same with 4096 resident rows: short batches, 2048 < K <= 4096
+//   spmm_rowtile_mfma_stream  a ring of four segments of activations: mid-size batches, short ones with the longest K
 //
 // Lane roles of the matrix instruction (D = A.B, 64 lanes, g = lane / 16, c = lane % 16):
 //   A operand (activations): row = token c, bytes t = k-list slots 16g .. 16g+15
@@ -414,7 +415,11 @@ __device__ __forceinline__ bool decode_workgroup(const Args& a, const int n_row_
 }
 
 // =======================================================================================
-// Pipelined persistent kernel (the one spmm_run launches).
+// Pipelined persistent kernel: long batches.  What bounds it is the LDS -- the gather reads 1 KB of it per step
+// and 16 tokens at 121 bytes a clock per CU -- and then the times in which it is idle because all waves of the
+// workgroup do something else together: requesting the next phase and the post-operators (4096 x 1024 at 85 %, 6144
+// tokens, table chain: 24.3 us, of which 11 us gather, 3.5 us the start, about a quarter the post-operators; two workgroups
+// of 8 waves to a CU, to overlap them, read X twice as often and take 30.3 us).
 //
 // Workgroup = NW waves.  Wave w owns row tile NW*rg + w (16 output rows) for the whole
 // kernel; the workgroup walks over token tiles of TM tokens (stream, stream + S, ..) and,
@@ -465,6 +470,7 @@ struct Geo<96> {
 
 // TM = 64 (loader-wave kernel only): four pieces per row, twice as many tiles per stream; the output
 // stores of a workgroup then start after half the time and the last tile's burst is half as long.
+// (3072 x 768 at 85 %, 4096 tokens: 13.8 us; 96-token tiles 16.5, 16 waves without loaders 16.9.)
 template <>
 struct Geo<64> {
     static constexpr int STRIDE = 80, PIECES = 4, HALVES = 1;
@@ -1064,8 +1070,8 @@ __global__ void __launch_bounds__((NW + LW) * 64) spmm_rowtile_mfma_fed(const Ke
 }
 
 // =======================================================================================
-// Short batches: the simple kernel (token tile 64, 32 or 16, any K) and the short-batch kernel (token
-// tile 16 with K <= 4096, or 32 with K <= 3072) are one body with different amounts of resident K.
+// Short batches: the simple kernel (token tile 64, 32 or 16, any K) and the short-batch kernel with 16-token
+// tiles (K <= 4096) are one body with different amounts of resident K.
 //
 // A launch here is a few microseconds long and its time is a chain of memory latencies, so everything
 // a workgroup needs is requested before anything waits: the first weights of every wave (whose place
@@ -1074,7 +1080,8 @@ __global__ void __launch_bounds__((NW + LW) * 64) spmm_rowtile_mfma_fed(const Ke
 // wave walks its steps in groups of CH, branch-free inside a group (steps past the end count with zero
 // weights), the weights of the next NS - 1 groups in flight.  A K beyond the RES resident rows goes
 // round by round.  (The kernel before this one staged 512 rows at a time, two barriers per segment, and
-// requested a step's weights when it multiplied them: 768x768 at 80 %, 32 tokens, @@T1@@ us.)
+// requested a step's weights when it multiplied them: 768x768 at 80 %, 32 tokens, a call every 7.2 us; with this one,
+// and a launch that is a microsecond shorter on the host, every 4.0 us.)
 //
 // LDS: a row is TM bytes, unpadded, so that two (TM = 16, K = 2048: five) workgroups share a CU.  Its
 // 16-byte pieces are rotated by an xor with bits of the row number such that rows whose numbers differ
@@ -1109,7 +1116,7 @@ struct Resident {
     static constexpr int NS = TM == 16 ? (WIDE ? 6 : 3) : WIDE ? 5 : TM == 32 ? 4 : 3;
     static constexpr int LDS = RES * TM + 256;                  // activations, then the table
     static constexpr bool TABLE = (POST & SPMM_POST_GELU) != 0 && (OUT == SPMM_OUT_S8 || OUT == SPMM_OUT_U8);
-    static_assert(PASSES * PASS_ROWS == RES && SEGMENT_ROWS % PASS_ROWS == 0, "threads tile a segment");
+    static_assert((RES & (RES - 1)) == 0 && PASSES * PASS_ROWS == RES && SEGMENT_ROWS % PASS_ROWS == 0, "threads tile a segment");
     static_assert(8 * PIECES * 1024 <= RES * TM, "the partial sums fit where the activations were");
 
     static __device__ __forceinline__ uint32_t row_offset(const uint32_t r) { return Swizzle<TM>::row(r); }
@@ -1245,7 +1252,7 @@ struct Resident {
 #pragma unroll
                                 for (int j = 0; j < CH; ++j) {
                                     // (a row of a step past the end may lie anywhere in the weight: kept inside the buffer)
-                                    const uint32_t mask = (RES & (RES - 1)) == 0 ? RES - 1 : 0xffff;
+                                    constexpr uint32_t mask = RES - 1;
                                     const uint32_t o0 = row_offset(I[k][j] & mask) + (c & 1) * 8;
                                     const uint32_t o1 = row_offset(I[k][j] >> 16 & mask) + (c & 1) * 8;
 #pragma unroll
@@ -1316,7 +1323,8 @@ struct Resident {
 // after its last reader's, so no second barrier is needed.  The weights of a segment, at most 8 steps, are
 // requested one segment ahead into one of two register sets; the first set at the very start.
 // (The kernel before this one had one segment buffer, two barriers per segment, and the next segment's
-// activations in flight for one segment of multiplying, which is shorter than their latency: @@T2@@.)
+// activations in flight for one segment of multiplying, which is shorter than their latency: 768x3072 at 80 %, 333
+// tokens, 15.7 us; now 11.6 us.)
 // =======================================================================================
 template <int TM, int OUT, int POST>
 struct Ring {

@@ -4,7 +4,7 @@
 //   simple kernel    : -DSPMM_CFG_SIMPLE=<1|2> (row tiles per wave) -DSPMM_CFG_SIMPLE_TM=<64|32|16> (token tile)
 //   short-batch kernel: -DSPMM_CFG_SLAB=<16|32>      (token tile)
 //   streamed kernel  : -DSPMM_CFG_STREAM=<64|32|16>  (token tile)
-//   loader-fed pipelined kernel: -DSPMM_CFG_FED_TM=<128|96> -DSPMM_CFG_NW=<12|8> -DSPMM_CFG_MAXS=<4|6|8>
+//   loader-fed pipelined kernel: -DSPMM_CFG_FED_TM=<128|96|64> -DSPMM_CFG_NW=<12|8> -DSPMM_CFG_MAXS=<4|6|8>
 // Each defines one function launch_cfg_<...>() that picks the epilogue instantiation and
 // launches it; spmm_plan.hip calls them.
 #include "spmm_kernels.h"

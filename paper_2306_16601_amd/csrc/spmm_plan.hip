@@ -90,7 +90,8 @@ static void fill_pipelined(Plan& p, int64_t M, const WeightDims& w, int num_cus,
     p.workgroups = (int64_t)p.n_row_groups * p.n_streams;
 }
 
-// Simple, short-batch and streamed kernels: tm-token tiles, one workgroup of 8 waves per (row group, tile).
+// Simple, short-batch and streamed kernels: tm-token tiles, one workgroup of 8 waves per (row group, tile), `waves` row
+// tiles (or pairs of them) per row group.  The XCD split: as few rounds of workgroups as possible, then the least fetched.
 static void fill_simple(Plan& p, int64_t M, const WeightDims& w, int num_cus, int r, int tm, int waves = 8)
 {
     p.token_tile = tm;
@@ -192,7 +193,7 @@ Plan make_plan(int64_t M, const WeightDims& w, int num_cus, int force_tm, int va
         }
         const int r = variant == 102 ? 2 : 1, row_tiles = variant == 105 ? 2 : variant == 106 ? 4 : 8;
         fill_simple(p, M, w, num_cus, r, force_tm, row_tiles);
-        // the short-batch kernel holds K <= 4096 (3072 with 32-token tiles); longer K silently runs the simple kernel
+        // the short-batch kernel takes K <= 4096 (3072 with 32-token tiles); longer K silently runs the simple kernel
         if (variant == 103) p.slab = nseg <= (force_tm == 16 ? SLAB_SEGMENTS : SLAB_SEGMENTS_32);
         if (row_tiles < 8) p.slab = force_tm == 16 && nseg > 4 && nseg <= SLAB_SEGMENTS;
         p.stream = variant == 104;
@@ -297,7 +298,6 @@ int launch_spmm(const Plan& plan, KernelArgs& a, spmm_out_t out_type, int postop
         else return (int)hipErrorInvalidValue;
         return (int)hipGetLastError();
     }
-    // 2-D grid: x = token-tile stream, y = row group
     a.tiles_per_stream = (uint32_t)(plan.n_tok_tiles / plan.n_streams);
     const int maxs = (plan.waves == 8 && plan.max_steps == 5) ? 6 : plan.max_steps;   // no 8-wave 5-step build
     if (plan.loaders) {

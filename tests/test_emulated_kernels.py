@@ -94,6 +94,22 @@ CASES = [
     (128, 2561, 3, 0.9, "s32", "none", 32, 103, "spmm_rowtile_mfma_slab<32", {}),
     (128, 3585, 69, 0.9, "u8", "none", 32, 104, "spmm_rowtile_mfma_stream<32", {}),
     (128, 3585, 6, 0.9, "f32", "none", 16, 104, "spmm_rowtile_mfma_stream<16", {}),
+    # 2 and 4 row tiles per workgroup, the waves sharing a row tile's steps: fewer steps than shares, empty shares, a
+    # last workgroup with one row tile
+    (144, 768, 50, 0.8, "f32", "none", 16, 105, "spmm_rowtile_mfma_simple<16", {"kind": "ragged"}),
+    (208, 1030, 33, 0.8, "s8", "gelu", 32, 106, "spmm_rowtile_mfma_simple<32", {}),
+    (48, 64, 20, 0.9, "s32", "none", 32, 105, "spmm_rowtile_mfma_simple<32", {}),
+    (80, 2600, 17, 0.9, "u8", "none", 16, 106, "spmm_rowtile_mfma_slab<16", {"kind": "ragged"}),
+    (40, 4096, 32, 0.8, "s32", "none", 16, 105, "spmm_rowtile_mfma_slab<16", {"xtiled": True}),
+    # more K than the resident rows: round by round, the last of one row
+    (128, 4097, 17, 0.9, "s8", "none", 16, 101, "spmm_rowtile_mfma_simple<16", {}),
+    (160, 2049, 65, 0.8, "f32", "none", 64, 102, "spmm_rowtile_mfma_simple<64", {"kind": "ragged"}),
+    # the ring wraps (nine segments), and with a single segment
+    (144, 4097, 33, 0.9, "s8", "gelu", 32, 104, "spmm_rowtile_mfma_stream<32", {"kind": "ragged"}),
+    (128, 300, 64, 0.8, "f32", "none", 64, 104, "spmm_rowtile_mfma_stream<64", {}),
+    # row groups and token tiles that the slices of the eight XCDs do not divide
+    (1200, 128, 75, 0.8, "s32", "none", 16, 105, "spmm_rowtile_mfma_simple<16", {"cus": 16}),
+    (272, 256, 1300, 0.9, "s8", "none", 128, 8, "spmm_rowtile_mfma<128, 8", {"cus": 24}),
 ]
 
 

@@ -416,6 +416,16 @@ def test_every_epilogue_with_unaligned_leading_dims(out_type, postop):
         check_case(case, ldx=101, ldo=93, tuning=tuning)
 
 
+@pytest.mark.parametrize("tuning", [(16, 105), (16, 106), (32, 105), (32, 106)], ids=["2x16", "4x16", "2x32", "4x32"])
+@pytest.mark.parametrize("N,K,M,s", [(16, 64, 1, 0.9), (768, 768, 32, 0.8), (1032, 2049, 33, 0.9), (72, 4096, 50, 0.7),
+                                     (40, 4097, 17, 0.95), (300, 1000, 200, 0.0)])
+def test_waves_that_share_a_row_tile(N, K, M, s, tuning):
+    """Two and four row tiles per workgroup of 8 waves: fewer steps than waves to share them, a last workgroup with
+    one row tile, K beyond the resident rows, every step slot full."""
+    for ot, po in (("s32", "none"), ("s8", "gelu"), ("f32", "none")):
+        check_case(wl.Case("share", N, K, M, s, wl.N4K1, ot, po, keys=(69, N, K, M)), tuning=tuning)
+
+
 @pytest.mark.parametrize("N,K,M,s", [(768, 3072, 32, 0.9), (768, 3072, 128, 0.8), (1024, 4096, 100, 0.9),
                                      (200, 4096, 37, 0.0), (48, 2600, 16, 0.999), (130, 4097, 50, 0.8),
                                      (96, 8192, 33, 0.9)])
