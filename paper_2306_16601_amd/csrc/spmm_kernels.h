@@ -133,6 +133,19 @@ struct __attribute__((packed)) v4f_any { v4f v; };
 struct __attribute__((packed)) u32_any { uint32_t v; };
 __device__ __forceinline__ v4i load16_any(const void* p) { return ((const v4i_any*)p)->v; }
 
+// v, as a value the compiler knows nothing of: what is worked out from it is worked out where it stands, and not ahead
+// of the phase loop of a persistent kernel, where it would occupy registers throughout.  The 16-wave kernels have 128
+// and need them: with addresses, columns and rows kept across the phases up to 20 were spilled, weight rows among them,
+// and a spilled load is waited for as soon as it is issued, with every load before it.  Measured, kept -> worked out
+// (6144 tokens, table chain, tile-major, 80 %): 1024 x 1024 11.2 -> 9.7 us, 4096 x 1024 27.8 -> 26.4; 1024 x 4096 with
+// Sum, int8 31.7 -> 29.7; 1024 x 1024 with Sum, binary32 rows 18.5 -> 16.6.
+template <typename T>
+__device__ __forceinline__ T pinned(T v)
+{
+    asm volatile("" : "+v"(v));
+    return v;
+}
+
 constexpr int FLIP = (int)0x80808080;   // x ^ 0x80 == x - 128 as a signed byte
 
 // GELU in its erf form, y * Phi(y) = 0.5 * y * erfc(-y / sqrt(2)), in binary32, branch-free.
@@ -228,8 +241,10 @@ __device__ __forceinline__ uint32_t quantise4(const Args& a, const float (&y)[4]
     }
 }
 
-// The second operand of Sum for tokens m0 .. m0 + 3 of output row n (none of it is read outside [N][M])
-template <int POST>
+// The second operand of Sum for tokens m0 .. m0 + 3 of output row n, m0 < M (none of it is read outside [N][M])
+// TIGHT: tokens past the end repeat the first one instead of being zero (either way they are never stored): zeros
+// would be kept in registers all through a persistent kernel.
+template <int POST, bool TIGHT = false>
 __device__ __forceinline__ v4f load_sum4(const Args& a, const int n, const int m0)
 {
     v4f v = {0.0f, 0.0f, 0.0f, 0.0f};
@@ -238,8 +253,9 @@ __device__ __forceinline__ v4f load_sum4(const Args& a, const int n, const int m
         if (m0 + 4 <= a.M) {
             v = ((const v4f_any*)sp)->v;
         } else {
+            if constexpr (TIGHT) v = (v4f){sp[0], sp[0], sp[0], sp[0]};
 #pragma unroll
-            for (int r = 0; r < 3; ++r)
+            for (int r = TIGHT; r < 3; ++r)
                 if (m0 + r < a.M) v[r] = sp[r];
         }
     }
@@ -506,9 +522,7 @@ __device__ __forceinline__ void finish_tile_fast(const Args& a, const v4i (&acc)
                                                  const int tok0, int lane, const int wave, uint8_t* lds)
 {
     using G = Geo<TM>;
-    // Keep the address arithmetic below local to the epilogue: without this the compiler hoists
-    // it out of the phase loop and the long-lived results push the kernel into register spills.
-    asm volatile("" : "+v"(lane));
+    lane = pinned(lane);
     const int g = lane >> 4, c = lane & 15;
     if constexpr (OUT == SPMM_OUT_S32) {
         // fast path: the whole output is < 2 GiB (checked on the host), 32-bit offsets suffice
@@ -589,6 +603,24 @@ __device__ __forceinline__ void finish_tile_fast(const Args& a, const v4i (&acc)
     }
 }
 
+// The same for a tile that takes the general path: cut by the end of the tokens, or an output that takes_fast_stores
+// refuses.  TIGHT: nothing of it is to stay in registers across the phases (see pinned).
+template <int TM, int OUT, int POST, bool WIDE, bool TIGHT, int OT = -1>
+__device__ __forceinline__ void finish_tile_any(const Args& a, const v4i (&acc)[Geo<TM>::PIECES], const float scale,
+                                                const float bias, const int tile, const int tok0, int lane, const uint8_t* lds)
+{
+    if constexpr (TIGHT) lane = pinned(lane);
+    const int g = lane >> 4, n = tile * TILE_ROWS + (lane & 15);
+    if (n < a.N) {
+        const LdsLut<TM> lut{lds};
+#pragma unroll
+        for (int i = 0; i < Geo<TM>::PIECES; ++i) {
+            const int m0 = tok0 + 16 * i + 4 * g;
+            if (m0 < a.M) finish4<OUT, POST, WIDE, OT>(a, acc[i], scale, bias, n, m0, lut, load_sum4<POST, TIGHT>(a, n, m0));
+        }
+    }
+}
+
 template <int TM, int NW, int MAXS, int OUT, int POST, int LAYOUT = 0>
 __global__ void __launch_bounds__(NW * 64) spmm_rowtile_mfma(const KernelArgs args)
 {
@@ -609,7 +641,13 @@ __global__ void __launch_bounds__(NW * 64) spmm_rowtile_mfma(const KernelArgs ar
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int g = lane >> 4, c = lane & 15;
+    const int c = lane & 15;
+    // 16 waves have 128 registers each: the thread id is all of a thread's position that is kept across the phases
+    constexpr bool TIGHT = NW > 8;
+    auto mine = [&]() __attribute__((always_inline)) {
+        if constexpr (TIGHT) return pinned(tid);
+        else return tid;
+    };
 
     // workgroup -> (row group, token-tile stream)
     const int S = a.n_streams;
@@ -636,8 +674,6 @@ __global__ void __launch_bounds__(NW * 64) spmm_rowtile_mfma(const KernelArgs ar
 
     // per-thread staging coordinates: XLOADS rows (ROWS_PER_PASS apart), one 16-byte piece
     const bool stager = (STAGERS == NTHREADS) || wave < STAGERS / 64;
-    const int x_row0 = tid / PIECES, x_piece = tid % PIECES;
-    const uint32_t x_lds0 = G::X0 + (uint32_t)x_row0 * G::STRIDE + x_piece * 16;
 
     // Where a phase is, in scalar registers and stepped from one phase to the next: worked out from its number, it took a
     // division at every use, on the vector units and by every wave (2048 x 2048 at 75 %, 4096 tokens: 21.4 -> 20.6 us).
@@ -657,6 +693,7 @@ __global__ void __launch_bounds__(NW * 64) spmm_rowtile_mfma(const KernelArgs ar
         const int tok0 = f.tok0, k0 = f.seg * SEGMENT_ROWS;
         const int last = min(SEGMENT_ROWS, a.K - k0) - 1;
         if (!stager) return;
+        const int t = mine(), x_row0 = t / PIECES, x_piece = t % PIECES;
         if constexpr (XT == 0) {
             if (tok0 + TM <= a.M) {
                 // 32-bit offsets from a uniform base (x_fast)
@@ -682,11 +719,7 @@ __global__ void __launch_bounds__(NW * 64) spmm_rowtile_mfma(const KernelArgs ar
             // token-tile-major activations: the layout is 16-byte aligned and padded to whole 32-token tiles, so
             // a piece that starts before M is read whole and one that starts at or after M is not needed at
             // all (its columns are never stored): one branch-free form, no masks, no unaligned path
-            // (the piece's offset is worked out again at every call, from a thread id the compiler cannot
-            // see through: kept in a register across the phases it would be one register too many)
-            int t = tid;
-            asm volatile("" : "+v"(t));
-            const int col = tok0 + (t % PIECES) * 16;
+            const int col = tok0 + x_piece * 16;
             const uint8_t* src = a.X + (int64_t)k0 * 32;
             const uint32_t off = col < a.M ? (uint32_t)xcol<1>(a, col) : 0u;
 #pragma unroll
@@ -700,7 +733,8 @@ __global__ void __launch_bounds__(NW * 64) spmm_rowtile_mfma(const KernelArgs ar
     // ---- ... and from registers into LDS buffer q % 2, as x - 128
     auto x_commit_from = [&](const v4i (&xr)[XH], const int q, const int h) {
         if (!stager) return;
-        uint8_t* buf = lds + (q & 1) * G::BUF + x_lds0 + h * XH * ROWS_PER_PASS * G::STRIDE;
+        const int t = mine();
+        uint8_t* buf = lds + (G::X0 + (q & 1) * G::BUF + h * XH * ROWS_PER_PASS * G::STRIDE) + (t / PIECES * G::STRIDE + t % PIECES * 16);
 #pragma unroll
         for (int u = 0; u < XH; ++u)
             *(v4i*)(buf + u * ROWS_PER_PASS * G::STRIDE) = xr[u] ^ (v4i){FLIP, FLIP, FLIP, FLIP};
@@ -710,6 +744,7 @@ __global__ void __launch_bounds__(NW * 64) spmm_rowtile_mfma(const KernelArgs ar
     // ---- compressed weights + activation-row indices of (tile, segment of phase q).  Loads are
     // unconditional (slots past the segment's step count re-read step 0 and are never used).
     auto w_issue_at = [&](const int s0, v4i (&A)[MAXS], uint32_t (&I)[MAXS], const int cnt) {
+        const int lane = mine() & 63;
 #pragma unroll
         for (int s = 0; s < MAXS; ++s) {
             const int step = (s < cnt) ? s0 + s : 0;
@@ -729,7 +764,7 @@ __global__ void __launch_bounds__(NW * 64) spmm_rowtile_mfma(const KernelArgs ar
     // Half-way (after step slot MAXS/2 - 1, executed or not) the first half of the next phase's
     // activations is committed and the second half's loads are issued.
     auto multiply = [&](const int q, const bool nxt, const v4i (&A)[MAXS], const uint32_t (&I)[MAXS], const int cnt) {
-        const uint32_t base = G::X0 + (uint32_t)(q & 1) * G::BUF + (c & 1) * 8;
+        const uint32_t base = G::X0 + (uint32_t)(q & 1) * G::BUF + (uint32_t)(mine() & 1) * 8;
 #pragma unroll
         for (int s = 0; s < MAXS; ++s) {
             if (s < cnt) {
@@ -755,16 +790,12 @@ __global__ void __launch_bounds__(NW * 64) spmm_rowtile_mfma(const KernelArgs ar
         if (cur.seg != a.nseg - 1) return;
         const bool fast_out = takes_fast_stores<OUT>(a);
         const int tok0 = cur.tok0;
+        const int lane = mine() & 63;
         if (have_tile) {
             if (fast_out && tok0 + TM <= a.M) {
                 finish_tile_fast<TM, OUT, POST, OTILED>(a, acc, scale, bias, tile, tok0, lane, wave, lds);
-            } else if (n < a.N) {
-                const LdsLut<TM> lut{lds};
-#pragma unroll
-                for (int i = 0; i < PIECES; ++i) {
-                    const int m0 = tok0 + 16 * i + 4 * g;
-                    if (m0 < a.M) finish4<OUT, POST, NW != 16, OTILED>(a, acc[i], scale, bias, n, m0, lut, load_sum4<POST>(a, n, m0));
-                }
+            } else {
+                finish_tile_any<TM, OUT, POST, NW != 16, TIGHT, OTILED>(a, acc, scale, bias, tile, tok0, lane, lds);
             }
         }
 #pragma unroll
@@ -878,6 +909,8 @@ __global__ void __launch_bounds__((NW + LW) * 64) spmm_rowtile_mfma_fed(const Ke
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int g = lane >> 4, c = lane & 15;
+    // the forms whose weights and accumulators take most of the 128 registers that each of 16 waves has (see pinned)
+    constexpr bool FULL = NW > 8 && MAXS > 4 && TM > 64;
 
     // workgroup -> (row group, token-tile stream)
     const int S = a.n_streams;
@@ -982,7 +1015,7 @@ __global__ void __launch_bounds__((NW + LW) * 64) spmm_rowtile_mfma_fed(const Ke
     // issued in one go they kept the wave from its first gather for as long as the CU's address path took to
     // work through everyone's requests (4096 x 4096 at 85 %, 1024 tokens, cycles per phase: 1000-1350 issuing, then
     // 1800-2150 multiplying).  They have landed when the phase ends, and are waited for there, before any store.
-    auto multiply = [&](auto LOAD, const int q, const v4i (&A)[MAXS], const uint32_t (&I)[MAXS], const int cnt,
+    auto multiply = [&](auto LOAD, const int q, const v4i (&A)[MAXS], uint32_t (&I)[MAXS], const int cnt,
                         v4i (&An)[MAXS], uint32_t (&In)[MAXS], const Range next) __attribute__((always_inline)) {
         const uint32_t base = G::X0 + (uint32_t)(q & 1) * G::BUF + (c & 1) * 8;
 #pragma unroll
@@ -993,6 +1026,8 @@ __global__ void __launch_bounds__((NW + LW) * 64) spmm_rowtile_mfma_fed(const Ke
                     if (l < next.count) load_step(a, next.first + l, lane, An[l], In[l]);
             }
             if (s < cnt) {
+                // (weights that stay: or their rows' LDS addresses would be kept beside them, two registers for each one)
+                if constexpr (!LOAD.value && FULL) I[s] = pinned(I[s]);
                 const uint32_t a0 = first_row(I[s]) * G::STRIDE + base;
                 const uint32_t a1 = second_row(I[s]) * G::STRIDE + base;
 #pragma unroll
@@ -1014,12 +1049,16 @@ __global__ void __launch_bounds__((NW + LW) * 64) spmm_rowtile_mfma_fed(const Ke
         if (have_tile) {
             if (fast_out && tok0 + TM <= a.M) {
                 finish_tile_fast<TM, OUT, POST>(a, acc, scale, bias, tile, tok0, lane, wave, lds);
+            } else if constexpr (FULL && (POST & POST_SUM_BIT) && (OUT == SPMM_OUT_S8 || OUT == SPMM_OUT_U8)) {
+                finish_tile_any<TM, OUT, POST, false, FULL>(a, acc, scale, bias, tile, tok0, lane, lds);
             } else if (n < a.N) {
+                // (finish_tile_any but for the pin, which costs more than it saves where nothing spills without it: 3018 x 3018
+                // at 86 %, 1886 tokens, GELU to binary32: 19.7 us, with it 20.3)
                 const LdsLut<TM> lut{lds};
 #pragma unroll
                 for (int i = 0; i < PIECES; ++i) {
                     const int m0 = tok0 + 16 * i + 4 * g;
-                    if (m0 < a.M) finish4<OUT, POST, false>(a, acc[i], scale, bias, n, m0, lut, load_sum4<POST>(a, n, m0));
+                    if (m0 < a.M) finish4<OUT, POST, false>(a, acc[i], scale, bias, n, m0, lut, load_sum4<POST, FULL>(a, n, m0));
                 }
             }
         }

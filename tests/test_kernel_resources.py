@@ -1,0 +1,57 @@
+"""What the compiler made of the kernels: registers and scratch memory, read from the metadata of the built library.
+
+No kernel may spill vector registers.  The persistent kernels are written to fit their budget (128 registers in the
+16-wave forms) exactly, and a change that costs them one register shows nowhere else: the results stay right, and the
+spilled value, often a weight that has just been requested, is waited for in every phase."""
+import struct
+
+import pytest
+
+import paper_2306_16601_amd as sp
+
+msgpack = pytest.importorskip("msgpack")
+
+
+def _code_objects(path):
+    """The gfx950 ELF images in the library's offload bundles (one bundle per translation unit)."""
+    data, magic = open(path, "rb").read(), b"__CLANG_OFFLOAD_BUNDLE__"
+    at = data.find(magic)
+    while at >= 0:
+        count, = struct.unpack_from("<Q", data, at + 24)
+        p = at + 32
+        for _ in range(count):
+            offset, size, length = struct.unpack_from("<QQQ", data, p)
+            if b"gfx950" in data[p + 24:p + 24 + length] and size:
+                yield data[at + offset:at + offset + size]
+            p += 24 + length
+        at = data.find(magic, at + 24)
+
+
+def _kernels(elf):
+    """Kernel descriptions of the AMDGPU metadata note (type 32)."""
+    table, = struct.unpack_from("<Q", elf, 40)
+    entry, sections = struct.unpack_from("<HH", elf, 58)
+    for k in range(sections):
+        at = table + k * entry
+        kind, = struct.unpack_from("<I", elf, at + 4)
+        p, size = struct.unpack_from("<QQ", elf, at + 24)
+        end = p + size
+        while kind == 7 and p < end:
+            name, desc, note = struct.unpack_from("<III", elf, p)
+            p += 12 + (name + 3) // 4 * 4
+            if note == 32:
+                yield from msgpack.unpackb(elf[p:p + desc]).get("amdhsa.kernels", [])
+            p += (desc + 3) // 4 * 4
+
+
+@pytest.fixture(scope="module")
+def kernels():
+    sp.lib()
+    return [k for elf in _code_objects(sp.binding.LIB_PATH) for k in _kernels(elf) if "rowtile" in k[".name"]]
+
+
+def test_no_kernel_spills_vector_registers(kernels):
+    assert len(kernels) > 400
+    spilled = {k[".name"]: (k[".vgpr_spill_count"], k[".private_segment_fixed_size"]) for k in kernels
+               if k[".vgpr_spill_count"] or k[".private_segment_fixed_size"]}
+    assert not spilled, spilled
