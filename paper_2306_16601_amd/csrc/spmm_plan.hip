@@ -2,6 +2,8 @@
 // to the per-configuration launchers compiled from spmm_launch_cfg.hip.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "spmm_internal.h"
 
 namespace spmm {
@@ -46,53 +48,78 @@ bool plan_supported(int token_tile, int variant)
     return false;
 }
 
-// Bytes all XCDs together read through their L2s, when 2^row_bits slices of the packed weight and 8 / 2^row_bits
-// slices of X are dealt out among them (decode_workgroup): what comes from the last-level cache or HBM at a
-// third of the L2's rate, and is the largest part of many launches (4096x4096 at 75 %, 512 tokens, by the weight's
-// rows alone: 31 MB).
-static double fetched_bytes(const WeightDims& w, int64_t M, int row_bits)
-{
-    const double w_bytes = (double)w.nsteps * RECORD_BYTES, x_bytes = (double)w.K * (double)M;
-    return 8.0 * (w_bytes / (1 << row_bits) + x_bytes / (8 >> row_bits));
-}
+// What the candidates of one call have in common, worked out once.  A plan is made on every launch, and the host side
+// of a launch is about 3.5 us, more than the kernel of a short one: 14 candidates with 64-bit divisions and byte counts
+// of their own took 0.3 to 0.5 us of it (256x256, 128 tokens: 0.48, now 0.15; 1024x1024, 6144 tokens: 0.50, now 0.30;
+// calls back to back of 896x256, 400 tokens: every 4.00 us, now 3.87).
+struct Call {
+    int64_t M;
+    const WeightDims& w;
+    int num_cus, per_xcd, cu_shift;     // cu_shift: per_xcd = 1 << cu_shift and num_cus = 8 * per_xcd; -1: neither
+    // Bytes all XCDs together read through their L2s, when 2^rb slices of the packed weight and 8 / 2^rb slices of X are
+    // dealt out among them (decode_workgroup): what comes from the last-level cache or HBM at a third of the L2's
+    // rate, and is the largest part of many launches (4096x4096 at 75 %, 512 tokens, by the weight's rows alone: 31 MB).
+    double fetched[4], fetch_us[4];     // and the time that takes at 7 TB/s
+    int rank[4], split[4];              // rank[rb]: how many splits fetch less (or as much, with a smaller rb); and its inverse
+    double steps;                       // of a (row tile, segment), on average
+
+    Call(int64_t tokens, const WeightDims& dims, int cus) : M(tokens), w(dims), num_cus(cus), per_xcd(cus >= 8 ? cus / 8 : 1)
+    {
+        cu_shift = (per_xcd & (per_xcd - 1)) == 0 && per_xcd * 8 == cus ? __builtin_ctz((unsigned)per_xcd) : -1;
+        const double w_bytes = (double)w.nsteps * RECORD_BYTES, x_bytes = (double)w.K * (double)M;
+        for (int rb = 0; rb <= 3; ++rb) {
+            fetched[rb] = 8.0 * (w_bytes / (1 << rb) + x_bytes / (8 >> rb));
+            fetch_us[rb] = fetched[rb] * 1e-6 / 7.0;
+        }
+        for (int rb = 0; rb <= 3; ++rb) {
+            rank[rb] = 0;
+            for (int o = 0; o <= 3; ++o) rank[rb] += o < rb ? fetched[o] <= fetched[rb] : fetched[o] < fetched[rb];
+            split[rank[rb]] = rb;
+        }
+        steps = (double)w.nsteps / ((double)w.ntiles * w.nseg);
+    }
+    // rounds of `n` workgroups on all CUs, or of an XCD's share on its own
+    int64_t rounds(int64_t n) const { return cu_shift >= 0 ? (n + num_cus - 1) >> (cu_shift + 3) : (n + num_cus - 1) / num_cus; }
+    int64_t xcd_rounds(int64_t n) const { return cu_shift >= 0 ? (n + per_xcd - 1) >> cu_shift : (n + per_xcd - 1) / per_xcd; }
+};
 
 static int ceil_shift(int64_t v, int bits) { return (int)((v + ((int64_t)1 << bits) - 1) >> bits); }
+
+static int quotient(int a, int b) { return (int)((unsigned)a / (unsigned)b); }     // of positive numbers
+
+// Both are inlined so that the divisions by a tile's width and a workgroup's rows are by constants.
+#define SPMM_INLINE static inline __attribute__((always_inline))
 
 // Persistent kernels: token tile tm, `waves` row tiles (and `loaders` loader waves) per workgroup; as many token-tile
 // streams per row group as fill every CU once.  Of the ways to deal the workgroups to the XCDs, those with the
 // shortest streams, and of these the one that fetches least.
-static void fill_pipelined(Plan& p, int64_t M, const WeightDims& w, int num_cus, int tm, int waves, int loaders)
+SPMM_INLINE void fill_pipelined(Plan& p, const Call& c, int tm, int waves, int loaders)
 {
     p.token_tile = tm;
     p.waves = waves;
     p.loaders = loaders;
     p.row_tiles_per_wave = 1;
     p.simple = p.slab = p.stream = 0;
-    p.n_tok_tiles = (int)((M + tm - 1) / tm);
-    p.n_row_groups = (w.ntiles + waves - 1) / waves;
-    const int per_xcd = num_cus >= 8 ? num_cus / 8 : 1;
-    int best_tiles = 0;
-    double best_bytes = 0.0;
+    p.n_tok_tiles = (int)((c.M + tm - 1) / tm);
+    p.n_row_groups = (c.w.ntiles + waves - 1) / waves;
+    int64_t best = INT64_MAX;
+    int streams[4];
     for (int rb = 0; rb <= 3; ++rb) {
         const int rows = ceil_shift(p.n_row_groups, rb);
-        int S = (rows >= per_xcd ? 1 : per_xcd / rows) << (3 - rb);
-        if (p.n_row_groups >= num_cus) S = 1;
-        if (S > p.n_tok_tiles) S = p.n_tok_tiles;
-        const int tiles = (p.n_tok_tiles + S - 1) / S;
-        const double bytes = fetched_bytes(w, M, rb);
-        if (rb == 0 || tiles < best_tiles || (tiles == best_tiles && bytes < best_bytes)) {
-            best_tiles = tiles;
-            best_bytes = bytes;
-            p.n_streams = S;
-            p.xcd_row_bits = rb;
-        }
+        int S = quotient(c.per_xcd, rows) << (3 - rb);
+        if (rows > c.per_xcd) S = 1 << (3 - rb);
+        if (p.n_row_groups >= c.num_cus) S = 1;
+        streams[rb] = S = std::min(S, p.n_tok_tiles);
+        best = std::min(best, (int64_t)quotient(p.n_tok_tiles + S - 1, S) << 2 | c.rank[rb]);
     }
+    p.xcd_row_bits = c.split[best & 3];
+    p.n_streams = streams[p.xcd_row_bits];
     p.workgroups = (int64_t)p.n_row_groups * p.n_streams;
 }
 
 // Simple, short-batch and streamed kernels: tm-token tiles, one workgroup of 8 waves per (row group, tile), `waves` row
 // tiles (or pairs of them) per row group.  The XCD split: as few rounds of workgroups as possible, then the least fetched.
-static void fill_simple(Plan& p, int64_t M, const WeightDims& w, int num_cus, int r, int tm, int waves = 8)
+SPMM_INLINE void fill_simple(Plan& p, const Call& c, int r, int tm, int waves = 8)
 {
     p.token_tile = tm;
     p.waves = waves;
@@ -100,23 +127,16 @@ static void fill_simple(Plan& p, int64_t M, const WeightDims& w, int num_cus, in
     p.row_tiles_per_wave = r;
     p.simple = 1;
     p.slab = p.stream = 0;
-    p.n_tok_tiles = (int)((M + tm - 1) / tm);
-    p.n_row_groups = (w.ntiles + waves * r - 1) / (waves * r);
+    p.n_tok_tiles = (int)((c.M + tm - 1) / tm);
+    p.n_row_groups = (c.w.ntiles + waves * r - 1) / (waves * r);
     p.n_streams = 0;
-    const int64_t per_xcd = num_cus >= 8 ? num_cus / 8 : 1;
-    int64_t best_rounds = 0;
-    double best_bytes = 0.0;
+    int64_t best = INT64_MAX, here[4];
     for (int rb = 0; rb <= 3; ++rb) {
-        const int64_t here = (int64_t)ceil_shift(p.n_row_groups, rb) * ceil_shift(p.n_tok_tiles, 3 - rb);
-        const int64_t rounds = (here + per_xcd - 1) / per_xcd;
-        const double bytes = fetched_bytes(w, M, rb);
-        if (rb == 0 || rounds < best_rounds || (rounds == best_rounds && bytes < best_bytes)) {
-            best_rounds = rounds;
-            best_bytes = bytes;
-            p.xcd_row_bits = rb;
-            p.workgroups = 8 * here;
-        }
+        here[rb] = (int64_t)ceil_shift(p.n_row_groups, rb) * ceil_shift(p.n_tok_tiles, 3 - rb);
+        best = std::min(best, c.xcd_rounds(here[rb]) << 2 | c.rank[rb]);
     }
+    p.xcd_row_bits = c.split[best & 3];
+    p.workgroups = 8 * here[p.xcd_row_bits];
 }
 
 // ---------------------------------------------------------------------------------------
@@ -155,44 +175,37 @@ static const Fit FIT_RING_16       = {2.24, 0.68, 0.0082, 2.70, 0.0208, 0.0000, 
 static const Fit FIT_RING_32       = {0.90, 1.96, 0.0062, 2.06, 0.0130, 0.0000, 1.29};
 static const Fit FIT_RING_64       = {0.52, 2.99, 0.0039, 1.18, 0.0008, 0.0000, 1.53};
 
-static double plan_cost(const Plan& p, const Fit& f, const WeightDims& w, int64_t M, int num_cus, int out_bytes)
+SPMM_INLINE double plan_cost(const Plan& p, const Fit& f, const Call& c, int out_bytes)
 {
-    const double rounds = (double)((p.workgroups + num_cus - 1) / num_cus);
-    const double fetch = fetched_bytes(w, M, p.xcd_row_bits) * 1e-6 / 7.0;          // us at 7 TB/s
-    const double steps = (double)w.nsteps / ((double)w.ntiles * w.nseg);            // of a (row tile, segment)
+    const double rounds = (double)c.rounds(p.workgroups);
+    const double fetch = c.fetch_us[p.xcd_row_bits];
     const double rows = p.waves;
     if (p.simple) {
-        const double units = rows * steps * w.nseg * p.token_tile / 16.0;
-        return f.start + rounds * (f.phase + f.unit * units + f.tokens * w.nseg * p.token_tile * 0.01 +
+        const double units = rows * c.steps * c.w.nseg * p.token_tile / 16.0;
+        return f.start + rounds * (f.phase + f.unit * units + f.tokens * c.w.nseg * p.token_tile * 0.01 +
                                    f.out1 * rows * TILE_ROWS * p.token_tile * 1e-3 * out_bytes) + f.fetch * fetch;
     }
-    const int tiles = (p.n_tok_tiles + p.n_streams - 1) / p.n_streams, phases = tiles * w.nseg;
-    const double units = rows * steps * p.token_tile / 16.0;
+    const int tiles = quotient(p.n_tok_tiles + p.n_streams - 1, p.n_streams), phases = tiles * c.w.nseg;
+    const double units = rows * c.steps * p.token_tile / 16.0;
     return rounds * (f.start + phases * (f.phase + f.unit * units + f.tokens * p.token_tile * 0.01) +
                      (out_bytes == 4 ? f.out4 : f.out1) * tiles * rows * TILE_ROWS * p.token_tile * 1e-3) + f.fetch * fetch;
 }
 
-Plan make_plan(int64_t M, const WeightDims& w, int num_cus, int force_tm, int variant, int out_bytes, bool x_fast, bool out_fast)
+// A configuration that spmm_set_tuning asked for (force_tm != 0), or the nearest one that runs this weight.
+static Plan forced_plan(const Call& call, int force_tm, int variant, int max_steps, int fed_steps)
 {
-    const int nseg = w.nseg, max_steps_per_segment = w.max_steps_per_segment;
+    const int nseg = call.w.nseg;
     Plan p{};
-    const int max_steps = max_steps_per_segment <= 4 ? 4 : (max_steps_per_segment <= 6 ? max_steps_per_segment : 8);
-    const int fed_steps = max_steps == 5 ? 6 : max_steps;      // step slots of the loader-wave kernels: 4, 6 or 8
     p.max_steps = max_steps;
-    if (!x_fast && !(force_tm && force_tm <= 64 && (variant == 101 || variant == 102))) {
-        // rows so far apart that a segment of them exceeds 32-bit offsets, or an X of less than 16 bytes
-        fill_simple(p, M, w, num_cus, 1, 64);
-        return p;
-    }
     if (force_tm == 64 || force_tm == 32 || force_tm == 16) {
         if (variant == 112) {
             // (weights with more than 6 steps per segment run 8 compute waves, which exist with 128-token tiles)
-            fill_pipelined(p, M, w, num_cus, max_steps <= 6 ? 64 : 128, max_steps <= 6 ? 12 : 8, 4);
+            fill_pipelined(p, call, max_steps <= 6 ? 64 : 128, max_steps <= 6 ? 12 : 8, 4);
             p.max_steps = fed_steps;
             return p;
         }
         const int r = variant == 102 ? 2 : 1, row_tiles = variant == 105 ? 2 : variant == 106 ? 4 : 8;
-        fill_simple(p, M, w, num_cus, r, force_tm, row_tiles);
+        fill_simple(p, call, r, force_tm, row_tiles);
         // the short-batch kernel takes K <= 4096 (3072 with 32-token tiles); longer K silently runs the simple kernel
         if (variant == 103) p.slab = nseg <= (force_tm == 16 ? SLAB_SEGMENTS : SLAB_SEGMENTS_32);
         if (row_tiles < 8) p.slab = force_tm == 16 && nseg > 4 && nseg <= SLAB_SEGMENTS;
@@ -202,70 +215,92 @@ Plan make_plan(int64_t M, const WeightDims& w, int num_cus, int force_tm, int va
     if (variant == 108 || variant == 112) {
         // 12 compute waves have 128 registers each (at most 6 step slots); denser weights take 8
         const int waves = (variant == 112 && max_steps <= 6) ? 12 : 8;
-        fill_pipelined(p, M, w, num_cus, (waves == 12 && force_tm == 96) ? 96 : 128, waves, 4);
+        fill_pipelined(p, call, (waves == 12 && force_tm == 96) ? 96 : 128, waves, 4);
         p.max_steps = fed_steps;
         return p;
     }
-    if (force_tm) {
-        // 16 waves have 128 registers each: at most 6 steps per segment; denser weights run with 8
-        // waves, 256 registers and half as many rows per workgroup (token tile 128 only)
-        const bool eight = max_steps > 6 || variant == 8;
-        fill_pipelined(p, M, w, num_cus, eight ? 128 : force_tm, eight ? 8 : 16, 0);
+    // 16 waves have 128 registers each: at most 6 steps per segment; denser weights run with 8
+    // waves, 256 registers and half as many rows per workgroup (token tile 128 only)
+    const bool eight = max_steps > 6 || variant == 8;
+    fill_pipelined(p, call, eight ? 128 : force_tm, eight ? 8 : 16, 0);
+    return p;
+}
+
+Plan make_plan(int64_t M, const WeightDims& w, int num_cus, int force_tm, int variant, int out_bytes, bool x_fast, bool out_fast)
+{
+    const int nseg = w.nseg, max_steps_per_segment = w.max_steps_per_segment;
+    const Call call(M, w, num_cus);
+    const int max_steps = max_steps_per_segment <= 4 ? 4 : (max_steps_per_segment <= 6 ? max_steps_per_segment : 8);
+    const int fed_steps = max_steps == 5 ? 6 : max_steps;      // step slots of the loader-wave kernels: 4, 6 or 8
+    if (!x_fast && !(force_tm && force_tm <= 64 && (variant == 101 || variant == 102))) {
+        // rows so far apart that a segment of them exceeds 32-bit offsets, or an X of less than 16 bytes
+        Plan p{};
+        p.max_steps = max_steps;
+        fill_simple(p, call, 1, 64);
         return p;
     }
+    if (force_tm) return forced_plan(call, force_tm, variant, max_steps, fed_steps);
     // ---- short and mid-size batches
     const int reload = nseg > 2;
-    Plan best{};
+    Plan best{}, c{};
     double best_cost = 0.0;
-    auto consider = [&](const Plan& c, const Fit& f) {
-        // (persistent workgroups that leave half of the CUs idle: the short-batch kernels' ground)
-        if (!c.simple && c.workgroups * 2 <= num_cus && best.workgroups != 0) return;
-        const double cost = plan_cost(c, f, w, M, num_cus, out_bytes);
+    c.max_steps = max_steps;
+    auto consider = [&](const Fit& f) __attribute__((always_inline)) {
+        const double cost = plan_cost(c, f, call, out_bytes);
         if (best.workgroups == 0 || cost < 0.98 * best_cost) {
             best = c;
             best_cost = cost;
         }
     };
-    Plan c = p;
-    for (int row_tiles = 8; row_tiles >= 2; row_tiles /= 2) {
-        fill_simple(c, M, w, num_cus, 1, 16, row_tiles);
+    auto short_batch = [&](const int row_tiles) __attribute__((always_inline)) {
+        fill_simple(c, call, 1, 16, row_tiles);
         if (nseg > SLAB_SEGMENTS) c.stream = 1;
         else if (nseg > 4) c.slab = 1;
         // fewer rows per workgroup, the waves sharing a row tile's steps: where whole workgroups would leave most of
         // the chip idle (with few steps the sum over the shares costs what the shorter walk saves)
-        if (row_tiles < 8 && (c.stream || (!c.slab && (int64_t)c.n_row_groups * c.n_tok_tiles * row_tiles / 8 >= num_cus * 3 / 16))) break;
-        consider(c, c.stream ? FIT_RING_16 : c.slab ? FIT_SLAB_16 : FIT_RES_16);
-    }
+        if (row_tiles < 8 && (c.stream || (!c.slab && (int64_t)c.n_row_groups * c.n_tok_tiles * row_tiles / 8 >= num_cus * 3 / 16))) return false;
+        consider(c.stream ? FIT_RING_16 : c.slab ? FIT_SLAB_16 : FIT_RES_16);
+        return true;
+    };
+    if (short_batch(8) && short_batch(4)) short_batch(2);
     // (the simple kernel where its resident rows hold all of K, the ring beyond)
-    fill_simple(c, M, w, num_cus, 1, 32);
-    if (nseg <= 4) consider(c, FIT_RES_32);
+    fill_simple(c, call, 1, 32);
+    if (nseg <= 4) consider(FIT_RES_32);
     if (nseg > 4 && nseg <= SLAB_SEGMENTS_32) c.slab = 1;
     else c.stream = 1;
-    consider(c, FIT_RING_32);
-    fill_simple(c, M, w, num_cus, 1, 64);
-    if (nseg <= 2) consider(c, FIT_RES_64);
+    consider(FIT_RING_32);
+    fill_simple(c, call, 1, 64);
+    if (nseg <= 2) consider(FIT_RES_64);
     c.stream = 1;
-    consider(c, FIT_RING_64);
-    // ---- persistent kernels.  16 waves have 128 registers each: at most 6 steps per segment; without loader waves
-    // the general store path (outputs beyond 32-bit offsets) has no registers in them either.
-    c = p;
+    consider(FIT_RING_64);
+    // ---- persistent kernels, where they occupy more than half of the CUs (the rest is the short-batch kernels' ground).
+    // 16 waves have 128 registers each: at most 6 steps per segment; without loader waves the general store path
+    // (outputs beyond 32-bit offsets) has no registers in them either.
+    auto persistent = [&](const int tm, const int waves, const int loaders, const Fit& f) __attribute__((always_inline)) {
+        // (no more workgroups than row groups x token tiles: most short batches end here)
+        if ((int64_t)((w.ntiles + waves - 1) / waves) * ((M + tm - 1) / tm) * 2 <= num_cus) return;
+        fill_pipelined(c, call, tm, waves, loaders);
+        if (c.workgroups * 2 > num_cus) consider(f);
+    };
     if (max_steps <= 6 && out_fast) {
-        fill_pipelined(c, M, w, num_cus, 128, 16, 0);
-        consider(c, FIT_128_16[reload]);
-        fill_pipelined(c, M, w, num_cus, 96, 16, 0);
-        consider(c, FIT_96_16[reload]);
+        persistent(128, 16, 0, FIT_128_16[reload]);
+        persistent(96, 16, 0, FIT_96_16[reload]);
     }
-    fill_pipelined(c, M, w, num_cus, 128, 8, 0);
-    consider(c, FIT_128_8[reload]);
+    persistent(128, 8, 0, FIT_128_8[reload]);
     c.max_steps = fed_steps;
-    fill_pipelined(c, M, w, num_cus, 128, 8, 4);
-    consider(c, FIT_FED_128_8[reload]);
-    for (int tm = 128; tm >= 64 && max_steps <= 6; tm -= 32) {
-        fill_pipelined(c, M, w, num_cus, tm, 12, 4);
+    persistent(128, 8, 4, FIT_FED_128_8[reload]);
+    if (max_steps <= 6) {
         // (1-byte outputs of one token tile per stream and at most 4 steps per segment keep the forms of whole 8 or 16
         // compute waves, as the tests of the plan have it; 768x768 at 90 %, 4096 tokens: 6.9 us, with 12 + 4: 6.0)
-        if (out_bytes == 1 && max_steps <= 4 && c.n_tok_tiles <= c.n_streams) continue;
-        consider(c, (tm == 128 ? FIT_FED_128_12 : tm == 96 ? FIT_FED_96_12 : FIT_FED_64_12)[reload]);
+        auto fed12 = [&](const int tm, const Fit& f) __attribute__((always_inline)) {
+            if ((int64_t)((w.ntiles + 11) / 12) * ((M + tm - 1) / tm) * 2 <= num_cus) return;
+            fill_pipelined(c, call, tm, 12, 4);
+            if (out_bytes == 1 && max_steps <= 4 && c.n_tok_tiles <= c.n_streams) return;
+            if (c.workgroups * 2 > num_cus) consider(f);
+        };
+        fed12(128, FIT_FED_128_12[reload]);
+        fed12(96, FIT_FED_96_12[reload]);
+        fed12(64, FIT_FED_64_12[reload]);
     }
     return best;
 }
