@@ -301,11 +301,10 @@ static spmm_status_t run_common(const spmm_handle_t* h, const uint8_t* X_dev, in
         ld_sum = ep->ld_sum;
         out_fast = out_fast && N * ld_sum * 4 < limit;
     }
-    // the kernels take 40-bit pitches; the pitch of a single row is nothing
+    // the pitch of a single row is nothing
     if (K == 1 && !x_tiled) ldx = M;
     if (N == 1 && !out_tiled) ldo = M;
     if (N == 1) ld_sum = M;
-    if ((ldx | ldo | ld_sum) >> 40) return SPMM_E_UNSUPPORTED;
     a.X = X_dev;
     a.weight = h->d_weight;
     a.out = out_dev;
@@ -314,7 +313,7 @@ static spmm_status_t run_common(const spmm_handle_t* h, const uint8_t* X_dev, in
     a.ldx = (uint32_t)ldx;
     a.ldo = (uint32_t)ldo;
     a.ld_sum = (uint32_t)ld_sum;
-    a.ld_high = (uint32_t)(ldx >> 32 & 0xff) | (uint32_t)(ldo >> 32 & 0xff) << 8 | (uint32_t)(ld_sum >> 32 & 0xff) << 16;
+    a.ld_high = (uint32_t)(ldx >> 32) | (uint32_t)(ldo >> 32) << spmm::LD_HIGH_BITS | (uint32_t)(ld_sum >> 32) << 2 * spmm::LD_HIGH_BITS;
     a.M = (int32_t)M;
     a.N = (int32_t)N;
     a.k_flags = (uint32_t)K | (uint32_t)ep->x_zero_point << 24 | (x_tiled ? spmm::ARG_X_TILED : 0) |

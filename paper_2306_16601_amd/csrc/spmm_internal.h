@@ -95,7 +95,7 @@ struct KernelArgs {
     const float* bias;
     const void* aux;            // the table of a table chain, or the second operand of Sum
     uint32_t ldx, ldo, ld_sum;  // low 32 bits,
-    uint32_t ld_high;           // and bits 32 .. 39 of the three, 8 bits each
+    uint32_t ld_high;           // and bits 32 .. 40 of the three (a pitch is at most 2^40), LD_HIGH_BITS each
     int32_t M, N;
     uint32_t k_flags;           // K (17 bits), ARG_* flags, x_zero_point << 24
     float x_scale, inv, out_zp_f;   // inv: 1 / out_scale, or 1 / mid_scale of a table chain; out_zp_f: zero point - smallest code
@@ -105,6 +105,7 @@ struct KernelArgs {
     uint32_t tiles_per_stream;  // token tiles / n_streams, rounded down
 };
 static_assert(sizeof(KernelArgs) == 96, "kernel arguments");
+constexpr int LD_HIGH_BITS = 9;
 constexpr int ARG_K_BITS = 17;
 constexpr int GRID_Y_BITS = 15;                  // of the token axis of a grid: the rest goes into z
 constexpr uint32_t ARG_X_TILED = 1u << 17;      // X token-tile-major [ceil(M/32)][K][32], ldx = 32; else row-major [K][ldx]

@@ -96,9 +96,10 @@ __device__ __forceinline__ Args unpack(const KernelArgs& p)
     a.bias = p.bias;
     a.lut = (const int8_t*)p.aux;
     a.sum = (const float*)p.aux;
-    a.ldx = (int64_t)((uint64_t)p.ldx | (uint64_t)(p.ld_high & 0xff) << 32);
-    a.ldo = (int64_t)((uint64_t)p.ldo | (uint64_t)(p.ld_high >> 8 & 0xff) << 32);
-    a.ld_sum = (int64_t)((uint64_t)p.ld_sum | (uint64_t)(p.ld_high >> 16 & 0xff) << 32);
+    constexpr uint32_t high = (1u << LD_HIGH_BITS) - 1;
+    a.ldx = (int64_t)((uint64_t)p.ldx | (uint64_t)(p.ld_high & high) << 32);
+    a.ldo = (int64_t)((uint64_t)p.ldo | (uint64_t)(p.ld_high >> LD_HIGH_BITS & high) << 32);
+    a.ld_sum = (int64_t)((uint64_t)p.ld_sum | (uint64_t)(p.ld_high >> 2 * LD_HIGH_BITS & high) << 32);
     const int tiles32 = (a.M + SPMM_X_TILE - 1) / SPMM_X_TILE;
     const bool xt = p.k_flags & ARG_X_TILED, ot = p.k_flags & ARG_OUT_TILED;
     a.x_tile_stride = xt ? a.K * SPMM_X_TILE : 0;
