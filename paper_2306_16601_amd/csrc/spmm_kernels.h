@@ -1150,11 +1150,17 @@ struct Resident {
     static constexpr int PASSES = RES / PASS_ROWS;
     static constexpr int SEGS = RES / SEGMENT_ROWS;             // segments per round
     // weights in flight: NS sets of CH steps, gathered CH steps at a time (the slabs have 256 registers, the others
-    // 128, for two workgroups on a CU)
+    // 128, for two workgroups on a CU; with Sum, 16- and 32-token tiles have 131 and 135 and run one, see SUM_LATE)
     static constexpr bool WIDE = RES > 2048;
     static constexpr int CH = TM == 16 || WIDE ? 4 : 2;
     static constexpr int NS = TM == 16 ? (WIDE ? 6 : 3) : WIDE ? 5 : TM == 32 ? 4 : 3;
     static constexpr int LDS = RES * TM + 256;                  // activations, then the table
+    // The operand of Sum is requested with everything else at the start, where the grid is one round of workgroups, as
+    // it is with narrow tiles: its latency is hidden (768 x 768, 128 tokens: 4.76 us, requested after the last step 4.90).
+    // 64-token tiles are planned for grids of several rounds, where the second workgroup on a CU is worth more than that
+    // and the 16 registers of the operand would cost it (147 of 128): 2688 x 672 at 71 %, 1400 tokens, binary32: 15.8 ->
+    // 11.6 us, 2800 tokens 28.7 -> 20.0, int8 26.3 -> 19.0; 800 x 800 at 72 %, 5024 tokens 19.3 -> 17.2.
+    static constexpr bool SUM = (POST & POST_SUM_BIT) != 0, SUM_LATE = TM == 64;
     static constexpr bool TABLE = (POST & SPMM_POST_GELU) != 0 && (OUT == SPMM_OUT_S8 || OUT == SPMM_OUT_U8);
     static_assert((RES & (RES - 1)) == 0 && PASSES * PASS_ROWS == RES && SEGMENT_ROWS % PASS_ROWS == 0, "threads tile a segment");
     static_assert(8 * PIECES * 1024 <= RES * TM, "the partial sums fit where the activations were");
@@ -1265,7 +1271,7 @@ struct Resident {
                 acc[r][i] = (v4i){init, init, init, init};
                 sum4[r][i] = (v4f){0.0f, 0.0f, 0.0f, 0.0f};
                 const int m0 = tok0 + 16 * i + 4 * g;
-                if ((POST & POST_SUM_BIT) && part == 0 && n < a.N && m0 < a.M) sum4[r][i] = load_sum4<POST>(a, n, m0);
+                if (SUM && !SUM_LATE && part == 0 && n < a.N && m0 < a.M) sum4[r][i] = load_sum4<POST>(a, n, m0);
             }
         }
         int table_byte = 0;
@@ -1344,6 +1350,13 @@ struct Resident {
         for (int r = 0; r < R; ++r) {
             const int n = (tile0 + r) * TILE_ROWS + c;
             if (n >= a.N) continue;
+            if constexpr (SUM && SUM_LATE) {
+#pragma unroll
+                for (int i = 0; i < PIECES; ++i) {
+                    const int m0 = tok0 + 16 * i + 4 * g;
+                    if (m0 < a.M) sum4[r][i] = load_sum4<POST>(a, n, m0);
+                }
+            }
 #pragma unroll
             for (int i = 0; i < PIECES; ++i) {
                 const int m0 = tok0 + 16 * i + 4 * g;

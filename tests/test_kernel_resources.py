@@ -3,6 +3,7 @@
 No kernel may spill vector registers.  The persistent kernels are written to fit their budget (128 registers in the
 16-wave forms) exactly, and a change that costs them one register shows nowhere else: the results stay right, and the
 spilled value, often a weight that has just been requested, is waited for in every phase."""
+import re
 import struct
 
 import pytest
@@ -55,3 +56,15 @@ def test_no_kernel_spills_vector_registers(kernels):
     spilled = {k[".name"]: (k[".vgpr_spill_count"], k[".private_segment_fixed_size"]) for k in kernels
                if k[".vgpr_spill_count"] or k[".private_segment_fixed_size"]}
     assert not spilled, spilled
+
+
+def test_resident_kernels_leave_room_for_a_second_workgroup(kernels):
+    """128 registers: two workgroups of 8 waves on a CU.  (Sum with 16- and 32-token tiles: one, their grids are one
+    round of workgroups.)"""
+    seen = 0
+    for k in kernels:
+        m = re.search(r"simpleILi(\d+)ELi8ELi1ELi\d+ELi(\d+)E", k[".name"])
+        if m and (m[1] == "64" or not int(m[2]) & 4):
+            seen += 1
+            assert k[".vgpr_count"] <= 128, k[".name"]
+    assert seen == 25
