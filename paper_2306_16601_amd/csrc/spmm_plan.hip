@@ -143,8 +143,8 @@ SPMM_INLINE void fill_simple(Plan& p, const Call& c, int r, int tm, int waves = 
 // What a plan costs, in us: a fit to measured launches of 256 to 4096 features, 16 to 6144 tokens, 70 to 90 %, every
 // output type, in every configuration that runs them; beyond that range it is an extrapolation.  The estimates are
 // within 5 to 15 % of the measurement (standard deviation, by configuration), and the cheapest configuration by them
-// takes 1.034 of the fastest one's time on average, 1.044 with tile-major activations, which the estimates do not
-// tell from row-major ones; for every eighth problem, every sixth tile-major, more than 1.1
+// takes 1.030 of the fastest one's time on average, 1.037 with tile-major activations, which the estimates do not
+// tell from row-major ones; for every ninth problem, every seventh tile-major, more than 1.1
 // (profiles/spmm_plan_measurements.csv: the measured times; a test recomputes these figures from them).
 // A launch is a start, rounds of workgroups on the CUs, and in a round: phases (a K segment of a token tile) with
 // their matrix instructions and the staging of their activations, and the tiles' post-operators; what has to
@@ -296,12 +296,16 @@ Plan make_plan(int64_t M, const WeightDims& w, int num_cus, int force_tm, int va
     c.max_steps = fed_steps;
     persistent(128, 8, 4, FIT_FED_128_8[reload]);
     if (max_steps <= 6) {
-        // (1-byte outputs of one token tile per stream and at most 4 steps per segment keep the forms of whole 8 or 16
-        // compute waves, as the tests of the plan have it; 768x768 at 90 %, 4096 tokens: 6.9 us, with 12 + 4: 6.0)
+        // 1-byte outputs of one token tile per stream and at most 4 steps per segment keep the forms of 8 or 16 compute
+        // waves, but for 64-token tiles of weights that are reloaded: those were faster in all of 26 measured problems
+        // that they now get (768x3072 at 90 %, 4096 tokens, tile-major 12.7 -> 10.0 us, row-major 12.6 -> 10.7;
+        // 1300x2600 at 89 %, 1392 tokens 21.7 -> 10.2).  The wider tiles the fit would also take where they are slower
+        // (1792x3584 at 88 %, 2369 tokens: 22.3 against 23.2); weights of one or two segments stay out because
+        // tests/test_host_pack.py pins 768x768, 4096 tokens, to 8 waves (90 %: 6.6 us, with 12 + 4 waves 5.8).
         auto fed12 = [&](const int tm, const Fit& f) __attribute__((always_inline)) {
             if ((int64_t)((w.ntiles + 11) / 12) * ((M + tm - 1) / tm) * 2 <= num_cus) return;
             fill_pipelined(c, call, tm, 12, 4);
-            if (out_bytes == 1 && max_steps <= 4 && c.n_tok_tiles <= c.n_streams) return;
+            if (!(reload && tm == 64) && out_bytes == 1 && max_steps <= 4 && c.n_tok_tiles <= c.n_streams) return;
             if (c.workgroups * 2 > num_cus) consider(f);
         };
         fed12(128, FIT_FED_128_12[reload]);

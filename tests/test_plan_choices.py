@@ -55,7 +55,7 @@ def chosen(tmp_path_factory):
     return [(r, n, float(r[n]) / min(float(r[c]) for c in configurations if r[c])) for r, n in zip(rows, names)]
 
 
-@pytest.mark.parametrize("layout, mean, over_ten", [("row", 1.035, 0.13), ("tile", 1.046, 0.185)])
+@pytest.mark.parametrize("layout, mean, over_ten", [("row", 1.031, 0.12), ("tile", 1.038, 0.155)])
 def test_the_choice_is_close_to_the_fastest_configuration(chosen, layout, mean, over_ten):
     ratio = np.array([t for r, _, t in chosen if (r["layout"] == "tile") == (layout == "tile")])
     assert len(ratio) > 100
@@ -63,6 +63,7 @@ def test_the_choice_is_close_to_the_fastest_configuration(chosen, layout, mean, 
 
 
 @pytest.mark.parametrize("N, K, M, sparsity, configuration", [
+    (768, 3072, 4096, 90, "FED_64_12"),     # reloaded weights, one token tile per stream, 1-byte outputs
     (4096, 1024, 6144, 85, "128_16"),       # a near tie with 96_16, which the measurement does not bear out in either layout
     (4096, 1024, 6144, 90, "128_16"),
     (1024, 4096, 6144, 85, "96_16"),
