@@ -121,7 +121,7 @@ struct Plan {
     int waves;               // waves that own a row tile; short-batch kernels: row tiles (or pairs) per workgroup of 8 waves
     int loaders;             // pipelined kernel: extra waves that only stage activations (0 or 4)
     int simple;              // 1: simple kernel
-    int slab;                // 1: the short-batch kernel (token tile 16: K <= 4096 resident in LDS; 32: the ring) in its place
+    int slab;                // 1: spmm_rowtile_mfma_slab in its place (token tile 16: K <= 4096 resident in LDS; 32: the ring's other name)
     int stream;              // 1: the streamed kernel (a ring of segments) in its place
     int max_steps;           // unroll bound of the per-segment step loop (pipelined kernel)
     int n_row_groups, n_tok_tiles, n_streams;
@@ -136,7 +136,7 @@ struct Plan {
 // 105 / 106 = simple or, from 5 segments on with 16-token tiles, short-batch kernel with 2 / 4 row tiles per workgroup,
 // whose waves share a row tile's steps (token tile 32 or 16)
 constexpr int SLAB_SEGMENTS = 8;      // K segments the short-batch kernel keeps in LDS, token tile 16
-constexpr int SLAB_SEGMENTS_32 = 6;   // K segments it takes with token tile 32
+constexpr int SLAB_SEGMENTS_32 = 6;   // K segments up to which the ring with 32-token tiles goes by that kernel's name
 // what the plan needs to know of a packed weight
 struct WeightDims {
     int ntiles, nseg, K;

@@ -22,15 +22,17 @@
 //    workgroup decomposition: a workgroup owns a group of row tiles and walks over token
 //    tiles, so the compressed weights it needs stay in registers.
 //
-// Five kernels share the layout and the inner step (two transposing LDS reads, one matrix
+// Four kernels share the layout and the inner step (two transposing LDS reads, one matrix
 // instruction per 16 tokens); the host's plan (spmm_plan.hip) picks one by its estimate of their times:
 //   spmm_rowtile_mfma         persistent, software-pipelined: long batches
 //   spmm_rowtile_mfma_fed     the same with waves that only stage activations: long batches with 4-byte
-//                             outputs, or with weights that do not stay in registers
+//                             outputs, weights that do not stay in registers, or rows that 12 waves divide better
 //   spmm_rowtile_mfma_simple  one workgroup per 32 to 128 rows x 16/32/64 tokens, the whole K slab (up to
-//                             2048 rows at a time) in LDS at once: small problems
-//   spmm_rowtile_mfma_slab    the same with 4096 resident rows: short batches, 2048 < K <= 4096
-//   spmm_rowtile_mfma_stream  a ring of four segments of activations: mid-size batches, short ones with the longest K
+//                             2048 rows at a time, 1024 with 64 tokens) in LDS at once: small problems.
+//                             spmm_rowtile_mfma_slab<16> is the same with 4096 resident rows
+//   spmm_rowtile_mfma_stream  a ring of four segments of activations: mid-size batches, short ones with the longest K.
+//                             spmm_rowtile_mfma_slab<32> is the same code under the name by which the plan reports
+//                             32-token tiles of 5 to 6 segments
 //
 // Lane roles of the matrix instruction (D = A.B, 64 lanes, g = lane / 16, c = lane % 16):
 //   A operand (activations): row = token c, bytes t = k-list slots 16g .. 16g+15
@@ -435,8 +437,8 @@ __device__ __forceinline__ bool decode_workgroup(const Args& a, const int n_row_
 // Pipelined persistent kernel: long batches.  What bounds it is the LDS -- the gather reads 1 KB of it per step
 // and 16 tokens at 121 bytes a clock per CU -- and then the times in which it is idle because all waves of the
 // workgroup do something else together: requesting the next phase and the post-operators (4096 x 1024 at 85 %, 6144
-// tokens, table chain: 24.3 us, of which 11 us gather, 3.5 us the start, about a quarter the post-operators; two workgroups
-// of 8 waves to a CU, to overlap them, read X twice as often and take 30.3 us).
+// tokens, table chain, row-major: 24.7 us, tile-major 22.3, of which 11 us gather, 3.5 us the start, about a quarter the
+// post-operators; workgroups of 8 waves, to overlap them, read X twice as often and take 31.0 us row-major).
 //
 // Workgroup = NW waves.  Wave w owns row tile NW*rg + w (16 output rows) for the whole
 // kernel; the workgroup walks over token tiles of TM tokens (stream, stream + S, ..) and,
@@ -449,11 +451,11 @@ __device__ __forceinline__ bool decode_workgroup(const Args& a, const int n_row_
 // tile, otherwise they are prefetched one phase ahead.
 //
 // Two token-tile widths, both with one workgroup per CU, the table at LDS offset 0 and the
-// buffers behind it:
-//   TM = 128: the default.
-//   TM =  96: chosen by the plan when it divides the tokens into a number of tiles that fills
-//             the CUs more evenly (6144 tokens and 4 row groups: 256 workgroups instead of 192).
-//             A row is 6 pieces of 16 bytes; 3/4 of the threads stage them.
+// buffers behind it; the plan takes the one it estimates to be faster (spmm_plan.hip):
+//   TM = 128: fewer phases for the same tokens.
+//   TM =  96: where it divides the tokens into a number of tiles that fills the CUs more evenly
+//             (1024 x 1024 at 90 %, 6144 tokens: 256 workgroups instead of 192, 8.7 us instead of 9.1,
+//             tile-major 7.6 instead of 8.9).  A row is 6 pieces of 16 bytes; 3/4 of the threads stage them.
 // Every LDS row has 16 spare bytes behind its TM tokens (the pitch TM + 16 makes consecutive
 // rows start 4 banks apart).  These spare chunks carry the output staging for 1-byte outputs:
 // wave w transposes its 16 rows x 64 tokens through chunks 64w .. 64w+63 so that a row's
@@ -487,7 +489,8 @@ struct Geo<96> {
 
 // TM = 64 (loader-wave kernel only): four pieces per row, twice as many tiles per stream; the output
 // stores of a workgroup then start after half the time and the last tile's burst is half as long.
-// (3072 x 768 at 85 %, 4096 tokens: 13.8 us; 96-token tiles 16.5, 16 waves without loaders 16.9.)
+// (3072 x 768 at 85 %, 4096 tokens, row-major: int8 13.1 us, 128-token tiles 13.2, 96 15.9, 16 waves without loaders 15.6;
+// binary32 16.6, 16.7, 18.6 and 22.0.)
 template <>
 struct Geo<64> {
     static constexpr int STRIDE = 80, PIECES = 4, HALVES = 1;
