@@ -287,10 +287,11 @@ Plan make_plan(int64_t M, const WeightDims& w, int num_cus, int force_tm, int va
     };
     if (max_steps <= 6 && out_fast) {
         persistent(128, 16, 0, FIT_128_16[reload]);
-        // (against wider tiles of the same waves the fit favours 96 tokens by 2.5 % in row-major order, and in both orders
-        // where a stream then has more tiles: a near tie goes to the wider.  4096x1024 at 85 %, 6144 tokens, estimated
-        // 31.5 us and 30.8: 128 tokens 24.9 us, 96 tokens 26.0; tile-major 22.3 and 23.1)
-        persistent(96, 16, 0, FIT_96_16[reload], best.waves == 16 ? 0.96 : 0.98);
+        // Against wider tiles of the same waves the fit favours 96 tokens by 2.5 % in row-major order, and in both orders
+        // where a stream then has more tiles: a near tie goes to the wider (4096x1024 at 85 %, 6144 tokens, estimated
+        // 31.5 us and 30.8: 128 tokens 24.9 us, 96 tokens 26.0; tile-major 22.3 and 23.1).  Not with 6 step slots, which
+        // leave the wider form few registers for gathers in flight (80 %: 27.7 and 27.9; tile-major 26.3 and 25.1).
+        persistent(96, 16, 0, FIT_96_16[reload], best.waves == 16 && max_steps <= 5 ? 0.96 : 0.98);
     }
     persistent(128, 8, 0, FIT_128_8[reload]);
     c.max_steps = fed_steps;

@@ -65,6 +65,7 @@ def test_the_choice_is_close_to_the_fastest_configuration(chosen, layout, mean, 
 @pytest.mark.parametrize("N, K, M, sparsity, configuration", [
     (768, 3072, 4096, 90, "FED_64_12"),     # reloaded weights, one token tile per stream, 1-byte outputs
     (4096, 1024, 6144, 85, "128_16"),       # a near tie with 96_16, which the measurement does not bear out in either layout
+    (4096, 1024, 6144, 80, "96_16"),        # ... and one that it does
     (4096, 1024, 6144, 90, "128_16"),
     (1024, 4096, 6144, 85, "96_16"),
     (1024, 1024, 6144, 85, "96_16"),
