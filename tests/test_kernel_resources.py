@@ -3,12 +3,15 @@
 No kernel may spill vector registers.  The persistent kernels are written to fit their budget (128 registers in the
 16-wave forms) exactly, and a change that costs them one register shows nowhere else: the results stay right, and the
 spilled value, often a weight that has just been requested, is waited for in every phase."""
+import os
 import re
 import struct
+import subprocess
 
 import pytest
 
 import paper_2306_16601_amd as sp
+from paper_2306_16601_amd import build as B
 
 msgpack = pytest.importorskip("msgpack")
 
@@ -68,3 +71,22 @@ def test_resident_kernels_leave_room_for_a_second_workgroup(kernels):
             seen += 1
             assert k[".vgpr_count"] <= 128, k[".name"]
     assert seen == 25
+
+
+HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+
+
+@pytest.mark.skipif(not os.path.exists(HIPCC), reason="no hipcc")
+@pytest.mark.parametrize("waves, slots", [(8, 8), (12, 4), (8, 4)])
+def test_weight_requests_of_int32_outputs_wait_for_no_stores(tmp_path, waves, slots):
+    """The loader-wave kernels store int32 accumulators as they are, and must not wait for those stores before they
+    request the next phase's weights: no more full waits in the code than with binary32 outputs."""
+    waits = []
+    for out in ("SPMM_OUT_S32", "SPMM_OUT_F32"):
+        src, asm = tmp_path / (out + ".hip"), tmp_path / (out + ".s")
+        src.write_text('#include "spmm_kernels.h"\nnamespace spmm { template __global__ void spmm_rowtile_mfma_fed<128, %d, 4, %d, %s, 0>'
+                       "(const KernelArgs); }\n" % (waves, slots, out))
+        subprocess.run([HIPCC, *B.HIPCC_FLAGS, "-x", "hip", "--cuda-device-only", "-S", str(src), "-o", str(asm)], check=True,
+                       capture_output=True)
+        waits.append(len(re.findall(r"s_waitcnt vmcnt\(0\)\s", asm.read_text())))
+    assert waits[0] <= waits[1], waits
