@@ -58,6 +58,9 @@ bool aligned(const void* p, size_t a) { return (reinterpret_cast<uintptr_t>(p) %
 
 spmm::Plan plan_for(const spmm_handle* h, int64_t M, int out_bytes, bool x_fast = true, bool out_fast = true)
 {
+    // (spmm_run takes at most 2^30 tokens; the calls that only report a plan take any number, and the plan counts token
+    // tiles in 32 bits)
+    M = std::min(M, (int64_t)1 << 34);
     const spmm::WeightDims w{h->ntiles, h->nseg, (int)h->bsr.K, h->nsteps, h->max_steps_per_segment,
                              h->max_steps_per_tile};
     return spmm::make_plan(M, w, h->num_cus, h->force_tm, h->force_r, out_bytes, x_fast, out_fast);

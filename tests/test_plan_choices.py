@@ -4,6 +4,7 @@ import csv
 import os
 import shutil
 import subprocess
+import sys
 
 import numpy as np
 import pytest
@@ -76,3 +77,13 @@ def test_long_batches_take_the_fastest_form_in_both_layouts(chosen, N, K, M, spa
     assert len(here) >= 2
     for n, t in here:
         assert n == configuration and t < 1.02, (n, t)
+
+
+def test_a_plan_for_any_number_of_tokens():
+    """spmm_plan and spmm_kernel_variant report, whatever M is (a process of its own: a division by zero ends it)."""
+    code = ("import numpy as np, paper_2306_16601_amd as sp\n"
+            "h = sp.spmm_pack_host(np.ones((64, 64), dtype=np.int8))\n"
+            "for e in (30, 33, 35, 36, 39, 62):\n"
+            "    assert sp.spmm_plan(h, 2 ** e, 's8')[2] > 0 and 'mfma' in sp.spmm_kernel_variant(h, 2 ** e, 's8', 'none'), e\n")
+    r = subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0, (r.returncode, r.stderr[-500:])
