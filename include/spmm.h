@@ -221,6 +221,10 @@ spmm_status_t spmm_plan(const spmm_handle_t *h, int64_t M, spmm_out_t out_type,
  *                   weights silently use token tile 128 with 8 waves).
  *   token_tile 128, 96, 64: variant 112 = the pipelined kernel with 12 waves and 4 more that only stage
  *                   activations; 128: variant 108 = with 8 + 4 (what denser weights silently use).
+ *   token_tile 128, 96, 64: variant 132 = row tiles of 32 rows, 8 compute waves and 4 that stage activations;
+ *                   64, 32: variant 134 = with 4 + 2, two workgroups on a CU.  (Sum takes tiles of at most 64 tokens, GELU in
+ *                   binary32 of at most 96, whatever is asked for; weights too dense for that form, with more than two of
+ *                   every four listed k in a row, silently use 128 / 108.)
  *   token_tile 64, 32, 16: variant 101 = the simple kernel, the K slab of activations of a token tile
  *                   in LDS at once (64: variant 102 = 2 row tiles per wave): small problems.
  *   token_tile 32, 16: variant 105 / 106 = the same with 2 / 4 row tiles per workgroup instead of 8, whose

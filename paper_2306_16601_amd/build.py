@@ -28,7 +28,9 @@ FED = [(128, 12, 4), (128, 12, 6), (128, 8, 4), (128, 8, 6), (128, 8, 8), (96, 1
 SIMPLE = [(64, 1), (64, 2), (32, 1), (16, 1)]      # (token tile, row tiles per wave) of the simple kernel
 SLAB = [16, 32]            # token tiles of the short-batch kernel
 STREAM = [64, 32, 16]      # token tiles of the streamed kernel
-HEADERS = [os.path.join(CSRC, "spmm_internal.h"), os.path.join(CSRC, "spmm_kernels.h"),
+# (token tile, compute waves, step slots) of the persistent kernel over the wide form
+WIDE = [(tm, nw, maxs) for tm, nw in ((128, 8), (96, 8), (64, 8), (64, 4), (32, 4)) for maxs in (5, 6, 7, 8)]
+HEADERS = [os.path.join(CSRC, "spmm_internal.h"), os.path.join(CSRC, "spmm_kernels.h"), os.path.join(CSRC, "spmm_wide.h"),
            os.path.join(ROOT, "include", "spmm.h")]
 
 HIPCC_FLAGS = [
@@ -48,6 +50,8 @@ def units():
         out.append((f"cfg_{tm}_{nw}_{maxs}.o", cfg, [f"-DSPMM_CFG_TM={tm}", f"-DSPMM_CFG_NW={nw}", f"-DSPMM_CFG_MAXS={maxs}"]))
     for tm, nw, maxs in FED:
         out.append((f"cfg_fed_{tm}_{nw}_{maxs}.o", cfg, [f"-DSPMM_CFG_FED_TM={tm}", f"-DSPMM_CFG_NW={nw}", f"-DSPMM_CFG_MAXS={maxs}"]))
+    for tm, nw, maxs in WIDE:
+        out.append((f"cfg_wide_{tm}_{nw}_{maxs}.o", cfg, [f"-DSPMM_CFG_WIDE_TM={tm}", f"-DSPMM_CFG_NW={nw}", f"-DSPMM_CFG_MAXS={maxs}"]))
     for tm, r in SIMPLE:
         out.append((f"cfg_simple_{tm}_{r}.o", cfg, [f"-DSPMM_CFG_SIMPLE={r}", f"-DSPMM_CFG_SIMPLE_TM={tm}"]))
     for tm in SLAB:
@@ -96,7 +100,7 @@ def build(force: bool = True, verbose: bool = False, jobs: int | None = None) ->
     try:
         us = units()
         # the heaviest objects (pipelined kernels) first
-        us.sort(key=lambda u: 0 if u[0].startswith("cfg_1") or u[0].startswith("cfg_9") or u[0].startswith("cfg_fed") else 1)
+        us.sort(key=lambda u: 0 if u[0].startswith("cfg_wide_1") else 1 if u[0].startswith(("cfg_1", "cfg_9", "cfg_fed", "cfg_wide")) else 2)
         cmds = [[hipcc, *HIPCC_FLAGS, *defs, "-x", "hip", "-c", src, "-o", os.path.join(objdir, obj)]
                 for obj, src, defs in us]
         with ThreadPoolExecutor(max_workers=jobs) as pool:

@@ -22,8 +22,11 @@ struct spmm_handle {
     int nseg = 0, ntiles = 0, max_steps_per_tile = 0, max_steps_per_segment = 0;
     int num_cus = 256;
     int64_t nsteps = 0;
-    uint8_t* d_weight = nullptr;   // rowsum, bounds and step records (spmm_internal.h)
+    uint8_t* d_weight = nullptr;   // rowsum, bounds and step records (spmm_internal.h), then the wide form
     int tile_steps = 0;
+    // the wide form, in the same allocation (wide_max_steps = 0: the weight has none)
+    int64_t wide_offset = 0, wide_nsteps = 0;
+    int wide_max_steps = 0, wide_tile_steps = 0;
     int64_t device_bytes = 0;
     int force_tm = 0, force_r = 0;
 };
@@ -31,7 +34,7 @@ struct spmm_handle {
 namespace {
 
 // The packed weight in its device form (spmm_internal.h), in one allocation and one copy.
-hipError_t upload_weight(spmm_handle* h)
+hipError_t upload_weight(spmm_handle* h, const spmm::Bsr& ordered)
 {
     const spmm::HostLayout& hl = h->hl;
     const int64_t nt = hl.ntiles;
@@ -42,10 +45,18 @@ hipError_t upload_weight(spmm_handle* h)
     const int64_t bytes = spmm::records_offset(nt, hl.nseg) + records * spmm::RECORD_BYTES;
     std::unique_ptr<uint8_t[]> form(new uint8_t[(size_t)bytes]);
     spmm::device_form(hl, h->tile_steps, records, form.get());
-    hipError_t e = hipMalloc((void**)&h->d_weight, (size_t)bytes);
+    spmm::WideForm wide;
+    const bool has_wide = spmm::wide_from_bsr(ordered, wide);
+    h->wide_offset = (bytes + 127) & ~(int64_t)127;
+    h->device_bytes = has_wide ? h->wide_offset + wide.size : bytes;
+    hipError_t e = hipMalloc((void**)&h->d_weight, (size_t)h->device_bytes);
     if (e != hipSuccess) return e;
-    h->device_bytes = bytes;
-    return hipMemcpy(h->d_weight, form.get(), (size_t)bytes, hipMemcpyHostToDevice);
+    e = hipMemcpy(h->d_weight, form.get(), (size_t)bytes, hipMemcpyHostToDevice);
+    if (e != hipSuccess || !has_wide) return e;
+    h->wide_nsteps = wide.nsteps;
+    h->wide_max_steps = std::max(1, wide.max_steps_per_segment);
+    h->wide_tile_steps = wide.tile_steps;
+    return hipMemcpy(h->d_weight + h->wide_offset, wide.bytes.get(), (size_t)wide.size, hipMemcpyHostToDevice);
 }
 
 void free_device(spmm_handle* h)
@@ -56,14 +67,14 @@ void free_device(spmm_handle* h)
 
 bool aligned(const void* p, size_t a) { return (reinterpret_cast<uintptr_t>(p) % a) == 0; }
 
-spmm::Plan plan_for(const spmm_handle* h, int64_t M, int out_bytes, bool x_fast = true, bool out_fast = true)
+spmm::Plan plan_for(const spmm_handle* h, int64_t M, int out_bytes, bool x_fast = true, bool out_fast = true, int widest = 128)
 {
     // (spmm_run takes at most 2^30 tokens; the calls that only report a plan take any number, and the plan counts token
     // tiles in 32 bits)
     M = std::min(M, (int64_t)1 << 34);
     const spmm::WeightDims w{h->ntiles, h->nseg, (int)h->bsr.K, h->nsteps, h->max_steps_per_segment,
-                             h->max_steps_per_tile};
-    return spmm::make_plan(M, w, h->num_cus, h->force_tm, h->force_r, out_bytes, x_fast, out_fast);
+                             h->max_steps_per_tile, h->wide_max_steps, h->wide_nsteps};
+    return spmm::make_plan(M, w, h->num_cus, h->force_tm, h->force_r, out_bytes, x_fast, out_fast, widest);
 }
 
 }  // namespace
@@ -79,13 +90,13 @@ static spmm_status_t pack_common(const int8_t* W_host, int64_t N, int64_t K, int
     if (K > 65536 || N > (int64_t)1 << 24) return SPMM_E_UNSUPPORTED;
 
     spmm_handle* h = nullptr;
+    spmm::Bsr ordered;      // the weight with its rows in the order chosen, if that is not the caller's
     try {
         h = new spmm_handle();
         spmm::bsr_from_dense(W_host, N, K, ldw, block, h->bsr);
         h->nnz_blocks = (int64_t)h->bsr.index.size();
         if (reorder) {
             spmm::order_rows_by_k_overlap(h->bsr, spmm::SEGMENT_ROWS, h->row_order);
-            spmm::Bsr ordered;
             spmm::bsr_permute_rows(h->bsr, h->row_order, ordered);
             spmm::layout_from_bsr(ordered, spmm::SEGMENT_ROWS, h->hl);
         } else {
@@ -109,7 +120,7 @@ static spmm_status_t pack_common(const int8_t* W_host, int64_t N, int64_t K, int
         }
         if (e == hipSuccess) {
             try {
-                e = upload_weight(h);
+                e = upload_weight(h, reorder ? ordered : h->bsr);
             } catch (...) {
                 e = hipErrorOutOfMemory;
             }
@@ -325,7 +336,11 @@ static spmm_status_t run_common(const spmm_handle_t* h, const uint8_t* X_dev, in
     a.x_scale = ep->x_scale;
     a.tile_steps = (uint16_t)h->tile_steps;
 
-    const spmm::Plan p = plan_for(h, M, (int)esz, x_fast, out_fast);
+    const spmm::Plan p = plan_for(h, M, (int)esz, x_fast, out_fast, spmm::wide_tile(!quant && gelu, ep->sum != nullptr));
+    if (p.wide) {
+        a.weight = h->d_weight + h->wide_offset;
+        a.tile_steps = (uint16_t)h->wide_tile_steps;
+    }
     const int rc = spmm::launch_spmm(p, a, ot, (gelu ? SPMM_POST_GELU : SPMM_POST_NONE) | (ep->sum ? spmm::POST_SUM_BIT : 0),
                                      hip_stream);
     return rc == 0 ? SPMM_OK : SPMM_E_DEVICE;
@@ -367,7 +382,8 @@ spmm_status_t spmm_kernel_variant_tiled(const spmm_handle_t* h, int64_t M, spmm_
     if (out_type < SPMM_OUT_S32 || out_type > SPMM_OUT_U8) return SPMM_E_ARG;
     if (postop != SPMM_POST_NONE && postop != SPMM_POST_GELU && postop != SPMM_POST_TABLE) return SPMM_E_ARG;
     if (postop == SPMM_POST_TABLE) postop = SPMM_POST_GELU;   // same kernels
-    const spmm::Plan p = plan_for(h, M, (out_type == SPMM_OUT_S32 || out_type == SPMM_OUT_F32) ? 4 : 1);
+    const spmm::Plan p = plan_for(h, M, (out_type == SPMM_OUT_S32 || out_type == SPMM_OUT_F32) ? 4 : 1, true, true,
+                                  spmm::wide_tile(out_type == SPMM_OUT_F32 && postop == SPMM_POST_GELU, false));
     const int post = (out_type == SPMM_OUT_S32) ? 0 : (int)postop;   // S32 output ignores the post-operator
     if (p.stream)
         std::snprintf(buf, (size_t)buflen, "void spmm::spmm_rowtile_mfma_stream<%d, %d, %d, %d>(spmm::KernelArgs)",
@@ -378,6 +394,9 @@ spmm_status_t spmm_kernel_variant_tiled(const spmm_handle_t* h, int64_t M, spmm_
     else if (p.simple)
         std::snprintf(buf, (size_t)buflen, "void spmm::spmm_rowtile_mfma_simple<%d, %d, %d, %d, %d>(spmm::KernelArgs)",
                       p.token_tile, 8, p.row_tiles_per_wave, (int)out_type, post);
+    else if (p.wide)
+        std::snprintf(buf, (size_t)buflen, "void spmm::spmm_rowtile_smfmac<%d, %d, %d, %d, %d>(spmm::KernelArgs)", p.token_tile, p.waves,
+                      p.max_steps, (int)out_type, post);
     else if (p.loaders)
         std::snprintf(buf, (size_t)buflen, "void spmm::spmm_rowtile_mfma_fed<%d, %d, %d, %d, %d, %d>(spmm::KernelArgs)",
                       p.token_tile, p.waves, p.loaders, p.max_steps, (int)out_type, post);

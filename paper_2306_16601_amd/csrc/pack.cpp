@@ -10,6 +10,7 @@
 #include <atomic>
 #include <cstring>
 #include <exception>
+#include <memory>
 #include <thread>
 
 #include "spmm_internal.h"
@@ -505,6 +506,257 @@ void device_form(const HostLayout& hl, int tile_steps, int64_t records, uint8_t*
             if (tile_steps) std::memset(rec + (past + shift) * RECORD_BYTES, 0, (size_t)(tile_steps - (past - first)) * RECORD_BYTES);
         }
     });
+}
+
+// ---------------------------------------------------------------------------------------
+// The wide form (spmm_internal.h): 32 rows share a list, and of every 4 consecutive slots (a quad) a row may use two.
+//
+// Two conditions bind the listed k of a segment to slots.  Quads: no unit (block-row, or row of 1x4 blocks) has more than
+// two of a quad's k.  Banks: a gather of half a wave reads the 8 activation rows of one octet of slots, 32 bytes each,
+// and rows lie 32 bytes apart in LDS, so they hit distinct banks when their residues mod 8 differ.  Both are met by
+// dealing, octet by octet, one k of every residue class, the heaviest that still fits its quad.  What is left when a
+// class or a fit runs out goes to the holes that remain, by an exchange if need be, and to a new step at the worst.
+// (512 random positions at 70 to 90 %, 8 block-rows: no step more than the list's length asks for, and 0 to 9 of 100
+// octets with a residue twice; 32 rows of 1x4 blocks at 75 %: 8.4 steps where 8 would hold the list.)
+// ---------------------------------------------------------------------------------------
+namespace {
+
+struct WideSegment {
+    int32_t slot[WIDE_MAX_STEPS * STEP_K];      // segment-local k, -1: padding
+    int steps;
+};
+
+// false: more than WIDE_MAX_STEPS
+bool arrange_wide(const uint32_t* mask, int rows, WideSegment& out)
+{
+    constexpr int CLASSES = 8, MAX_QUADS = WIDE_MAX_STEPS * STEP_K / 4;
+    // candidates of every class, heaviest first, and for every unit which of them it uses
+    int32_t cand[CLASSES][SEGMENT_ROWS / CLASSES];
+    uint64_t alive[CLASSES], uses[CLASSES][32];
+    std::memset(uses, 0, sizeof(uses));
+    int n = 0;
+    for (int c = 0; c < CLASSES; ++c) {
+        uint8_t weight[SEGMENT_ROWS / CLASSES];
+        int start[34] = {0}, m = 0;
+        for (int k = c, i = 0; k < rows; k += CLASSES, ++i) {
+            weight[i] = (uint8_t)__builtin_popcount(mask[k]);
+            if (weight[i]) { ++start[32 - weight[i] + 1]; ++m; }
+        }
+        for (int w = 1; w < 34; ++w) start[w] += start[w - 1];
+        for (int k = c, i = 0; k < rows; k += CLASSES, ++i) {
+            if (!weight[i]) continue;
+            const int at = start[32 - weight[i]]++;
+            cand[c][at] = k;
+            for (uint32_t u = mask[k]; u; u &= u - 1) uses[c][__builtin_ctz(u)] |= (uint64_t)1 << at;
+        }
+        alive[c] = m == 64 ? ~(uint64_t)0 : ((uint64_t)1 << m) - 1;
+        n += m;
+    }
+    out.steps = (n + STEP_K - 1) / STEP_K;
+    uint32_t one[MAX_QUADS] = {0}, two[MAX_QUADS] = {0};       // units with a k, with two, in the quad
+    auto put = [&](int slot, int32_t k) {
+        out.slot[slot] = k;
+        two[slot / 4] |= one[slot / 4] & mask[k];
+        one[slot / 4] |= mask[k];
+    };
+    for (int i = 0; i < out.steps * STEP_K; ++i) out.slot[i] = -1;
+    for (int o = 0; o < out.steps * 8; ++o) {
+        for (int j = 0; j < 8; ++j) {
+            const int c = (j + o) & 7;
+            uint64_t fit = alive[c];
+            for (uint32_t u = two[2 * o + j / 4]; u; u &= u - 1) fit &= ~uses[c][__builtin_ctz(u)];
+            if (!fit) continue;
+            alive[c] &= ~(fit & (0 - fit));
+            put(8 * o + j, cand[c][__builtin_ctzll(fit)]);
+        }
+    }
+    // what is left over
+    int exchanges = 256;                            // (a bound on the work; then a new step)
+    for (int c = 0; c < CLASSES; ++c) {
+        while (alive[c]) {
+            const int32_t k = cand[c][__builtin_ctzll(alive[c])];
+            const uint32_t m = mask[k];
+            bool done = false;
+            auto hole_of = [&](int q) {
+                for (int s = 4 * q; s < 4 * q + 4; ++s)
+                    if (out.slot[s] < 0) return s;
+                return -1;
+            };
+            int holes[MAX_QUADS], nholes = 0;
+            for (int q = 0; q < out.steps * 16; ++q)
+                if (hole_of(q) >= 0) holes[nholes++] = q;
+            for (int i = 0; i < nholes && !done; ++i)
+                if (!(two[holes[i]] & m)) {
+                    put(hole_of(holes[i]), k);
+                    done = true;
+                }
+            // a k of another quad into the hole, and this one into its place
+            for (int i = 0; i < nholes && !done && exchanges-- > 0; ++i) {
+                const int q = holes[i];
+                for (int s = 0; s < out.steps * STEP_K && !done; ++s) {
+                    const int r = s / 4;
+                    if (r == q || out.slot[s] < 0 || (two[q] & mask[out.slot[s]])) continue;
+                    uint32_t o1 = 0, t1 = 0;        // quad r without slot s
+                    for (int z = 4 * r; z < 4 * r + 4; ++z)
+                        if (z != s && out.slot[z] >= 0) {
+                            t1 |= o1 & mask[out.slot[z]];
+                            o1 |= mask[out.slot[z]];
+                        }
+                    if (t1 & m) continue;
+                    put(hole_of(q), out.slot[s]);
+                    one[r] = o1;
+                    two[r] = t1;
+                    put(s, k);
+                    done = true;
+                }
+            }
+            if (!done) {
+                if (out.steps == WIDE_MAX_STEPS) return false;
+                for (int i = 0; i < STEP_K; ++i) out.slot[out.steps * STEP_K + i] = -1;
+                ++out.steps;
+                continue;                           // (and again, now that there are holes)
+            }
+            alive[c] &= alive[c] - 1;
+        }
+    }
+    return true;
+}
+
+}  // namespace
+
+// activation row of slot z of a record, at the lanes that gather it
+static void set_row(uint8_t* record, int z, int row)
+{
+    uint16_t* const r = (uint16_t*)(record + WIDE_VAL_BYTES);
+    const int lane = 32 * (z >> 5) + 2 * (z & 7) + (z >> 4 & 1), half = z >> 3 & 1;
+    r[4 * lane + 2 + half] = r[4 * (lane + 16) + 2 + half] = (uint16_t)(32 * row);
+}
+
+bool wide_from_bsr(const Bsr& b, WideForm& out)
+{
+    const int64_t N = b.N, K = b.K;
+    const bool n4 = b.block == SPMM_BLOCK_N4K1;
+    const int units = n4 ? WIDE_ROWS / 4 : WIDE_ROWS;
+    out.nseg = (int)((K + SEGMENT_ROWS - 1) / SEGMENT_ROWS);
+    out.ntiles = (int)((N + WIDE_ROWS - 1) / WIDE_ROWS);
+    const int nseg = out.nseg;
+    const int64_t nt = out.ntiles, grain = std::max<int64_t>(1, 262144 / (K * WIDE_ROWS));
+    std::vector<int32_t> steps((size_t)(nt * nseg));
+    // of every k listed in a tile: 64 * step + slot, and the units that have a k in an earlier slot of its quad
+    struct Place { int32_t slot; uint32_t before; };
+    std::unique_ptr<Place[]> places(new Place[(size_t)(nt * K)]);
+    std::atomic<bool> fits{true};
+    parallel_for(nt, grain, [&](int64_t begin, int64_t end) {
+        std::vector<uint32_t> mask((size_t)K);
+        WideSegment seg_slots;
+        for (int64_t t = begin; t < end && fits; ++t) {
+            std::fill(mask.begin(), mask.end(), 0u);
+            for (int u = 0; u < units && t * units + u < b.block_rows; ++u) {
+                const int64_t br = t * units + u;
+                for (int64_t e = b.row_ptr[(size_t)br]; e < b.row_ptr[(size_t)br + 1]; ++e) {
+                    if (n4) {
+                        mask[(size_t)b.index[(size_t)e]] |= 1u << u;
+                    } else {
+                        for (int j = 0; j < 4; ++j)
+                            if (b.vals[(size_t)e * 4 + j]) mask[(size_t)b.index[(size_t)e] * 4 + j] |= 1u << u;
+                    }
+                }
+            }
+            int first = 0;
+            for (int seg = 0; seg < nseg; ++seg) {
+                const int64_t k0 = (int64_t)seg * SEGMENT_ROWS;
+                const int rows = (int)std::min<int64_t>(SEGMENT_ROWS, K - k0);
+                if (!arrange_wide(&mask[(size_t)k0], rows, seg_slots)) {
+                    fits = false;
+                    return;
+                }
+                for (int q = 0; q < seg_slots.steps * 16; ++q) {
+                    uint32_t before = 0;
+                    for (int s = 4 * q; s < 4 * q + 4; ++s)
+                        if (seg_slots.slot[s] >= 0) {
+                            places[(size_t)(t * K + k0 + seg_slots.slot[s])] = {first * STEP_K + s, before};
+                            before |= mask[(size_t)(k0 + seg_slots.slot[s])];
+                        }
+                }
+                steps[(size_t)(t * nseg + seg)] = seg_slots.steps;
+                first += seg_slots.steps;
+            }
+        }
+    });
+    if (!fits) return false;
+    out.nsteps = 0;
+    out.max_steps_per_tile = out.max_steps_per_segment = 0;
+    std::vector<int64_t> first((size_t)nt + 1, 0);
+    for (int64_t t = 0; t < nt; ++t) {
+        int all = 0;
+        for (int seg = 0; seg < nseg; ++seg) {
+            all += steps[(size_t)(t * nseg + seg)];
+            out.max_steps_per_segment = std::max(out.max_steps_per_segment, steps[(size_t)(t * nseg + seg)]);
+        }
+        out.max_steps_per_tile = std::max(out.max_steps_per_tile, all);
+        first[(size_t)t + 1] = first[(size_t)t] + all;
+    }
+    out.nsteps = first[(size_t)nt];
+    const bool strided = nt * out.max_steps_per_tile <= out.nsteps + out.nsteps / 2;
+    out.tile_steps = strided ? out.max_steps_per_tile : 0;
+    const int64_t records = std::max<int64_t>(1, strided ? nt * out.tile_steps : out.nsteps), at = wide_records_offset(nt, nseg);
+    out.size = at + records * WIDE_RECORD_BYTES;
+    out.bytes.reset(new uint8_t[(size_t)out.size]);
+    std::memset(out.bytes.get(), 0, (size_t)at);
+    int32_t* const rowsum = (int32_t*)out.bytes.get();
+    int32_t* const bounds = (int32_t*)(out.bytes.get() + wide_bounds_offset(nt));
+    uint8_t* const rec = out.bytes.get() + at;
+    if (out.nsteps == 0) std::memset(rec, 0, (size_t)(records * WIDE_RECORD_BYTES));
+    parallel_for(nt, grain, [&](int64_t begin, int64_t end) {
+        for (int64_t t = begin; t < end; ++t) {
+            const int64_t base = out.tile_steps ? t * out.tile_steps : first[(size_t)t];
+            const int64_t count = first[(size_t)t + 1] - first[(size_t)t], room = out.tile_steps ? out.tile_steps : count;
+            uint8_t* const mine = rec + base * WIDE_RECORD_BYTES;
+            std::memset(mine, 0, (size_t)(room * WIDE_RECORD_BYTES));
+            bounds[t * (nseg + 1)] = (int32_t)base;
+            for (int seg = 0; seg < nseg; ++seg) bounds[t * (nseg + 1) + seg + 1] = bounds[t * (nseg + 1) + seg] + steps[(size_t)(t * nseg + seg)];
+            // rows of padding slots: the residue that the octet lacks (see above)
+            for (int seg = 0, s = 0; seg < nseg; ++seg) {
+                const int rows = (int)std::min<int64_t>(SEGMENT_ROWS, K - (int64_t)seg * SEGMENT_ROWS);
+                for (int i = 0; i < steps[(size_t)(t * nseg + seg)]; ++i, ++s) {
+                    uint8_t* const r = mine + (int64_t)s * WIDE_RECORD_BYTES;
+                    for (int z = 0; z < STEP_K; ++z) {
+                        const int row = ((z & 7) + (z >> 3)) & 7;
+                        set_row(r, z, row < rows ? row : 0);
+                    }
+                }
+            }
+            int32_t* const sum = rowsum + t * WIDE_ROWS;
+            auto add = [&](const int64_t k, const int u, const int row, const int rows, const uint32_t v) {
+                const Place& p = places[(size_t)(t * K + k)];
+                const int z = p.slot & (STEP_K - 1), h = z >> 4 & 1, which = 8 * (z >> 5) + 2 * (z >> 2 & 3) + (int)(p.before >> u & 1);
+                uint8_t* const r = mine + (int64_t)(p.slot / STEP_K) * WIDE_RECORD_BYTES;
+                uint8_t* const val = r + (32 * h + row) * 16 + which;
+                uint32_t* const sel = (uint32_t*)(r + WIDE_VAL_BYTES) + 2 * (32 * h + row);
+                for (int i = 0; i < rows; ++i) {
+                    val[16 * i] = (uint8_t)(v >> (8 * i));
+                    sel[2 * i] |= (uint32_t)(z & 3) << (2 * which);
+                    sum[row + i] += (int8_t)(v >> (8 * i));
+                }
+                set_row(r, z, (int)(k & (SEGMENT_ROWS - 1)));
+            };
+            for (int u = 0; u < units && t * units + u < b.block_rows; ++u) {
+                const int64_t br = t * units + u;
+                for (int64_t e = b.row_ptr[(size_t)br]; e < b.row_ptr[(size_t)br + 1]; ++e) {
+                    uint32_t v;
+                    std::memcpy(&v, &b.vals[(size_t)e * 4], 4);
+                    const int64_t k = b.index[(size_t)e];
+                    if (n4) {
+                        add(k, u, 4 * u, 4, v);
+                    } else {
+                        for (int j = 0; j < 4; ++j)
+                            if (v >> (8 * j) & 0xff) add(4 * k + j, u, u, 1, v >> (8 * j) & 0xff);
+                    }
+                }
+            }
+        }
+    });
+    return true;
 }
 
 }  // namespace spmm

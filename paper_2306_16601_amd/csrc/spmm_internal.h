@@ -3,6 +3,7 @@
 #pragma once
 
 #include <cstdint>
+#include <memory>
 #include <vector>
 
 #include "spmm.h"
@@ -84,6 +85,38 @@ constexpr int64_t records_offset(int64_t ntiles, int64_t nseg)
 // the packed weight in that form (tile_steps as above; `records` of them, at least one)
 void device_form(const HostLayout& hl, int tile_steps, int64_t records, uint8_t* out);
 
+// The wide form, for long batches: row tiles of WIDE_ROWS = 32 rows, the same segments, steps of 64 listed k for
+// v_smfmac_i32_32x32x64_i8.  That instruction takes, of every 4 consecutive list slots, at most 2 values per row, and a
+// selector that says which: the packer deals the listed k to groups of 4 in which no row has more than two (pack.cpp).
+//     int32   rowsum[ntiles][32]
+//     int32   bounds[ntiles][nseg + 1]
+//     (padding to 128 bytes)
+//     records                            one per step, WIDE_RECORD_BYTES = 1536:
+//         int8  vals[64][16]     lane l = 32 h + row: two stored values for each group of 4 of slots 16 h .. 16 h + 15, then
+//                                the same of slots 32 + 16 h .. (the operand's layout, as observed on the device)
+//         { u32 sel, rows }[64]  sel: 2 bits for each of the 16, its slot within the group.  rows: 32 times the activation rows
+//                                (within the segment) of slots 32 h + t and 32 h + 8 + t (low and high half; t = l % 16 / 2),
+//                                in odd lanes of slots 32 h + 16 + t and 32 h + 24 + t
+constexpr int WIDE_ROWS = 32;
+constexpr int WIDE_VAL_BYTES = 1024, WIDE_RECORD_BYTES = WIDE_VAL_BYTES + 64 * 8;
+constexpr int WIDE_MAX_STEPS = 8;                    // of a (row tile, segment): a weight with more has no wide form
+constexpr int64_t wide_bounds_offset(int64_t ntiles) { return ntiles * WIDE_ROWS * 4; }
+constexpr int64_t wide_records_offset(int64_t ntiles, int64_t nseg)
+{
+    return (wide_bounds_offset(ntiles) + ntiles * (nseg + 1) * 4 + 127) & ~(int64_t)127;
+}
+
+// The operand of Sum, and GELU in binary32, need registers that the accumulators of the widest tiles take.
+constexpr int wide_tile(bool gelu_f32, bool sum) { return sum ? 64 : gelu_f32 ? 96 : 128; }
+
+struct WideForm {
+    int nseg = 0, ntiles = 0, tile_steps = 0, max_steps_per_tile = 0, max_steps_per_segment = 0;
+    int64_t nsteps = 0, size = 0;
+    std::unique_ptr<uint8_t[]> bytes;
+};
+// false: the weight has none (too dense)
+bool wide_from_bsr(const Bsr& b, WideForm& out);
+
 // What a launch passes to a kernel.  96 bytes: the runtime writes the arguments of every launch through the
 // bus, and from 128 bytes on a launch takes 3.3 us of the host instead of 2.7 us (measured; this was a plain
 // 232-byte struct).  The kernels unpack it into an Args (spmm_kernels.h).
@@ -123,6 +156,7 @@ struct Plan {
     int simple;              // 1: simple kernel
     int slab;                // 1: spmm_rowtile_mfma_slab in its place (token tile 16: K <= 4096 resident in LDS; 32: the ring's other name)
     int stream;              // 1: the streamed kernel (a ring of segments) in its place
+    int wide;                // 1: persistent kernel over the wide form
     int max_steps;           // unroll bound of the per-segment step loop (pipelined kernel)
     int n_row_groups, n_tok_tiles, n_streams;
     int xcd_row_bits;        // the 8 XCDs take 2^this slices of the row groups and 8 / 2^this of the tokens
@@ -142,14 +176,18 @@ struct WeightDims {
     int ntiles, nseg, K;
     int64_t nsteps;
     int max_steps_per_segment, max_steps_per_tile;
+    // the wide form, if there is one
+    int wide_max_steps = 0;         // of a (row tile, segment); 0: there is none
+    int64_t wide_nsteps = 0;
 };
 bool plan_supported(int token_tile, int variant);
 // out_bytes: size of an output element
 // x_fast: see KernelArgs; an X without it takes the simple kernel, whatever was forced
 // out_fast: 32-bit offsets suffice for out; if not, the automatic choice avoids the 16-wave pipelined
 // kernels, whose general store path is slow for want of registers
+// widest: widest token tile of the wide form that the post-operators run with (wide_tile)
 Plan make_plan(int64_t M, const WeightDims& w, int num_cus, int force_tm, int variant, int out_bytes = 1,
-               bool x_fast = true, bool out_fast = true);
+               bool x_fast = true, bool out_fast = true, int widest = 128);
 // Launches the SpMM kernel; returns a hipError_t value as int (0 = success).
 // postop: SPMM_POST_* value, plus POST_SUM_BIT when a.sum is to be added
 constexpr int POST_SUM_BIT = 4;   // (a bit no SPMM_POST_* value uses)

@@ -4,10 +4,15 @@
 //   simple kernel    : -DSPMM_CFG_SIMPLE=<1|2> (row tiles per wave) -DSPMM_CFG_SIMPLE_TM=<64|32|16> (token tile)
 //   short-batch kernel: -DSPMM_CFG_SLAB=<16|32>      (token tile)
 //   streamed kernel  : -DSPMM_CFG_STREAM=<64|32|16>  (token tile)
+//   persistent kernel over the wide form: -DSPMM_CFG_WIDE_TM=<128|96|64> -DSPMM_CFG_NW=8, or <64|32> and 4, -DSPMM_CFG_MAXS=<5|6|7|8>
 //   loader-fed pipelined kernel: -DSPMM_CFG_FED_TM=<128|96|64> -DSPMM_CFG_NW=<12|8> -DSPMM_CFG_MAXS=<4|6|8>
 // Each defines one function launch_cfg_<...>() that picks the epilogue instantiation and
 // launches it; spmm_plan.hip calls them.
+#if defined(SPMM_CFG_WIDE_TM)
+#include "spmm_wide.h"
+#else
 #include "spmm_kernels.h"
+#endif
 
 namespace spmm {
 
@@ -47,7 +52,26 @@ static void dispatch_epilogue(spmm_out_t out_type, int postop, dim3 grid, dim3 b
 // different instantiations: internal linkage keeps the linker from folding their member functions
 // into one (which would launch the wrong kernel for every configuration but the one it kept).
 
-#if defined(SPMM_CFG_FED_TM)
+#if defined(SPMM_CFG_WIDE_TM)
+namespace {
+template <int TM, int NW, int MAXS>
+struct WideLaunch {
+    template <int OUT, int POST>
+    static void go(dim3 grid, dim3 block, hipStream_t st, const KernelArgs& a)
+    {
+        if constexpr (TM <= wide_tile(OUT == SPMM_OUT_F32 && (POST & SPMM_POST_GELU), POST & POST_SUM_BIT))
+            hipLaunchKernelGGL((spmm_rowtile_smfmac<TM, NW, MAXS, OUT, POST>), grid, block, 0, st, a);
+    }
+};
+}  // namespace
+
+void SPMM_CAT(SPMM_CAT(SPMM_CAT(SPMM_CAT(SPMM_CAT(launch_cfg_wide_, SPMM_CFG_WIDE_TM), _), SPMM_CFG_NW), _), SPMM_CFG_MAXS)(
+    spmm_out_t out_type, int postop, const unsigned* grid, unsigned block, void* stream, const KernelArgs& a)
+{
+    dispatch_epilogue<WideLaunch<SPMM_CFG_WIDE_TM, SPMM_CFG_NW, SPMM_CFG_MAXS>>(out_type, postop, dim3(grid[0], grid[1], grid[2]), dim3(block),
+                                                                   (hipStream_t)stream, a);
+}
+#elif defined(SPMM_CFG_FED_TM)
 namespace {
 template <int TM, int NW, int MAXS>
 struct FedLaunch {

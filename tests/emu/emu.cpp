@@ -18,6 +18,7 @@ struct Wave {
     unsigned gen = 0;
     const void* ptr[64];
     v4i_t a[64], b[64], c[64];
+    v8i_t b8[64];
     int iv[64];
 };
 struct Fiber {
@@ -128,6 +129,41 @@ v4i_t mfma_i8_16x16x64(v4i_t a, v4i_t b, v4i_t c)
     wave_sync(w, "mfma (collect)");
     return d;
 }
+// D[row][col] += sum of A[row][k] B[k][col] over 64 k, A held 2 of 4.  Lane l: A row l % 32, stored value e belongs to k
+// 32 (e / 8) + 16 (l / 32) + 4 (e % 8 / 2) + selector e; B column l % 32, k 32 (l / 32) + byte; D column l % 32, register r row
+// 8 (r / 4) + 4 (l / 32) + r % 4  (as observed on the device)
+v16i_t smfmac_i8_32x32x64(v4i_t a, v8i_t b, v16i_t c, int sel)
+{
+    Wave& w = my_wave();
+    const int lane = cur()->linear & 63;
+    w.a[lane] = a;
+    w.b8[lane] = b;
+    w.iv[lane] = sel;
+    wave_sync(w, "smfmac (deposit)");
+    const int col = lane & 31;
+    v16i_t d = c;
+    for (int r = 0; r < 16; ++r) {
+        const int row = 8 * (r / 4) + 4 * (lane / 32) + r % 4;
+        int32_t s = 0;
+        for (int h = 0; h < 2; ++h) {
+            int8_t av[16], bv[2][32];
+            memcpy(av, &w.a[32 * h + row], 16);
+            memcpy(bv[0], &w.b8[col], 32);
+            memcpy(bv[1], &w.b8[32 + col], 32);
+            const uint32_t pick = (uint32_t)w.iv[32 * h + row];
+            for (int e = 0; e < 16; ++e) s += (int32_t)av[e] * (int32_t)bv[e / 8][16 * h + 4 * (e % 8 / 2) + (pick >> (2 * e) & 3)];
+        }
+        d[r] = (int32_t)((uint32_t)d[r] + (uint32_t)s);
+    }
+    wave_sync(w, "smfmac (collect)");
+    return d;
+}
+void sleep()
+{
+    cur()->waiting = "a count of arrivals";
+    yield_fiber();
+    cur()->waiting = "";
+}
 void wave_barrier() { wave_sync(my_wave(), "wave_barrier"); }
 // swap16: ret0 = [a.row0, b.row0, a.row2, b.row2], ret1 = [a.row1, b.row1, a.row3, b.row3] (rows of 16 lanes);
 // swap32: ret0 = [a.lo32, b.lo32], ret1 = [a.hi32, b.hi32]  (as observed on the device)
@@ -150,6 +186,19 @@ v2u_t permlane_swap(unsigned a, unsigned b, int rows)
         r[1] = half ? (unsigned)w.c[32 + l][0] : (unsigned)w.iv[32 + l];
     }
     wave_sync(w, "permlane_swap (collect)");
+    return r;
+}
+// DPP: quad permutation (lane 4 j + i receives from lane 4 j + the two bits of the control at 2 i), or a broadcast of lane
+// control & 15 of every 16
+int dpp(int v, int control)
+{
+    if (control > 0xff && (control & ~15) != 0x150) { fprintf(stderr, "emu: DPP control 0x%x\n", control); abort(); }
+    Wave& w = my_wave();
+    const int lane = cur()->linear & 63;
+    w.iv[lane] = v;
+    wave_sync(w, "dpp (deposit)");
+    const int r = control > 0xff ? w.iv[(lane & ~15) + (control & 15)] : w.iv[(lane & ~3) + (control >> (2 * (lane & 3)) & 3)];
+    wave_sync(w, "dpp (collect)");
     return r;
 }
 int readfirstlane(int v)

@@ -47,6 +47,11 @@ dim3& block_dim();
 void syncthreads();
 v2i_t tr8(const void* p);
 v4i_t mfma_i8_16x16x64(v4i_t a, v4i_t b, v4i_t c);
+typedef int v8i_t __attribute__((ext_vector_type(8)));
+typedef int v16i_t __attribute__((ext_vector_type(16)));
+v16i_t smfmac_i8_32x32x64(v4i_t a, v8i_t b, v16i_t c, int sel);
+void sleep();
+int dpp(int v, int control);
 int readfirstlane(int v);
 void wave_barrier();
 typedef unsigned v2u_t __attribute__((ext_vector_type(2)));
@@ -67,6 +72,11 @@ void dev_free(void* p);
 #define __builtin_amdgcn_readlane(v, l) emu::readlane((int)(v), (int)(l))
 #define __builtin_amdgcn_ds_read_tr8_b64_v2i32(p) emu::tr8((const void*)(uintptr_t)(p))
 #define __builtin_amdgcn_mfma_i32_16x16x64_i8(a, b, c, x, y, z) emu::mfma_i8_16x16x64((a), (b), (c))
+#define __builtin_amdgcn_smfmac_i32_32x32x64_i8(a, b, c, sel, x, y) emu::smfmac_i8_32x32x64((a), (b), (c), (sel))
+#define __builtin_amdgcn_mov_dpp(v, control, rows, banks, bound) emu::dpp((v), (control))
+#define __builtin_amdgcn_wave_barrier() emu::wave_barrier()
+#define __builtin_amdgcn_fence(order, scope) ((void)0)
+#define __builtin_amdgcn_s_sleep(n) emu::sleep()
 #define __builtin_amdgcn_sched_barrier(m) ((void)0)
 #define __builtin_amdgcn_permlane16_swap(a, b, fi, bc) emu::permlane_swap((a), (b), 16)
 #define __builtin_amdgcn_permlane32_swap(a, b, fi, bc) emu::permlane_swap((a), (b), 32)
@@ -90,6 +100,17 @@ static inline uint32_t emu_cvt_pk_u8_f32(float f, uint32_t sel, uint32_t old)
     return (old & ~(0xffu << sh)) | ((uint32_t)v << sh);
 }
 #define __builtin_amdgcn_cvt_pk_u8_f32(f, sel, old) emu_cvt_pk_u8_f32((f), (sel), (old))
+static inline uint32_t emu_perm(uint32_t hi, uint32_t lo, uint32_t sel)
+{
+    const uint64_t v = ((uint64_t)hi << 32) | lo;
+    uint32_t r = 0;
+    for (int i = 0; i < 4; ++i) {
+        const uint32_t s = sel >> (8 * i) & 0xff;
+        r |= (s < 8 ? (uint32_t)(v >> (8 * s)) & 0xff : 0u) << (8 * i);      // (0x0c: zero; the kernels use no other)
+    }
+    return r;
+}
+#define __builtin_amdgcn_perm(hi, lo, sel) emu_perm((hi), (lo), (sel))
 static inline uint32_t emu_alignbyte(uint32_t hi, uint32_t lo, uint32_t sh)
 {
     const uint64_t v = ((uint64_t)hi << 32) | lo;
@@ -113,6 +134,7 @@ static inline void emu_buffer_store(const V v, const emu_buffer_rsrc r, const in
     memcpy(r.base + off, &v, sizeof(V));
 }
 #define __builtin_amdgcn_raw_buffer_store_b128(v, r, vo, so, aux) emu_buffer_store((v), (r), (vo), (so))
+#define __builtin_amdgcn_raw_buffer_store_b32(v, r, vo, so, aux) emu_buffer_store((v), (r), (vo), (so))
 using std::min;
 using std::max;
 

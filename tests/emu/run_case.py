@@ -51,6 +51,11 @@ def main():
             W[80:96] = wl.rng_for(5, N, K).integers(1, 127, size=(16, K), dtype=np.int8)
         if N > 128:
             W[112:128, : max(0, K - 500)] = 0
+    if kind == "empty":
+        # no blocks in the first rows, in the middle of K (more than a segment), in the last rows' first segment
+        W[: min(N, 64)] = 0
+        W[:, 300: max(300, K - 100)] = 0
+        W[N - 20:, :512] = 0
     ldx = ldx or M
     ldo = ldo or M
     Xp = np.full((K, ldx), 0xEE, dtype=np.uint8)
