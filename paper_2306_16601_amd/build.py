@@ -30,7 +30,7 @@ SLAB = [16, 32]            # token tiles of the short-batch kernel
 STREAM = [64, 32, 16]      # token tiles of the streamed kernel
 # (token tile, compute waves, step slots) of the persistent kernel over the wide form
 WIDE = [(tm, nw, maxs) for tm, nw in ((128, 8), (96, 8), (64, 8), (64, 4), (32, 4)) for maxs in (5, 6, 7, 8)]
-HEADERS = [os.path.join(CSRC, "spmm_internal.h"), os.path.join(CSRC, "spmm_kernels.h"), os.path.join(CSRC, "spmm_wide.h"),
+HEADERS = [os.path.join(CSRC, "spmm_internal.h"), os.path.join(CSRC, "spmm_kernels.h"), os.path.join(CSRC, "spmm_wide.h"), os.path.join(CSRC, "team.h"),
            os.path.join(ROOT, "include", "spmm.h")]
 
 HIPCC_FLAGS = [

@@ -10,6 +10,7 @@
 #include <new>
 
 #include "spmm_internal.h"
+#include "team.h"
 
 struct spmm_handle {
     spmm::Bsr bsr;                 // canonical host copy (unpack / info), rows in the caller's order
@@ -22,47 +23,27 @@ struct spmm_handle {
     int nseg = 0, ntiles = 0, max_steps_per_tile = 0, max_steps_per_segment = 0;
     int num_cus = 256;
     int64_t nsteps = 0;
-    uint8_t* d_weight = nullptr;   // rowsum, bounds and step records (spmm_internal.h), then the wide form
-    int tile_steps = 0;
-    // the wide form, in the same allocation (wide_max_steps = 0: the weight has none)
-    int64_t wide_offset = 0, wide_nsteps = 0;
-    int wide_max_steps = 0, wide_tile_steps = 0;
+    uint8_t *d_weight = nullptr, *d_wide = nullptr;     // rowsum, bounds and step records of both forms (spmm_internal.h),
+    uint8_t* wide = nullptr;       // the second one's: in an allocation of its own, or behind the first
+    spmm::DeviceForms forms;       // their dimensions (wide_max_steps = 0: no wide form), and the first one's bytes
     int64_t device_bytes = 0;
     int force_tm = 0, force_r = 0;
 };
 
 namespace {
 
-// The packed weight in its device form (spmm_internal.h), in one allocation and one copy.
-hipError_t upload_weight(spmm_handle* h, const spmm::Bsr& ordered)
+hipError_t upload(uint8_t** to, const uint8_t* from, int64_t bytes)
 {
-    const spmm::HostLayout& hl = h->hl;
-    const int64_t nt = hl.ntiles;
-    const bool strided = nt * hl.max_steps_per_tile <= hl.nsteps + hl.nsteps / 2;
-    h->tile_steps = strided ? hl.max_steps_per_tile : 0;
-    // (at least one record, so that a step index of 0 is always readable)
-    const int64_t records = std::max<int64_t>(1, strided ? nt * hl.max_steps_per_tile : hl.nsteps);
-    const int64_t bytes = spmm::records_offset(nt, hl.nseg) + records * spmm::RECORD_BYTES;
-    std::unique_ptr<uint8_t[]> form(new uint8_t[(size_t)bytes]);
-    spmm::device_form(hl, h->tile_steps, records, form.get());
-    spmm::WideForm wide;
-    const bool has_wide = spmm::wide_from_bsr(ordered, wide);
-    h->wide_offset = (bytes + 127) & ~(int64_t)127;
-    h->device_bytes = has_wide ? h->wide_offset + wide.size : bytes;
-    hipError_t e = hipMalloc((void**)&h->d_weight, (size_t)h->device_bytes);
-    if (e != hipSuccess) return e;
-    e = hipMemcpy(h->d_weight, form.get(), (size_t)bytes, hipMemcpyHostToDevice);
-    if (e != hipSuccess || !has_wide) return e;
-    h->wide_nsteps = wide.nsteps;
-    h->wide_max_steps = std::max(1, wide.max_steps_per_segment);
-    h->wide_tile_steps = wide.tile_steps;
-    return hipMemcpy(h->d_weight + h->wide_offset, wide.bytes.get(), (size_t)wide.size, hipMemcpyHostToDevice);
+    const hipError_t e = hipMalloc((void**)to, (size_t)bytes);
+    return e == hipSuccess ? hipMemcpy(*to, from, (size_t)bytes, hipMemcpyHostToDevice) : e;
 }
 
 void free_device(spmm_handle* h)
 {
-    if (h->d_weight) (void)hipFree(h->d_weight);
-    h->d_weight = nullptr;
+    for (uint8_t** p : {&h->d_weight, &h->d_wide}) {
+        if (*p) (void)hipFree(*p);
+        *p = nullptr;
+    }
 }
 
 bool aligned(const void* p, size_t a) { return (reinterpret_cast<uintptr_t>(p) % a) == 0; }
@@ -73,7 +54,7 @@ spmm::Plan plan_for(const spmm_handle* h, int64_t M, int out_bytes, bool x_fast 
     // tiles in 32 bits)
     M = std::min(M, (int64_t)1 << 34);
     const spmm::WeightDims w{h->ntiles, h->nseg, (int)h->bsr.K, h->nsteps, h->max_steps_per_segment,
-                             h->max_steps_per_tile, h->wide_max_steps, h->wide_nsteps};
+                             h->max_steps_per_tile, h->forms.wide_max_steps, h->forms.wide_nsteps};
     return spmm::make_plan(M, w, h->num_cus, h->force_tm, h->force_r, out_bytes, x_fast, out_fast, widest);
 }
 
@@ -90,48 +71,55 @@ static spmm_status_t pack_common(const int8_t* W_host, int64_t N, int64_t K, int
     if (K > 65536 || N > (int64_t)1 << 24) return SPMM_E_UNSUPPORTED;
 
     spmm_handle* h = nullptr;
-    spmm::Bsr ordered;      // the weight with its rows in the order chosen, if that is not the caller's
+    hipError_t e = hipSuccess;
     try {
         h = new spmm_handle();
-        spmm::bsr_from_dense(W_host, N, K, ldw, block, h->bsr);
+        spmm::Team team;
+        spmm::bsr_from_dense(W_host, N, K, ldw, block, h->bsr, team);
         h->nnz_blocks = (int64_t)h->bsr.index.size();
+        spmm::Bsr reordered;
         if (reorder) {
             spmm::order_rows_by_k_overlap(h->bsr, spmm::SEGMENT_ROWS, h->row_order);
-            spmm::bsr_permute_rows(h->bsr, h->row_order, ordered);
-            spmm::layout_from_bsr(ordered, spmm::SEGMENT_ROWS, h->hl);
+            spmm::bsr_permute_rows(h->bsr, h->row_order, reordered);
+        }
+        const spmm::Bsr& ordered = reorder ? reordered : h->bsr;
+        if (to_device) {
+            e = hipGetDevice(&h->device);
+            int cus = 0;
+            if (e == hipSuccess && hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, h->device) == hipSuccess && cus > 0)
+                h->num_cus = cus;
+            spmm::DeviceForms& f = h->forms;
+            // (the first form is on its way while the other threads pack the second)
+            spmm::forms_from_bsr(ordered, h->hl, f, team, [&] {
+                if (e == hipSuccess && !f.together) e = upload(&h->d_weight, f.bytes.get(), f.size);
+            });
+            // (a form that did not fit where it was meant to be has a buffer of its own after all)
+            if (e == hipSuccess && !h->d_weight) e = upload(&h->d_weight, f.bytes.get(), f.size + (f.together ? f.wide_size : 0));
+            if (e == hipSuccess && f.together) h->wide = h->d_weight + f.size;
+            if (e == hipSuccess && !f.together && f.wide_size) {
+                e = upload(&h->d_wide, f.wide.get(), f.wide_size);
+                h->wide = h->d_wide;
+            }
+            f.wide.reset();
+            h->device_bytes = f.size + f.wide_size;
+            h->on_device = true;
         } else {
-            spmm::layout_from_bsr(h->bsr, spmm::SEGMENT_ROWS, h->hl);
+            spmm::layout_from_bsr(ordered, spmm::SEGMENT_ROWS, h->hl, team);
         }
     } catch (...) {   // bad_alloc, length_error, ...: nothing crosses the C boundary
+        if (h) free_device(h);
         delete h;
         return SPMM_E_ALLOC;
+    }
+    if (e != hipSuccess) {
+        free_device(h);
+        delete h;
+        return (e == hipErrorOutOfMemory) ? SPMM_E_ALLOC : SPMM_E_DEVICE;
     }
     const spmm::HostLayout& hl = h->hl;
     h->nseg = hl.nseg; h->ntiles = hl.ntiles; h->nsteps = hl.nsteps;
     h->max_steps_per_tile = hl.max_steps_per_tile;
     h->max_steps_per_segment = hl.max_steps_per_segment;
-
-    if (to_device) {
-        hipError_t e = hipGetDevice(&h->device);
-        if (e == hipSuccess) {
-            int cus = 0;
-            if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, h->device) == hipSuccess && cus > 0)
-                h->num_cus = cus;
-        }
-        if (e == hipSuccess) {
-            try {
-                e = upload_weight(h, reorder ? ordered : h->bsr);
-            } catch (...) {
-                e = hipErrorOutOfMemory;
-            }
-        }
-        if (e != hipSuccess) {
-            free_device(h);
-            delete h;
-            return (e == hipErrorOutOfMemory) ? SPMM_E_ALLOC : SPMM_E_DEVICE;
-        }
-        h->on_device = true;
-    }
     *out_handle = h;
     return SPMM_OK;
 }
@@ -181,6 +169,7 @@ spmm_status_t spmm_layout_export(const spmm_handle_t* h, uint8_t* vals_host, uin
 {
     if (!h) return SPMM_E_ARG;
     const spmm::HostLayout& hl = h->hl;
+    if (h->on_device) spmm::export_steps(hl, h->forms, vals_host, idx_host);
     if (vals_host && !hl.vals.empty()) std::memcpy(vals_host, hl.vals.data(), hl.vals.size());
     if (idx_host && !hl.idx.empty()) std::memcpy(idx_host, hl.idx.data(), hl.idx.size() * sizeof(uint32_t));
     if (seg_ptr_host) std::memcpy(seg_ptr_host, hl.seg_ptr.data(), hl.seg_ptr.size() * sizeof(int32_t));
@@ -334,12 +323,12 @@ static spmm_status_t run_common(const spmm_handle_t* h, const uint8_t* X_dev, in
                 (out_tiled ? spmm::ARG_OUT_TILED : 0) | (x_fast ? spmm::ARG_X_FAST : 0) |
                 (out_fast ? spmm::ARG_OUT_FAST : 0) | (out_fast && out_aligned ? spmm::ARG_OUT_ALIGNED : 0);
     a.x_scale = ep->x_scale;
-    a.tile_steps = (uint16_t)h->tile_steps;
+    a.tile_steps = (uint16_t)h->forms.tile_steps;
 
     const spmm::Plan p = plan_for(h, M, (int)esz, x_fast, out_fast, spmm::wide_tile(!quant && gelu, ep->sum != nullptr));
     if (p.wide) {
-        a.weight = h->d_weight + h->wide_offset;
-        a.tile_steps = (uint16_t)h->wide_tile_steps;
+        a.weight = h->wide;
+        a.tile_steps = (uint16_t)h->forms.wide_tile_steps;
     }
     const int rc = spmm::launch_spmm(p, a, ot, (gelu ? SPMM_POST_GELU : SPMM_POST_NONE) | (ep->sum ? spmm::POST_SUM_BIT : 0),
                                      hip_stream);

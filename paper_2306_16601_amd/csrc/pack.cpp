@@ -7,50 +7,15 @@
 // after Algorithm 1).  Here that instruction is the 16x16x64 int8 matrix op, so the unit
 // of padding is 64 listed k positions per 16-row tile.
 #include <algorithm>
-#include <atomic>
 #include <cstring>
-#include <exception>
 #include <memory>
-#include <thread>
 
 #include "spmm_internal.h"
+#include "team.h"
 
 namespace spmm {
 
 namespace {
-
-// f(begin, end) over [0, n) in at most 8 threads, each with at least `grain` items; the first exception of a
-// thread is rethrown here.  (Packing a model's weights is what its load waits for; row tiles are independent.)
-template <typename F>
-void parallel_for(int64_t n, int64_t grain, const F& f)
-{
-    const int64_t hw = std::max<int64_t>(1, std::thread::hardware_concurrency());
-    const int64_t parts = std::max<int64_t>(1, std::min<int64_t>({8, hw, n / std::max<int64_t>(1, grain)}));
-    if (parts == 1) {
-        f((int64_t)0, n);
-        return;
-    }
-    std::vector<std::exception_ptr> failed((size_t)parts);
-    std::vector<std::thread> threads;
-    threads.reserve((size_t)parts - 1);
-    auto part = [&](int64_t i) {
-        try {
-            f(n * i / parts, n * (i + 1) / parts);
-        } catch (...) {
-            failed[(size_t)i] = std::current_exception();
-        }
-    };
-    int64_t started = 1;
-    try {
-        for (; started < parts; ++started) threads.emplace_back(part, started);
-    } catch (...) {      // no more threads to be had: the rest of the work is done here
-    }
-    part(0);
-    for (int64_t i = started; i < parts; ++i) part(i);
-    for (std::thread& t : threads) t.join();
-    for (const std::exception_ptr& e : failed)
-        if (e) std::rethrow_exception(e);
-}
 
 inline uint64_t load8(const int8_t* p)
 {
@@ -110,53 +75,64 @@ int64_t blocks_of_row(const int8_t* W, int64_t N, int64_t K, int64_t ldw, spmm_b
 
 void bsr_from_dense(const int8_t* W, int64_t N, int64_t K, int64_t ldw, spmm_block_t block, Bsr& out)
 {
+    Team team;
+    bsr_from_dense(W, N, K, ldw, block, out, team);
+}
+
+void bsr_from_dense(const int8_t* W, int64_t N, int64_t K, int64_t ldw, spmm_block_t block, Bsr& out, Team& team)
+{
     out.N = N;
     out.K = K;
     out.block = block;
     out.block_rows = (block == SPMM_BLOCK_N4K1) ? (N + 3) / 4 : N;
     out.row_ptr.assign((size_t)out.block_rows + 1, 0);
-    // every thread collects its block-rows, then the pieces are put together
-    struct Piece { int64_t first; std::vector<int32_t> index; std::vector<uint32_t> vals; };
-    std::vector<Piece> pieces(8);
-    std::atomic<int> used{0};
+    // pieces of block-rows, which are then put together
+    struct Piece { std::unique_ptr<int32_t[]> index; std::unique_ptr<uint32_t[]> vals; int64_t count = 0, at = 0; };
     const int64_t rows_per_block_row = (block == SPMM_BLOCK_N4K1) ? 4 : 1;
-    parallel_for(out.block_rows, std::max<int64_t>(1, 131072 / (K * rows_per_block_row)), [&](int64_t begin, int64_t end) {
-        Piece& p = pieces[(size_t)used.fetch_add(1)];
-        p.first = begin;
-        p.index.reserve((size_t)((end - begin) * K / 3));
-        p.vals.reserve((size_t)((end - begin) * K / 3));
-        std::vector<int32_t> index((size_t)K);
-        std::vector<uint32_t> vals((size_t)K);
+    const int64_t piece = std::max<int64_t>(1, 65536 / (K * rows_per_block_row)), most = (block == SPMM_BLOCK_N4K1) ? K : (K + 3) / 4;
+    std::vector<Piece> pieces((size_t)((out.block_rows + piece - 1) / piece));
+    team.run(out.block_rows, piece, [&](int64_t begin, int64_t end) {
+        Piece& p = pieces[(size_t)(begin / piece)];
+        int64_t room = std::max<int64_t>(most, (end - begin) * most / 3);
+        p.index.reset(new int32_t[(size_t)room]);
+        p.vals.reset(new uint32_t[(size_t)room]);
         for (int64_t br = begin; br < end; ++br) {
-            const int64_t n = blocks_of_row(W, N, K, ldw, block, br, index.data(), vals.data());
-            p.index.insert(p.index.end(), index.begin(), index.begin() + n);
-            p.vals.insert(p.vals.end(), vals.begin(), vals.begin() + n);
-            out.row_ptr[(size_t)br + 1] = (int64_t)p.index.size();      // within the piece, for now
+            if (p.count + most > room) {
+                room = std::min(std::max(2 * room, p.count + most), (end - begin) * most);
+                std::unique_ptr<int32_t[]> index(new int32_t[(size_t)room]);
+                std::unique_ptr<uint32_t[]> vals(new uint32_t[(size_t)room]);
+                std::memcpy(index.get(), p.index.get(), (size_t)p.count * 4);
+                std::memcpy(vals.get(), p.vals.get(), (size_t)p.count * 4);
+                p.index.swap(index);
+                p.vals.swap(vals);
+            }
+            p.count += blocks_of_row(W, N, K, ldw, block, br, p.index.get() + p.count, p.vals.get() + p.count);
+            out.row_ptr[(size_t)br + 1] = p.count;              // within the piece, for now
         }
     });
-    pieces.resize((size_t)used.load());
-    std::sort(pieces.begin(), pieces.end(), [](const Piece& x, const Piece& y) { return x.first < y.first; });
     int64_t total = 0;
-    for (size_t i = 0; i < pieces.size(); ++i) {
-        const int64_t end = i + 1 < pieces.size() ? pieces[i + 1].first : out.block_rows;
-        for (int64_t br = pieces[i].first; br < end; ++br) out.row_ptr[(size_t)br + 1] += total;
-        total += (int64_t)pieces[i].index.size();
+    for (Piece& p : pieces) {
+        p.at = total;
+        total += p.count;
     }
     out.index.resize((size_t)total);
     out.vals.resize((size_t)total * 4);
-    int64_t at = 0;
-    for (const Piece& p : pieces) {
-        if (p.index.empty()) continue;
-        std::memcpy(&out.index[(size_t)at], p.index.data(), p.index.size() * sizeof(int32_t));
-        std::memcpy(&out.vals[(size_t)at * 4], p.vals.data(), p.vals.size() * 4);
-        at += (int64_t)p.index.size();
-    }
+    team.run((int64_t)pieces.size(), 1, [&](int64_t begin, int64_t end) {
+        for (int64_t i = begin; i < end; ++i) {
+            const Piece& p = pieces[(size_t)i];
+            for (int64_t br = i * piece; br < std::min(out.block_rows, (i + 1) * piece); ++br) out.row_ptr[(size_t)br + 1] += p.at;
+            if (!p.count) continue;
+            std::memcpy(&out.index[(size_t)p.at], p.index.get(), (size_t)p.count * 4);
+            std::memcpy(&out.vals[(size_t)p.at * 4], p.vals.get(), (size_t)p.count * 4);
+        }
+    });
 }
 
 void bsr_to_dense(const Bsr& b, int8_t* W, int64_t ldw)
 {
     const bool n4 = b.block == SPMM_BLOCK_N4K1;
-    parallel_for(b.block_rows, std::max<int64_t>(1, 262144 / (b.K * (n4 ? 4 : 1))), [&](int64_t begin, int64_t end) {
+    Team team;
+    team.finish(b.block_rows, std::max<int64_t>(1, 262144 / (b.K * (n4 ? 4 : 1))), [&](int64_t begin, int64_t end) {
         for (int64_t br = begin; br < end; ++br) {
             const int rows = n4 ? (int)std::min<int64_t>(4, b.N - br * 4) : 1;
             int8_t* const w = W + br * (n4 ? 4 : 1) * ldw;
@@ -186,65 +162,67 @@ void bsr_to_dense(const Bsr& b, int8_t* W, int64_t ldw)
 // The entries are dealt out so that a half-read holds every residue mod 16 at most once
 // whenever the counts allow it; padding slots (zero weights) are pointed at a row of a
 // residue the half-read still lacks instead of all hitting row 0.
-// slot_k[s*64 + 16*g + t] = segment-local k or -1 (padding); slot_row = row actually read.
-static void arrange_for_lds_banks(const int32_t* list, int n_listed, int rows_in_segment, int nsteps, int32_t* slot_k,
-                                  int32_t* slot_row)
+// place(k, slot, row) is called for every slot of the steps once: k = -1 is padding, row the row that it reads.
+template <typename P>
+static void arrange_for_lds_banks(const uint32_t* mask, const uint32_t mine, int rows, int nsteps, const P& place)
 {
-    constexpr int MAXH = 4 * SEGMENT_ROWS / STEP_K;     // half-reads of the longest list
-    const int H = 4 * nsteps;
     if (nsteps == 0) return;
+    const int H = 4 * nsteps;                           // half-reads, at most 32
     // entries by residue
-    int32_t by_res[16][SEGMENT_ROWS / 16];
-    int n_res[16] = {0};
-    for (int i = 0; i < n_listed; ++i) by_res[list[i] & 15][n_res[list[i] & 15]++] = list[i];
-    int order[16];
-    for (int r = 0; r < 16; ++r) order[r] = r;
-    std::stable_sort(order, order + 16, [&](int x, int y) { return n_res[x] > n_res[y]; });
-
-    // Largest residue class first; each class is spread over the least-filled half-reads, one
-    // entry per half-read, so that no half-read runs out of room while others still have
-    // holes.  Only a class with more than H entries is forced to double up somewhere.
-    int32_t hr[MAXH][16];
-    int load[MAXH] = {0}, by_load[MAXH];
-    uint32_t mask[MAXH] = {0};
+    int16_t by_res[16][SEGMENT_ROWS / 16 + 1];
+    int n_res[16] = {0}, order[16];
+    for (int k = 0; k < rows; ++k) {
+        by_res[k & 15][n_res[k & 15]] = (int16_t)k;
+        n_res[k & 15] += (mask[k] & mine) != 0;
+    }
+    for (int r = 0; r < 16; ++r) {                      // largest class first, stable
+        int i = r;
+        for (; i > 0 && n_res[order[i - 1]] < n_res[r]; --i) order[i] = order[i - 1];
+        order[i] = r;
+    }
+    // Largest residue class first; each class is spread over the least-filled half-reads, one entry per half-read, so that
+    // no half-read runs out of room while others still have holes.  Only a class with more than H entries is forced to
+    // double up somewhere.  Filled that way, the half-reads hold `load` entries (those in `low`) or one more.
+    const uint32_t all = H == 32 ? ~0u : (1u << H) - 1;
+    uint32_t low = all, present[32] = {0};
+    int load = 0;
+    auto slot_of = [](int h, int j) { return h / 4 * STEP_K + 16 * (2 * (h & 1) + j / 8) + 8 * (h / 2 % 2) + j % 8; };
     for (int oi = 0; oi < 16; ++oi) {
         const int r = order[oi];
         int next = 0;
-        while (next < n_res[r]) {
-            int count[18] = {0};                        // half-reads by load (at most 16), stable
-            for (int h = 0; h < H; ++h) ++count[load[h] + 1];
-            for (int l = 1; l < 18; ++l) count[l] += count[l - 1];
-            for (int h = 0; h < H; ++h) by_load[count[load[h]]++] = h;
-            bool placed = false;
-            for (int i = 0; i < H && next < n_res[r]; ++i) {
-                const int h = by_load[i];
-                if (load[h] >= 16) break;
-                hr[h][load[h]++] = by_res[r][next++];
-                mask[h] |= 1u << r;
-                placed = true;
+        auto deal = [&](uint32_t to, int j) {           // an entry to each, in order; those that had none left are returned
+            for (; to && next < n_res[r]; to &= to - 1) {
+                const int h = __builtin_ctz(to), k = by_res[r][next++];
+                present[h] |= 1u << r;
+                place(k, slot_of(h, j), k);
             }
-            if (!placed) break;   // cannot happen: 16 * H slots >= n_listed
+            return to;
+        };
+        while (next < n_res[r]) {
+            const uint32_t high = all & ~low, left = deal(low, load);
+            if (left) {
+                low = left;
+            } else {
+                const uint32_t still = deal(high, load + 1);
+                low |= still;
+                ++load;
+                if (!low) {                             // (cannot be: `low` was not empty)
+                    low = all;
+                    ++load;
+                }
+            }
         }
     }
     for (int h = 0; h < H; ++h) {
-        const int s = h / 4, instr = (h / 2) % 2, pair = h % 2;
         int next_res = 0;
-        for (int j = 0; j < 16; ++j) {
-            const int g = 2 * pair + j / 8, t = 8 * instr + j % 8;
-            const int slot = s * STEP_K + 16 * g + t;
-            if (j < load[h]) {
-                slot_k[slot] = hr[h][j];
-                slot_row[slot] = hr[h][j];
-            } else {
-                while (next_res < 16 && (mask[h] & (1u << next_res))) ++next_res;
-                int row = 0;
-                if (next_res < 16) {
-                    if (next_res < rows_in_segment) row = next_res;
-                    mask[h] |= 1u << next_res;
-                }
-                slot_k[slot] = -1;
-                slot_row[slot] = row;
+        for (int j = load + !(low >> h & 1); j < 16; ++j) {
+            while (next_res < 16 && (present[h] & (1u << next_res))) ++next_res;
+            int row = 0;
+            if (next_res < 16) {
+                if (next_res < rows) row = next_res;
+                present[h] |= 1u << next_res;
             }
+            place(-1, slot_of(h, j), row);
         }
     }
 }
@@ -370,142 +348,174 @@ void bsr_permute_rows(const Bsr& b, const std::vector<int32_t>& row_order, Bsr& 
     }
 }
 
-void layout_from_bsr(const Bsr& b, int kc, HostLayout& out)
-{
-    const int64_t N = b.N, K = b.K;
-    const bool n4 = b.block == SPMM_BLOCK_N4K1;
-    out.kc = kc;                                            // SEGMENT_ROWS
-    out.nseg = (int)((K + kc - 1) / kc);
-    out.ntiles = (int)((N + TILE_ROWS - 1) / TILE_ROWS);
-    out.rowsum.assign((size_t)out.ntiles * TILE_ROWS, 0);
-    out.max_steps_per_tile = 0;
-    out.max_steps_per_segment = 0;
-    const int nseg = out.nseg, seg_words = kc / 64;
-    const int units = n4 ? TILE_ROWS / 4 : TILE_ROWS;       // block-rows of a tile
-    const int64_t grain = std::max<int64_t>(1, 262144 / (K * TILE_ROWS));
+// ---------------------------------------------------------------------------------------
+// Both layouts start from the lists of 32 rows: which of their units (block-rows, or rows of 1x4 blocks) list a k.
+// ---------------------------------------------------------------------------------------
+namespace {
 
-    // ---- the union of every tile's k lists, one bit per k; rows past N and block-rows past the end have none
-    std::vector<uint64_t> listed((size_t)out.ntiles * nseg * seg_words, 0);
-    std::vector<int32_t> steps((size_t)out.ntiles * nseg);
-    parallel_for(out.ntiles, grain, [&](int64_t begin, int64_t end) {
-        for (int64_t tile = begin; tile < end; ++tile) {
-            uint64_t* const bits = &listed[(size_t)(tile * nseg) * seg_words];
-            int32_t* const sum = &out.rowsum[(size_t)tile * TILE_ROWS];
-            for (int q = 0; q < units && tile * units + q < b.block_rows; ++q) {
-                const int64_t br = tile * units + q;
-                for (int64_t e = b.row_ptr[(size_t)br]; e < b.row_ptr[(size_t)br + 1]; ++e) {
-                    const int8_t* v = &b.vals[(size_t)e * 4];
+struct Lists {
+    const Bsr& b;
+    const bool n4;
+    const int64_t K;
+    const int units;                        // of a wide tile; half as many of a row tile
+    const uint32_t half;                    // the units of a wide tile's first row tile
+    const int nseg, ntiles;
+    const int64_t nt, grain;                // wide tiles; and of them, how many make a piece of work
+    std::unique_ptr<uint32_t[]> masks;      // [wide tile][k]: the units that list k
+    std::vector<int32_t> steps, wide_steps; // of every (row tile, segment); of every (wide tile, segment), if none needs more
+
+    // (rows past N and block-rows past the end list nothing)
+    Lists(const Bsr& bsr, int32_t* rowsum, Team& team)
+        : b(bsr), n4(b.block == SPMM_BLOCK_N4K1), K(b.K), units(n4 ? WIDE_ROWS / 4 : WIDE_ROWS), half(n4 ? 0xfu : 0xffffu),
+          nseg((int)((K + SEGMENT_ROWS - 1) / SEGMENT_ROWS)), ntiles((int)((b.N + TILE_ROWS - 1) / TILE_ROWS)), nt((ntiles + 1) / 2),
+          grain(std::max<int64_t>(1, 65536 / (K * WIDE_ROWS))), masks(new uint32_t[(size_t)(nt * K)]), steps((size_t)ntiles * nseg),
+          wide_steps((size_t)nt * nseg)
+    {
+        team.run(nt, grain, [&](int64_t begin, int64_t end) {
+            for (int64_t t = begin; t < end; ++t) {
+                uint32_t* const mask = &masks[(size_t)(t * K)];
+                std::memset(mask, 0, (size_t)K * 4);
+                for (int u = 0; u < units && t * units + u < b.block_rows; ++u) {
+                    const int64_t first = b.row_ptr[(size_t)(t * units + u)], past = b.row_ptr[(size_t)(t * units + u + 1)];
+                    const int32_t* const index = b.index.data();
+                    const int8_t* const v = b.vals.data();
+                    const uint32_t bit = 1u << u;
+                    int32_t sum[4] = {0, 0, 0, 0};
+                    for (int64_t e = first; e < past; ++e)
+                        for (int j = 0; j < 4; ++j) sum[j] += v[4 * e + j];
                     if (n4) {
-                        const int32_t k = b.index[(size_t)e];
-                        bits[k >> 6] |= (uint64_t)1 << (k & 63);
-                        for (int i = 0; i < 4; ++i) sum[4 * q + i] += v[i];
+                        for (int64_t e = first; e < past; ++e) mask[index[e]] |= bit;
+                        for (int j = 0; j < 4; ++j)
+                            if (t * WIDE_ROWS + 4 * u + j < (int64_t)ntiles * TILE_ROWS) rowsum[t * WIDE_ROWS + 4 * u + j] = sum[j];
                     } else {
-                        for (int j = 0; j < 4; ++j) {
-                            const int32_t k = b.index[(size_t)e] * 4 + j;
-                            if (v[j]) bits[k >> 6] |= (uint64_t)1 << (k & 63);
-                            sum[q] += v[j];
-                        }
+                        for (int64_t e = first; e < past; ++e)
+                            for (int j = 0; j < 4; ++j)
+                                if (v[4 * e + j]) mask[index[e] * 4 + j] |= bit;
+                        rowsum[t * WIDE_ROWS + u] = sum[0] + sum[1] + sum[2] + sum[3];
                     }
                 }
+                for (int seg = 0; seg < nseg; ++seg) {
+                    const int rows = rows_of(seg);
+                    const uint32_t* const m = mask + seg * SEGMENT_ROWS;
+                    int all = 0, low = 0, high = 0;
+                    for (int k = 0; k < rows; ++k) {
+                        all += m[k] != 0;
+                        low += (m[k] & half) != 0;
+                        high += (m[k] & ~half) != 0;
+                    }
+                    wide_steps[(size_t)(t * nseg + seg)] = (all + STEP_K - 1) / STEP_K;
+                    steps[(size_t)(2 * t * nseg + seg)] = (low + STEP_K - 1) / STEP_K;
+                    if (2 * t + 1 < ntiles) steps[(size_t)((2 * t + 1) * nseg + seg)] = (high + STEP_K - 1) / STEP_K;
+                }
             }
-            for (int seg = 0; seg < nseg; ++seg) {
-                int n = 0;
-                for (int w = 0; w < seg_words; ++w) n += __builtin_popcountll(bits[seg * seg_words + w]);
-                steps[(size_t)(tile * nseg + seg)] = (n + STEP_K - 1) / STEP_K;
+        });
+    }
+    int rows_of(int seg) const { return (int)std::min<int64_t>(SEGMENT_ROWS, K - (int64_t)seg * SEGMENT_ROWS); }
+};
+
+// The steps of a row tile: listed k dealt to slots, every block's values scattered to their lanes (vals[step][lane = 16 g +
+// row][t] of slot 16 g + t).  The values of a step and its positions lie `stride` bytes from those of the step before; `place`
+// is scratch of K numbers; positions are relative to the segment, or to the weight.
+void arrange_tile(const Lists& l, int64_t tile, uint8_t* vals, int64_t val_stride, uint8_t* idx, int64_t idx_stride, bool of_weight,
+                  int32_t* place)
+{
+    const Bsr& b = l.b;
+    const uint32_t* const mask = &l.masks[(size_t)(tile / 2 * l.K)];
+    const uint32_t mine = tile & 1 ? ~l.half : l.half;
+    int step = 0;
+    for (int seg = 0; seg < l.nseg; ++seg) {
+        const int k_lo = seg * SEGMENT_ROWS, rows = l.rows_of(seg), count = l.steps[(size_t)(tile * l.nseg + seg)];
+        const int base = of_weight ? k_lo : 0;
+        arrange_for_lds_banks(mask + k_lo, mine, rows, count, [&](int k, int slot, int row) {
+            const int t = slot & (STEP_K - 1), s = step + slot / STEP_K;
+            if (k >= 0) place[k_lo + k] = (int32_t)(s * val_stride + (t & ~15) * 16 + (t & 15));     // of row 0; row r is 16 r bytes on
+            // 8 g + t % 8 of the pairs, low half for slot 16 g + t % 8 and high half for 8 more
+            const uint16_t at = (uint16_t)(base + row);
+            std::memcpy(idx + s * idx_stride + 4 * (8 * (t >> 4) + (t & 7)) + 2 * (t >> 3 & 1), &at, 2);
+        });
+        for (int s = 0; s < count; ++s, ++step) std::memset(vals + step * val_stride, 0, STEP_VAL_BYTES);
+    }
+    const int units = l.units / 2;
+    for (int q = 0; q < units && tile * units + q < b.block_rows; ++q) {
+        const int64_t br = tile * units + q;
+        for (int64_t e = b.row_ptr[(size_t)br]; e < b.row_ptr[(size_t)br + 1]; ++e) {
+            uint32_t v;
+            std::memcpy(&v, &b.vals[(size_t)e * 4], 4);
+            const int32_t at = b.index[(size_t)e];
+            if (l.n4) {
+                uint8_t* const to = vals + place[at] + 4 * q * 16;
+                for (int j = 0; j < 4; ++j) to[16 * j] = (uint8_t)(v >> (8 * j));
+            } else {
+                for (int j = 0; j < 4; ++j)
+                    if (v >> (8 * j) & 0xff) vals[place[at * 4 + j] + q * 16] = (uint8_t)(v >> (8 * j));
             }
         }
-    });
-    out.seg_ptr.assign((size_t)out.ntiles * nseg + 1, 0);
-    for (int64_t tile = 0; tile < out.ntiles; ++tile) {
+    }
+}
+
+// dimensions and bounds of the row tiles
+void layout_dims(const Lists& l, HostLayout& out)
+{
+    out.kc = SEGMENT_ROWS;
+    out.nseg = l.nseg;
+    out.ntiles = l.ntiles;
+    out.max_steps_per_tile = 0;
+    out.max_steps_per_segment = 0;
+    out.seg_ptr.assign((size_t)l.ntiles * l.nseg + 1, 0);
+    for (int64_t tile = 0; tile < l.ntiles; ++tile) {
         int steps_this_tile = 0;
-        for (int seg = 0; seg < nseg; ++seg) {
-            const size_t i = (size_t)(tile * nseg + seg);
-            steps_this_tile += steps[i];
-            out.max_steps_per_segment = std::max(out.max_steps_per_segment, steps[i]);
-            out.seg_ptr[i + 1] = out.seg_ptr[i] + steps[i];
+        for (int seg = 0; seg < l.nseg; ++seg) {
+            const size_t i = (size_t)(tile * l.nseg + seg);
+            steps_this_tile += l.steps[i];
+            out.max_steps_per_segment = std::max(out.max_steps_per_segment, l.steps[i]);
+            out.seg_ptr[i + 1] = out.seg_ptr[i] + l.steps[i];
         }
         out.max_steps_per_tile = std::max(out.max_steps_per_tile, steps_this_tile);
     }
     out.nsteps = out.seg_ptr.back();
+}
+
+}  // namespace
+
+void layout_from_bsr(const Bsr& b, int kc, HostLayout& out)
+{
+    Team team;
+    layout_from_bsr(b, kc, out, team);
+}
+
+void layout_from_bsr(const Bsr& b, int kc, HostLayout& out, Team& team)
+{
+    (void)kc;                                               // SEGMENT_ROWS
+    out.rowsum.assign((size_t)((b.N + TILE_ROWS - 1) / TILE_ROWS) * TILE_ROWS, 0);
+    const Lists l(b, out.rowsum.data(), team);
+    layout_dims(l, out);
     out.vals.assign((size_t)out.nsteps * STEP_VAL_BYTES, 0);
     out.idx.assign((size_t)out.nsteps * STEP_IDX_DWORDS, 0);
-
-    // ---- the steps: listed k dealt to slots, every block's values scattered to their lanes
-    parallel_for(out.ntiles, grain, [&](int64_t begin, int64_t end) {
-        std::vector<int32_t> place((size_t)K);              // k -> 64 * step + slot, for the k listed in this tile
-        int32_t list[SEGMENT_ROWS], slot_k[SEGMENT_ROWS], slot_row[SEGMENT_ROWS];
-        for (int64_t tile = begin; tile < end; ++tile) {
-            for (int seg = 0; seg < nseg; ++seg) {
-                const size_t i = (size_t)(tile * nseg + seg);
-                const int k_lo = seg * kc, rows = (int)std::min<int64_t>(kc, K - k_lo);
-                int n = 0;
-                for (int w = 0; w < seg_words; ++w)
-                    for (uint64_t m = listed[i * seg_words + w]; m; m &= m - 1) list[n++] = 64 * w + __builtin_ctzll(m);
-                arrange_for_lds_banks(list, n, rows, steps[i], slot_k, slot_row);
-                for (int s = 0; s < steps[i]; ++s) {
-                    const int32_t* sk = slot_k + s * STEP_K;     // segment-local k, -1 = padding
-                    const int32_t* sr = slot_row + s * STEP_K;   // activation row the slot reads
-                    const int32_t step = out.seg_ptr[i] + s;
-                    for (int t = 0; t < STEP_K; ++t)
-                        if (sk[t] >= 0) place[(size_t)(k_lo + sk[t])] = (s + out.seg_ptr[i] - out.seg_ptr[(size_t)(tile * nseg)]) * STEP_K + t;
-                    uint32_t* const ix = &out.idx[(size_t)step * STEP_IDX_DWORDS];
-                    for (int g = 0; g < 4; ++g)
-                        for (int t = 0; t < 8; ++t) ix[8 * g + t] = (uint32_t)sr[16 * g + t] | ((uint32_t)sr[16 * g + 8 + t] << 16);
-                }
-            }
-            if (out.seg_ptr[(size_t)(tile * nseg)] == out.seg_ptr[(size_t)((tile + 1) * nseg)]) continue;
-            // vals[step][lane = 16 g + row][t] of slot 16 g + t
-            uint8_t* const vals = &out.vals[(size_t)out.seg_ptr[(size_t)(tile * nseg)] * STEP_VAL_BYTES];
-            auto lane_bytes = [&](int32_t k) {              // of row 0; row r is 16 r bytes on
-                const int32_t p = place[(size_t)k], slot = p & (STEP_K - 1);
-                return vals + (size_t)(p / STEP_K) * STEP_VAL_BYTES + (size_t)(slot & ~15) * 16 + (slot & 15);
-            };
-            for (int q = 0; q < units && tile * units + q < b.block_rows; ++q) {
-                const int64_t br = tile * units + q;
-                for (int64_t e = b.row_ptr[(size_t)br]; e < b.row_ptr[(size_t)br + 1]; ++e) {
-                    uint32_t v;
-                    std::memcpy(&v, &b.vals[(size_t)e * 4], 4);
-                    const int32_t at = b.index[(size_t)e];
-                    if (n4) {
-                        uint8_t* const to = lane_bytes(at) + 4 * q * 16;
-                        for (int j = 0; j < 4; ++j) to[16 * j] = (uint8_t)(v >> (8 * j));
-                    } else {
-                        for (int j = 0; j < 4; ++j)
-                            if (v >> (8 * j) & 0xff) *(lane_bytes(at * 4 + j) + q * 16) = (uint8_t)(v >> (8 * j));
-                    }
-                }
-            }
+    team.finish(l.ntiles, 2 * l.grain, [&](int64_t begin, int64_t end) {
+        const std::unique_ptr<int32_t[]> place(new int32_t[(size_t)l.K]);
+        for (int64_t t = begin; t < end; ++t) {
+            const size_t first = (size_t)out.seg_ptr[(size_t)(t * l.nseg)];
+            arrange_tile(l, t, out.vals.data() + first * STEP_VAL_BYTES, STEP_VAL_BYTES, (uint8_t*)(out.idx.data() + first * STEP_IDX_DWORDS),
+                         4 * STEP_IDX_DWORDS, false, place.get());
         }
     });
 }
 
-void device_form(const HostLayout& hl, int tile_steps, int64_t records, uint8_t* out)
+void export_steps(const HostLayout& hl, const DeviceForms& f, uint8_t* vals, uint32_t* idx)
 {
-    const int64_t nt = hl.ntiles, ns = hl.nseg, at = records_offset(nt, ns);
-    std::memset(out, 0, (size_t)at);
-    std::memcpy(out, hl.rowsum.data(), hl.rowsum.size() * 4);
-    int32_t* const bounds = (int32_t*)(out + bounds_offset(nt));
-    uint8_t* const rec = out + at;
-    if (nt * tile_steps == 0 && hl.nsteps == 0) std::memset(rec, 0, (size_t)records * RECORD_BYTES);
-    parallel_for(nt, std::max<int64_t>(1, 262144 / std::max<int64_t>(1, records * RECORD_BYTES / nt)), [&](int64_t begin, int64_t end) {
-        for (int64_t t = begin; t < end; ++t) {
-            const int64_t first = hl.seg_ptr[(size_t)(t * ns)], past = hl.seg_ptr[(size_t)((t + 1) * ns)];
-            const int64_t shift = tile_steps ? t * tile_steps - first : 0;
-            for (int64_t g = 0; g <= ns; ++g) bounds[t * (ns + 1) + g] = (int32_t)(hl.seg_ptr[(size_t)(t * ns + g)] + shift);
-            for (int64_t g = 0; g < ns; ++g) {
-                const uint32_t base = (uint32_t)(g * SEGMENT_ROWS) * 0x10001u;      // the rows of the whole weight
-                for (int64_t s = hl.seg_ptr[(size_t)(t * ns + g)]; s < hl.seg_ptr[(size_t)(t * ns + g + 1)]; ++s) {
-                    uint8_t* const r = rec + (s + shift) * RECORD_BYTES;
-                    std::memcpy(r, &hl.vals[(size_t)s * STEP_VAL_BYTES], STEP_VAL_BYTES);
-                    for (int i = 0; i < STEP_IDX_DWORDS; ++i) {
-                        const uint32_t v = hl.idx[(size_t)s * STEP_IDX_DWORDS + i] + base;
-                        std::memcpy(r + STEP_VAL_BYTES + 4 * i, &v, 4);
-                    }
-                }
+    const int64_t ns = hl.nseg;
+    const uint8_t* const rec = f.bytes.get() + records_offset(hl.ntiles, ns);
+    for (int64_t t = 0; t < hl.ntiles; ++t) {
+        const int64_t shift = f.tile_steps ? t * f.tile_steps - hl.seg_ptr[(size_t)(t * ns)] : 0;
+        for (int64_t g = 0; g < ns; ++g)
+            for (int64_t s = hl.seg_ptr[(size_t)(t * ns + g)]; s < hl.seg_ptr[(size_t)(t * ns + g + 1)]; ++s) {
+                const uint8_t* const r = rec + (s + shift) * RECORD_BYTES;
+                if (vals) std::memcpy(vals + s * STEP_VAL_BYTES, r, STEP_VAL_BYTES);
+                if (!idx) continue;
+                std::memcpy(idx + s * STEP_IDX_DWORDS, r + STEP_VAL_BYTES, 4 * STEP_IDX_DWORDS);
+                for (int i = 0; i < STEP_IDX_DWORDS; ++i) idx[s * STEP_IDX_DWORDS + i] -= (uint32_t)(g * SEGMENT_ROWS) * 0x10001u;
             }
-            if (tile_steps) std::memset(rec + (past + shift) * RECORD_BYTES, 0, (size_t)(tile_steps - (past - first)) * RECORD_BYTES);
-        }
-    });
+    }
 }
 
 // ---------------------------------------------------------------------------------------
@@ -521,43 +531,78 @@ void device_form(const HostLayout& hl, int tile_steps, int64_t records, uint8_t*
 // ---------------------------------------------------------------------------------------
 namespace {
 
+inline int set_bits(uint32_t v)
+{
+    v -= v >> 1 & 0x55555555u;
+    v = (v & 0x33333333u) + (v >> 2 & 0x33333333u);
+    return (int)(((v + (v >> 4)) & 0x0f0f0f0fu) * 0x01010101u >> 24);
+}
+
+// bit 8 i + j to bit 8 j + i
+inline uint64_t transposed8x8(uint64_t x)
+{
+    uint64_t t = (x ^ x >> 7) & 0x00aa00aa00aa00aaull;
+    x ^= t ^ t << 7;
+    t = (x ^ x >> 14) & 0x0000cccc0000ccccull;
+    x ^= t ^ t << 14;
+    t = (x ^ x >> 28) & 0x00000000f0f0f0f0ull;
+    return x ^ t ^ t << 28;
+}
+
 struct WideSegment {
     int32_t slot[WIDE_MAX_STEPS * STEP_K];      // segment-local k, -1: padding
     int steps;
 };
 
 // false: more than WIDE_MAX_STEPS
-bool arrange_wide(const uint32_t* mask, int rows, WideSegment& out)
+bool arrange_wide(const uint32_t* mask, int rows, int units, WideSegment& out)
 {
     constexpr int CLASSES = 8, MAX_QUADS = WIDE_MAX_STEPS * STEP_K / 4;
     // candidates of every class, heaviest first, and for every unit which of them it uses
-    int32_t cand[CLASSES][SEGMENT_ROWS / CLASSES];
+    int16_t cand[CLASSES][SEGMENT_ROWS / CLASSES + 1];
+    uint32_t users[CLASSES][SEGMENT_ROWS / CLASSES + 1];
     uint64_t alive[CLASSES], uses[CLASSES][32];
-    std::memset(uses, 0, sizeof(uses));
+    int16_t start[CLASSES][34] = {{0}};
+    uint8_t bucket[SEGMENT_ROWS];
+    for (int k = 0; k < rows; ++k) ++start[k % CLASSES][bucket[k] = (uint8_t)(33 - set_bits(mask[k]))];
     int n = 0;
     for (int c = 0; c < CLASSES; ++c) {
-        uint8_t weight[SEGMENT_ROWS / CLASSES];
-        int start[34] = {0}, m = 0;
-        for (int k = c, i = 0; k < rows; k += CLASSES, ++i) {
-            weight[i] = (uint8_t)__builtin_popcount(mask[k]);
-            if (weight[i]) { ++start[32 - weight[i] + 1]; ++m; }
+        int at = 0;
+        for (int w = 0; w < 33; ++w) {
+            const int count = start[c][w + 1];
+            start[c][w + 1] = (int16_t)at;
+            at += count;
+            if (w == 31) {                              // (w = 32: those that none uses, after all others)
+                alive[c] = at == 64 ? ~(uint64_t)0 : ((uint64_t)1 << at) - 1;
+                n += at;
+            }
         }
-        for (int w = 1; w < 34; ++w) start[w] += start[w - 1];
-        for (int k = c, i = 0; k < rows; k += CLASSES, ++i) {
-            if (!weight[i]) continue;
-            const int at = start[32 - weight[i]]++;
-            cand[c][at] = k;
-            for (uint32_t u = mask[k]; u; u &= u - 1) uses[c][__builtin_ctz(u)] |= (uint64_t)1 << at;
+    }
+    for (int k = 0; k < rows; ++k) {
+        const int c = k % CLASSES, at = start[c][bucket[k]]++;
+        cand[c][at] = (int16_t)k;
+        users[c][at] = mask[k];
+    }
+    for (int c = 0; c < CLASSES; ++c) {
+        const int m = (rows - c + CLASSES - 1) / CLASSES;
+        for (int i = m; i < SEGMENT_ROWS / CLASSES; ++i) users[c][i] = 0;
+        for (int u0 = 0; u0 < units; u0 += 8) {
+            uint64_t of[8] = {0};
+            for (int i = 0; i < m; i += 8) {
+                uint64_t block = 0;                     // byte j: candidate i + j, bit u: unit u0 + u; and the other way round
+                for (int j = 0; j < 8; ++j) block |= (uint64_t)(users[c][i + j] >> u0 & 0xff) << (8 * j);
+                block = transposed8x8(block);
+                for (int u = 0; u < 8; ++u) of[u] |= (block >> (8 * u) & 0xff) << i;
+            }
+            for (int u = 0; u < 8; ++u) uses[c][u0 + u] = of[u];
         }
-        alive[c] = m == 64 ? ~(uint64_t)0 : ((uint64_t)1 << m) - 1;
-        n += m;
     }
     out.steps = (n + STEP_K - 1) / STEP_K;
     uint32_t one[MAX_QUADS] = {0}, two[MAX_QUADS] = {0};       // units with a k, with two, in the quad
-    auto put = [&](int slot, int32_t k) {
+    auto put = [&](int slot, int32_t k, uint32_t m) {
         out.slot[slot] = k;
-        two[slot / 4] |= one[slot / 4] & mask[k];
-        one[slot / 4] |= mask[k];
+        two[slot / 4] |= one[slot / 4] & m;
+        one[slot / 4] |= m;
     };
     for (int i = 0; i < out.steps * STEP_K; ++i) out.slot[i] = -1;
     for (int o = 0; o < out.steps * 8; ++o) {
@@ -567,7 +612,7 @@ bool arrange_wide(const uint32_t* mask, int rows, WideSegment& out)
             for (uint32_t u = two[2 * o + j / 4]; u; u &= u - 1) fit &= ~uses[c][__builtin_ctz(u)];
             if (!fit) continue;
             alive[c] &= ~(fit & (0 - fit));
-            put(8 * o + j, cand[c][__builtin_ctzll(fit)]);
+            put(8 * o + j, cand[c][__builtin_ctzll(fit)], users[c][__builtin_ctzll(fit)]);
         }
     }
     // what is left over
@@ -587,7 +632,7 @@ bool arrange_wide(const uint32_t* mask, int rows, WideSegment& out)
                 if (hole_of(q) >= 0) holes[nholes++] = q;
             for (int i = 0; i < nholes && !done; ++i)
                 if (!(two[holes[i]] & m)) {
-                    put(hole_of(holes[i]), k);
+                    put(hole_of(holes[i]), k, m);
                     done = true;
                 }
             // a k of another quad into the hole, and this one into its place
@@ -603,10 +648,10 @@ bool arrange_wide(const uint32_t* mask, int rows, WideSegment& out)
                             o1 |= mask[out.slot[z]];
                         }
                     if (t1 & m) continue;
-                    put(hole_of(q), out.slot[s]);
+                    put(hole_of(q), out.slot[s], mask[out.slot[s]]);
                     one[r] = o1;
                     two[r] = t1;
-                    put(s, k);
+                    put(s, k, m);
                     done = true;
                 }
             }
@@ -624,139 +669,199 @@ bool arrange_wide(const uint32_t* mask, int rows, WideSegment& out)
 
 }  // namespace
 
+namespace {
+
 // activation row of slot z of a record, at the lanes that gather it
-static void set_row(uint8_t* record, int z, int row)
+inline void set_row(uint8_t* record, int z, int row)
 {
     uint16_t* const r = (uint16_t*)(record + WIDE_VAL_BYTES);
     const int lane = 32 * (z >> 5) + 2 * (z & 7) + (z >> 4 & 1), half = z >> 3 & 1;
     r[4 * lane + 2 + half] = r[4 * (lane + 16) + 2 + half] = (uint16_t)(32 * row);
 }
 
-bool wide_from_bsr(const Bsr& b, WideForm& out)
+// where a listed k has its values in the records of its tile: of row 0, in the first of the two stored; its slot's selector and
+// where that goes; and the units whose other stored value is in an earlier slot of the quad
+struct WidePlace {
+    uint32_t at, before;
+    uint16_t sel_word;      // 2 * step + h
+    uint8_t sel, shift;
+};
+
+// The records of a wide tile, `room` of them (the last unused ones cleared).  Its steps go to `steps`; false: in some segment
+// they are more than the list's length asks for (what was written is of no use then), or than there may be (too_dense).
+bool arrange_wide_tile(const Lists& l, int64_t t, uint8_t* rec, int64_t room, int32_t* steps, WidePlace* places, uint32_t* sels,
+                       bool& too_dense)
 {
-    const int64_t N = b.N, K = b.K;
-    const bool n4 = b.block == SPMM_BLOCK_N4K1;
-    const int units = n4 ? WIDE_ROWS / 4 : WIDE_ROWS;
-    out.nseg = (int)((K + SEGMENT_ROWS - 1) / SEGMENT_ROWS);
-    out.ntiles = (int)((N + WIDE_ROWS - 1) / WIDE_ROWS);
-    const int nseg = out.nseg;
-    const int64_t nt = out.ntiles, grain = std::max<int64_t>(1, 262144 / (K * WIDE_ROWS));
-    std::vector<int32_t> steps((size_t)(nt * nseg));
-    // of every k listed in a tile: 64 * step + slot, and the units that have a k in an earlier slot of its quad
-    struct Place { int32_t slot; uint32_t before; };
-    std::unique_ptr<Place[]> places(new Place[(size_t)(nt * K)]);
-    std::atomic<bool> fits{true};
-    parallel_for(nt, grain, [&](int64_t begin, int64_t end) {
-        std::vector<uint32_t> mask((size_t)K);
-        WideSegment seg_slots;
-        for (int64_t t = begin; t < end && fits; ++t) {
-            std::fill(mask.begin(), mask.end(), 0u);
-            for (int u = 0; u < units && t * units + u < b.block_rows; ++u) {
-                const int64_t br = t * units + u;
-                for (int64_t e = b.row_ptr[(size_t)br]; e < b.row_ptr[(size_t)br + 1]; ++e) {
-                    if (n4) {
-                        mask[(size_t)b.index[(size_t)e]] |= 1u << u;
-                    } else {
-                        for (int j = 0; j < 4; ++j)
-                            if (b.vals[(size_t)e * 4 + j]) mask[(size_t)b.index[(size_t)e] * 4 + j] |= 1u << u;
-                    }
+    const Bsr& b = l.b;
+    const uint32_t* const mask = &l.masks[(size_t)(t * l.K)];
+    WideSegment slots;
+    int first = 0;
+    bool as_expected = true;
+    for (int seg = 0; seg < l.nseg; ++seg) {
+        const int rows = l.rows_of(seg);
+        const uint32_t* const m = mask + (int64_t)seg * SEGMENT_ROWS;
+        if (!arrange_wide(m, rows, l.units, slots)) {
+            too_dense = true;
+            return false;
+        }
+        as_expected = as_expected && slots.steps <= steps[seg];
+        steps[seg] = slots.steps;
+        if (!as_expected) continue;
+        for (int s = 0; s < slots.steps; ++s) {
+            uint8_t* const r = rec + (int64_t)(first + s) * WIDE_RECORD_BYTES;
+            std::memset(r, 0, WIDE_VAL_BYTES);
+            const int32_t* const slot = slots.slot + s * STEP_K;
+            for (int q = 0; q < STEP_K / 4; ++q) {
+                uint32_t before = 0;
+                for (int z = 4 * q; z < 4 * q + 4; ++z) {
+                    const int k = slot[z], pad = ((z & 7) + (z >> 3)) & 7;
+                    set_row(r, z, k >= 0 ? k : pad < rows ? pad : 0);
+                    if (k < 0) continue;
+                    const int h = z >> 4 & 1, which = 8 * (z >> 5) + 2 * (z >> 2 & 3);
+                    places[(size_t)(seg * SEGMENT_ROWS + k)] = {(uint32_t)((first + s) * WIDE_RECORD_BYTES + 32 * h * 16 + which), before,
+                                                               (uint16_t)(2 * (first + s) + h), (uint8_t)(z & 3), (uint8_t)(2 * which)};
+                    before |= m[k];
                 }
             }
-            int first = 0;
-            for (int seg = 0; seg < nseg; ++seg) {
-                const int64_t k0 = (int64_t)seg * SEGMENT_ROWS;
-                const int rows = (int)std::min<int64_t>(SEGMENT_ROWS, K - k0);
-                if (!arrange_wide(&mask[(size_t)k0], rows, seg_slots)) {
-                    fits = false;
-                    return;
-                }
-                for (int q = 0; q < seg_slots.steps * 16; ++q) {
-                    uint32_t before = 0;
-                    for (int s = 4 * q; s < 4 * q + 4; ++s)
-                        if (seg_slots.slot[s] >= 0) {
-                            places[(size_t)(t * K + k0 + seg_slots.slot[s])] = {first * STEP_K + s, before};
-                            before |= mask[(size_t)(k0 + seg_slots.slot[s])];
-                        }
-                }
-                steps[(size_t)(t * nseg + seg)] = seg_slots.steps;
-                first += seg_slots.steps;
-            }
         }
-    });
-    if (!fits) return false;
-    out.nsteps = 0;
-    out.max_steps_per_tile = out.max_steps_per_segment = 0;
-    std::vector<int64_t> first((size_t)nt + 1, 0);
-    for (int64_t t = 0; t < nt; ++t) {
-        int all = 0;
-        for (int seg = 0; seg < nseg; ++seg) {
-            all += steps[(size_t)(t * nseg + seg)];
-            out.max_steps_per_segment = std::max(out.max_steps_per_segment, steps[(size_t)(t * nseg + seg)]);
-        }
-        out.max_steps_per_tile = std::max(out.max_steps_per_tile, all);
-        first[(size_t)t + 1] = first[(size_t)t] + all;
+        first += slots.steps;
     }
-    out.nsteps = first[(size_t)nt];
-    const bool strided = nt * out.max_steps_per_tile <= out.nsteps + out.nsteps / 2;
-    out.tile_steps = strided ? out.max_steps_per_tile : 0;
-    const int64_t records = std::max<int64_t>(1, strided ? nt * out.tile_steps : out.nsteps), at = wide_records_offset(nt, nseg);
-    out.size = at + records * WIDE_RECORD_BYTES;
-    out.bytes.reset(new uint8_t[(size_t)out.size]);
-    std::memset(out.bytes.get(), 0, (size_t)at);
-    int32_t* const rowsum = (int32_t*)out.bytes.get();
-    int32_t* const bounds = (int32_t*)(out.bytes.get() + wide_bounds_offset(nt));
-    uint8_t* const rec = out.bytes.get() + at;
-    if (out.nsteps == 0) std::memset(rec, 0, (size_t)(records * WIDE_RECORD_BYTES));
-    parallel_for(nt, grain, [&](int64_t begin, int64_t end) {
-        for (int64_t t = begin; t < end; ++t) {
-            const int64_t base = out.tile_steps ? t * out.tile_steps : first[(size_t)t];
-            const int64_t count = first[(size_t)t + 1] - first[(size_t)t], room = out.tile_steps ? out.tile_steps : count;
-            uint8_t* const mine = rec + base * WIDE_RECORD_BYTES;
-            std::memset(mine, 0, (size_t)(room * WIDE_RECORD_BYTES));
-            bounds[t * (nseg + 1)] = (int32_t)base;
-            for (int seg = 0; seg < nseg; ++seg) bounds[t * (nseg + 1) + seg + 1] = bounds[t * (nseg + 1) + seg] + steps[(size_t)(t * nseg + seg)];
-            // rows of padding slots: the residue that the octet lacks (see above)
-            for (int seg = 0, s = 0; seg < nseg; ++seg) {
-                const int rows = (int)std::min<int64_t>(SEGMENT_ROWS, K - (int64_t)seg * SEGMENT_ROWS);
-                for (int i = 0; i < steps[(size_t)(t * nseg + seg)]; ++i, ++s) {
-                    uint8_t* const r = mine + (int64_t)s * WIDE_RECORD_BYTES;
-                    for (int z = 0; z < STEP_K; ++z) {
-                        const int row = ((z & 7) + (z >> 3)) & 7;
-                        set_row(r, z, row < rows ? row : 0);
-                    }
-                }
-            }
-            int32_t* const sum = rowsum + t * WIDE_ROWS;
-            auto add = [&](const int64_t k, const int u, const int row, const int rows, const uint32_t v) {
-                const Place& p = places[(size_t)(t * K + k)];
-                const int z = p.slot & (STEP_K - 1), h = z >> 4 & 1, which = 8 * (z >> 5) + 2 * (z >> 2 & 3) + (int)(p.before >> u & 1);
-                uint8_t* const r = mine + (int64_t)(p.slot / STEP_K) * WIDE_RECORD_BYTES;
-                uint8_t* const val = r + (32 * h + row) * 16 + which;
-                uint32_t* const sel = (uint32_t*)(r + WIDE_VAL_BYTES) + 2 * (32 * h + row);
-                for (int i = 0; i < rows; ++i) {
-                    val[16 * i] = (uint8_t)(v >> (8 * i));
-                    sel[2 * i] |= (uint32_t)(z & 3) << (2 * which);
-                    sum[row + i] += (int8_t)(v >> (8 * i));
-                }
-                set_row(r, z, (int)(k & (SEGMENT_ROWS - 1)));
-            };
-            for (int u = 0; u < units && t * units + u < b.block_rows; ++u) {
-                const int64_t br = t * units + u;
-                for (int64_t e = b.row_ptr[(size_t)br]; e < b.row_ptr[(size_t)br + 1]; ++e) {
-                    uint32_t v;
-                    std::memcpy(&v, &b.vals[(size_t)e * 4], 4);
-                    const int64_t k = b.index[(size_t)e];
-                    if (n4) {
-                        add(k, u, 4 * u, 4, v);
-                    } else {
-                        for (int j = 0; j < 4; ++j)
-                            if (v >> (8 * j) & 0xff) add(4 * k + j, u, u, 1, v >> (8 * j) & 0xff);
-                    }
-                }
+    if (!as_expected) return false;
+    const int units = l.units, rows_of_unit = WIDE_ROWS / units;
+    std::memset(sels, 0, (size_t)(2 * first * units) * 4);
+    auto add = [&](const WidePlace& p, const int u, const int row, const int rows, const uint32_t v) {
+        const uint32_t second = p.before >> u & 1;
+        uint8_t* const to = rec + p.at + second + 16 * row;
+        for (int i = 0; i < rows; ++i) to[16 * i] = (uint8_t)(v >> (8 * i));
+        sels[(size_t)(p.sel_word * units + u)] |= (uint32_t)p.sel << (p.shift + 2 * second);
+    };
+    for (int u = 0; u < units && t * units + u < b.block_rows; ++u) {
+        const int64_t br = t * units + u;
+        for (int64_t e = b.row_ptr[(size_t)br]; e < b.row_ptr[(size_t)br + 1]; ++e) {
+            uint32_t v;
+            std::memcpy(&v, &b.vals[(size_t)e * 4], 4);
+            const int64_t k = b.index[(size_t)e];
+            if (l.n4) {
+                add(places[(size_t)k], u, 4 * u, 4, v);
+            } else {
+                for (int j = 0; j < 4; ++j)
+                    if (v >> (8 * j) & 0xff) add(places[(size_t)(4 * k + j)], u, u, 1, v >> (8 * j) & 0xff);
             }
         }
-    });
+    }
+    for (int s = 0; s < first; ++s) {
+        uint8_t* const to = rec + (int64_t)s * WIDE_RECORD_BYTES + WIDE_VAL_BYTES;
+        for (int h = 0; h < 2; ++h)
+            for (int row = 0; row < WIDE_ROWS; ++row) std::memcpy(to + 8 * (32 * h + row), &sels[(size_t)((2 * s + h) * units + row / rows_of_unit)], 4);
+    }
+    std::memset(rec + (int64_t)first * WIDE_RECORD_BYTES, 0, (size_t)((room - first) * WIDE_RECORD_BYTES));
     return true;
+}
+
+// what the steps of every (wide tile, segment) come to
+struct WideDims {
+    std::vector<int64_t> first;     // record of every tile
+    int64_t records = 0;
+    explicit WideDims(const Lists& l, const std::vector<int32_t>& steps, DeviceForms& f) : first((size_t)l.nt + 1, 0)
+    {
+        f.wide_max_steps = 0;
+        int most = 0;
+        for (int64_t t = 0; t < l.nt; ++t) {
+            int all = 0;
+            for (int seg = 0; seg < l.nseg; ++seg) {
+                all += steps[(size_t)(t * l.nseg + seg)];
+                f.wide_max_steps = std::max(f.wide_max_steps, steps[(size_t)(t * l.nseg + seg)]);
+            }
+            most = std::max(most, all);
+            first[(size_t)t + 1] = first[(size_t)t] + all;
+        }
+        f.wide_max_steps = std::max(1, f.wide_max_steps);
+        f.wide_nsteps = first.back();
+        f.wide_tile_steps = l.nt * most <= f.wide_nsteps + f.wide_nsteps / 2 ? most : 0;
+        if (f.wide_tile_steps)
+            for (int64_t t = 0; t <= l.nt; ++t) first[(size_t)t] = t * most;
+        records = std::max<int64_t>(1, first.back());
+        f.wide_size = wide_records_offset(l.nt, l.nseg) + records * WIDE_RECORD_BYTES;
+    }
+};
+
+}  // namespace
+
+void forms_from_bsr(const Bsr& b, HostLayout& hl, DeviceForms& f, Team& team, const std::function<void()>& first_form)
+{
+    hl.rowsum.assign((size_t)((b.N + TILE_ROWS - 1) / TILE_ROWS) * TILE_ROWS, 0);
+    Lists l(b, hl.rowsum.data(), team);
+    layout_dims(l, hl);
+    const int64_t nt16 = l.ntiles, ns = l.nseg;
+    f.tile_steps = nt16 * hl.max_steps_per_tile <= hl.nsteps + hl.nsteps / 2 ? hl.max_steps_per_tile : 0;
+    const int64_t records = std::max<int64_t>(1, f.tile_steps ? nt16 * f.tile_steps : hl.nsteps);
+    f.size = (records_offset(nt16, ns) + records * RECORD_BYTES + 127) & ~(int64_t)127;
+    WideDims dims(l, l.wide_steps, f);
+    f.together = f.size + f.wide_size <= 256 * 1024;
+    f.bytes.reset(new uint8_t[(size_t)(f.size + (f.together ? f.wide_size : 0))]);
+    if (!f.together) f.wide.reset(new uint8_t[(size_t)f.wide_size]);
+
+    auto narrow_tile = [&](int64_t t, int32_t* place) {
+        uint8_t* const rec = f.bytes.get() + records_offset(nt16, ns);
+        int32_t* const bounds = (int32_t*)(f.bytes.get() + bounds_offset(nt16)) + t * (ns + 1);
+        const int64_t first = hl.seg_ptr[(size_t)(t * ns)], at = f.tile_steps ? t * f.tile_steps : first;
+        for (int64_t g = 0; g <= ns; ++g) bounds[g] = (int32_t)(hl.seg_ptr[(size_t)(t * ns + g)] - first + at);
+        uint8_t* const to = rec + at * RECORD_BYTES;
+        arrange_tile(l, t, to, RECORD_BYTES, to + STEP_VAL_BYTES, RECORD_BYTES, true, place);
+        const int64_t used = hl.seg_ptr[(size_t)((t + 1) * ns)] - first, room = f.tile_steps ? f.tile_steps : used;
+        std::memset(to + used * RECORD_BYTES, 0, (size_t)((room - used) * RECORD_BYTES));
+    };
+    std::atomic<bool> too_dense{false}, longer{false};
+    auto wide_tile = [&](int64_t t, WidePlace* places, uint32_t* sels) {
+        uint8_t* const form = f.wide_bytes();
+        int32_t* const steps = &l.wide_steps[(size_t)(t * ns)];
+        bool dense = false;
+        if (!arrange_wide_tile(l, t, form + wide_records_offset(l.nt, ns) + dims.first[(size_t)t] * WIDE_RECORD_BYTES,
+                               dims.first[(size_t)t + 1] - dims.first[(size_t)t], steps, places, sels, dense)) {
+            if (dense) too_dense = true;
+            else longer = true;
+            return;
+        }
+        int32_t* const bounds = (int32_t*)(form + wide_bounds_offset(l.nt)) + t * (ns + 1);
+        bounds[0] = (int32_t)dims.first[(size_t)t];
+        for (int64_t g = 0; g < ns; ++g) bounds[g + 1] = bounds[g] + steps[g];
+    };
+    team.run(nt16, 2 * l.grain, [&](int64_t begin, int64_t end) {
+        const std::unique_ptr<int32_t[]> place(new int32_t[(size_t)l.K]);
+        for (int64_t t = begin; t < end; ++t) narrow_tile(t, place.get());
+    });
+    // row sums, and what is between the bounds and the records
+    const size_t sums = hl.rowsum.size() * 4, narrow_end = (size_t)(bounds_offset(nt16) + nt16 * (ns + 1) * 4);
+    std::memcpy(f.bytes.get(), hl.rowsum.data(), sums);
+    std::memset(f.bytes.get() + narrow_end, 0, (size_t)records_offset(nt16, ns) - narrow_end);
+    if (!hl.nsteps) std::memset(f.bytes.get() + records_offset(nt16, ns), 0, RECORD_BYTES);
+
+    auto wide_tiles = [&](int64_t begin, int64_t end) {
+        const std::unique_ptr<WidePlace[]> places(new WidePlace[(size_t)l.K]);
+        const std::unique_ptr<uint32_t[]> sels(new uint32_t[(size_t)(2 * ns * WIDE_MAX_STEPS * l.units)]);
+        for (int64_t t = begin; t < end && !too_dense; ++t) wide_tile(t, places.get(), sels.get());
+    };
+    team.finish(l.nt, l.grain, wide_tiles, first_form);
+    // (lists that two of a quad lengthen, 1x4 blocks at 75 % for instance: again, now that their steps are known)
+    if (longer && !too_dense) {
+        dims = WideDims(l, l.wide_steps, f);
+        f.wide.reset(new uint8_t[(size_t)f.wide_size]);
+        f.together = false;
+        Team again;
+        again.finish(l.nt, l.grain, wide_tiles);
+    }
+    if (too_dense) {
+        f.wide_size = f.wide_nsteps = 0;
+        f.wide_max_steps = f.wide_tile_steps = 0;
+        f.wide.reset();
+        return;
+    }
+    uint8_t* const form = f.wide_bytes();
+    const size_t wide_end = (size_t)(wide_bounds_offset(l.nt) + l.nt * (ns + 1) * 4);
+    std::memcpy(form, hl.rowsum.data(), sums);
+    std::memset(form + sums, 0, (size_t)wide_bounds_offset(l.nt) - sums);
+    std::memset(form + wide_end, 0, (size_t)wide_records_offset(l.nt, ns) - wide_end);
+    if (!f.wide_nsteps) std::memset(form + wide_records_offset(l.nt, ns), 0, WIDE_RECORD_BYTES);
 }
 
 }  // namespace spmm

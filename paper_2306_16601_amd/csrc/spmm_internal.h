@@ -3,7 +3,10 @@
 #pragma once
 
 #include <cstdint>
+#include <functional>
 #include <memory>
+#include <new>
+#include <utility>
 #include <vector>
 
 #include "spmm.h"
@@ -45,19 +48,34 @@ struct HostLayout {
     std::vector<int32_t> rowsum;    // ntiles * 16
 };
 
+// what resize() adds is not cleared first (it is all written next, by several threads)
+template <typename T>
+struct Unfilled : std::allocator<T> {
+    template <typename U> struct rebind { using other = Unfilled<U>; };
+    template <typename U, typename... A>
+    void construct(U* p, A&&... a)
+    {
+        if constexpr (sizeof...(A) == 0) ::new ((void*)p) U;
+        else ::new ((void*)p) U(std::forward<A>(a)...);
+    }
+};
+
 // Canonical 4x1 block-sparse-row form (host): what spmm_unpack and spmm_info read.
 struct Bsr {
     int64_t N = 0, K = 0;
     spmm_block_t block = SPMM_BLOCK_N4K1;
     int64_t block_rows = 0;             // ceil(N/4) (N4K1) or N (N1K4)
     std::vector<int64_t> row_ptr;       // block_rows + 1
-    std::vector<int32_t> index;         // k (N4K1) or K-block c (N1K4), ascending per block-row
-    std::vector<int8_t> vals;           // 4 per block
+    std::vector<int32_t, Unfilled<int32_t>> index;      // k (N4K1) or K-block c (N1K4), ascending per block-row
+    std::vector<int8_t, Unfilled<int8_t>> vals;         // 4 per block
 };
 
+class Team;     // (threads of one call, team.h)
 void bsr_from_dense(const int8_t* W, int64_t N, int64_t K, int64_t ldw, spmm_block_t block, Bsr& out);
+void bsr_from_dense(const int8_t* W, int64_t N, int64_t K, int64_t ldw, spmm_block_t block, Bsr& out, Team& team);
 void bsr_to_dense(const Bsr& b, int8_t* W, int64_t ldw);
 void layout_from_bsr(const Bsr& b, int kc, HostLayout& out);
+void layout_from_bsr(const Bsr& b, int kc, HostLayout& out, Team& team);
 // row_order[i] = row of the weight that becomes row i (a permutation of 0..N-1 that moves whole
 // block-rows), chosen so that rows with overlapping k lists share a row tile
 void order_rows_by_k_overlap(const Bsr& b, int kc, std::vector<int32_t>& row_order);
@@ -66,7 +84,7 @@ void bsr_permute_rows(const Bsr& b, const std::vector<int32_t>& row_order, Bsr& 
 // ---------------------------------------------------------------------------------------
 // Kernel launch interface (plan and dispatch in spmm_plan.hip, kernels in spmm_kernels.h).
 // ---------------------------------------------------------------------------------------
-// The packed weight on the device is one allocation (device_form in pack.cpp):
+// The packed weight on the device is one allocation (forms_from_bsr in pack.cpp):
 //     int32   rowsum[ntiles][16]
 //     int32   bounds[ntiles][nseg + 1]   first record of every segment of the tile, and one past its last
 //     (padding to 128 bytes)
@@ -81,9 +99,6 @@ constexpr int64_t records_offset(int64_t ntiles, int64_t nseg)
 {
     return (bounds_offset(ntiles) + ntiles * (nseg + 1) * 4 + 127) & ~(int64_t)127;
 }
-
-// the packed weight in that form (tile_steps as above; `records` of them, at least one)
-void device_form(const HostLayout& hl, int tile_steps, int64_t records, uint8_t* out);
 
 // The wide form, for long batches: row tiles of WIDE_ROWS = 32 rows, the same segments, steps of 64 listed k for
 // v_smfmac_i32_32x32x64_i8.  That instruction takes, of every 4 consecutive list slots, at most 2 values per row, and a
@@ -109,13 +124,20 @@ constexpr int64_t wide_records_offset(int64_t ntiles, int64_t nseg)
 // The operand of Sum, and GELU in binary32, need registers that the accumulators of the widest tiles take.
 constexpr int wide_tile(bool gelu_f32, bool sum) { return sum ? 64 : gelu_f32 ? 96 : 128; }
 
-struct WideForm {
-    int nseg = 0, ntiles = 0, tile_steps = 0, max_steps_per_tile = 0, max_steps_per_segment = 0;
-    int64_t nsteps = 0, size = 0;
-    std::unique_ptr<uint8_t[]> bytes;
+// The bytes of both device forms; a weight that is too dense for the wide one has none (wide_size = 0).  In two buffers, of
+// which the first is kept and the second given back once it is on the device; small ones in one, for one copy there.
+struct DeviceForms {
+    int tile_steps = 0, wide_tile_steps = 0, wide_max_steps = 0;
+    int64_t size = 0, wide_nsteps = 0, wide_size = 0;
+    std::unique_ptr<uint8_t[]> bytes, wide;
+    bool together = false;
+    uint8_t* wide_bytes() const { return together ? bytes.get() + size : wide.get(); }
 };
-// false: the weight has none (too dense)
-bool wide_from_bsr(const Bsr& b, WideForm& out);
+// both forms, and of the layout all but the steps, which the first form holds; first_form is called when that one is whole, and
+// the other threads work on the second meanwhile
+void forms_from_bsr(const Bsr& b, HostLayout& hl, DeviceForms& f, Team& team, const std::function<void()>& first_form);
+// those steps as HostLayout has them (either may be null)
+void export_steps(const HostLayout& hl, const DeviceForms& f, uint8_t* vals, uint32_t* idx);
 
 // What a launch passes to a kernel.  96 bytes: the runtime writes the arguments of every launch through the
 // bus, and from 128 bytes on a launch takes 3.3 us of the host instead of 2.7 us (measured; this was a plain
