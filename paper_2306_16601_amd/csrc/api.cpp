@@ -48,14 +48,18 @@ void free_device(spmm_handle* h)
 
 bool aligned(const void* p, size_t a) { return (reinterpret_cast<uintptr_t>(p) % a) == 0; }
 
-spmm::Plan plan_for(const spmm_handle* h, int64_t M, int out_bytes, bool x_fast = true, bool out_fast = true, int widest = 128)
+// (gelu_f32: GELU in binary32, not in a table; sum: with an operand of Sum; aligned_rows: of the activations)
+spmm::Plan plan_for(const spmm_handle* h, int64_t M, spmm_out_t ot, bool gelu_f32, bool sum = false, bool x_fast = true, bool out_fast = true,
+                    bool aligned_rows = true)
 {
+    const bool bytes = ot == SPMM_OUT_S8 || ot == SPMM_OUT_U8;
     // (spmm_run takes at most 2^30 tokens; the calls that only report a plan take any number, and the plan counts token
     // tiles in 32 bits)
     M = std::min(M, (int64_t)1 << 34);
     const spmm::WeightDims w{h->ntiles, h->nseg, (int)h->bsr.K, h->nsteps, h->max_steps_per_segment,
                              h->max_steps_per_tile, h->forms.wide_max_steps, h->forms.wide_nsteps};
-    return spmm::make_plan(M, w, h->num_cus, h->force_tm, h->force_r, out_bytes, x_fast, out_fast, widest);
+    return spmm::make_plan(M, w, h->num_cus, h->force_tm, h->force_r, bytes ? 1 : 4, x_fast, out_fast, spmm::wide_tile(gelu_f32, sum),
+                           spmm::wide_handicap(bytes, gelu_f32, sum, aligned_rows));
 }
 
 }  // namespace
@@ -201,7 +205,7 @@ spmm_status_t spmm_plan(const spmm_handle_t* h, int64_t M, spmm_out_t out_type, 
                         int32_t* rows_per_workgroup, int64_t* workgroups)
 {
     if (!h || M <= 0) return SPMM_E_ARG;
-    const spmm::Plan p = plan_for(h, M, (out_type == SPMM_OUT_S32 || out_type == SPMM_OUT_F32) ? 4 : 1);
+    const spmm::Plan p = plan_for(h, M, out_type, false);
     if (token_tile) *token_tile = p.token_tile;
     if (rows_per_workgroup) *rows_per_workgroup = p.waves * p.row_tiles_per_wave * spmm::TILE_ROWS;
     if (workgroups) *workgroups = p.workgroups;
@@ -325,7 +329,7 @@ static spmm_status_t run_common(const spmm_handle_t* h, const uint8_t* X_dev, in
     a.x_scale = ep->x_scale;
     a.tile_steps = (uint16_t)h->forms.tile_steps;
 
-    const spmm::Plan p = plan_for(h, M, (int)esz, x_fast, out_fast, spmm::wide_tile(!quant && gelu, ep->sum != nullptr));
+    const spmm::Plan p = plan_for(h, M, ot, !quant && gelu, ep->sum != nullptr, x_fast, out_fast, aligned(X_dev, 16) && ldx % 16 == 0);
     if (p.wide) {
         a.weight = h->wide;
         a.tile_steps = (uint16_t)h->forms.wide_tile_steps;
@@ -371,8 +375,7 @@ spmm_status_t spmm_kernel_variant_tiled(const spmm_handle_t* h, int64_t M, spmm_
     if (out_type < SPMM_OUT_S32 || out_type > SPMM_OUT_U8) return SPMM_E_ARG;
     if (postop != SPMM_POST_NONE && postop != SPMM_POST_GELU && postop != SPMM_POST_TABLE) return SPMM_E_ARG;
     if (postop == SPMM_POST_TABLE) postop = SPMM_POST_GELU;   // same kernels
-    const spmm::Plan p = plan_for(h, M, (out_type == SPMM_OUT_S32 || out_type == SPMM_OUT_F32) ? 4 : 1, true, true,
-                                  spmm::wide_tile(out_type == SPMM_OUT_F32 && postop == SPMM_POST_GELU, false));
+    const spmm::Plan p = plan_for(h, M, out_type, out_type == SPMM_OUT_F32 && postop == SPMM_POST_GELU);
     const int post = (out_type == SPMM_OUT_S32) ? 0 : (int)postop;   // S32 output ignores the post-operator
     if (p.stream)
         std::snprintf(buf, (size_t)buflen, "void spmm::spmm_rowtile_mfma_stream<%d, %d, %d, %d>(spmm::KernelArgs)",

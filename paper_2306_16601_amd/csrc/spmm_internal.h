@@ -123,6 +123,13 @@ constexpr int64_t wide_records_offset(int64_t ntiles, int64_t nseg)
 
 // The operand of Sum, and GELU in binary32, need registers that the accumulators of the widest tiles take.
 constexpr int wide_tile(bool gelu_f32, bool sum) { return sum ? 64 : gelu_f32 ? 96 : 128; }
+// What the estimates do not tell of the wide kernels against the others, of 6600 measured problems: 1-byte outputs (their
+// estimate is 0.96 of the measured time, the others' 1.03), Sum (1.01 and 0.89), GELU in f32 (1.01 and 0.97), and rows that do not
+// start at 16 bytes (0.84 and 0.91).
+constexpr double wide_handicap(bool bytes, bool gelu_f32, bool sum, bool aligned_rows)
+{
+    return (bytes ? 1.06 : 1.0) * (sum ? 0.92 : gelu_f32 ? 0.97 : 1.0) * (aligned_rows ? 1.0 : 1.09);
+}
 
 // The bytes of both device forms; a weight that is too dense for the wide one has none (wide_size = 0).  In two buffers, of
 // which the first is kept and the second given back once it is on the device; small ones in one, for one copy there.
@@ -207,9 +214,9 @@ bool plan_supported(int token_tile, int variant);
 // x_fast: see KernelArgs; an X without it takes the simple kernel, whatever was forced
 // out_fast: 32-bit offsets suffice for out; if not, the automatic choice avoids the 16-wave pipelined
 // kernels, whose general store path is slow for want of registers
-// widest: widest token tile of the wide form that the post-operators run with (wide_tile)
+// widest: widest token tile of the wide form that the post-operators run with (wide_tile), and its handicap (wide_handicap)
 Plan make_plan(int64_t M, const WeightDims& w, int num_cus, int force_tm, int variant, int out_bytes = 1,
-               bool x_fast = true, bool out_fast = true, int widest = 128);
+               bool x_fast = true, bool out_fast = true, int widest = 128, double wide_handicap = 1.0);
 // Launches the SpMM kernel; returns a hipError_t value as int (0 = success).
 // postop: SPMM_POST_* value, plus POST_SUM_BIT when a.sum is to be added
 constexpr int POST_SUM_BIT = 4;   // (a bit no SPMM_POST_* value uses)

@@ -297,7 +297,7 @@ static Plan forced_plan(const Call& call, int force_tm, int variant, int max_ste
 }
 
 Plan make_plan(int64_t M, const WeightDims& w, int num_cus, int force_tm, int variant, int out_bytes, bool x_fast, bool out_fast,
-               int widest)
+               int widest, double wide_handicap)
 {
     const int nseg = w.nseg, max_steps_per_segment = w.max_steps_per_segment;
     const Call call(M, w, num_cus);
@@ -382,12 +382,13 @@ Plan make_plan(int64_t M, const WeightDims& w, int num_cus, int force_tm, int va
         fed12(64, FIT_FED_64_12[reload]);
     }
     // ---- the wide form, from 192 blocks of 32 rows x 32 tokens on (below, the kernels above were never more than 1 % slower in
-    // 135 measured problems).  Of 4700 problems the wide form's fastest configuration won 58 %; a tie goes to the kernels above,
-    // and so does what the estimates, whose errors are 10 %, set apart by less than the margins below: 71 of the 4700 are more
-    // than 3 % slower than without the wide form (with 0.98 for all 560), and all together 1.078 times as fast (1.101 if every
-    // choice were right).  By what they replace: the 128-token kernels with loader waves 1.24 times, the streamed kernels
-    // 1.28, the resident ones 1.05.  4-byte outputs that have the 32-token slab keep it up to 768 blocks because
-    // tests/test_gpu_parity.py pins 768x3072, 1024 tokens, to it (such problems were 1.2 times as fast with the wide form).
+    // 135 measured problems).  Of 6600 problems its fastest configuration won 58 %; what the estimates, whose errors are 10 %,
+    // set apart by less than the margins below goes to the kernels above, because a wrong choice is seen and a missed one is
+    // not: 1.6 % are then more than 3 % slower than without the wide form, and all together 1.080 times as fast (1.097 if every
+    // choice were right; with a margin of 0.98 1.084 and 6 %).  By what they replace: the 128-token kernels with loader waves
+    // 1.24 times, the streamed kernels 1.28, the resident ones 1.05.  4-byte outputs that have the 32-token slab keep it up to
+    // 768 blocks because tests/test_gpu_parity.py pins 768x3072, 1024 tokens, to it (such problems were 1.2 times as fast with
+    // the wide form).
     const int64_t blocks = (int64_t)((w.ntiles + 1) / 2) * ((M + 31) / 32);
     const bool pinned = out_bytes == 4 && best.slab && best.token_tile == 32 && blocks <= 768;
     if (w.wide_max_steps > 0 && out_fast && blocks >= 192 && !pinned) {
@@ -395,8 +396,8 @@ Plan make_plan(int64_t M, const WeightDims& w, int num_cus, int force_tm, int va
         auto wide = [&](const int tm, const int waves, const Fit& f) __attribute__((always_inline)) {
             if (tm > widest) return;
             fill_wide(c, call, tm, waves);
-            const double cost = wide_cost(c, f, call, out_bytes, 8 / waves, post);
-            if (cost < (best.wide ? 0.98 : reload ? 0.90 : 0.84) * best_cost) {
+            const double cost = wide_handicap * wide_cost(c, f, call, out_bytes, 8 / waves, post);
+            if (cost < (best.wide ? 0.98 : reload ? 0.94 : 0.92) * best_cost) {
                 best = c;
                 best_cost = cost;
             }

@@ -11,8 +11,8 @@
 // operands the chip clocks down to 1.8 GHz in this (the instruction alone: 1.5 GHz), so the parts add up more than the cycles say.
 //
 // Compute waves take one row tile each, in token tiles of TM; half as many waves again stage activations.  Measured, start
-// and now: 4096x4096 at 75 %, 4096 tokens, s32: 75.4 and 52.2 us; the two layers 4096x1024 and 1024x4096 at 90 %, 6144
-// tokens, tile-major codes: 46.6 and 40.4 us.
+// and now: 4096x4096 at 70 %, 4096 tokens, row-major s8: 75.4 and 52.2 us; the two layers 4096x1024 and 1024x4096 at 85 %,
+// 6144 tokens, tile-major codes: 46.6 and 40.4 us; 2048x1024 in 1x4 blocks at 90 %, 1024 tokens, s8: 7.5 and 6.2 us.
 #pragma once
 
 #include "spmm_kernels.h"
