@@ -351,8 +351,7 @@ struct Wide {
             };
             if constexpr (TABLE) {
                 // The look-ups of two pieces are under way together: one by one, their latency behind the other waves' gathers
-                // was most of the time.  key = sat_s8(rint(y / mid_scale)) + 128: the product is clamped, scaled so that one is the
-                // smallest denormal, and 128 of those added, rounded once, half to even (128 is even): the bits are the key.
+                // was most of the time.
                 uint32_t v[2][4][4];
                 auto look_up = [&](const int i0) __attribute__((always_inline)) {
                     each<4>([&](auto Q) {
@@ -362,10 +361,7 @@ struct Wide {
                         for (int i = 0; i < 2; ++i)
 #pragma unroll
                             for (int r = 0; r < 4; ++r)
-                                if (i0 + i < PIECES) {
-                                    const float z = __builtin_amdgcn_fmed3f(y[i][r] * a.inv, -128.0f, 127.0f);
-                                    v[i][Q.value][r] = __builtin_bit_cast(uint32_t, __fmaf_rn(z, 0x1p-149f, 0x1p-142f));
-                                }
+                                if (i0 + i < PIECES) v[i][Q.value][r] = table_key<true>(y[i][r] * a.inv);
                         if constexpr (PIECES == 4) __builtin_amdgcn_sched_barrier(0);
                     });
                     __builtin_amdgcn_sched_barrier(0);
