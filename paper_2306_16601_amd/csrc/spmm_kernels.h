@@ -134,6 +134,8 @@ typedef __attribute__((address_space(3))) v2i* lds_v2i_ptr;
 struct __attribute__((packed)) v4i_any { v4i v; };
 struct __attribute__((packed)) v4f_any { v4f v; };
 struct __attribute__((packed)) u32_any { uint32_t v; };
+struct __attribute__((packed)) v2i_any { v2i v; };
+struct __attribute__((packed)) u16_any { uint16_t v; };
 __device__ __forceinline__ v4i load16_any(const void* p) { return ((const v4i_any*)p)->v; }
 
 // v, as a value the compiler knows nothing of: what is worked out from it is worked out where it stands, and not ahead
@@ -528,12 +530,35 @@ __device__ __forceinline__ bool takes_fast_stores(const Args& a)
     return (OUT == SPMM_OUT_S8 || OUT == SPMM_OUT_U8) ? a.out_fast : a.out_aligned;
 }
 
+// The first `count` of 16 bytes, 1 .. 15 of them.  (Every byte of a wave's store goes to a row of its own, 64 lines a store: one
+// by one, the last tokens of a tile took as long as a third of its multiplying.  1024x1024 at 90 %, 6143 tokens, s8: 10.4 us,
+// 6144 tokens 8.7.)
+__device__ __forceinline__ void store_cut16(uint8_t* to, v4i v, const int count)
+{
+    if (count & 8) {
+        ((v2i_any*)to)->v = (v2i){v[0], v[1]};
+        to += 8;
+        v = (v4i){v[2], v[3], 0, 0};
+    }
+    if (count & 4) {
+        ((u32_any*)to)->v = (uint32_t)v[0];
+        to += 4;
+        v[0] = v[1];
+    }
+    if (count & 2) {
+        ((u16_any*)to)->v = (uint16_t)v[0];
+        to += 2;
+        v[0] = (int)((uint32_t)v[0] >> 16);
+    }
+    if (count & 1) *to = (uint8_t)v[0];
+}
+
 // Post-operators + store for one full token tile of one wave, everything in bounds (4-byte outputs:
 // and aligned): lane (g, c) holds tokens tok0 + 16 i + 4 g + {0..3} of output row 16 * tile + c.
 // 4-byte outputs are stored straight from the accumulator layout (16 bytes per lane, 64-byte
-// runs per row); 1-byte outputs go through the LDS staging chunks.
+// runs per row); 1-byte outputs go through the LDS staging chunks, also of a tile that the end of the tokens cuts (CUT).
 // TIGHT: without a register for table_key's constants (the forms of 16 waves with 6 step slots spill one)
-template <int TM, int OUT, int POST, int OT = -1, bool TIGHT = false>
+template <int TM, int OUT, int POST, int OT = -1, bool TIGHT = false, bool CUT = false>
 __device__ __forceinline__ void finish_tile_fast(const Args& a, const v4i (&acc)[Geo<TM>::PIECES],
                                                  const float scale, const float bias, const int tile,
                                                  const int tok0, int lane, const int wave, uint8_t* lds)
@@ -597,8 +622,10 @@ __device__ __forceinline__ void finish_tile_fast(const Args& a, const v4i (&acc)
 #pragma unroll
                 for (int r = 0; r < 4; ++r) y[r] = __fmaf_rn((float)acc[i][r], scale, bias);
                 if constexpr ((POST & POST_SUM_BIT) != 0) {
-                    if (sum_row_ok) {
-                        const v4f t = ((const v4f_any*)(sp + 16 * i))->v;
+                    if (sum_row_ok && (!CUT || tok0 + 16 * i + 4 * g < a.M)) {
+                        v4f t;
+                        if constexpr (CUT) t = load_sum4<POST, true>(a, tile * TILE_ROWS + c, tok0 + 16 * i + 4 * g);
+                        else t = ((const v4f_any*)(sp + 16 * i))->v;
 #pragma unroll
                         for (int r = 0; r < 4; ++r) y[r] = y[r] + t[r];
                     }
@@ -606,8 +633,11 @@ __device__ __forceinline__ void finish_tile_fast(const Args& a, const v4i (&acc)
                 *(uint32_t*)(lds + wbase + (uint32_t)(j ^ wsw) * G::STRIDE) = quantise4<OUT, POST>(a, y, lut);
             }
             const v4i v = *(const v4i*)(lds + raddr);   // same wave: LDS operations complete in order
-            if (orow < a.N && 4 * h + rj < G::PIECES) {
-                if constexpr (OT == 1) {
+            const int left = CUT ? a.M - (tok0 + 16 * (4 * h + rj)) : 16;
+            if (orow < a.N && 4 * h + rj < G::PIECES && left > 0) {
+                if (CUT && left < 16) {
+                    store_cut16((uint8_t*)a.out + (off + half_step * h), v, left);
+                } else if constexpr (OT == 1) {
                     store16_out<SCOPE_AGENT>(rs, off, v, half_step * h);
                 } else if constexpr (OT == 0) {
                     ((v4i_any*)((uint8_t*)a.out + off + half_step * h))->v = v;
@@ -803,6 +833,8 @@ __global__ void __launch_bounds__(NW * 64) spmm_rowtile_mfma(const KernelArgs ar
         }
     };
     // ---- after the last segment of a token tile: post-operators, store, reset accumulators
+    // (16 waves with 6 step slots spill with a second copy of the staged stores)
+    constexpr bool CUT_FAST = (OUT == SPMM_OUT_S8 || OUT == SPMM_OUT_U8) && !(NW == 16 && MAXS == 6);
     auto finish = [&]() __attribute__((always_inline)) {
         if (cur.seg != a.nseg - 1) return;
         const bool fast_out = takes_fast_stores<OUT>(a);
@@ -811,6 +843,8 @@ __global__ void __launch_bounds__(NW * 64) spmm_rowtile_mfma(const KernelArgs ar
         if (have_tile) {
             if (fast_out && tok0 + TM <= a.M) {
                 finish_tile_fast<TM, OUT, POST, OTILED, NW == 16 && MAXS == 6>(a, acc, scale, bias, tile, tok0, lane, wave, lds);
+            } else if (CUT_FAST && fast_out) {
+                finish_tile_fast<TM, OUT, POST, OTILED, false, true>(a, acc, scale, bias, tile, tok0, lane, wave, lds);
             } else {
                 finish_tile_any<TM, OUT, POST, NW != 16, TIGHT, OTILED>(a, acc, scale, bias, tile, tok0, lane, lds);
             }
@@ -1060,6 +1094,10 @@ __global__ void __launch_bounds__((NW + LW) * 64) spmm_rowtile_mfma_fed(const Ke
             }
         }
     };
+    // (The forms without registers for a second copy of the staged stores do without: they spill, or, 12 waves with 6 step
+    // slots on 96 tokens, are slower for it: 2304x768 at 85 %, 1771 tokens, s8 9.6 and 9.9 us.)
+    constexpr bool CUT_FAST = (OUT == SPMM_OUT_S8 || OUT == SPMM_OUT_U8) &&
+                              (MAXS == 4 || (NW == 8 && MAXS == 6) || (TM == 64 && !(POST & POST_SUM_BIT)));
     auto finish = [&]() __attribute__((always_inline)) {        // (and steps to the next phase)
         const Phase at = cur;
         cur = after(cur);
@@ -1069,6 +1107,8 @@ __global__ void __launch_bounds__((NW + LW) * 64) spmm_rowtile_mfma_fed(const Ke
         if (have_tile) {
             if (fast_out && tok0 + TM <= a.M) {
                 finish_tile_fast<TM, OUT, POST>(a, acc, scale, bias, tile, tok0, lane, wave, lds);
+            } else if (CUT_FAST && fast_out) {
+                finish_tile_fast<TM, OUT, POST, -1, false, true>(a, acc, scale, bias, tile, tok0, lane, wave, lds);
             } else if constexpr (FULL && (POST & POST_SUM_BIT) && (OUT == SPMM_OUT_S8 || OUT == SPMM_OUT_U8)) {
                 finish_tile_any<TM, OUT, POST, false, FULL>(a, acc, scale, bias, tile, tok0, lane, lds);
             } else if (n < a.N) {

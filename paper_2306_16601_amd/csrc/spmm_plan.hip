@@ -84,7 +84,7 @@ struct Call {
     double fetched[4], fetch_us[4];     // and the time that takes at 7 TB/s
     int rank[4], split[4];              // rank[rb]: how many splits fetch less (or as much, with a smaller rb); and its inverse
     double steps;                       // of a (row tile, segment), on average
-    double wide_steps;                  // the same of the wide form
+    double wide_steps = 0.0;            // the same of the wide form (set_wide_steps)
 
     Call(int64_t tokens, const WeightDims& dims, int cus) : M(tokens), w(dims), num_cus(cus), per_xcd(cus >= 8 ? cus / 8 : 1)
     {
@@ -100,8 +100,8 @@ struct Call {
             split[rank[rb]] = rb;
         }
         steps = (double)w.nsteps / ((double)w.ntiles * w.nseg);
-        wide_steps = (double)w.wide_nsteps / ((double)((w.ntiles + 1) / 2) * w.nseg);
     }
+    void set_wide_steps() { wide_steps = (double)w.wide_nsteps / ((double)((w.ntiles + 1) / 2) * w.nseg); }
     // rounds of `n` workgroups on all CUs, or of an XCD's share on its own
     int64_t rounds(int64_t n) const { return cu_shift >= 0 ? (n + num_cus - 1) >> (cu_shift + 3) : (n + num_cus - 1) / num_cus; }
     int64_t xcd_rounds(int64_t n) const { return cu_shift >= 0 ? (n + per_xcd - 1) >> cu_shift : (n + per_xcd - 1) / per_xcd; }
@@ -300,7 +300,7 @@ Plan make_plan(int64_t M, const WeightDims& w, int num_cus, int force_tm, int va
                int widest, double wide_handicap)
 {
     const int nseg = w.nseg, max_steps_per_segment = w.max_steps_per_segment;
-    const Call call(M, w, num_cus);
+    Call call(M, w, num_cus);
     const int max_steps = max_steps_per_segment <= 4 ? 4 : (max_steps_per_segment <= 6 ? max_steps_per_segment : 8);
     const int fed_steps = max_steps == 5 ? 6 : max_steps;      // step slots of the loader-wave kernels: 4, 6 or 8
     if (!x_fast && !(force_tm && force_tm <= 64 && (variant == 101 || variant == 102))) {
@@ -391,7 +391,9 @@ Plan make_plan(int64_t M, const WeightDims& w, int num_cus, int force_tm, int va
     // the wide form).
     const int64_t blocks = (int64_t)((w.ntiles + 1) / 2) * ((M + 31) / 32);
     const bool pinned = out_bytes == 4 && best.slab && best.token_tile == 32 && blocks <= 768;
-    if (w.wide_max_steps > 0 && out_fast && blocks >= 192 && !pinned) {
+    // (nor where the others are under 5 us: of 230 such problems the choice would gain nothing, and its estimates take 0.15 us)
+    if (w.wide_max_steps > 0 && out_fast && blocks >= 192 && best_cost > 5.0 && !pinned) {
+        call.set_wide_steps();
         const double post = widest < 128 ? 1.8 : 1.0;      // (Sum, GELU in f32: of the fits with each, the closest)
         auto wide = [&](const int tm, const int waves, const Fit& f) __attribute__((always_inline)) {
             if (tm > widest) return;

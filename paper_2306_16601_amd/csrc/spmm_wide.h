@@ -290,10 +290,8 @@ struct Wide {
                 if (FULL.value || (n < a.N && m + 16 <= a.M)) {
                     if (ot) store16_out<SCOPE_AGENT>(rs, off, v);
                     else ((v4i_any*)((uint8_t*)a.out + off))->v = v;
-                } else if (n < a.N) {
-#pragma unroll
-                    for (int j = 0; j < 16; ++j)
-                        if (m + j < a.M) ((uint8_t*)a.out)[off + j] = (uint8_t)((uint32_t)v[j >> 2] >> (8 * (j & 3)));
+                } else if (n < a.N && m < a.M) {
+                    store_cut16((uint8_t*)a.out + off, v, a.M - m);
                 }
             };
             // the four rows of q (I = 4 q + r) of pieces i0 and i0 + 1
