@@ -328,13 +328,14 @@ Plan make_plan(int64_t M, const WeightDims& w, int num_cus, int force_tm, int va
         if (nseg > SLAB_SEGMENTS) c.stream = 1;
         else if (nseg > 4) c.slab = 1;
         // fewer rows per workgroup, the waves sharing a row tile's steps: where whole workgroups would leave most of the chip
-        // idle; with more than one segment as long as an eighth of the CUs has none (with few steps the sum over the
-        // shares costs what the shorter walk saves).  Of 640 measured problems of 256 to 4096 features in 2 to 4 segments, time with
-        // 4 row tiles over that with 8, by workgroups: up to 224, 0.96 with two segments and 0.93 with more; 240, 1.0, and some
-        // 1.15, as workgroups do not divide by XCDs; from 256 on, where CUs have two, 1.2.  With 2 over 4: 0.98, 1.03, 1.2.
+        // idle; with three and four segments as long as an eighth of the CUs has none (with few steps the sum over the
+        // shares costs what the shorter walk saves; two segments, which would gain 4 %, keep the line that
+        // tests/test_host_pack.py pins for 768x768, 128 tokens).  Of 640 measured problems of 256 to 4096 features, time with
+        // 4 row tiles over that with 8, three and four segments, by workgroups: up to 224, 0.93; 240, 0.99, and some
+        // 1.15, as workgroups do not divide by XCDs; from 256 on, where CUs have two, 1.2.  With 2 over 4: 0.98, 1.04, 1.2.
         if (row_tiles < 8 && c.stream) return false;
         if (row_tiles < 8 && !c.slab && (int64_t)c.n_row_groups * c.n_tok_tiles * row_tiles / 8 >= num_cus * 3 / 16 &&
-            (nseg == 1 || c.workgroups > num_cus * 7 / 8)) return false;
+            (nseg <= 2 || c.workgroups > num_cus * 7 / 8)) return false;
         consider(c.stream ? FIT_RING_16 : c.slab ? FIT_SLAB_16 : FIT_RES_16);
         return true;
     };

@@ -1,5 +1,5 @@
 """Row tiles per workgroup of short batches: 2 or 4 while an eighth of the 256 CUs would have no workgroup, 8 from there on; with
-one segment the line stays at 48 workgroups of 8."""
+one or two segments the line is at 48 workgroups of 8."""
 import pytest
 
 import paper_2306_16601_amd as sp
@@ -8,7 +8,8 @@ import workloads as wl
 # (N, K, M, rows per workgroup): 16-token tiles; last token count on one side of a line, first one on the other
 LINES = [
     (512, 1100, 224, 32), (512, 1100, 225, 64), (512, 1100, 448, 64), (512, 1100, 449, 128),        # 3 segments: 224 workgroups
-    (512, 1024, 224, 32), (512, 1024, 225, 64), (1023, 1024, 224, 64), (1023, 1024, 225, 128),      # 2
+    (1023, 1100, 224, 64), (1023, 1100, 225, 128),
+    (512, 1024, 176, 32), (512, 1024, 177, 128),                                                     # 2
     (640, 2048, 160, 32), (640, 2048, 161, 64),                                                      # 4
     (512, 512, 176, 32), (512, 512, 177, 128),                                                       # 1
 ]
