@@ -111,7 +111,10 @@ struct Wide {
         // while the other multiplies.
         unsigned* const counts = (unsigned*)(lds + COUNTS);           // [0 .. 3]: written, [4 .. 7]: multiplied
         constexpr int WRITTEN = 0, MULTIPLIED = 4;
+        // (Released on either side: written activations are in LDS, and gathers, also those requested past a segment's last step,
+        // have been read, before the count says so.)
         auto signal = [&](const int which, const int q) __attribute__((always_inline)) {
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
             __builtin_amdgcn_wave_barrier();
             if (lane == 0) __atomic_fetch_add(counts + which + (q & 3), 1u, __ATOMIC_RELAXED);
         };
@@ -178,7 +181,6 @@ struct Wide {
             for (int q = 1; q < total; ++q) {
                 if (q >= BUFFERS) wait_for(MULTIPLIED, q - BUFFERS, 0);
                 x_commit(q);
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
                 signal(WRITTEN, q);
                 if (q + 1 < total) x_issue();
             }

@@ -26,6 +26,7 @@ struct Fiber {
     dim3 tid;
     int linear = 0;
     bool done = false;
+    bool released = false;      // a release fence since this thread's last transposing read and its last count
     const char* waiting = "";
     void* stack = nullptr;
 };
@@ -93,6 +94,7 @@ v2i_t tr8(const void* p)
 {
     Wave& w = my_wave();
     const int lane = cur()->linear & 63;
+    cur()->released = false;
     w.ptr[lane] = p;
     wave_sync(w, "ds_read_tr8 (deposit)");
     const int base = lane & ~15, pp = lane & 15;
@@ -163,6 +165,18 @@ void sleep()
     cur()->waiting = "a count of arrivals";
     yield_fiber();
     cur()->waiting = "";
+}
+void released() { cur()->released = true; }
+// A count in LDS that another wave waits for: it hands memory over, so that everything before it must have been released.
+// (Nothing is out of order here: a missing fence is only seen by this check.)
+unsigned count_up(unsigned* p, unsigned v, int order)
+{
+    if (!cur()->released && order != __ATOMIC_RELEASE && order != __ATOMIC_ACQ_REL && order != __ATOMIC_SEQ_CST) {
+        fprintf(stderr, "emu: thread %d of block (%u,%u) hands LDS over without a release\n", cur()->linear, G->block.x, G->block.y);
+        _exit(87);
+    }
+    cur()->released = false;
+    return __atomic_fetch_add(p, v, __ATOMIC_SEQ_CST);
 }
 void wave_barrier() { wave_sync(my_wave(), "wave_barrier"); }
 // swap16: ret0 = [a.row0, b.row0, a.row2, b.row2], ret1 = [a.row1, b.row1, a.row3, b.row3] (rows of 16 lanes);
@@ -239,7 +253,7 @@ static void run_block(Group& g, const std::function<void()>& fn)
     for (auto& w : g.w) w.arrived = 0;
     for (int i = 0; i < g.n; ++i) {
         Fiber& f = g.f[i];
-        f.done = false;
+        f.done = f.released = false;
         f.waiting = "";
         getcontext(&f.ctx);
         f.ctx.uc_stack.ss_sp = f.stack;

@@ -54,6 +54,8 @@ void sleep();
 int dpp(int v, int control);
 int readfirstlane(int v);
 void wave_barrier();
+void released();
+unsigned count_up(unsigned* p, unsigned v, int order);
 typedef unsigned v2u_t __attribute__((ext_vector_type(2)));
 v2u_t permlane_swap(unsigned a, unsigned b, int rows);
 int readlane(int v, int lane);
@@ -75,7 +77,8 @@ void dev_free(void* p);
 #define __builtin_amdgcn_smfmac_i32_32x32x64_i8(a, b, c, sel, x, y) emu::smfmac_i8_32x32x64((a), (b), (c), (sel))
 #define __builtin_amdgcn_mov_dpp(v, control, rows, banks, bound) emu::dpp((v), (control))
 #define __builtin_amdgcn_wave_barrier() emu::wave_barrier()
-#define __builtin_amdgcn_fence(order, scope) ((void)0)
+// (what a wave read or wrote in LDS before a release fence is over when it counts up after it: see count_up)
+#define __builtin_amdgcn_fence(order, ...) ((order) == __ATOMIC_RELEASE ? emu::released() : (void)0)
 #define __builtin_amdgcn_s_sleep(n) emu::sleep()
 #define __builtin_amdgcn_sched_barrier(m) ((void)0)
 #define __builtin_amdgcn_permlane16_swap(a, b, fi, bc) emu::permlane_swap((a), (b), 16)

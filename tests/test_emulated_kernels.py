@@ -138,3 +138,30 @@ int main() { hipLaunchKernelGGL((kernel), dim3(1), dim3(128), 0, nullptr); retur
                     os.path.join(HERE, "emu", "emu.cpp"), "-lpthread", "-o", exe], check=True)
     r = subprocess.run([exe], capture_output=True, text=True, timeout=60)
     assert r.returncode == 86 and "DEADLOCK" in r.stderr, (r.returncode, r.stderr[-500:])
+
+
+@pytest.mark.parametrize("fence, rc", [("", 87), ('__builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");', 0)])
+def test_a_count_without_a_release_would_be_reported(fence, rc):
+    """The check of memory that is handed to another wave: a tiny program that reads and then counts."""
+    src = r'''
+#include <hip/hip_runtime.h>
+static uint8_t lds[512];
+static unsigned count;
+static void kernel()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    __builtin_amdgcn_ds_read_tr8_b64_v2i32(lds + 8 * threadIdx.x);
+    FENCE
+    if (threadIdx.x == 0) emu::count_up(&count, 1, __ATOMIC_RELAXED);
+}
+int main() { hipLaunchKernelGGL((kernel), dim3(1), dim3(64), 0, nullptr); return 0; }
+'''.replace("FENCE", fence)
+    build_emu.build()
+    work = os.path.join(build_emu.OUT, "selftest")
+    os.makedirs(work, exist_ok=True)
+    open(os.path.join(work, "r.cpp"), "w").write(src)
+    exe = os.path.join(work, "r")
+    subprocess.run([build_emu.CXX, "-std=c++17", "-O1", "-w", "-I", os.path.join(HERE, "emu", "include"), os.path.join(work, "r.cpp"),
+                    os.path.join(HERE, "emu", "emu.cpp"), "-lpthread", "-o", exe], check=True)
+    r = subprocess.run([exe], capture_output=True, text=True, timeout=60)
+    assert r.returncode == rc and ("without a release" in r.stderr) == (rc != 0), (r.returncode, r.stderr[-500:])
