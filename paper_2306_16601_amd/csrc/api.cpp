@@ -32,18 +32,53 @@ struct spmm_handle {
 
 namespace {
 
-hipError_t upload(uint8_t** to, const uint8_t* from, int64_t bytes)
+void free_device(uint8_t** p)
 {
-    const hipError_t e = hipMalloc((void**)to, (size_t)bytes);
-    return e == hipSuccess ? hipMemcpy(*to, from, (size_t)bytes, hipMemcpyHostToDevice) : e;
+    if (*p) (void)hipFree(*p);
+    *p = nullptr;
 }
 
 void free_device(spmm_handle* h)
 {
-    for (uint8_t** p : {&h->d_weight, &h->d_wide}) {
-        if (*p) (void)hipFree(*p);
-        *p = nullptr;
+    free_device(&h->d_weight);
+    free_device(&h->d_wide);
+}
+
+hipError_t upload(uint8_t** to, const uint8_t* from, int64_t bytes)
+{
+    hipError_t e = hipMalloc((void**)to, (size_t)bytes);
+    if (e != hipSuccess) *to = nullptr;
+    else e = hipMemcpy(*to, from, (size_t)bytes, hipMemcpyHostToDevice);
+    if (e != hipSuccess) {
+        free_device(to);
+        (void)hipGetLastError();        // (reported by the result: the next launch is not the one that failed)
     }
+    return e;
+}
+
+// What is left of the device forms when forms_from_bsr has packed them.  A weight runs without the wide form: where there is no
+// memory for that one, the weight has only the first.
+hipError_t upload_forms(spmm_handle* h)
+{
+    spmm::DeviceForms& f = h->forms;
+    hipError_t e = hipSuccess;
+    if (f.together) {
+        e = upload(&h->d_weight, f.bytes.get(), f.size + f.wide_size);
+        if (e == hipErrorOutOfMemory) f.drop_wide();
+        else if (e == hipSuccess) h->wide = h->d_weight + f.size;
+    }
+    if (!f.together && !h->d_weight) e = upload(&h->d_weight, f.bytes.get(), f.size);
+    if (e == hipSuccess && !f.together && f.wide_size) {
+        e = upload(&h->d_wide, f.wide.get(), f.wide_size);
+        h->wide = h->d_wide;
+        if (e == hipErrorOutOfMemory) {
+            f.drop_wide();
+            e = hipSuccess;
+        }
+    }
+    f.wide.reset();
+    h->device_bytes = f.size + f.wide_size;
+    return e;
 }
 
 bool aligned(const void* p, size_t a) { return (reinterpret_cast<uintptr_t>(p) % a) == 0; }
@@ -97,15 +132,7 @@ static spmm_status_t pack_common(const int8_t* W_host, int64_t N, int64_t K, int
             spmm::forms_from_bsr(ordered, h->hl, f, team, [&] {
                 if (e == hipSuccess && !f.together) e = upload(&h->d_weight, f.bytes.get(), f.size);
             });
-            // (a form that did not fit where it was meant to be has a buffer of its own after all)
-            if (e == hipSuccess && !h->d_weight) e = upload(&h->d_weight, f.bytes.get(), f.size + (f.together ? f.wide_size : 0));
-            if (e == hipSuccess && f.together) h->wide = h->d_weight + f.size;
-            if (e == hipSuccess && !f.together && f.wide_size) {
-                e = upload(&h->d_wide, f.wide.get(), f.wide_size);
-                h->wide = h->d_wide;
-            }
-            f.wide.reset();
-            h->device_bytes = f.size + f.wide_size;
+            if (e == hipSuccess) e = upload_forms(h);
             h->on_device = true;
         } else {
             spmm::layout_from_bsr(ordered, spmm::SEGMENT_ROWS, h->hl, team);

@@ -799,7 +799,16 @@ void forms_from_bsr(const Bsr& b, HostLayout& hl, DeviceForms& f, Team& team, co
     WideDims dims(l, l.wide_steps, f);
     f.together = f.size + f.wide_size <= 256 * 1024;
     f.bytes.reset(new uint8_t[(size_t)(f.size + (f.together ? f.wide_size : 0))]);
-    if (!f.together) f.wide.reset(new uint8_t[(size_t)f.wide_size]);
+    // The wide form is not needed to run the weight: without memory for it there is none.
+    std::atomic<bool> none{false}, longer{false};
+    auto wide_memory = [&](const auto& get) {
+        try {
+            get();
+        } catch (const std::bad_alloc&) {
+            none = true;
+        }
+    };
+    if (!f.together) wide_memory([&] { f.wide.reset(new uint8_t[(size_t)f.wide_size]); });
 
     auto narrow_tile = [&](int64_t t, int32_t* place) {
         uint8_t* const rec = f.bytes.get() + records_offset(nt16, ns);
@@ -811,14 +820,13 @@ void forms_from_bsr(const Bsr& b, HostLayout& hl, DeviceForms& f, Team& team, co
         const int64_t used = hl.seg_ptr[(size_t)((t + 1) * ns)] - first, room = f.tile_steps ? f.tile_steps : used;
         std::memset(to + used * RECORD_BYTES, 0, (size_t)((room - used) * RECORD_BYTES));
     };
-    std::atomic<bool> too_dense{false}, longer{false};
     auto wide_tile = [&](int64_t t, WidePlace* places, uint32_t* sels) {
         uint8_t* const form = f.wide_bytes();
         int32_t* const steps = &l.wide_steps[(size_t)(t * ns)];
         bool dense = false;
         if (!arrange_wide_tile(l, t, form + wide_records_offset(l.nt, ns) + dims.first[(size_t)t] * WIDE_RECORD_BYTES,
                                dims.first[(size_t)t + 1] - dims.first[(size_t)t], steps, places, sels, dense)) {
-            if (dense) too_dense = true;
+            if (dense) none = true;
             else longer = true;
             return;
         }
@@ -837,23 +845,26 @@ void forms_from_bsr(const Bsr& b, HostLayout& hl, DeviceForms& f, Team& team, co
     if (!hl.nsteps) std::memset(f.bytes.get() + records_offset(nt16, ns), 0, RECORD_BYTES);
 
     auto wide_tiles = [&](int64_t begin, int64_t end) {
-        const std::unique_ptr<WidePlace[]> places(new WidePlace[(size_t)l.K]);
-        const std::unique_ptr<uint32_t[]> sels(new uint32_t[(size_t)(2 * ns * WIDE_MAX_STEPS * l.units)]);
-        for (int64_t t = begin; t < end && !too_dense; ++t) wide_tile(t, places.get(), sels.get());
+        std::unique_ptr<WidePlace[]> places;
+        std::unique_ptr<uint32_t[]> sels;
+        wide_memory([&] {
+            places.reset(new WidePlace[(size_t)l.K]);
+            sels.reset(new uint32_t[(size_t)(2 * ns * WIDE_MAX_STEPS * l.units)]);
+        });
+        for (int64_t t = begin; t < end && !none; ++t) wide_tile(t, places.get(), sels.get());
     };
     team.finish(l.nt, l.grain, wide_tiles, first_form);
     // (lists that two of a quad lengthen, 1x4 blocks at 75 % for instance: again, now that their steps are known)
-    if (longer && !too_dense) {
+    if (longer && !none) {
         dims = WideDims(l, l.wide_steps, f);
-        f.wide.reset(new uint8_t[(size_t)f.wide_size]);
+        f.wide.reset();
+        wide_memory([&] { f.wide.reset(new uint8_t[(size_t)f.wide_size]); });
         f.together = false;
         Team again;
         again.finish(l.nt, l.grain, wide_tiles);
     }
-    if (too_dense) {
-        f.wide_size = f.wide_nsteps = 0;
-        f.wide_max_steps = f.wide_tile_steps = 0;
-        f.wide.reset();
+    if (none) {
+        f.drop_wide();
         return;
     }
     uint8_t* const form = f.wide_bytes();

@@ -131,14 +131,22 @@ constexpr double wide_handicap(bool bytes, bool gelu_f32, bool sum, bool aligned
     return (bytes ? 1.06 : 1.0) * (sum ? 0.92 : gelu_f32 ? 0.97 : 1.0) * (aligned_rows ? 1.0 : 1.09);
 }
 
-// The bytes of both device forms; a weight that is too dense for the wide one has none (wide_size = 0).  In two buffers, of
-// which the first is kept and the second given back once it is on the device; small ones in one, for one copy there.
+// The bytes of both device forms; a weight that is too dense for the wide one, or that memory for it could not be had for, has
+// none (wide_size = 0).  In two buffers, of which the first is kept and the second given back once it is on the device; small
+// ones in one, for one copy there.
 struct DeviceForms {
     int tile_steps = 0, wide_tile_steps = 0, wide_max_steps = 0;
     int64_t size = 0, wide_nsteps = 0, wide_size = 0;
     std::unique_ptr<uint8_t[]> bytes, wide;
     bool together = false;
     uint8_t* wide_bytes() const { return together ? bytes.get() + size : wide.get(); }
+    void drop_wide()
+    {
+        wide_nsteps = wide_size = 0;
+        wide_tile_steps = wide_max_steps = 0;
+        wide.reset();
+        together = false;
+    }
 };
 // both forms, and of the layout all but the steps, which the first form holds; first_form is called when that one is whole, and
 // the other threads work on the second meanwhile

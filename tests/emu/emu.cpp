@@ -328,6 +328,8 @@ void launch(dim3 grid, dim3 block, const std::function<void()>& fn)
 static std::mutex alloc_mu;
 struct Alloc { void* base; size_t total; };
 static std::vector<std::pair<void*, Alloc>> allocs;
+unsigned failing_mallocs = 0;
+thread_local int last_error = 0;
 void* dev_alloc(size_t bytes)
 {
     const size_t page = (size_t)sysconf(_SC_PAGESIZE);
@@ -383,4 +385,6 @@ struct Install { Install() {
 // the instruction-rate measurement has no meaning on the host
 extern "C" int spmm_measure_peak(int, double*) { return 2; /* SPMM_E_UNSUPPORTED */ }
 extern "C" void* emu_alloc(size_t bytes) { return emu::dev_alloc(bytes); }
+extern "C" void emu_fail_mallocs(unsigned which) { emu::failing_mallocs = which; }
+extern "C" long emu_allocations() { return (long)emu::allocs.size(); }
 extern "C" void emu_free(void* p) { emu::dev_free(p); }

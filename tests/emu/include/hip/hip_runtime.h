@@ -62,6 +62,8 @@ int readlane(int v, int lane);
 void launch(dim3 grid, dim3 block, const std::function<void()>& fn);
 void* dev_alloc(size_t bytes);
 void dev_free(void* p);
+extern unsigned failing_mallocs;        // bit i: the i-th hipMalloc from here on finds no memory
+extern thread_local int last_error;     // as the runtime keeps it: of the last call that failed, until it is asked for
 }  // namespace emu
 
 #define threadIdx (emu::thread_idx())
@@ -141,7 +143,14 @@ static inline void emu_buffer_store(const V v, const emu_buffer_rsrc r, const in
 using std::min;
 using std::max;
 
-static inline hipError_t hipMalloc(void** p, size_t n) { *p = emu::dev_alloc(n); return *p ? hipSuccess : hipErrorOutOfMemory; }
+static inline hipError_t hipMalloc(void** p, size_t n)
+{
+    const bool fails = emu::failing_mallocs & 1;
+    emu::failing_mallocs >>= 1;
+    *p = fails ? nullptr : emu::dev_alloc(n);
+    if (!*p) emu::last_error = hipErrorOutOfMemory;
+    return *p ? hipSuccess : hipErrorOutOfMemory;
+}
 static inline hipError_t hipFree(void* p) { emu::dev_free(p); return hipSuccess; }
 static inline hipError_t hipMemset(void* p, int v, size_t n) { memset(p, v, n); return hipSuccess; }
 static inline hipError_t hipMemcpy(void* d, const void* s, size_t n, int) { memcpy(d, s, n); return hipSuccess; }
@@ -152,6 +161,11 @@ static inline hipError_t hipDeviceGetAttribute(int* v, int, int)
     *v = e ? atoi(e) : 256;
     return hipSuccess;
 }
-static inline hipError_t hipGetLastError() { return hipSuccess; }
+static inline hipError_t hipGetLastError()
+{
+    const hipError_t e = emu::last_error;
+    emu::last_error = hipSuccess;
+    return e;
+}
 #define hipLaunchKernelGGL(kernel, grid, block, shmem, stream, ...) \
     emu::launch((grid), (block), [=]() { kernel(__VA_ARGS__); })
