@@ -549,6 +549,21 @@ inline uint64_t transposed8x8(uint64_t x)
     return x ^ t ^ t << 28;
 }
 
+// bit i of words[u]: bit u of masks[i], for the first `count` of 64 masks (those up to the next multiple of 8 are read)
+inline void transposed(const uint32_t* masks, int count, int units, uint64_t* words)
+{
+    for (int u0 = 0; u0 < units; u0 += 8) {
+        uint64_t of[8] = {0};
+        for (int i = 0; i < count; i += 8) {
+            uint64_t block = 0;
+            for (int j = 0; j < 8; ++j) block |= (uint64_t)(masks[i + j] >> u0 & 0xff) << (8 * j);
+            block = transposed8x8(block);
+            for (int u = 0; u < 8; ++u) of[u] |= (block >> (8 * u) & 0xff) << i;
+        }
+        for (int u = 0; u < 8; ++u) words[u0 + u] = of[u];
+    }
+}
+
 struct WideSegment {
     int32_t slot[WIDE_MAX_STEPS * STEP_K];      // segment-local k, -1: padding
     int steps;
@@ -586,16 +601,7 @@ bool arrange_wide(const uint32_t* mask, int rows, int units, WideSegment& out)
     for (int c = 0; c < CLASSES; ++c) {
         const int m = (rows - c + CLASSES - 1) / CLASSES;
         for (int i = m; i < SEGMENT_ROWS / CLASSES; ++i) users[c][i] = 0;
-        for (int u0 = 0; u0 < units; u0 += 8) {
-            uint64_t of[8] = {0};
-            for (int i = 0; i < m; i += 8) {
-                uint64_t block = 0;                     // byte j: candidate i + j, bit u: unit u0 + u; and the other way round
-                for (int j = 0; j < 8; ++j) block |= (uint64_t)(users[c][i + j] >> u0 & 0xff) << (8 * j);
-                block = transposed8x8(block);
-                for (int u = 0; u < 8; ++u) of[u] |= (block >> (8 * u) & 0xff) << i;
-            }
-            for (int u = 0; u < 8; ++u) uses[c][u0 + u] = of[u];
-        }
+        transposed(users[c], m, units, uses[c]);
     }
     out.steps = (n + STEP_K - 1) / STEP_K;
     uint32_t one[MAX_QUADS] = {0}, two[MAX_QUADS] = {0};       // units with a k, with two, in the quad
@@ -615,50 +621,90 @@ bool arrange_wide(const uint32_t* mask, int rows, int units, WideSegment& out)
             put(8 * o + j, cand[c][__builtin_ctzll(fit)], users[c][__builtin_ctzll(fit)]);
         }
     }
-    // what is left over
+    // What is left over, into the quads with holes, or by an exchange: a k of another quad into the hole, and this one into its
+    // place.  The other k fits quad q if none of its units has two there, and this one's units m fit in its place if each of
+    // them that has two in that quad has one of the two in it.  For all slots at once, 64 of a step in a word: the slots whose k
+    // unit u uses (a hole: all units), and those in whose quad u has two.  (256x256 in 1x4 blocks at 70 %, 97 tries a tile: 30 us
+    // of a tile slot by slot, 11 so.)
+    int holes[MAX_QUADS], nholes = 0;
+    uint64_t used[WIDE_MAX_STEPS][32], twice[WIDE_MAX_STEPS][32];
+    int words = 0;                                  // (steps that these are filled in of, as exchanges come to look at them)
+    auto users_at = [&](int z) { return out.slot[z] < 0 ? ~0u : mask[out.slot[z]]; };
+    auto fill_in_words = [&] {
+        uint32_t of_slot[STEP_K], of_quad[STEP_K];
+        for (int i = 0; i < STEP_K; ++i) {
+            of_slot[i] = users_at(words * STEP_K + i);
+            of_quad[i] = two[words * STEP_K / 4 + i / 4];
+        }
+        transposed(of_slot, STEP_K, units, used[words]);
+        transposed(of_quad, STEP_K, units, twice[words]);
+    };
+    auto refresh = [&](int z) {                     // slot z, and its quad
+        const uint64_t slot_bit = (uint64_t)1 << (z & 63), quad_bits = (uint64_t)15 << (z & 60);
+        const uint32_t m = users_at(z), t = two[z / 4];
+        for (int u = 0; u < units; ++u) {
+            used[z / 64][u] = (used[z / 64][u] & ~slot_bit) | ((0 - (uint64_t)(m >> u & 1)) & slot_bit);
+            twice[z / 64][u] = (twice[z / 64][u] & ~quad_bits) | ((0 - (uint64_t)(t >> u & 1)) & quad_bits);
+        }
+    };
+    auto add_quads = [&](int first, int past) {
+        for (int q = first; q < past; ++q) {
+            bool hole = false;
+            for (int z = 4 * q; z < 4 * q + 4; ++z) hole = hole || out.slot[z] < 0;
+            if (hole) holes[nholes++] = q;
+        }
+    };
+    add_quads(0, out.steps * 16);
+    auto place = [&](int z, int32_t k, uint32_t m) {
+        put(z, k, m);
+        if (z / STEP_K < words) refresh(z);
+    };
+    auto fill = [&](int i, int32_t k, uint32_t m) {             // the first hole of quad holes[i]
+        int z = 4 * holes[i], left = 0;
+        while (out.slot[z] >= 0) ++z;
+        place(z, k, m);
+        for (z = 4 * holes[i]; z < 4 * holes[i] + 4; ++z) left += out.slot[z] < 0;
+        if (!left) std::copy(holes + i + 1, holes + nholes--, holes + i);
+    };
     int exchanges = 256;                            // (a bound on the work; then a new step)
     for (int c = 0; c < CLASSES; ++c) {
         while (alive[c]) {
             const int32_t k = cand[c][__builtin_ctzll(alive[c])];
             const uint32_t m = mask[k];
             bool done = false;
-            auto hole_of = [&](int q) {
-                for (int s = 4 * q; s < 4 * q + 4; ++s)
-                    if (out.slot[s] < 0) return s;
-                return -1;
-            };
-            int holes[MAX_QUADS], nholes = 0;
-            for (int q = 0; q < out.steps * 16; ++q)
-                if (hole_of(q) >= 0) holes[nholes++] = q;
             for (int i = 0; i < nholes && !done; ++i)
                 if (!(two[holes[i]] & m)) {
-                    put(hole_of(holes[i]), k, m);
+                    fill(i, k, m);
                     done = true;
                 }
-            // a k of another quad into the hole, and this one into its place
+            uint64_t no_room[WIDE_MAX_STEPS];       // the slots in whose place it does not fit, of the first `looked` steps
+            int looked = 0;
             for (int i = 0; i < nholes && !done && exchanges-- > 0; ++i) {
                 const int q = holes[i];
-                for (int s = 0; s < out.steps * STEP_K && !done; ++s) {
-                    const int r = s / 4;
-                    if (r == q || out.slot[s] < 0 || (two[q] & mask[out.slot[s]])) continue;
-                    uint32_t o1 = 0, t1 = 0;        // quad r without slot s
-                    for (int z = 4 * r; z < 4 * r + 4; ++z)
-                        if (z != s && out.slot[z] >= 0) {
-                            t1 |= o1 & mask[out.slot[z]];
-                            o1 |= mask[out.slot[z]];
-                        }
-                    if (t1 & m) continue;
-                    put(hole_of(q), out.slot[s], mask[out.slot[s]]);
-                    one[r] = o1;
-                    two[r] = t1;
-                    put(s, k, m);
+                for (int s = 0; s < out.steps && !done; ++s) {
+                    for (; words <= s; ++words) fill_in_words();
+                    if (looked == s) {
+                        no_room[looked++] = 0;
+                        for (uint32_t u = m; u; u &= u - 1) no_room[s] |= twice[s][__builtin_ctz(u)] & ~used[s][__builtin_ctz(u)];
+                    }
+                    uint64_t no = no_room[s] | (s == q / 16 ? (uint64_t)15 << (4 * (q & 15)) : 0);
+                    for (uint32_t u = two[q]; u; u &= u - 1) no |= used[s][__builtin_ctz(u)];
+                    if (!~no) continue;
+                    const int z = s * STEP_K + __builtin_ctzll(~no), r = z / 4;
+                    const int32_t other = out.slot[z];
+                    const uint32_t u = mask[other];
+                    one[r] = (one[r] & ~u) | (two[r] & u);
+                    two[r] &= ~u;
+                    fill(i, other, u);
+                    place(z, k, m);
                     done = true;
                 }
             }
             if (!done) {
                 if (out.steps == WIDE_MAX_STEPS) return false;
-                for (int i = 0; i < STEP_K; ++i) out.slot[out.steps * STEP_K + i] = -1;
+                for (int z = 0; z < STEP_K; ++z) out.slot[out.steps * STEP_K + z] = -1;
                 ++out.steps;
+                add_quads(out.steps * 16 - 16, out.steps * 16);
                 continue;                           // (and again, now that there are holes)
             }
             alive[c] &= alive[c] - 1;
@@ -687,30 +733,30 @@ struct WidePlace {
     uint8_t sel, shift;
 };
 
-// The records of a wide tile, `room` of them (the last unused ones cleared).  Its steps go to `steps`; false: in some segment
-// they are more than the list's length asks for (what was written is of no use then), or than there may be (too_dense).
-bool arrange_wide_tile(const Lists& l, int64_t t, uint8_t* rec, int64_t room, int32_t* steps, WidePlace* places, uint32_t* sels,
-                       bool& too_dense)
+// The listed k of a wide tile dealt to the slots of its segments, whose steps go to `steps`.  false: a segment has too many.
+// `longer`: in some segment they are more than steps[] had, what the list's length asks for.
+bool arrange_segments(const Lists& l, int64_t t, WideSegment* segments, int32_t* steps, bool& longer)
+{
+    for (int seg = 0; seg < l.nseg; ++seg) {
+        if (!arrange_wide(&l.masks[(size_t)(t * l.K + (int64_t)seg * SEGMENT_ROWS)], l.rows_of(seg), l.units, segments[seg])) return false;
+        longer = longer || segments[seg].steps > steps[seg];
+        steps[seg] = segments[seg].steps;
+    }
+    return true;
+}
+
+// The records of a wide tile so arranged, `room` of them (the last unused ones cleared).
+void write_wide_tile(const Lists& l, int64_t t, const WideSegment* segments, uint8_t* rec, int64_t room, WidePlace* places, uint32_t* sels)
 {
     const Bsr& b = l.b;
-    const uint32_t* const mask = &l.masks[(size_t)(t * l.K)];
-    WideSegment slots;
     int first = 0;
-    bool as_expected = true;
     for (int seg = 0; seg < l.nseg; ++seg) {
         const int rows = l.rows_of(seg);
-        const uint32_t* const m = mask + (int64_t)seg * SEGMENT_ROWS;
-        if (!arrange_wide(m, rows, l.units, slots)) {
-            too_dense = true;
-            return false;
-        }
-        as_expected = as_expected && slots.steps <= steps[seg];
-        steps[seg] = slots.steps;
-        if (!as_expected) continue;
-        for (int s = 0; s < slots.steps; ++s) {
+        const uint32_t* const m = &l.masks[(size_t)(t * l.K + (int64_t)seg * SEGMENT_ROWS)];
+        for (int s = 0; s < segments[seg].steps; ++s) {
             uint8_t* const r = rec + (int64_t)(first + s) * WIDE_RECORD_BYTES;
             std::memset(r, 0, WIDE_VAL_BYTES);
-            const int32_t* const slot = slots.slot + s * STEP_K;
+            const int32_t* const slot = segments[seg].slot + s * STEP_K;
             for (int q = 0; q < STEP_K / 4; ++q) {
                 uint32_t before = 0;
                 for (int z = 4 * q; z < 4 * q + 4; ++z) {
@@ -724,9 +770,8 @@ bool arrange_wide_tile(const Lists& l, int64_t t, uint8_t* rec, int64_t room, in
                 }
             }
         }
-        first += slots.steps;
+        first += segments[seg].steps;
     }
-    if (!as_expected) return false;
     const int units = l.units, rows_of_unit = WIDE_ROWS / units;
     std::memset(sels, 0, (size_t)(2 * first * units) * 4);
     auto add = [&](const WidePlace& p, const int u, const int row, const int rows, const uint32_t v) {
@@ -755,7 +800,6 @@ bool arrange_wide_tile(const Lists& l, int64_t t, uint8_t* rec, int64_t room, in
             for (int row = 0; row < WIDE_ROWS; ++row) std::memcpy(to + 8 * (32 * h + row), &sels[(size_t)((2 * s + h) * units + row / rows_of_unit)], 4);
     }
     std::memset(rec + (int64_t)first * WIDE_RECORD_BYTES, 0, (size_t)((room - first) * WIDE_RECORD_BYTES));
-    return true;
 }
 
 // what the steps of every (wide tile, segment) come to
@@ -820,20 +864,6 @@ void forms_from_bsr(const Bsr& b, HostLayout& hl, DeviceForms& f, Team& team, co
         const int64_t used = hl.seg_ptr[(size_t)((t + 1) * ns)] - first, room = f.tile_steps ? f.tile_steps : used;
         std::memset(to + used * RECORD_BYTES, 0, (size_t)((room - used) * RECORD_BYTES));
     };
-    auto wide_tile = [&](int64_t t, WidePlace* places, uint32_t* sels) {
-        uint8_t* const form = f.wide_bytes();
-        int32_t* const steps = &l.wide_steps[(size_t)(t * ns)];
-        bool dense = false;
-        if (!arrange_wide_tile(l, t, form + wide_records_offset(l.nt, ns) + dims.first[(size_t)t] * WIDE_RECORD_BYTES,
-                               dims.first[(size_t)t + 1] - dims.first[(size_t)t], steps, places, sels, dense)) {
-            if (dense) none = true;
-            else longer = true;
-            return;
-        }
-        int32_t* const bounds = (int32_t*)(form + wide_bounds_offset(l.nt)) + t * (ns + 1);
-        bounds[0] = (int32_t)dims.first[(size_t)t];
-        for (int64_t g = 0; g < ns; ++g) bounds[g + 1] = bounds[g] + steps[g];
-    };
     team.run(nt16, 2 * l.grain, [&](int64_t begin, int64_t end) {
         const std::unique_ptr<int32_t[]> place(new int32_t[(size_t)l.K]);
         for (int64_t t = begin; t < end; ++t) narrow_tile(t, place.get());
@@ -844,24 +874,63 @@ void forms_from_bsr(const Bsr& b, HostLayout& hl, DeviceForms& f, Team& team, co
     std::memset(f.bytes.get() + narrow_end, 0, (size_t)records_offset(nt16, ns) - narrow_end);
     if (!hl.nsteps) std::memset(f.bytes.get() + records_offset(nt16, ns), 0, RECORD_BYTES);
 
-    auto wide_tiles = [&](int64_t begin, int64_t end) {
+    // Every tile is packed where it goes if no list needs more steps than its length asks for.  Those that do are kept as they
+    // are arranged, for a second pass.  (256x256 in 1x4 blocks at 70 %, where all do, on the host: 0.38 ms; 1.0 when the second
+    // pass arranged all tiles anew, slot by slot; 0.30 for the first form alone.)
+    std::vector<std::unique_ptr<WideSegment[]>> kept;
+    wide_memory([&] { kept.resize((size_t)l.nt); });
+    auto wide_tiles = [&](int64_t begin, int64_t end, const auto& tile) {
         std::unique_ptr<WidePlace[]> places;
         std::unique_ptr<uint32_t[]> sels;
         wide_memory([&] {
             places.reset(new WidePlace[(size_t)l.K]);
             sels.reset(new uint32_t[(size_t)(2 * ns * WIDE_MAX_STEPS * l.units)]);
         });
-        for (int64_t t = begin; t < end && !none; ++t) wide_tile(t, places.get(), sels.get());
+        uint8_t* const form = f.wide_bytes();
+        for (int64_t t = begin; t < end && !none; ++t) {
+            const int64_t first = dims.first[(size_t)t], room = dims.first[(size_t)t + 1] - first;
+            uint8_t* const rec = form + wide_records_offset(l.nt, ns) + first * WIDE_RECORD_BYTES;
+            if (const WideSegment* const segments = tile(t, rec, room)) write_wide_tile(l, t, segments, rec, room, places.get(), sels.get());
+            int32_t* const bounds = (int32_t*)(form + wide_bounds_offset(l.nt)) + t * (ns + 1);
+            bounds[0] = (int32_t)first;
+            for (int64_t g = 0; g < ns; ++g) bounds[g + 1] = bounds[g] + l.wide_steps[(size_t)(t * ns + g)];
+        }
     };
-    team.finish(l.nt, l.grain, wide_tiles, first_form);
-    // (lists that two of a quad lengthen, 1x4 blocks at 75 % for instance: again, now that their steps are known)
+    team.finish(l.nt, l.grain, [&](int64_t begin, int64_t end) {
+        std::unique_ptr<WideSegment[]> segments;
+        wide_tiles(begin, end, [&](int64_t t, uint8_t*, int64_t) -> const WideSegment* {
+            bool more = false;
+            wide_memory([&] {
+                if (!segments) segments.reset(new WideSegment[(size_t)ns]);
+            });
+            if (none || !arrange_segments(l, t, segments.get(), &l.wide_steps[(size_t)(t * ns)], more)) {
+                none = true;
+                return nullptr;
+            }
+            if (!more) return segments.get();
+            longer = true;
+            kept[(size_t)t] = std::move(segments);
+            return nullptr;
+        });
+    }, first_form);
+    // (lists that two of a quad lengthen, 1x4 blocks at 75 % for instance: the tiles to where they go now that all steps are known)
     if (longer && !none) {
+        const std::vector<int64_t> was_at = dims.first;
+        const std::unique_ptr<uint8_t[]> old = std::move(f.wide);
+        const uint8_t* const from = f.together ? f.bytes.get() + f.size : old.get();
         dims = WideDims(l, l.wide_steps, f);
-        f.wide.reset();
         wide_memory([&] { f.wide.reset(new uint8_t[(size_t)f.wide_size]); });
         f.together = false;
         Team again;
-        again.finish(l.nt, l.grain, wide_tiles);
+        again.finish(l.nt, l.grain, [&](int64_t begin, int64_t end) {
+            wide_tiles(begin, end, [&](int64_t t, uint8_t* rec, int64_t room) -> const WideSegment* {
+                if (kept[(size_t)t]) return kept[(size_t)t].get();
+                const int64_t records = was_at[(size_t)t + 1] - was_at[(size_t)t];
+                std::memcpy(rec, from + wide_records_offset(l.nt, ns) + was_at[(size_t)t] * WIDE_RECORD_BYTES, (size_t)(records * WIDE_RECORD_BYTES));
+                std::memset(rec + records * WIDE_RECORD_BYTES, 0, (size_t)((room - records) * WIDE_RECORD_BYTES));
+                return nullptr;
+            });
+        });
     }
     if (none) {
         f.drop_wide();
