@@ -15,7 +15,8 @@ namespace spmm {
 // f(begin, end) over [0, n) in pieces of `piece`, by the calling thread and up to 7 others; `own`, where there is one, is run
 // first by the calling thread.  Packing a model's weights is what its load waits for, in several passes over independent
 // rows, and starting 7 threads for each of them took 50 to 100 us a pass.  They are started once, each by one started before, and
-// wait for the next pass; nothing of it outlives the call that packs.  (1024x4096 at 80 %, onto the device: 0.99 ms with
+// wait for the next pass, as many as the first pass that is shared has pieces for (the others have as many: rows of a weight);
+// nothing of it outlives the call that packs.  (1024x4096 at 80 %, onto the device: 0.99 ms with
 // threads started for each pass and one form, 1.7 with both; now 0.91 with both.)
 class Team {
 public:
@@ -65,8 +66,8 @@ private:
         }
         work_.notify_all();
         if (!started_) {
-            started_ = true;
-            if (last) most_ = (int)std::min<int64_t>(most_, pieces - 1);
+            started_ = true;        // (300x300 is two pieces: 0.24 ms with 7 threads started, 0.15 with one)
+            most_ = (int)std::min<int64_t>(most_, pieces - 1);
             start(0);
         }
         std::exception_ptr failed;

@@ -66,3 +66,43 @@ def test_lists_that_need_exchanges_and_more_steps_cost_little_more(tmp_path):
     and every tile arranged a second time)."""
     sparse, dense = (float(v) for v in run(tmp_path, FORMS).split())
     assert dense < 4 * sparse, (dense, sparse)
+
+
+THREADS = r"""
+#include <chrono>
+#include <cstdio>
+#include <filesystem>
+#include <iterator>
+#include <set>
+#include "team.h"
+using namespace spmm;
+
+int main()
+{
+    auto threads = [] { return std::distance(std::filesystem::directory_iterator("/proc/self/task"), std::filesystem::directory_iterator()); };
+    for (const int pieces : {1, 2, 3, 20}) {
+        std::atomic<long> most{0};
+        std::atomic<int> done{0};
+        {
+            Team team;
+            for (int pass = 0; pass < 3; ++pass)
+                team.run(pieces, 1, [&](int64_t, int64_t) {
+                    std::this_thread::sleep_for(std::chrono::milliseconds(20));     // (time for any other thread to start)
+                    const long now = threads();
+                    for (long seen = most; seen < now && !most.compare_exchange_weak(seen, now);) {}
+                    ++done;
+                });
+            team.finish(100, 1, [&](int64_t, int64_t) { ++done; });
+        }
+        if (done != 3 * pieces + 100) return 1;
+        std::printf("%d %ld\n", pieces, (long)most);
+    }
+}
+"""
+
+
+def test_a_weight_of_two_pieces_starts_one_thread(tmp_path):
+    """(The threads are started by each other, 15 to 30 us each: for small weights that was half of the time.)"""
+    for line in run(tmp_path, THREADS).splitlines():
+        pieces, threads = (int(v) for v in line.split())
+        assert 1 <= threads <= min(pieces, 8), (pieces, threads)
