@@ -211,8 +211,10 @@ spmm_status_t spmm_make_gelu_lut(float mid_scale, float out_scale, int32_t out_z
 
 /* Kernel configuration chosen for a problem (reporting / tuning aid, Section 3.2 notes
  * that the tile size is tunable offline).  Writes the token-tile width, rows per
- * workgroup and the launch grid spmm_run would use for M tokens (outputs of 2 GiB and more may take
- * a different kernel: the widest configurations have no registers for their general store path). */
+ * workgroup and the launch grid spmm_run would use for M tokens with activation rows that start at 16-byte
+ * addresses (row-major or tile-major), outputs under 2 GiB, without the Sum operand and, where out_type is F32,
+ * without GELU: the choice depends on these too.  A handle of spmm_pack_host has no second form of the weight
+ * (see spmm_pack), and reports the plan of the first where spmm_pack's would take the second. */
 spmm_status_t spmm_plan(const spmm_handle_t *h, int64_t M, spmm_out_t out_type,
                         int32_t *token_tile, int32_t *rows_per_workgroup, int64_t *workgroups);
 
@@ -242,12 +244,12 @@ spmm_status_t spmm_plan(const spmm_handle_t *h, int64_t M, spmm_out_t out_type,
  * concurrent spmm_run on the same handle. */
 spmm_status_t spmm_set_tuning(spmm_handle_t *h, int32_t token_tile, int32_t variant);
 
-/* Base name of the device kernels spmm_run launches (for profilers). */
+/* What the names of all device kernels that spmm_run launches start with, after "void spmm::" (for profilers). */
 const char *spmm_kernel_name(void);
 
 /* Full name, as a profiler prints it, of the kernel instantiation spmm_run would launch for
  * M tokens with this output type and post-operator, for 16-byte aligned operands and without
- * the Sum operand (see spmm_plan).  buf is HOST memory of buflen bytes; the name is
+ * the Sum operand, on a handle of spmm_pack (see spmm_plan).  buf is HOST memory of buflen bytes; the name is
  * NUL-terminated and truncated if it does not fit. */
 spmm_status_t spmm_kernel_variant(const spmm_handle_t *h, int64_t M, spmm_out_t out_type,
                                   spmm_postop_t postop, char *buf, int64_t buflen);

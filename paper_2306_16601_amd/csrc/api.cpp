@@ -384,7 +384,7 @@ spmm_status_t spmm_make_gelu_lut(float mid_scale, float out_scale, int32_t out_z
     return SPMM_OK;
 }
 
-const char* spmm_kernel_name(void) { return "spmm_rowtile_mfma"; }
+const char* spmm_kernel_name(void) { return "spmm_rowtile"; }
 
 spmm_status_t spmm_kernel_variant(const spmm_handle_t* h, int64_t M, spmm_out_t out_type, spmm_postop_t postop,
                                   char* buf, int64_t buflen)

@@ -61,6 +61,14 @@ def test_no_kernel_spills_vector_registers(kernels):
     assert not spilled, spilled
 
 
+def test_the_base_name_is_that_of_every_kernel(kernels):
+    """A profiler's filter on spmm_kernel_name() shows all that spmm_run launches, and nothing else of the library."""
+    name = sp.spmm_kernel_name()
+    assert all(re.match(r"_ZN4spmm\d+" + name, k[".name"]) for k in kernels)
+    others = [k[".name"] for elf in _code_objects(sp.binding.LIB_PATH) for k in _kernels(elf) if "rowtile" not in k[".name"]]
+    assert others and not any(name in n for n in others)
+
+
 def test_resident_kernels_leave_room_for_a_second_workgroup(kernels):
     """128 registers: two workgroups of 8 waves on a CU.  (Sum with 16- and 32-token tiles: one, their grids are one
     round of workgroups.)"""
