@@ -2,7 +2,8 @@
 Called as a subprocess by tests/test_emulated_kernels.py (a kernel that reads or writes outside
 its buffers ends this process with a segmentation fault, a barrier that not every wave reaches
 ends it with the emulator's deadlock report): prints one JSON line.
-usage: python run_case.py N K M sparsity out_type postop token_tile variant ldx ldo cus [weight kind [xtiled]]"""
+usage: python run_case.py N K M sparsity out_type postop token_tile variant ldx ldo cus [weight kind [xtiled [ld_sum]]]
+(xtiled: xtiled, xotiled or rowmajor; ld_sum: with an operand of Sum of this pitch, its rows' padding poisoned)"""
 import ctypes
 import json
 import os
@@ -23,6 +24,7 @@ def main():
     kind = sys.argv[12] if len(sys.argv) > 12 else "uniform"
     x_tiled = len(sys.argv) > 13 and sys.argv[13] in ("xtiled", "xotiled")
     o_tiled = len(sys.argv) > 13 and sys.argv[13] == "xotiled"
+    ld_sum = int(sys.argv[14]) if len(sys.argv) > 14 else 0
     os.environ["EMU_CUS"] = str(cus)
     import build_emu
     import paper_2306_16601_amd.binding as b
@@ -65,8 +67,15 @@ def main():
     lut = None
     if po == "gelu" and ot in ("s8", "u8"):
         lut = dev(sp.spmm_make_gelu_lut(d["mid_scale"], d["out_scale"], d["out_zero_point"], ot))
+    R = Rp = None
+    if ld_sum:
+        R = (wl.rng_for(6, N, M).standard_normal((N, M)) * wl.preact_sigma(K, sparsity)).astype(np.float32)
+        # (an allocation of exactly what the call may read: nothing behind the last row's last value)
+        Rp = np.full((N, ld_sum), np.nan, dtype=np.float32)
+        Rp[:, :M] = R
+        Rp = Rp.reshape(-1)[:(N - 1) * ld_sum + M]
     ep = sp.make_epilogue(dev(d["w_scale"]), d["x_scale"], d["x_zero_point"], dev(d["bias"]), po, ot,
-                          d["out_scale"], d["out_zero_point"], d["mid_scale"], lut)
+                          d["out_scale"], d["out_zero_point"], d["mid_scale"], lut, dev(Rp) if ld_sum else None, ld_sum)
     dt = {"s32": np.int32, "f32": np.float32, "s8": np.int8, "u8": np.uint8}[ot]
     tiles = (M + 31) // 32
     nbytes = tiles * N * 32 if o_tiled else N * ldo * np.dtype(dt).itemsize
@@ -91,7 +100,7 @@ def main():
         ctypes.memmove(full.ctypes.data, od, nbytes)
     got = full[:, :M]
     ref = oracle.spmm(W, X, d["w_scale"], d["x_scale"], d["bias"], po, ot, d["out_scale"], d["out_zero_point"],
-                      d["mid_scale"], d["x_zero_point"])
+                      d["mid_scale"], d["x_zero_point"], **({"sum": R} if ld_sum else {}))
     if ot == "f32" and po == "gelu":
         err = np.abs(got.astype(np.float64) - ref.astype(np.float64))
         ok = bool((err <= 1e-4 * np.abs(ref.astype(np.float64)) + 1e-6).all())   # (host exp2 / reciprocal stand-ins)

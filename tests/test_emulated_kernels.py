@@ -32,10 +32,10 @@ def emu_lib():
     return build_emu.build()
 
 
-def run_case(N, K, M, sparsity, out_type, postop, tm, variant, ldx=0, ldo=0, cus=4, kind="uniform", xtiled=False):
+def run_case(N, K, M, sparsity, out_type, postop, tm, variant, ldx=0, ldo=0, cus=4, kind="uniform", xtiled=False, ld_sum=0):
     # xtiled: True = tile-major activations, "out" = tile-major activations and tile-major 1-byte output
     cmd = [sys.executable, os.path.join(HERE, "emu", "run_case.py"), str(N), str(K), str(M), str(sparsity), out_type,
-           postop, str(tm), str(variant), str(ldx), str(ldo), str(cus), kind] + (["xotiled"] if xtiled == "out" else ["xtiled"] if xtiled else [])
+           postop, str(tm), str(variant), str(ldx), str(ldo), str(cus), kind, "xotiled" if xtiled == "out" else "xtiled" if xtiled else "rowmajor"] + ([str(ld_sum)] if ld_sum else [])
     r = subprocess.run(cmd, capture_output=True, text=True, timeout=600)
     assert r.returncode == 0, "emulated kernel run failed (rc %d):\n%s" % (r.returncode, r.stderr[-3000:])
     return json.loads(r.stdout.strip().splitlines()[-1])

@@ -1,7 +1,9 @@
 """The kernels over the wide form (32-row tiles, 2 of every 4 listed k): run on the CPU where tiles, token counts, segments
 and step lists have their edges, and on the device in every form against the oracle.  Results are exact: whole numbers
 and codes to the bit, f32 to the bit without GELU and within the bound of test_gpu_parity with it."""
+import json
 import os
+import subprocess
 import sys
 
 import numpy as np
@@ -34,6 +36,17 @@ EMULATED = [
     (300, 1700, 200, 0.9, "s32", "none", 96, 132, "spmm_rowtile_smfmac<96, 8", {"cus": 2, "ldo": 208, "kind": "empty"}),
     (300, 1700, 200, 0.9, "s8", "gelu", 32, 134, "spmm_rowtile_smfmac<32, 4", {"cus": 2, "kind": "empty", "xtiled": "out"}),
     (260, 1100, 200, 0.8, "u8", "gelu", 128, 132, "spmm_rowtile_smfmac<128, 8", {"cus": 2, "xtiled": True}),
+    # lists of 6 steps
+    (289, 1100, 201, 0.86, "s8", "gelu", 128, 132, "spmm_rowtile_smfmac<128, 8, 6", {"cus": 2}),
+    (257, 512, 129, 0.85, "f32", "none", 96, 132, "spmm_rowtile_smfmac<96, 8, 6", {"cus": 2, "ldo": 131}),
+    (130, 1024, 200, 0.86, "u8", "none", 64, 132, "spmm_rowtile_smfmac<64, 8, 6", {"cus": 2, "xtiled": "out"}),
+    (289, 1100, 70, 0.86, "f32", "gelu", 64, 134, "spmm_rowtile_smfmac<64, 4, 6", {"cus": 2}),
+    (257, 512, 129, 0.85, "s32", "none", 32, 134, "spmm_rowtile_smfmac<32, 4, 6", {"cus": 2, "ldx": 136}),
+    # the operand of Sum, read to its last value and no further
+    (257, 513, 129, 0.9, "f32", "none", 64, 132, "spmm_rowtile_smfmac<64, 8", {"cus": 2, "ld_sum": 129}),
+    (289, 1100, 70, 0.86, "s8", "none", 64, 134, "spmm_rowtile_smfmac<64, 4, 6", {"cus": 2, "ld_sum": 73, "xtiled": "out"}),
+    (100, 1100, 203, 0.7, "u8", "none", 32, 134, "spmm_rowtile_smfmac<32, 4", {"cus": 2, "ld_sum": 208}),
+    (64, 600, 128, 0.9, "f32", "none", 128, 132, "spmm_rowtile_smfmac<", {"cus": 2, "ld_sum": 128, "ldo": 128}),
 ]
 
 
@@ -50,6 +63,72 @@ def test_wide_kernel_on_the_cpu_matches_oracle_and_stays_in_bounds(case):
 
 TUNINGS = [(128, 132), (96, 132), (64, 132), (64, 134), (32, 134)]
 SHAPES = [(31, 100, 33, 0.8), (289, 1100, 701, 0.9), (260, 513, 1299, 0.8), (96, 9000, 130, 0.9), (1024, 1024, 1531, 0.75)]
+# 6 step slots in 4x1 blocks, and in 1x4 blocks
+SIX = [(289, 1100, 701, 0.86, wl.N4K1), (289, 1100, 701, 0.97, wl.N1K4), (512, 512, 1531, 0.87, wl.N4K1)]
+# what the weights of this file's device tests run with: step slots, None = too dense for the form
+SLOTS = [(31, 100, 0.8, wl.N4K1, 101, 5), (289, 1100, 0.9, wl.N4K1, 101, 5), (260, 513, 0.8, wl.N4K1, 101, 7), (96, 9000, 0.9, wl.N4K1, 101, 5),
+         (1024, 1024, 0.75, wl.N4K1, 101, 8), (31, 100, 0.8, wl.N1K4, 101, 5), (289, 1100, 0.9, wl.N1K4, 101, 8), (260, 513, 0.8, wl.N1K4, 101, 8),
+         (96, 9000, 0.9, wl.N1K4, 101, 8), (1024, 1024, 0.75, wl.N1K4, 101, None),
+         (31, 100, 0.8, wl.N4K1, 102, 5), (289, 1100, 0.9, wl.N4K1, 102, 5), (260, 513, 0.8, wl.N4K1, 102, 7), (96, 9000, 0.9, wl.N4K1, 102, 5),
+         (1024, 1024, 0.75, wl.N4K1, 102, 8)]
+
+
+KERNELS = """
+import json, sys
+sys.path[:0] = sys.argv[1:3]
+import build_emu, paper_2306_16601_amd.binding as b
+b.LIB_PATH = build_emu.LIB
+import paper_2306_16601_amd as sp, workloads as wl
+for (N, K, M, s, block, key), tunings in json.load(sys.stdin):
+    h = sp.spmm_pack(wl.make(wl.Case("slots", N, K, M, s, block, "s8", "gelu", keys=(key, N, K, M)))["W"], block)
+    for tuning in tunings:
+        sp.spmm_set_tuning(h, *tuning)
+        print(sp.spmm_kernel_variant(h, M, "s8", "gelu"))
+    sp.spmm_destroy(h)
+"""
+
+
+@pytest.mark.skipif(not build_emu.available(), reason="no host clang++ for the emulation build")
+def test_the_device_tests_run_the_kernels_they_name():
+    """The step slots of every weight that is run on the device, from the plan over its packed form."""
+    build_emu.build()
+    tokens = {(N, K, s): M for N, K, M, s in SHAPES}
+    cases = [((N, K, tokens[N, K, s], s, block, key), slots) for N, K, s, block, key, slots in SLOTS]
+    cases += [((N, K, M, s, block, key), 6) for N, K, M, s, block in SIX for key in (108, 109)]
+    here = os.path.dirname(os.path.abspath(__file__))
+    r = subprocess.run([sys.executable, "-c", KERNELS, os.path.dirname(here), os.path.join(here, "emu")], text=True, timeout=300, capture_output=True,
+                       input=json.dumps([(c, TUNINGS) for c, _ in cases]), env=dict(os.environ, EMU_CUS="256"))
+    assert r.returncode == 0, r.stderr[-2000:]
+    expected = ["smfmac<%d, %d, %d, 2, 1>" % (tm, 8 if variant == 132 else 4, slots) if slots else "spmm_rowtile_mfma_fed<128, 8, 4, 8, 2, 1>"
+                for _, slots in cases for tm, variant in TUNINGS]
+    names = r.stdout.splitlines()
+    assert len(names) == len(expected)
+    for name, want in zip(names, expected):
+        assert want in name, (name, want)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("out_type,postop", [("s32", "none"), ("f32", "none"), ("f32", "gelu"), ("s8", "none"), ("u8", "gelu")])
+@pytest.mark.parametrize("N,K,M,s,block", SIX)
+def test_six_step_slots_on_the_device(N, K, M, s, block, out_type, postop):
+    from test_gpu_parity import _run_sum, _run_tiled_out, assert_parity, check_case, oracle_spmm
+    case = wl.Case("six", N, K, M, s, block, out_type, postop, keys=(108, N, K, M))
+    for i, tuning in enumerate(TUNINGS):
+        check_case(case, tuning=tuning, ldx=M + i, ldo=M + 3 * (i % 2))
+    if out_type in ("s8", "u8"):
+        d = wl.make(case)
+        ref = oracle_spmm(d["W"], d["X"], d, case)
+        for i, tuning in enumerate(TUNINGS):
+            assert_parity(_run_tiled_out(d, case, tuning, i % 2 == 0), ref, case)
+    if out_type == "s32" or postop == "gelu":
+        return
+    case = wl.Case("sixsum", N, K, M, s, block, out_type, postop, keys=(109, N, K, M))
+    d = wl.make(case)
+    R = (wl.rng_for(110, N, M).standard_normal((N, M)) * wl.preact_sigma(K, case.sparsity)).astype(np.float32)
+    ref = oracle.spmm(d["W"], d["X"], d["w_scale"], d["x_scale"], d["bias"], postop, out_type, d["out_scale"], d["out_zero_point"], d["mid_scale"],
+                      d["x_zero_point"], sum=R)
+    for i, tuning in enumerate(TUNINGS):
+        assert_parity(_run_sum(d, case, R, M + i, tuning, i % 4), ref, case)
 
 
 @pytest.mark.gpu
