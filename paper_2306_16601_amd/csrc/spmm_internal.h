@@ -123,9 +123,10 @@ constexpr int64_t wide_records_offset(int64_t ntiles, int64_t nseg)
 
 // The operand of Sum, and GELU in binary32, need registers that the accumulators of the widest tiles take.
 constexpr int wide_tile(bool gelu_f32, bool sum) { return sum ? 64 : gelu_f32 ? 96 : 128; }
-// What the estimates do not tell of the wide kernels against the others, of 6600 measured problems: 1-byte outputs (their
-// estimate is 0.96 of the measured time, the others' 1.03), Sum (1.01 and 0.89), GELU in f32 (1.01 and 0.97), and rows that do not
-// start at 16 bytes (0.84 and 0.91).
+// What the estimates do not tell of the wide kernels against the others.  In the problems of
+// profiles/spmm_plan_wide_measurements.csv, estimate over measured time of the wide kernels and of the others: 1-byte outputs
+// 0.97 and 1.04, 4-byte ones 0.99 and 1.00, of these with GELU 0.96 and 0.96; Sum 0.94 and 0.93; rows that do not start at 16
+// bytes 0.82 and 0.89.  (The factors are of 6600 problems of other sizes, where Sum was 1.01 and 0.89.)
 constexpr double wide_handicap(bool bytes, bool gelu_f32, bool sum, bool aligned_rows)
 {
     return (bytes ? 1.06 : 1.0) * (sum ? 0.92 : gelu_f32 ? 0.97 : 1.0) * (aligned_rows ? 1.0 : 1.09);
@@ -186,15 +187,15 @@ constexpr uint32_t ARG_OUT_ALIGNED = 1u << 21;  // ARG_OUT_FAST, out base 16-byt
 constexpr int ARG_XCD_SHIFT = 22;               // 2 bits: how a workgroup id decodes, see decode_workgroup
 
 struct Plan {
-    int token_tile;          // TM: 128, 96 or (with loaders) 64 for the persistent kernels, 64, 32 or 16 for the others
-    int row_tiles_per_wave;  // 1, or 2 (simple kernel)
+    int token_tile;          // TM: 128, 96, with loaders 64, over the wide form 32 for the persistent kernels, 64, 32 or 16 for the others
+    int row_tiles_per_wave;  // 1, or 2 (simple kernel; the wide form: one of its own, of 32 rows)
     int waves;               // waves that own a row tile; short-batch kernels: row tiles (or pairs) per workgroup of 8 waves
-    int loaders;             // pipelined kernel: extra waves that only stage activations (0 or 4)
+    int loaders;             // persistent kernels: extra waves that only stage activations (0 or 4; the wide form: waves / 2)
     int simple;              // 1: simple kernel
     int slab;                // 1: spmm_rowtile_mfma_slab in its place (token tile 16: K <= 4096 resident in LDS; 32: the ring's other name)
     int stream;              // 1: the streamed kernel (a ring of segments) in its place
     int wide;                // 1: persistent kernel over the wide form
-    int max_steps;           // unroll bound of the per-segment step loop (pipelined kernel)
+    int max_steps;           // unroll bound of the per-segment step loop (persistent kernels)
     int n_row_groups, n_tok_tiles, n_streams;
     int xcd_row_bits;        // the 8 XCDs take 2^this slices of the row groups and 8 / 2^this of the tokens
     int64_t workgroups;
@@ -205,7 +206,8 @@ struct Plan {
 // 101 / 102 = simple kernel with 1 / 2 row tiles per wave (token tile 64; 101 also 32 and 16),
 // 103 = short-batch kernel (token tile 16 or 32), 104 = streamed kernel (token tile 64, 32 or 16),
 // 105 / 106 = simple or, from 5 segments on with 16-token tiles, short-batch kernel with 2 / 4 row tiles per workgroup,
-// whose waves share a row tile's steps (token tile 32 or 16)
+// whose waves share a row tile's steps (token tile 32 or 16),
+// 132 / 134 = over the wide form with 8 compute and 4 loader waves (token tile 128, 96 or 64) / 4 and 2 (64 or 32)
 constexpr int SLAB_SEGMENTS = 8;      // K segments the short-batch kernel keeps in LDS, token tile 16
 constexpr int SLAB_SEGMENTS_32 = 6;   // K segments up to which the ring with 32-token tiles goes by that kernel's name
 // what the plan needs to know of a packed weight

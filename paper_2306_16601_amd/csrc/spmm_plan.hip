@@ -211,7 +211,8 @@ static const Fit FIT_RING_32       = {0.90, 1.96, 0.0062, 2.06, 0.0130, 0.0000, 
 static const Fit FIT_RING_64       = {0.52, 2.99, 0.0039, 1.18, 0.0008, 0.0000, 1.53};
 
 // the wide form (units: 32 tokens of a step of 32 rows): 4700 other problems, 256 to 4096 features, 16 to 6144 tokens, 3e7
-// products and more, every layout; standard deviation 8 to 11 %
+// products and more, every layout; on the problems of profiles/spmm_plan_wide_measurements.csv, drawn on their own, the
+// estimates are 0.96 to 0.98 of the time, standard deviation 9 to 11 %
 static const Fit FIT_WIDE_128_8[2]   = {{2.88, 0.00, 0.0018, 0.84, 0.0745, 0.0841, 1.32},
                                       {2.73, 0.71, 0.0047, 0.00, 0.0940, 0.1020, 0.62}};
 static const Fit FIT_WIDE_96_8[2]    = {{2.82, 0.00, 0.0017, 0.81, 0.0869, 0.1050, 1.33},
@@ -387,17 +388,18 @@ Plan make_plan(int64_t M, const WeightDims& w, int num_cus, int force_tm, int va
         fed12(96, FIT_FED_96_12[reload]);
         fed12(64, FIT_FED_64_12[reload]);
     }
-    // ---- the wide form, from 192 blocks of 32 rows x 32 tokens on (below, the kernels above were never more than 1 % slower in
-    // 135 measured problems).  Of 6600 problems its fastest configuration won 58 %; what the estimates, whose errors are 10 %,
-    // set apart by less than the margins below goes to the kernels above, because a wrong choice is seen and a missed one is
-    // not: 1.6 % are then more than 3 % slower than without the wide form, and all together 1.080 times as fast (1.097 if every
-    // choice were right; with a margin of 0.98 1.084 and 6 %).  By what they replace: the 128-token kernels with loader waves
-    // 1.24 times, the streamed kernels 1.28, the resident ones 1.05.  4-byte outputs that have the 32-token slab keep it up to
+    // ---- the wide form, from 192 blocks of 32 rows x 32 tokens on (of 200 measured problems with fewer, some were 3 to 15 %
+    // faster with it, all of them launches of 3.4 to 4.8 us, which the host's 3.5 us bound).  Of the 700 problems of
+    // profiles/spmm_plan_wide_measurements.csv one of its configurations is the fastest in 65 %.  What the estimates, whose
+    // errors are 9 to 11 %, set apart by less than the margins below goes to the kernels above, because a wrong choice is seen
+    // and a missed one is not: 39 % get it, 1.0 % are more than 3 % slower than without it, and all together are 1.069 times as
+    // fast (1.090 if every choice were right; with a margin of 0.98 1.077, and 3.7 % slower).  By what it replaces: the 128-token
+    // kernels with 8 + 4 waves 1.25 times, the streamed kernels 1.25, the resident ones 1.07.  4-byte outputs that have the 32-token slab keep it up to
     // 768 blocks because tests/test_gpu_parity.py pins 768x3072, 1024 tokens, to it (such problems were 1.2 times as fast with
     // the wide form).
     const int64_t blocks = (int64_t)((w.ntiles + 1) / 2) * ((M + 31) / 32);
     const bool pinned = out_bytes == 4 && best.slab && best.token_tile == 32 && blocks <= 768;
-    // (nor where the others are under 5 us: of 230 such problems the choice would gain nothing, and its estimates take 0.15 us)
+    // (nor where the others are under 5 us: of 139 such problems the choice would gain nothing, and its estimates take 0.1 us)
     if (w.wide_max_steps > 0 && out_fast && blocks >= 192 && best_cost > 5.0 && !pinned) {
         call.set_wide_steps();
         const double post = widest < 128 ? 1.8 : 1.0;      // (Sum, GELU in f32: of the fits with each, the closest)

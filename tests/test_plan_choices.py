@@ -1,5 +1,7 @@
-"""What the plan chooses, against measured launch times (profiles/spmm_plan_measurements.csv): the plan is asked for every
-problem of the table, and the time of the configuration it picks is compared with the fastest one's."""
+"""What the plan chooses of the kernels over the 16-row form, against measured launch times
+(profiles/spmm_plan_measurements.csv): the plan is asked for every problem of the table, and the time of the configuration it
+picks is compared with the fastest one's.  The weights are given without a wide form here, which long batches run over on the
+device where they have one (4096x1024, 6144 tokens): that choice is tests/test_plan_wide.py's."""
 import csv
 import os
 import shutil
