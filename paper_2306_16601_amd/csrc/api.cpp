@@ -51,7 +51,7 @@ hipError_t upload(uint8_t** to, const uint8_t* from, int64_t bytes)
     else e = hipMemcpy(*to, from, (size_t)bytes, hipMemcpyHostToDevice);
     if (e != hipSuccess) {
         free_device(to);
-        (void)hipGetLastError();        // (reported by the result: the next launch is not the one that failed)
+        (void)hipGetLastError();        // (told by the result; what next asks for the last error is not what failed)
     }
     return e;
 }

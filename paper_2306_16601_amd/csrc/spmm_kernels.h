@@ -23,7 +23,8 @@
 //    tiles, so the compressed weights it needs stay in registers.
 //
 // Four kernels share the layout and the inner step (two transposing LDS reads, one matrix
-// instruction per 16 tokens); the host's plan (spmm_plan.hip) picks one by its estimate of their times:
+// instruction per 16 tokens), a fifth (spmm_wide.h) has a layout of its own; the host's plan
+// (spmm_plan.hip) picks one by its estimate of their times:
 //   spmm_rowtile_mfma         persistent, software-pipelined: long batches
 //   spmm_rowtile_mfma_fed     the same with waves that only stage activations: long batches with 4-byte
 //                             outputs, weights that do not stay in registers, or rows that 12 waves divide better
@@ -33,6 +34,8 @@
 //   spmm_rowtile_mfma_stream  a ring of four segments of activations: mid-size batches, short ones with the longest K.
 //                             spmm_rowtile_mfma_slab<32> is the same code under the name by which the plan reports
 //                             32-token tiles of 5 to 6 segments
+//   spmm_rowtile_smfmac       persistent, 32-row tiles on the structured-sparse instruction: long batches of weights
+//                             that have that form
 //
 // Lane roles of the matrix instruction (D = A.B, 64 lanes, g = lane / 16, c = lane % 16):
 //   A operand (activations): row = token c, bytes t = k-list slots 16g .. 16g+15
@@ -232,8 +235,8 @@ __device__ __forceinline__ void store16_out(const __amdgpu_buffer_rsrc_t rs, con
 // of a CU busy for as long as half a segment of multiplying does.)
 // key = sat_s8(rint(v)) + 128: v is clamped, scaled so that one is the smallest denormal, and 128 of those added, rounded once,
 // half to even (128 is even): the bits are the key.  Two instructions instead of the three of rounding, adding and
-// v_cvt_pk_u8_f32, which take no constant but those in the instruction (1024x1024 at 90 %, 6144 tokens, GELU to s8: 9.18 us,
-// now 9.02).
+// v_cvt_pk_u8_f32, which take no constant but those in the instruction (1024x1024 at 90 %, 6144 tokens, GELU to s8, on one
+// machine: 9.18 us, now 9.02; machines differ by as much).
 template <bool CONSTANTS>
 __device__ __forceinline__ uint32_t table_key(const float v)
 {

@@ -2,17 +2,18 @@
 // step, held 2 of 4 for the structured-sparse matrix instruction.
 //
 // What bounds the kernels of 16-row tiles in long batches is the gather: every listed k of every 16 rows is read from LDS
-// once, 64 bytes (one ds_read_b64_tr_b8 of a wave) for each 16 x 16 x 8 block of the product, and with 4x1 blocks at 75 to 90 %
-// most of what is read for 16 rows is listed by the next 16 as well.  32 rows share a list here.  Its length grows by less than
+// once, 16 bytes of it for 16 tokens (a ds_read_b64_tr_b8 of a wave, 512 bytes, reads 32 listed k), and with 4x1 blocks at 75 to
+// 90 % most of what is read for 16 rows is listed by the next 16 as well.  32 rows share a list here.  Its length grows by less than
 // twice (8 block-rows at 90 %: 57 % of all k against 34 % for 4), so that 5 gathers of 32 rows stand for 6 of two times 16;
 // and as no row uses more than two of every four slots (the packer sees to that), one v_smfmac_i32_32x32x64_i8 multiplies
 // 32 rows x 64 listed k x 32 tokens in the time of the dense instruction of half as many k.  For such a unit (4 gathers, one
 // instruction) a CU with 8 waves of nothing else takes 56 cycles; gathers alone 45, the instruction alone 33.  With random
 // operands the chip clocks down to 1.8 GHz in this (the instruction alone: 1.5 GHz), so the parts add up more than the cycles say.
 //
-// Compute waves take one row tile each, in token tiles of TM; half as many waves again stage activations.  Measured, start
-// and now: 4096x4096 at 70 %, 4096 tokens, row-major s8: 75.4 and 52.2 us; the two layers 4096x1024 and 1024x4096 at 85 %,
-// 6144 tokens, tile-major codes: 46.6 and 40.4 us; 2048x1024 in 1x4 blocks at 90 %, 1024 tokens, s8: 7.5 and 6.2 us.
+// Compute waves take one row tile each, in token tiles of TM; half as many waves again stage activations.  Measured, without
+// this kernel and with it: 4096x4096 at 70 %, rows uneven by 20 %, 4096 tokens, row-major s8: 79.6 and 54.6 us (75.4 and 53.5 on
+// another machine); the two layers 4096x1024 and 1024x4096 at 85 %, 6144 tokens, tile-major codes: 46.9 and 42.9 us (46.6 and
+// 42.2); 2048x1024 in 1x4 blocks at 90 %, 1024 tokens, s8: 7.5 and 6.3 us.
 #pragma once
 
 #include "spmm_kernels.h"
@@ -106,9 +107,9 @@ struct Wide {
 
         // ---- in step, but not in lock-step.  The loader waves write phase q's activations over those of phase q - BUFFERS, when all
         // compute waves have multiplied these; a compute wave multiplies phase q when all of its activations are written.
-        // Counts of both, for each of four consecutive phases.  Compute waves 0 .. 3, one on every SIMD, have priority at first,
-        // and so run ahead of waves 4 .. 7, which have it later and end no later: the post-operators of the one are worked out
-        // while the other multiplies.
+        // Counts of both, for each of four consecutive phases.  The first half of the compute waves (of 8, one on every SIMD; of 4,
+        // two of the four SIMDs', the other workgroup's on the others) has priority at first, and so runs ahead of the second,
+        // which has it later and ends no later: the post-operators of the one are worked out while the other multiplies.
         unsigned* const counts = (unsigned*)(lds + COUNTS);           // [0 .. 3]: written, [4 .. 7]: multiplied
         constexpr int WRITTEN = 0, MULTIPLIED = 4;
         // (Released on either side: written activations are in LDS, and gathers, also those requested past a segment's last step,
