@@ -100,7 +100,8 @@ typedef struct {
  * The weight is kept on the device in two forms: one that every call can run, and one for long batches, which some
  * dense weights do not have.  The second makes it 1.7 to 1.9 times the device memory of the first alone (1024x4096 at
  * 80 %: 3.1 + 2.8 MB; 4096x4096 at 70 %: 16.5 + 12.6 MB).  Where memory for the second cannot be had, the weight is
- * packed without it: same results, long batches up to 1.5 times slower; SPMM_E_ALLOC is for the first.
+ * packed without it: same results, the batches that would take it 1.2 times slower in the median (of 275 measured,
+ * 1.9 at most); SPMM_E_ALLOC is for the first.
  * Errors: SPMM_E_ARG, SPMM_E_UNSUPPORTED, SPMM_E_ALLOC, SPMM_E_DEVICE. */
 spmm_status_t spmm_pack(const int8_t *W_host, int64_t N, int64_t K, int64_t ldw,
                         spmm_block_t block, spmm_handle_t **out_handle);
