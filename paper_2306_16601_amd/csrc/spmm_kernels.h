@@ -1175,15 +1175,18 @@ __global__ void __launch_bounds__((NW + LW) * 64) spmm_rowtile_mfma_fed(const Ke
 // Short batches: the simple kernel (token tile 64, 32 or 16, any K) and the short-batch kernel with 16-token
 // tiles (K <= 4096) are one body with different amounts of resident K.
 //
-// A launch here is a few microseconds long and its time is a chain of memory latencies, so everything
-// a workgroup needs is requested before anything waits: the first weights of every wave (whose place
-// follows from tile_steps, without reading the bounds), the whole [K x TM] slab of activations, the
-// per-row constants, the operand of Sum, the table.  The slab then goes to LDS, one barrier, and each
-// wave walks its steps in groups of CH, branch-free inside a group (steps past the end count with zero
-// weights), the weights of the next NS - 1 groups in flight.  A K beyond the RES resident rows goes
-// round by round.  (The kernel before this one staged 512 rows at a time, two barriers per segment, and
-// requested a step's weights when it multiplied them: 768x768 at 80 %, 32 tokens, a call every 7.2 us; with this one,
-// and a launch that is a microsecond shorter on the host, every 4.0 us.)
+// A launch here is a few microseconds long, and its time is a chain of memory latencies and of the instructions between them:
+// a wave issues one every 4 cycles, every 8 where two share a SIMD, and a kernel of 2000 cycles has no room for a hundred that
+// do nothing for it.  So everything a workgroup needs is requested before anything waits, in the order in which it is needed:
+// the whole [K x TM] slab of activations, the first weights of every wave (whose place follows from tile_steps, without
+// reading the bounds), the per-row constants, the operand of Sum, the table; in code without branches for 1, 2, 4 .. passes of
+// rows, so that each wait is for what it needs and not for all; divisions are shifts, addresses 32-bit offsets; what only
+// K beyond the RES resident rows or far rows need is behind one branch (worked out ahead of a loop for both, it
+// took 700 cycles between the barrier and the first step).  The slab then goes to LDS, one barrier, and each wave walks its
+// steps in groups of CH, branch-free inside a group (steps past the end read as zero weights), the weights of the next NS - 1
+// groups in flight.  Start of a wave to its end, 256x256 at 90 %, 128 tokens, 2 row tiles per workgroup, in cycles: 5340
+// before, 3900 now.  Calls back to back, us: 3072x768 at 85 %, 128 tokens, u8 4.67 -> 4.16; 768x3072 at 80 %, 333 tokens with
+// Sum, binary32 11.8 -> 10.3; 2944x2944 at 80 %, 16 tokens 5.2 -> 4.0; below 4 us the host's launches bound them.
 //
 // LDS: a row is TM bytes, unpadded, so that two (TM = 16, K = 2048: five) workgroups share a CU.  Its
 // 16-byte pieces are rotated by an xor with bits of the row number such that rows whose numbers differ
@@ -1212,11 +1215,14 @@ struct Resident {
     static constexpr int PASSES = RES / PASS_ROWS;
     static constexpr int SEGS = RES / SEGMENT_ROWS;             // segments per round
     // weights in flight: NS sets of CH steps, gathered CH steps at a time (the slabs have 256 registers, the others
-    // 128, for two workgroups on a CU; with Sum, 16- and 32-token tiles have 131 and 135 and run one, see SUM_LATE)
+    // 128, for two workgroups on a CU)
     static constexpr bool WIDE = RES > 2048;
     static constexpr int CH = TM == 16 || WIDE ? 4 : 2;
     static constexpr int NS = TM == 16 ? (WIDE ? 6 : 3) : WIDE ? 5 : TM == 32 ? 4 : 3;
-    static constexpr int LDS = RES * TM + 256;                  // activations, then the table
+    // LDS: activations, the table, and what the waves that share a row tile hand to the first of them: of 6 waves at most
+    // (64-token workgroups have 8 row tiles, or pairs)
+    static constexpr bool SHARES = R == 1 && TM < 64;
+    static constexpr int TABLE_AT = RES * TM, SUMS_AT = TABLE_AT + 256, LDS = SUMS_AT + (SHARES ? 6 * PIECES * 1024 : 0);
     // The operand of Sum is requested with everything else at the start, where the grid is one round of workgroups, as
     // it is with narrow tiles: its latency is hidden (768 x 768, 128 tokens: 4.76 us, requested after the last step 4.90).
     // 64-token tiles are planned for grids of several rounds, where the second workgroup on a CU is worth more than that
@@ -1225,189 +1231,215 @@ struct Resident {
     static constexpr bool SUM = (POST & POST_SUM_BIT) != 0, SUM_LATE = TM == 64;
     static constexpr bool TABLE = (POST & SPMM_POST_GELU) != 0 && (OUT == SPMM_OUT_S8 || OUT == SPMM_OUT_U8);
     static_assert((RES & (RES - 1)) == 0 && PASSES * PASS_ROWS == RES && SEGMENT_ROWS % PASS_ROWS == 0, "threads tile a segment");
-    static_assert(8 * PIECES * 1024 <= RES * TM, "the partial sums fit where the activations were");
 
     static __device__ __forceinline__ uint32_t row_offset(const uint32_t r) { return Swizzle<TM>::row(r); }
 
     static __device__ __forceinline__ void run(const Args& a, uint8_t* const lds)
     {
+        // (row tiles per workgroup and waves per row tile are powers of two: everything here is a shift)
+        const int wt = __builtin_ctz((unsigned)a.wg_tiles), kb = 3 - wt;
+        const int group_bits = wt + (R == 2 ? 1 : 0);
         int tt, rg;
-        if (!decode_workgroup(a, (a.ntiles + a.wg_tiles * R - 1) / (a.wg_tiles * R), (a.M + TM - 1) / TM, rg, tt)) return;
+        if (!decode_workgroup(a, (a.ntiles + (1 << group_bits) - 1) >> group_bits, (a.M + TM - 1) / TM, rg, tt)) return;
         const int tid = threadIdx.x;
         const int lane = tid & 63;
         const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
         const int g = lane >> 4, c = lane & 15;
         const int tok0 = tt * TM;
-        const int ks = 8 / a.wg_tiles;                          // waves that share a row tile: 1, 2 or 4
-        const int part = wave & (ks - 1), local = wave / ks;
-        const int tile0 = (rg * a.wg_tiles + local) * R;        // this wave's first row tile
+        const int part = wave & ((1 << kb) - 1), local = wave >> kb;      // 1, 2 or 4 waves share a row tile
+        const int tile0 = ((rg << wt) + local) * R;             // this wave's first row tile
+        const bool have = tile0 < a.ntiles;
 
-        // ---- weights: NS rotating sets of CH steps
+        // ---- weights: NS rotating sets of CH steps of this wave's share of a row tile's steps.  The resource ends with the share:
+        // a load past it gives zeros, and fetches nothing.
         v4i A[NS][CH];
         uint32_t I[NS][CH];
-        int s_begin = 0, s_end = 0;                             // this wave's steps of the current round and row tile
-        auto w_load = [&](v4i (&w)[CH], uint32_t (&rows)[CH], const int step, const int last) __attribute__((always_inline)) {
-#pragma unroll
-            for (int j = 0; j < CH; ++j) load_step(a, min(step + j, last), lane, w[j], rows[j]);
+        __amdgpu_buffer_rsrc_t share;
+        int steps = 0;                                          // of the share
+        const int val_at = lane * 16, row_at = STEP_VAL_BYTES + 32 * g + 4 * (c >> 1);
+        auto w_open = [&](const int first, const int all) __attribute__((always_inline)) {      // steps first .. first + all - 1 of the weight
+            const int from = all * part >> kb;
+            steps = (all * (part + 1) >> kb) - from;
+            share = __builtin_amdgcn_make_buffer_rsrc((void*)(a.records + (int64_t)(first + from) * RECORD_BYTES), 0, steps * RECORD_BYTES, 0x00020000);
         };
-        // part `p` of `n` steps
-        auto share = [&](const int n, const int p) { return n * p / ks; };
-        // round 0 of the first row tile: requested up to the longest tile's length, before the bounds have arrived
-        const bool early = a.tile_steps != 0 && a.K <= RES && tile0 < a.ntiles;
-        if (early) {
-            s_begin = tile0 * a.tile_steps + share(a.tile_steps, part);
-            const int most = share(a.tile_steps, part + 1) - share(a.tile_steps, part), last = s_begin + max(most - 1, 0);
+        auto w_load = [&](v4i (&w)[CH], uint32_t (&rows)[CH], const int step) __attribute__((always_inline)) {
+#pragma unroll
+            for (int j = 0; j < CH; ++j) rows[j] = __builtin_amdgcn_raw_buffer_load_b32(share, row_at + j * RECORD_BYTES, step * RECORD_BYTES, 0);
+#pragma unroll
+            for (int j = 0; j < CH; ++j)
+                w[j] = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(share, val_at + j * RECORD_BYTES, step * RECORD_BYTES, 0));
+        };
+        auto w_first = [&]() __attribute__((always_inline)) {
 #pragma unroll
             for (int k = 0; k < NS; ++k)
-                if (k == 0 || k * CH < most) w_load(A[k], I[k], s_begin + k * CH, last);
-            s_end = s_begin + most;
-        }
-
-        // the same for the round of segments seg0 .. seg0 + SEGS - 1, from the bounds
-        auto begin = [&](const int r, const int seg0) __attribute__((always_inline)) {
-            const int32_t* const b = a.bounds + (int64_t)(tile0 + r) * (a.nseg + 1);
-            const int b0 = b[seg0], n = b[min(seg0 + SEGS, a.nseg)] - b0;
-            s_begin = b0 + share(n, part);
-            s_end = b0 + share(n, part + 1);
-#pragma unroll
-            for (int k = 0; k < NS; ++k)
-                if (s_begin + k * CH < s_end) w_load(A[k], I[k], s_begin + k * CH, s_end - 1);
+                if (k == 0 || k * CH < steps) w_load(A[k], I[k], k * CH);
         };
 
-        // ---- activations of the round that starts at row r0: 16-byte pieces, all requested at once (x_load) and
-        // written to LDS as x - 128 (x_store).  Rows past K repeat the last one of their pass (never multiplied).
-        v4i xs[PASSES];
-        const int x_row = tid / PIECES, x_col = tok0 + tid % PIECES * 16;
-        auto x_load = [&](const int r0) __attribute__((always_inline)) {
-#pragma unroll
-            for (int u = 0; u < PASSES; ++u) {
-                const int k0 = r0 + u * PASS_ROWS;
-                if (k0 < a.K && a.x_fast) {
-                    const RaggedPieces<> pieces(a, k0, PASS_ROWS - 1);
-                    xs[u] = pieces.load(min(x_row, a.K - k0 - 1), x_col);
-                }
-            }
-        };
-        auto x_store = [&](const int r0) __attribute__((always_inline)) {
-            const uint32_t at = row_offset((uint32_t)x_row) ^ (uint32_t)(tid % PIECES * 16);
-            if (__builtin_expect(a.x_fast, 1)) {
-                const bool cut = tok0 + TM > a.M && a.x_tile_stride == 0;      // (tile-major rows are padded)
-#pragma unroll
-                for (int u = 0; u < PASSES; ++u) {
-                    const int k0 = r0 + u * PASS_ROWS;
-                    if (k0 < a.K) {
-                        if (__builtin_expect(cut, 0)) {
-                            const RaggedPieces<> pieces(a, k0, min(PASS_ROWS, a.K - k0) - 1);
-                            if (!pieces.inside) xs[u] = pieces.shifted(xs[u], min(x_row, a.K - k0 - 1), x_col);
-                        }
-                        *(v4i*)(lds + at + u * PASS_ROWS * TM) = xs[u] ^ (v4i){FLIP, FLIP, FLIP, FLIP};
-                    }
-                }
-            } else {
-#pragma unroll 1
-                for (int k0 = r0; k0 < min(r0 + RES, a.K); k0 += PASS_ROWS)
-                    *(v4i*)(lds + at + (k0 - r0) * TM) =
-                        load_x16_far(a, min(k0 + x_row, a.K - 1), x_col) ^ (v4i){FLIP, FLIP, FLIP, FLIP};
-            }
-        };
-        x_load(0);
-
-        // ---- per-row constants, table, operand of Sum
         v4i acc[R][PIECES];
+        int rowsum[R];
         float scale[R], bias[R];
         v4f sum4[R][PIECES];
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-            const int n = (tile0 + r) * TILE_ROWS + c;
-            int init = 0;
-            scale[r] = bias[r] = 0.0f;
-            if (part == 0 && tile0 + r < a.ntiles) {
-                init = a.rowsum[n] * a.corr_mul;
-                if (OUT != SPMM_OUT_S32 && n < a.N) {
-                    scale[r] = a.w_scale[n] * a.x_scale;
-                    if (a.bias) bias[r] = a.bias[n];
-                }
-            }
-#pragma unroll
-            for (int i = 0; i < PIECES; ++i) {
-                acc[r][i] = (v4i){init, init, init, init};
-                sum4[r][i] = (v4f){0.0f, 0.0f, 0.0f, 0.0f};
-                const int m0 = tok0 + 16 * i + 4 * g;
-                if (SUM && !SUM_LATE && part == 0 && n < a.N && m0 < a.M) sum4[r][i] = load_sum4<POST>(a, n, m0);
-            }
-        }
         int table_byte = 0;
-        if (TABLE && tid < 256) table_byte = a.lut[tid];
-
-        if (!early && tile0 < a.ntiles) begin(0, 0);
-        x_store(0);
-        if (TABLE && tid < 256) lds[RES * TM + tid] = (uint8_t)table_byte;
-        __syncthreads();
-
-        for (int r0 = 0, seg0 = 0; r0 < a.K; r0 += RES, seg0 += SEGS) {
+        // ---- per-row constants, table, operand of Sum: requested, used when the last step has been multiplied
+        auto constants = [&]() __attribute__((always_inline)) {
 #pragma unroll
             for (int r = 0; r < R; ++r) {
-                const int tile = tile0 + r;
-                if (tile < a.ntiles) {
-                    if (r > 0) begin(r, seg0);
-                    else if (early) s_end = min(s_end, a.bounds[(int64_t)tile * (a.nseg + 1) + a.nseg]);
-                    for (int s = s_begin; s < s_end; s += NS * CH) {
+                const int n = (tile0 + r) * TILE_ROWS + c, nn = min(n, a.N - 1);      // (rows past the last one are not stored)
+                rowsum[r] = a.rowsum[nn];
+                scale[r] = bias[r] = 0.0f;
+                if constexpr (OUT != SPMM_OUT_S32) {
+                    scale[r] = a.w_scale[nn];
+                    if (a.bias) bias[r] = a.bias[nn];
+                }
 #pragma unroll
-                        for (int k = 0; k < NS; ++k) {
-                            const int at = s + k * CH;
-                            if (at < s_end) {
-                                v2i x[CH][PIECES][2];
+                for (int i = 0; i < PIECES; ++i) {
+                    acc[r][i] = (v4i){0, 0, 0, 0};
+                    sum4[r][i] = (v4f){0.0f, 0.0f, 0.0f, 0.0f};
+                    const int m0 = tok0 + 16 * i + 4 * g;
+                    if (SUM && !SUM_LATE && part == 0 && n < a.N && m0 < a.M) sum4[r][i] = load_sum4<POST>(a, n, m0);
+                }
+            }
+            if (TABLE && tid < 256) table_byte = a.lut[tid];
+        };
+
+        // ---- activations: 16-byte pieces, written to LDS as x - 128
+        const int x_row = tid / PIECES, x_col = tok0 + tid % PIECES * 16;
+        const uint32_t x_lds = row_offset((uint32_t)x_row) ^ (uint32_t)(tid % PIECES * 16);
+        const bool cut = tok0 + TM > a.M && a.x_tile_stride == 0;      // (tile-major rows are padded)
+        constexpr v4i FLIPS = {FLIP, FLIP, FLIP, FLIP};
+
+        // ---- multiply the share of row tile r
+        auto multiply = [&](const int r) __attribute__((always_inline)) {
+            for (int s = 0; s < steps; s += NS * CH) {
 #pragma unroll
-                                for (int j = 0; j < CH; ++j) {
-                                    // (a row of a step past the end may lie anywhere in the weight: kept inside the buffer)
-                                    constexpr uint32_t mask = RES - 1;
-                                    const uint32_t o0 = row_offset(I[k][j] & mask) + (c & 1) * 8;
-                                    const uint32_t o1 = row_offset(I[k][j] >> 16 & mask) + (c & 1) * 8;
+                for (int k = 0; k < NS; ++k) {
+                    const int at = s + k * CH;
+                    if (at < steps) {
+                        v2i x[CH][PIECES][2];
 #pragma unroll
-                                    for (int i = 0; i < PIECES; ++i) {
-                                        x[j][i][0] = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_v2i_ptr)(lds + (o0 ^ 16 * i)));
-                                        x[j][i][1] = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_v2i_ptr)(lds + (o1 ^ 16 * i)));
-                                    }
-                                }
+                        for (int j = 0; j < CH; ++j) {
+                            constexpr uint32_t mask = RES - 1;
+                            const uint32_t o0 = row_offset(I[k][j] & mask) + (c & 1) * 8;
+                            const uint32_t o1 = row_offset(I[k][j] >> 16 & mask) + (c & 1) * 8;
 #pragma unroll
-                                for (int j = 0; j < CH; ++j) {
-                                    const v4i w = at + j < s_end ? A[k][j] : (v4i){0, 0, 0, 0};
-#pragma unroll
-                                    for (int i = 0; i < PIECES; ++i) {
-                                        const v4i xa = {x[j][i][0][0], x[j][i][0][1], x[j][i][1][0], x[j][i][1][1]};
-                                        acc[r][i] = __builtin_amdgcn_mfma_i32_16x16x64_i8(xa, w, acc[r][i], 0, 0, 0);
-                                    }
-                                }
-                                if (at + NS * CH < s_end) w_load(A[k], I[k], at + NS * CH, s_end - 1);
+                            for (int i = 0; i < PIECES; ++i) {
+                                x[j][i][0] = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_v2i_ptr)(lds + (o0 ^ 16 * i)));
+                                x[j][i][1] = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_v2i_ptr)(lds + (o1 ^ 16 * i)));
                             }
                         }
+                        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                        for (int j = 0; j < CH; ++j) {
+#pragma unroll
+                            for (int i = 0; i < PIECES; ++i) {
+                                const v4i xa = {x[j][i][0][0], x[j][i][0][1], x[j][i][1][0], x[j][i][1][1]};
+                                acc[r][i] = __builtin_amdgcn_mfma_i32_16x16x64_i8(xa, A[k][j], acc[r][i], 0, 0, 0);
+                            }
+                        }
+                        if (at + NS * CH < steps) w_load(A[k], I[k], at + NS * CH);
                     }
                 }
             }
-            if (r0 + RES < a.K) {
-                x_load(r0 + RES);
-                if (tile0 < a.ntiles) begin(0, seg0 + SEGS);
-                __syncthreads();   // everyone has finished reading this round
-                x_store(r0 + RES);
-                __syncthreads();
+        };
+        // row tile r, segments seg0 .. seg0 + SEGS - 1 (placed: all of it, where tile_steps says; the records past its own are zero)
+        auto begin = [&](const int r, const int seg0, const bool placed = false) __attribute__((always_inline)) {
+            int first = (tile0 + r) * a.tile_steps, count = a.tile_steps;
+            if (!placed) {
+                const int32_t* const b = a.bounds + (int64_t)min(tile0 + r, a.ntiles - 1) * (a.nseg + 1);
+                first = b[seg0];
+                count = b[min(seg0 + SEGS, a.nseg)] - first;
             }
+            w_open(first, have ? count : 0);
+            w_first();
+        };
+
+        // All of K resident, and 32-bit offsets: no wait from the first request to the first piece written, and no branch on the way
+        // to it, for 1, 2, 4 .. passes of rows.
+        auto all_at_once = [&](auto PASSES_) __attribute__((always_inline)) {
+            constexpr int P = PASSES_.value;
+            v4i xs[P];
+            // (rows past K, never multiplied, read what lies there, or the matrix's last bytes)
+            const uint32_t x_at = (uint32_t)x_row * (uint32_t)a.ldx + (uint32_t)xcol(a, TM == 16 || x_col < a.M ? x_col : 0);
+#pragma unroll
+            for (int u = 0; u < P; ++u)
+                xs[u] = load16_any(a.X + min(x_at + (uint32_t)(u * PASS_ROWS) * (uint32_t)a.ldx, (uint32_t)a.x_last16));
+            begin(0, 0, a.tile_steps != 0);
+            constants();
+            auto store = [&]() __attribute__((always_inline)) {
+#pragma unroll
+                for (int u = 0; u < P; ++u) *(v4i*)(lds + x_lds + u * PASS_ROWS * TM) = xs[u] ^ FLIPS;
+            };
+            if (__builtin_expect(cut, 0)) {
+                const RaggedPieces<> last(a, 0, a.K - 1);      // (all of it as one segment; the last rows' pieces are shifted)
+                if (!last.inside) {
+#pragma unroll
+                    for (int u = 0; u < P; ++u) xs[u] = last.shifted(xs[u], min(x_row + u * PASS_ROWS, a.K - 1), x_col);
+                }
+                store();
+            } else {
+                store();
+            }
+            if (TABLE && tid < 256) lds[TABLE_AT + tid] = (uint8_t)table_byte;
+            __syncthreads();
+            multiply(0);
+            if (R == 2 && tile0 + 1 < a.ntiles) {
+                begin(1, 0);
+                multiply(1);
+            }
+        };
+        // (K round by round; far rows: the plan takes this kernel for neither where another one runs)
+        auto by_rounds = [&]() __attribute__((always_inline)) {
+            constants();
+            if (TABLE && tid < 256) lds[TABLE_AT + tid] = (uint8_t)table_byte;
+#pragma unroll 1
+            for (int r0 = 0, seg0 = 0; r0 < a.K; r0 += RES, seg0 += SEGS) {
+                if (r0 > 0) __syncthreads();   // everyone has finished reading the last round
+#pragma unroll 1
+                for (int k0 = r0; k0 < min(r0 + RES, a.K); k0 += PASS_ROWS) {
+                    const int row = min(x_row, a.K - k0 - 1);   // rows past K repeat the last one (never multiplied)
+                    v4i x;
+                    if (a.x_fast) {
+                        const RaggedPieces<> pieces(a, k0, min(PASS_ROWS, a.K - k0) - 1);
+                        x = pieces.load(row, x_col);
+                        if (cut && !pieces.inside) x = pieces.shifted(x, row, x_col);
+                    } else {
+                        x = load_x16_far(a, k0 + row, x_col);
+                    }
+                    *(v4i*)(lds + x_lds + (k0 - r0) * TM) = x ^ FLIPS;
+                }
+                begin(0, seg0);
+                __syncthreads();
+                multiply(0);
+                if (R == 2 && tile0 + 1 < a.ntiles) {
+                    begin(1, seg0);
+                    multiply(1);
+                }
+            }
+        };
+        if (__builtin_expect(a.K <= RES && a.x_fast && a.x_last16 < 0x40000000, 1)) {
+            const int passes = (a.K + PASS_ROWS - 1) / PASS_ROWS;
+            if (passes <= 1) all_at_once(std::integral_constant<int, 1>{});
+            else if (passes <= 2) all_at_once(std::integral_constant<int, 2>{});
+            else if (PASSES == 4 || passes <= 4) all_at_once(std::integral_constant<int, 4>{});
+            else all_at_once(std::integral_constant<int, PASSES>{});
+        } else {
+            by_rounds();
         }
 
-        if (R == 1 && ks > 1) {
-            v4i* const sums = (v4i*)lds + wave * PIECES * 64 + lane;
-            __syncthreads();
+        if (SHARES && kb > 0) {
+            v4i* const sums = (v4i*)(lds + SUMS_AT) + (local * ((1 << kb) - 1) - 1) * PIECES * 64 + lane;      // (of part 0; part 1 is the first)
             if (part > 0) {
 #pragma unroll
-                for (int i = 0; i < PIECES; ++i) sums[i * 64] = acc[0][i];
+                for (int i = 0; i < PIECES; ++i) sums[(part * PIECES + i) * 64] = acc[0][i];
             }
             __syncthreads();
             if (part > 0) return;
-            for (int q = 1; q < ks; ++q)
+            for (int q = 1; q < 1 << kb; ++q)
 #pragma unroll
                 for (int i = 0; i < PIECES; ++i) acc[0][i] = acc[0][i] + sums[(q * PIECES + i) * 64];
         }
 
-        const LdsTable lut{lds + RES * TM};
+        const LdsTable lut{lds + TABLE_AT};
 #pragma unroll
         for (int r = 0; r < R; ++r) {
             const int n = (tile0 + r) * TILE_ROWS + c;
@@ -1419,10 +1451,12 @@ struct Resident {
                     if (m0 < a.M) sum4[r][i] = load_sum4<POST>(a, n, m0);
                 }
             }
+            const int init = rowsum[r] * a.corr_mul;
 #pragma unroll
             for (int i = 0; i < PIECES; ++i) {
                 const int m0 = tok0 + 16 * i + 4 * g;
-                if (m0 < a.M) finish4<OUT, POST, true>(a, acc[r][i], scale[r], bias[r], n, m0, lut, sum4[r][i]);
+                const v4i sum = acc[r][i] + (v4i){init, init, init, init};
+                if (m0 < a.M) finish4<OUT, POST, true>(a, sum, scale[r] * a.x_scale, bias[r], n, m0, lut, sum4[r][i]);
             }
         }
     }

@@ -140,6 +140,19 @@ static inline void emu_buffer_store(const V v, const emu_buffer_rsrc r, const in
 }
 #define __builtin_amdgcn_raw_buffer_store_b128(v, r, vo, so, aux) emu_buffer_store((v), (r), (vo), (so))
 #define __builtin_amdgcn_raw_buffer_store_b32(v, r, vo, so, aux) emu_buffer_store((v), (r), (vo), (so))
+// ... and loads, which are zero beyond the end (whole dwords: the kernels' are aligned)
+template <typename V>
+static inline V emu_buffer_load(const emu_buffer_rsrc r, const int voff, const int soff)
+{
+    const uint64_t off = (uint64_t)(uint32_t)voff + (uint32_t)soff;
+    V v = {};
+    for (size_t i = 0; i < sizeof(V); i += 4)
+        if (off + i + 4 <= r.bytes) memcpy((uint8_t*)&v + i, r.base + off + i, 4);
+    return v;
+}
+typedef unsigned int emu_v4u __attribute__((vector_size(16)));
+#define __builtin_amdgcn_raw_buffer_load_b128(r, vo, so, aux) emu_buffer_load<emu_v4u>((r), (vo), (so))
+#define __builtin_amdgcn_raw_buffer_load_b32(r, vo, so, aux) emu_buffer_load<uint32_t>((r), (vo), (so))
 using std::min;
 using std::max;
 

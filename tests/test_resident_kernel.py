@@ -1,0 +1,68 @@
+"""The short-batch kernels that keep all of K in LDS: every number of passes of activation rows and one row more, rows cut by the
+end of the matrix in each of them, weights whose tiles are too uneven for a fixed place, K in rounds, activations beyond 1 GiB."""
+import os
+import sys
+
+import numpy as np
+import pytest
+
+import paper_2306_16601_amd as sp
+import workloads as wl
+
+sys.path.insert(0, os.path.join(os.path.dirname(os.path.abspath(__file__)), "emu"))
+import build_emu  # noqa: E402
+from test_emulated_kernels import run_case  # noqa: E402
+
+# (token tile, variant, rows of a pass, resident rows)
+KERNELS = [(16, 101, 512, 2048), (16, 105, 512, 2048), (32, 106, 256, 2048), (32, 101, 256, 2048), (64, 101, 128, 1024), (64, 102, 128, 1024),
+           (16, 103, 512, 4096), (16, 106, 512, 4096)]
+
+
+def ks(rows, resident):
+    passes = [1, 2, 3, 4, 5, 8]
+    return sorted({k for p in passes if p * rows <= resident for k in (p * rows, p * rows + 1)} | {3, resident - 1, resident, resident + 1})
+
+
+@pytest.mark.skipif(not build_emu.available(), reason="no host clang++ for the emulation build")
+@pytest.mark.parametrize("tm,variant,K,M,kind", [
+    (16, 101, 513, 21, "uniform"), (16, 105, 1025, 37, "ragged"), (32, 106, 257, 45, "uniform"), (32, 101, 1030, 70, "ragged"),
+    (64, 101, 129, 67, "uniform"), (64, 102, 1025, 65, "ragged"), (16, 106, 2600, 29, "uniform"), (16, 103, 4097, 17, "ragged")])
+def test_on_the_cpu(tm, variant, K, M, kind):
+    build_emu.build()
+    res = run_case(144, K, M, 0.8, "s8", "none", tm, variant, kind=kind)
+    assert res["match"] and res["padding_untouched"], res
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("tm,variant,rows,resident", KERNELS)
+def test_passes_on_the_device(tm, variant, rows, resident):
+    from test_gpu_parity import check_case
+    outs = [("s32", "none"), ("f32", "none"), ("u8", "gelu"), ("s8", "none")]
+    for i, K in enumerate(ks(rows, resident)):
+        out_type, postop = outs[i % 4]
+        M = tm * (1 + i % 2) + (i * 5) % tm + 1
+        case = wl.Case("resident", 80 + 16 * (i % 5), K, M, 0.8, wl.N4K1, out_type, postop, keys=(130, K, M))
+        check_case(case, tuning=(tm, variant))
+        check_case(case, tuning=(tm, variant), ldx=M + 3, ldo=M + 5)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("tm,variant", [(16, 101), (32, 106), (64, 101)])
+def test_activations_beyond_a_gibibyte(tm, variant):
+    import torch
+    N, K, M, ld = 64, 300, 45, (1 << 22) - 3
+    rng = np.random.default_rng(131)
+    h = sp.spmm_pack(rng.integers(-127, 128, size=(N, K), dtype=np.int8))
+    try:
+        x = torch.from_numpy(rng.integers(0, 256, size=(K, M), dtype=np.uint8)).cuda()
+        far = torch.empty((K - 1) * ld + M, dtype=torch.uint8, device="cuda")
+        far.as_strided((K, M), (ld, 1)).copy_(x)
+        ep = sp.make_epilogue(None, 1.0, 0, None, "none", "s32")
+        out = [torch.zeros((N, M), dtype=torch.int32, device="cuda") for _ in range(2)]
+        sp.spmm_set_tuning(h, tm, variant)
+        for X, ldx, o in ((x, M, out[0]), (far, ld, out[1])):
+            sp.spmm_run(h, X, M, ldx, ep, o, M, torch.cuda.current_stream().cuda_stream)
+        torch.cuda.synchronize()
+        assert torch.equal(out[0], out[1]) and out[0].any()
+    finally:
+        sp.spmm_destroy(h)
