@@ -98,3 +98,21 @@ def test_weight_requests_of_int32_outputs_wait_for_no_stores(tmp_path, waves, sl
                        capture_output=True)
         waits.append(len(re.findall(r"s_waitcnt vmcnt\(0\)\s", asm.read_text())))
     assert waits[0] <= waits[1], waits
+
+
+@pytest.mark.skipif(not os.path.exists(HIPCC), reason="no hipcc")
+@pytest.mark.parametrize("kernel", ["simple<16, 8, 1", "simple<32, 8, 1", "simple<64, 8, 1", "simple<64, 8, 2", "slab<16, 8"])
+def test_a_table_costs_the_resident_kernels_no_loops_over_lanes(tmp_path, kernel):
+    """The weights come through a buffer resource, the same in all lanes.  Where the compiler cannot tell, it reads the resource
+    lane by lane, in a loop around each load: the kernels with a table must have no more of that than those without, and read
+    the bounds that it is made of by scalar loads as they do."""
+    src, asm = tmp_path / "k.hip", tmp_path / "k.s"
+    src.write_text('#include "spmm_kernels.h"\nnamespace spmm {\n' + "".join(
+        "template __global__ void spmm_rowtile_mfma_%s, SPMM_OUT_U8, %s>(const KernelArgs);\n" % (kernel, post)
+        for post in ("SPMM_POST_NONE", "SPMM_POST_GELU")) + "}\n")
+    subprocess.run([HIPCC, *B.HIPCC_FLAGS, "-x", "hip", "--cuda-device-only", "-S", str(src), "-o", str(asm)], check=True, capture_output=True)
+    plain, table = (re.split(r"^; -- End function|^\s*\.end_amdhsa_kernel", k, flags=re.M)[0]
+                    for k in re.split(r"^\s*\.globl\s+_ZN4spmm", asm.read_text(), flags=re.M)[1:3])
+    lanes, scalar = ([len(re.findall(op, k)) for k in (plain, table)] for op in (r"\bv_readfirstlane_b32\b", r"\bs_load_dword"))
+    assert lanes[1] <= lanes[0] + 8, lanes
+    assert scalar[1] >= scalar[0], scalar
