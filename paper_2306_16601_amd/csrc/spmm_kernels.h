@@ -154,6 +154,15 @@ __device__ __forceinline__ T pinned(T v)
     return v;
 }
 
+// The same for a loop over `turn`, a uniform value that changes with every turn.  (pinned counts as a write to memory: what a
+// uniform address is read for after it comes through vector loads, not scalar ones.)
+template <typename T>
+__device__ __forceinline__ T pinned_in_turn(T v, const int turn)
+{
+    asm("" : "+v"(v) : "s"(turn));
+    return v;
+}
+
 constexpr int FLIP = (int)0x80808080;   // x ^ 0x80 == x - 128 as a signed byte
 
 // GELU in its erf form, y * Phi(y) = 0.5 * y * erfc(-y / sqrt(2)), in binary32, branch-free.
@@ -1391,26 +1400,45 @@ struct Resident {
                 multiply(1);
             }
         };
-        // (K round by round; far rows: the plan takes this kernel for neither where another one runs)
-        auto by_rounds = [&]() __attribute__((always_inline)) {
+        // K round by round, and rows that one 32-bit offset does not reach: here too a round's activations and weights are all
+        // requested before anything waits (1024x4096 at 80 %, 256 tokens, 64-token tiles: 14.9 us, pass after pass and the
+        // weights last 18.8).  Only FAR rows, beyond the offsets of a single pass, or an X of less than 16 bytes, come piece by
+        // piece; code of their own keeps the registers of the others within 128.
+        auto by_rounds = [&](auto FAR_) __attribute__((always_inline)) {
+            constexpr bool FAR = FAR_.value;
             constants();
 #pragma unroll 1
             for (int r0 = 0, seg0 = 0; r0 < a.K; r0 += RES, seg0 += SEGS) {
-                if (r0 > 0) __syncthreads();   // everyone has finished reading the last round
-#pragma unroll 1
-                for (int k0 = r0; k0 < min(r0 + RES, a.K); k0 += PASS_ROWS) {
-                    const int row = min(x_row, a.K - k0 - 1);   // rows past K repeat the last one (never multiplied)
-                    v4i x;
-                    if (a.x_fast) {
-                        const RaggedPieces<> pieces(a, k0, min(PASS_ROWS, a.K - k0) - 1);
-                        x = pieces.load(row, x_col);
-                        if (cut && !pieces.inside) x = pieces.shifted(x, row, x_col);
-                    } else {
-                        x = load_x16_far(a, k0 + row, x_col);
+                const int t = pinned_in_turn(tid, r0), row = t / PIECES, col = tok0 + t % PIECES * 16;
+                uint8_t* const to = lds + (row_offset((uint32_t)row) ^ (uint32_t)(t % PIECES * 16));
+                // (rows past K repeat the last one of their pass, never multiplied)
+                v4i xs[PASSES];
+                if constexpr (!FAR) {
+#pragma unroll
+                    for (int u = 0; u < PASSES; ++u) {
+                        const int left = a.K - r0 - u * PASS_ROWS;
+                        if (left > 0) xs[u] = RaggedPieces<>(a, a.K - left, PASS_ROWS - 1).load(min(row, left - 1), col);
                     }
-                    *(v4i*)(lds + x_lds + (k0 - r0) * TM) = x ^ FLIPS;
                 }
                 begin(0, seg0);
+                if (r0 > 0) __syncthreads();   // everyone has finished reading the last round
+                if constexpr (!FAR) {
+#pragma unroll
+                    for (int u = 0; u < PASSES; ++u) {
+                        const int left = a.K - r0 - u * PASS_ROWS;
+                        if (left > 0) {
+                            if (__builtin_expect(cut, 0)) {
+                                const RaggedPieces<> pieces(a, a.K - left, min(PASS_ROWS, left) - 1);
+                                if (!pieces.inside) xs[u] = pieces.shifted(xs[u], min(row, left - 1), col);
+                            }
+                            *(v4i*)(to + u * PASS_ROWS * TM) = xs[u] ^ FLIPS;
+                        }
+                    }
+                } else {
+#pragma unroll 1
+                    for (int k0 = r0; k0 < min(r0 + RES, a.K); k0 += PASS_ROWS)
+                        *(v4i*)(to + (k0 - r0) * TM) = load_x16_far(a, min(k0 + row, a.K - 1), col) ^ FLIPS;
+                }
                 __syncthreads();
                 multiply(0);
                 if (R == 2 && tile0 + 1 < a.ntiles) {
@@ -1430,8 +1458,10 @@ struct Resident {
             else if (passes <= 2) all_at_once(std::integral_constant<int, 2>{});
             else if (PASSES == 4 || passes <= 4) all_at_once(std::integral_constant<int, 4>{});
             else all_at_once(std::integral_constant<int, PASSES>{});
+        } else if (a.x_fast) {
+            by_rounds(std::false_type{});
         } else {
-            by_rounds();
+            by_rounds(std::true_type{});
         }
 
         if (SHARES && kb > 0) {

@@ -54,7 +54,7 @@ def build(force: bool = False) -> str:
     csrc = os.path.join(ROOT, "paper_2306_16601_amd", "csrc")
     for f in os.listdir(csrc):
         s = open(os.path.join(csrc, f)).read()
-        s = re.sub(r'asm volatile\(""\s*:\s*"\+v"\((\w+)\)\);', r'(void)\1;', s)
+        s = re.sub(r'asm(?: volatile)?\(""\s*:\s*"\+v"\((\w+)\)(?:\s*:\s*"s"\(\w+\))?\);', r'(void)\1;', s)
         s = s.replace('const v4i v = *(const v4i*)(lds + raddr);',
                       'emu::wave_barrier(); const v4i v = *(const v4i*)(lds + raddr); emu::wave_barrier();')
         s = s.replace('__atomic_fetch_add(', 'emu::count_up(')

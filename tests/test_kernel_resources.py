@@ -116,3 +116,17 @@ def test_a_table_costs_the_resident_kernels_no_loops_over_lanes(tmp_path, kernel
     lanes, scalar = ([len(re.findall(op, k)) for k in (plain, table)] for op in (r"\bv_readfirstlane_b32\b", r"\bs_load_dword"))
     assert lanes[1] <= lanes[0] + 8, lanes
     assert scalar[1] >= scalar[0], scalar
+
+
+@pytest.mark.skipif(not os.path.exists(HIPCC), reason="no hipcc")
+@pytest.mark.parametrize("kernel, passes", [("simple<16, 8, 1", 4), ("simple<32, 8, 1", 8), ("simple<64, 8, 1", 8), ("slab<16, 8", 8)])
+def test_rounds_of_k_request_their_activations_together(tmp_path, kernel, passes):
+    """A request for each pass of activation rows where K is resident, and as many for K in rounds (and rows too far apart for one
+    32-bit offset), not one that every pass waits for; beside them one where a single pass holds K, and one for rows beyond the
+    offsets of a pass.  (The compiler joins the requests that the starts for other numbers of passes share.)"""
+    src, asm = tmp_path / "k.hip", tmp_path / "k.s"
+    src.write_text('#include "spmm_kernels.h"\nnamespace spmm { template __global__ void spmm_rowtile_mfma_%s, SPMM_OUT_S32, 0>'
+                   "(const KernelArgs); }\n" % kernel)
+    subprocess.run([HIPCC, *B.HIPCC_FLAGS, "-x", "hip", "--cuda-device-only", "-S", str(src), "-o", str(asm)], check=True, capture_output=True)
+    requests = len(re.findall(r"\bglobal_load_dwordx4\b", asm.read_text()))
+    assert requests >= 2 * passes + 2, requests
