@@ -66,3 +66,29 @@ def test_activations_beyond_a_gibibyte(tm, variant):
         assert torch.equal(out[0], out[1]) and out[0].any()
     finally:
         sp.spmm_destroy(h)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("K, M, ld", [
+    (601, 262, 3579139),                    # the last 16 bytes at 2^31 - 2, the largest offset of the straight start
+    (601, 263, 3579139),                    # ... and at 2^31 - 1, one beyond it
+    (1025, 45, (1 << 22) - 3)])             # 4 GiB; one row more than the 64-token kernel keeps
+@pytest.mark.parametrize("tm,variant", [(16, 101), (16, 103), (32, 106), (64, 101), (64, 102)])
+def test_activations_at_the_last_32_bit_offset(tm, variant, K, M, ld):
+    import torch
+    N = 83
+    rng = np.random.default_rng(131)
+    h = sp.spmm_pack(rng.integers(-127, 128, size=(N, K), dtype=np.int8))
+    try:
+        x = torch.from_numpy(rng.integers(0, 256, size=(K, M), dtype=np.uint8)).cuda()
+        far = torch.empty((K - 1) * ld + M, dtype=torch.uint8, device="cuda")
+        far.as_strided((K, M), (ld, 1)).copy_(x)
+        ep = sp.make_epilogue(None, 1.0, 0, None, "none", "s32")
+        out = [torch.zeros((N, M), dtype=torch.int32, device="cuda") for _ in range(2)]
+        sp.spmm_set_tuning(h, tm, variant)
+        for X, ldx, o in ((x, M, out[0]), (far, ld, out[1])):
+            sp.spmm_run(h, X, M, ldx, ep, o, M, torch.cuda.current_stream().cuda_stream)
+        torch.cuda.synchronize()
+        assert torch.equal(out[0], out[1]) and out[0].any()
+    finally:
+        sp.spmm_destroy(h)
