@@ -108,10 +108,12 @@ v2i_t tr8(const void* p)
     memcpy(&r, out, 8);
     return r;
 }
+static std::atomic<long> products{0};      // of mfma_i8_16x16x64 by a wave, since the library was loaded
 v4i_t mfma_i8_16x16x64(v4i_t a, v4i_t b, v4i_t c)
 {
     Wave& w = my_wave();
     const int lane = cur()->linear & 63;
+    if (lane == 0) ++products;
     w.a[lane] = a;
     w.b[lane] = b;
     wave_sync(w, "mfma (deposit)");
@@ -386,5 +388,6 @@ struct Install { Install() {
 extern "C" int spmm_measure_peak(int, double*) { return 2; /* SPMM_E_UNSUPPORTED */ }
 extern "C" void* emu_alloc(size_t bytes) { return emu::dev_alloc(bytes); }
 extern "C" void emu_fail_mallocs(unsigned which) { emu::failing_mallocs = which; }
+extern "C" long emu_products() { return emu::products; }
 extern "C" long emu_allocations() { return (long)emu::allocs.size(); }
 extern "C" void emu_free(void* p) { emu::dev_free(p); }

@@ -53,6 +53,9 @@ def main():
             W[80:96] = wl.rng_for(5, N, K).integers(1, 127, size=(16, K), dtype=np.int8)
         if N > 128:
             W[112:128, : max(0, K - 500)] = 0
+    if kind == "uneven":
+        # one row tile whose step list is longer than the others', which lie at fixed places all the same
+        W[16:, K - K // 4:] = 0
     if kind == "empty":
         # no blocks in the first rows, in the middle of K (more than a segment), in the last rows' first segment
         W[: min(N, 64)] = 0
@@ -109,7 +112,7 @@ def main():
     else:
         ok = bool(np.array_equal(got, ref))
     pad_ok = bool((full[:, M:].view(np.uint8) == 0x5A).all())
-    print(json.dumps({"match": ok, "padding_untouched": pad_ok, "kernel": sp.spmm_kernel_variant(h, M, ot, po),
+    print(json.dumps({"match": ok, "padding_untouched": pad_ok, "kernel": sp.spmm_kernel_variant(h, M, ot, po), "products": L.emu_products(),
                       "mismatches": int((got != ref).sum())}))
 
 

@@ -33,6 +33,19 @@ def test_on_the_cpu(tm, variant, K, M, kind):
     assert res["match"] and res["padding_untouched"], res
 
 
+@pytest.mark.skipif(not build_emu.available(), reason="no host clang++ for the emulation build")
+@pytest.mark.parametrize("tm,variant,K,group", [(16, 101, 2048, 4), (32, 101, 2048, 2), (64, 101, 1024, 2), (64, 102, 1024, 2), (16, 103, 4096, 4)])
+def test_steps_that_a_tile_does_not_have_are_not_multiplied(tm, variant, K, group):
+    """Steps are requested up to the longest tile's number, before the bounds have arrived.  The ring multiplies just those that
+    there are; the resident kernels whole groups of them, and no more."""
+    build_emu.build()
+    N, M = 160, 50
+    res, ring = (run_case(N, K, M, 0.7, "s32", "none", tm, v, kind="uneven") for v in (variant, 104))
+    assert res["match"] and ring["match"], (res, ring)
+    slack = N // 16 * (group - 1) * -(-M // tm) * tm // 16
+    assert ring["products"] <= res["products"] <= ring["products"] + slack, (res, ring)
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("tm,variant,rows,resident", KERNELS)
 def test_passes_on_the_device(tm, variant, rows, resident):
