@@ -1,5 +1,6 @@
 """The short-batch kernels that keep all of K in LDS: every number of passes of activation rows and one row more, rows cut by the
-end of the matrix in each of them, weights whose tiles are too uneven for a fixed place, K in rounds, activations beyond 1 GiB."""
+end of the matrix in each of them, row-major and tile-major, weights whose tiles are uneven but placed or too uneven for that, Sum, K
+in rounds, activations that span gibibytes."""
 import os
 import sys
 
@@ -57,6 +58,53 @@ def test_passes_on_the_device(tm, variant, rows, resident):
         case = wl.Case("resident", 80 + 16 * (i % 5), K, M, 0.8, wl.N4K1, out_type, postop, keys=(130, K, M))
         check_case(case, tuning=(tm, variant))
         check_case(case, tuning=(tm, variant), ldx=M + 3, ldo=M + 5)
+
+
+def thinned(d, kind):
+    """Row tiles of very different lengths: one 1.3 times as long as the others, or step lists too uneven for a fixed place."""
+    W = d["W"] = d["W"].copy()
+    if kind == "uneven":
+        W[16:, W.shape[1] - W.shape[1] // 4:] = 0
+    elif kind == "ragged":
+        W[16:64] = 0
+        W[64:, :max(0, W.shape[1] - 300)] = 0
+    return d
+
+
+@pytest.mark.skipif(not build_emu.available(), reason="no host clang++ for the emulation build")
+@pytest.mark.parametrize("tm,variant,K", [(16, 105, 520), (16, 103, 2100), (32, 101, 700), (64, 101, 300), (64, 102, 650)])
+def test_tile_major_and_sum_on_the_cpu(tm, variant, K):
+    """Rows past K, which the last pass of activations has, lie in the next token tile, or past the end of an exactly sized
+    allocation; N is no multiple of 16, and Sum's operand has nothing behind its last value."""
+    build_emu.build()
+    for args in (dict(xtiled=True, kind="uneven"), dict(xtiled="out"), dict(ld_sum=51)):
+        res = run_case(83, K, 45, 0.8, "s8", "none", tm, variant, **args)
+        assert res["match"] and res["padding_untouched"], (args, res)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("kind", ["uniform", "uneven", "ragged"])
+@pytest.mark.parametrize("tm,variant,rows,resident", KERNELS)
+def test_weights_layouts_and_sum_on_the_device(tm, variant, rows, resident, kind):
+    from test_gpu_parity import _run_sum, assert_parity, gpu_spmm, oracle_spmm
+    import oracle
+    for i, K in enumerate((rows + 1, resident - resident // 4, resident // 2 + 1, resident)):
+        N, M = 83, tm * 2 + 5 + i
+        for out_type, postop in (("s32", "none"), ("u8", "gelu")):
+            case = wl.Case("resident", N, K, M, 0.8, wl.N4K1, out_type, postop, keys=(132, K, M))
+            d = thinned(wl.make(case), kind)
+            ref = oracle_spmm(d["W"], d["X"], d, case)
+            for x_tiled in (False, True):
+                got, guards_ok = gpu_spmm(d["W"], d["X"], d, case, tuning=(tm, variant), x_tiled=x_tiled)
+                assert guards_ok
+                assert_parity(got, ref, case)
+        for out_type in ("f32", "s8"):
+            case = wl.Case("resident", N, K, M, 0.8, wl.N4K1, out_type, "none", keys=(133, K, M))
+            d = thinned(wl.make(case), kind)
+            R = (wl.rng_for(134, N, M).standard_normal((N, M)) * wl.preact_sigma(K, case.sparsity)).astype(np.float32)
+            ref = oracle.spmm(d["W"], d["X"], d["w_scale"], d["x_scale"], d["bias"], "none", out_type, d["out_scale"],
+                              d["out_zero_point"], d["mid_scale"], d["x_zero_point"], sum=R)
+            assert_parity(_run_sum(d, case, R, M + i, (tm, variant), i), ref, case)
 
 
 @pytest.mark.gpu
