@@ -42,14 +42,17 @@ int main()
 
 @pytest.fixture(scope="module")
 def chosen(tmp_path_factory):
+    return choices(TABLE, tmp_path_factory.mktemp("plan"))
+
+
+def choices(table, d):
     """(row of the table, configuration chosen, its time / the fastest one's) of every problem"""
     sp.lib()
-    d = tmp_path_factory.mktemp("plan")
     (d / "plan.cpp").write_text(SOURCE)
     subprocess.run([CXX, "-O1", "-std=c++17", "-I", os.path.join(ROOT, "include"), "-I", os.path.join(ROOT, "paper_2306_16601_amd", "csrc"),
                     str(d / "plan.cpp"), sp.binding.LIB_PATH, "-Wl,--allow-shlib-undefined", "-Wl,-rpath," + os.path.dirname(sp.binding.LIB_PATH),
                     "-o", str(d / "plan")], check=True)
-    rows = list(csv.DictReader(line for line in open(TABLE) if not line.startswith("#")))
+    rows = list(csv.DictReader(line for line in open(table) if not line.startswith("#")))
     ask = "".join("%s %s %s %s %s %s %s %d\n" % (r["M"], r["tiles"], r["segments"], r["K"], r["steps"], r["max_segment"], r["max_tile"],
                                                4 if r["out"] in ("s32", "f32") else 1) for r in rows)
     names = subprocess.run([str(d / "plan")], input=ask, capture_output=True, text=True, check=True).stdout.split()
@@ -63,6 +66,14 @@ def test_the_choice_is_close_to_the_fastest_configuration(chosen, layout, mean, 
     ratio = np.array([t for r, _, t in chosen if (r["layout"] == "tile") == (layout == "tile")])
     assert len(ratio) > 100
     assert np.exp(np.log(ratio).mean()) <= mean and (ratio > 1.1).mean() <= over_ten, (np.exp(np.log(ratio).mean()), (ratio > 1.1).mean())
+
+
+@pytest.mark.parametrize("layout, mean, over_ten", [("row", 1.031, 0.14), ("tile", 1.038, 0.155)])
+def test_the_choice_with_the_resident_kernels_as_they_are(tmp_path, layout, mean, over_ten):
+    """The same problems timed again, with resident kernels that the estimates were not fitted to: 1.030 and 13.4 %, 1.037 and
+    14.8 % with tile-major activations."""
+    test_the_choice_is_close_to_the_fastest_configuration(choices(os.path.join(ROOT, "profiles", "spmm_plan_remeasured.csv"), tmp_path),
+                                                          layout, mean, over_ten)
 
 
 @pytest.mark.parametrize("N, K, M, sparsity, configuration", [

@@ -70,14 +70,17 @@ def few_blocks(r):
 
 @pytest.fixture(scope="module")
 def asked(tmp_path_factory):
+    return choices(TABLE, tmp_path_factory.mktemp("plan"))
+
+
+def choices(table, d):
     """([row, choice], us of a plan without the wide form, with it)"""
     sp.lib()
-    d = tmp_path_factory.mktemp("plan")
     (d / "plan.cpp").write_text(SOURCE)
     subprocess.run([CXX, "-O2", "-std=c++17", "-I", os.path.join(ROOT, "include"), "-I", os.path.join(ROOT, "paper_2306_16601_amd", "csrc"),
                     str(d / "plan.cpp"), sp.binding.LIB_PATH, "-Wl,--allow-shlib-undefined", "-Wl,-rpath," + os.path.dirname(sp.binding.LIB_PATH),
                     "-o", str(d / "plan")], check=True)
-    rows = list(csv.DictReader(line for line in open(TABLE) if not line.startswith("#")))
+    rows = list(csv.DictReader(line for line in open(table) if not line.startswith("#")))
     ask = "".join("%s %s %s %s %s %s %s %s %s %d %d %s %d\n" % (
         r["M"], r["tiles"], r["segments"], r["K"], r["steps"], r["max_segment"], r["max_tile"], r["wide_steps"], r["wide_max"], r["out"] in ("s8", "u8"),
         r["out"] == "f32" and r["post"] == "gelu", r["sum"], r["layout"] != "packed" or int(r["M"]) % 16 == 0) for r in rows)
@@ -122,6 +125,17 @@ def test_the_wide_form_is_taken_where_it_is_faster(asked):
     gain, off = np.array(gain), np.array(off)
     assert mean(gain) >= 1.065 and (gain < 1 / 1.03).mean() <= 0.012, (mean(gain), (gain < 1 / 1.03).mean())
     assert mean(off) <= 1.021 and (off > 1.1).mean() <= 0.075, (mean(off), (off > 1.1).mean())
+
+
+def test_the_choice_with_the_resident_kernels_as_they_are(tmp_path):
+    """The same problems timed again, with faster resident kernels than the estimates were fitted to: 1.064 times as fast as without
+    the form (1.079 if every choice were right); 4.7 % of the problems more than 3 % slower, nearly all of them taken from resident
+    kernels (over the 32-token one 0.926 of its speed)."""
+    rows = [(times(r), choice, r["other"]) for r, choice in choices(os.path.join(ROOT, "profiles", "spmm_plan_wide_remeasured.csv"), tmp_path)[0]]
+    gain = np.array([t["OTHER"] / t[c if c.startswith("WIDE") else "OTHER"] for t, c, _ in rows])
+    resident = np.array([o.startswith(("RES", "SLAB")) for _, _, o in rows])
+    assert mean(gain) >= 1.06 and (gain < 1 / 1.03).mean() <= 0.055, (mean(gain), (gain < 1 / 1.03).mean())
+    assert (gain[~resident] < 1 / 1.03).mean() <= 0.012, (gain[~resident] < 1 / 1.03).mean()
 
 
 @pytest.mark.parametrize("field, values", [("out", ("s32", "f32", "s8", "u8")), ("layout", ("row", "packed", "tile")), ("block", ("n4k1", "n1k4"))])
