@@ -1185,21 +1185,24 @@ __global__ void __launch_bounds__((NW + LW) * 64) spmm_rowtile_mfma_fed(const Ke
 // tiles (K <= 4096) are one body with different amounts of resident K.
 //
 // A launch here is a few microseconds long, and its time is a chain of memory latencies and of the instructions between them:
-// a wave issues one every 4 cycles, every 8 where two share a SIMD, and a kernel of 2000 cycles has no room for a hundred that
-// do nothing for it.  So everything a workgroup needs is requested before anything waits, in the order in which it is needed:
-// the whole [K x TM] slab of activations, the first weights of every wave (whose place follows from tile_steps, without
-// reading the bounds), the per-row constants, the operand of Sum, the table; in code without branches for 1, 2, 4 .. passes of
-// rows, so that each wait is for what it needs and not for all; divisions are shifts, addresses 32-bit offsets; what only
-// K beyond the RES resident rows or far rows need is behind one branch (worked out ahead of a loop for both, it
-// took 700 cycles between the barrier and the first step).  The slab then goes to LDS, one barrier, and each wave walks its
-// steps in groups of CH, branch-free inside a group (steps past the end read as zero weights), the weights of the next NS - 1
-// groups in flight.  Start of a wave to its end, 256x256 at 90 %, 128 tokens, 2 row tiles per workgroup, in cycles: 5340
-// before, 3900 now.  Calls back to back, us: 3072x768 at 85 %, 128 tokens, u8 4.67 -> 4.16; 768x3072 at 80 %, 333 tokens with
-// Sum, binary32 11.8 -> 10.3; 2944x2944 at 80 %, 16 tokens 5.2 -> 4.0; below 4 us the host's launches bound them.
+// a wave issues a vector instruction every 4 cycles, every 8 where two share a SIMD, and a kernel of 2000 cycles has no room for a
+// hundred that do nothing for it.  So what a workgroup needs is requested in the order in which it is needed: the whole [K x TM]
+// slab of activations, in code without branches for 1, 2, 4 .. passes of rows; the first weights of every wave (whose place
+// follows from tile_steps, without reading the bounds), a branch for each set after the first, so that short shares issue
+// nothing in vain (without these branches each wait is for what it needs alone, but calls are 5 to 30 % slower); the per-row
+// constants, the operand of Sum, the table.  Divisions are shifts, addresses 32-bit offsets; what only K beyond the RES resident
+// rows or far rows need is behind one branch (worked out ahead of a loop for both, it took 700 cycles between the barrier and the
+// first step).  The slab then goes to LDS, one barrier, and each wave walks its steps in groups of CH, branch-free inside a group
+// (steps past the end read as zero weights), the weights of the next NS - 1 groups in flight.  Kernel times against the ones
+// before, which had a branch per pass and step, divisions and a wait for everything (profiles/spmm_resident_kernel_times.txt, 360
+// problems), us: 256x256 at 90 %, 128 tokens 3.8 -> 2.8; 3072x768 at 85 %, 128 tokens, u8 with GELU 4.8 -> 3.9; 768x3072 at 80 %,
+// 333 tokens with Sum, binary32 10.3 -> 9.3; 2944x2944 at 80 %, 16 tokens 5.1 -> 3.9; calls of less than 4 us are bound by the
+// host's launches.
 //
-// LDS: a row is TM bytes, unpadded, so that two (TM = 16, K = 2048: five) workgroups share a CU.  Its
-// 16-byte pieces are rotated by an xor with bits of the row number such that rows whose numbers differ
-// mod 16 (the packer's order) lie in 16 different groups of four banks.
+// LDS: a row is TM bytes, unpadded.  Two workgroups share a CU (one of the slab, and one with pairs of row tiles, R = 2, which have
+// more than 128 registers); with 16-token tiles four would have the LDS, with 32 and 64 tokens two.  A row's 16-byte pieces are
+// rotated by an xor with bits of the row number such that rows whose numbers differ mod 16 (the packer's order) lie in 16 different
+// groups of four banks.
 //
 // A workgroup has 8 waves and 8, 4 or 2 row tiles (Args::wg_tiles): with fewer than 8, the waves share the row
 // tiles, each taking a part of its steps, and the partial sums meet in LDS.  For grids that leave most of the
@@ -1224,7 +1227,7 @@ struct Resident {
     static constexpr int PASSES = RES / PASS_ROWS;
     static constexpr int SEGS = RES / SEGMENT_ROWS;             // segments per round
     // weights in flight: NS sets of CH steps, gathered CH steps at a time (the slabs have 256 registers, the others
-    // 128, for two workgroups on a CU)
+    // 128, for two workgroups on a CU; with R = 2 up to 147, and one)
     static constexpr bool WIDE = RES > 2048;
     static constexpr int CH = TM == 16 || WIDE ? 4 : 2;
     static constexpr int NS = TM == 16 ? (WIDE ? 6 : 3) : WIDE ? 5 : TM == 32 ? 4 : 3;
@@ -1235,7 +1238,7 @@ struct Resident {
     // The operand of Sum is requested with everything else at the start, where the grid is one round of workgroups, as
     // it is with narrow tiles: its latency is hidden (768 x 768, 128 tokens: 4.76 us, requested after the last step 4.90).
     // 64-token tiles are planned for grids of several rounds, where the second workgroup on a CU is worth more than that
-    // and the 16 registers of the operand would cost it (147 of 128): 2688 x 672 at 71 %, 1400 tokens, binary32: 15.8 ->
+    // and the 16 registers of the operand would cost it (145 of 128): 2688 x 672 at 71 %, 1400 tokens, binary32: 15.8 ->
     // 11.6 us, 2800 tokens 28.7 -> 20.0, int8 26.3 -> 19.0; 800 x 800 at 72 %, 5024 tokens 19.3 -> 17.2.
     static constexpr bool SUM = (POST & POST_SUM_BIT) != 0, SUM_LATE = TM == 64;
     static constexpr bool TABLE = (POST & SPMM_POST_GELU) != 0 && (OUT == SPMM_OUT_S8 || OUT == SPMM_OUT_U8);
@@ -1519,7 +1522,7 @@ struct Resident {
 // requested one segment ahead into one of two register sets; the first set at the very start.
 // (The kernel before this one had one segment buffer, two barriers per segment, and the next segment's
 // activations in flight for one segment of multiplying, which is shorter than their latency: 768x3072 at 80 %, 333
-// tokens, 15.7 us; now 11.6 us.)
+// tokens with Sum, 15.7 us; 9.9 with 16-token tiles.  The resident kernel of 4096 rows, which the plan takes there, 8.9.)
 // =======================================================================================
 template <int TM, int OUT, int POST>
 struct Ring {

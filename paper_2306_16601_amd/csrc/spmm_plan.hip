@@ -177,7 +177,9 @@ SPMM_INLINE void fill_simple(Plan& p, const Call& c, int r, int tm, int waves = 
 // within 5 to 15 % of the measurement (standard deviation, by configuration), and the cheapest configuration by them
 // takes 1.030 of the fastest one's time on average, 1.037 with tile-major activations, which the estimates do not
 // tell from row-major ones; for every ninth problem, every seventh tile-major, more than 1.1
-// (profiles/spmm_plan_measurements.csv: the measured times; a test recomputes these figures from them).
+// (profiles/spmm_plan_measurements.csv: the measured times; a test recomputes these figures from them).  The fits of the
+// resident kernels (RES, SLAB) are of the ones before their straight-line start, which are up to 1.3 times slower: with the times
+// of now (profiles/spmm_plan_remeasured.csv) the choices take 1.030 and 1.037 of the fastest, and are over 1.1 in 13.4 and 14.8 %.
 // A launch is a start, rounds of workgroups on the CUs, and in a round: phases (a K segment of a token tile) with
 // their matrix instructions and the staging of their activations, and the tiles' post-operators; what has to
 // be fetched through the L2s adds to all of it.
@@ -394,7 +396,10 @@ Plan make_plan(int64_t M, const WeightDims& w, int num_cus, int force_tm, int va
     // errors are 9 to 11 %, set apart by less than the margins below goes to the kernels above, because a wrong choice is seen
     // and a missed one is not: 39 % get it, 1.0 % are more than 3 % slower than without it, and all together are 1.069 times as
     // fast (1.090 if every choice were right; with a margin of 0.98 1.077, and 3.7 % slower).  By what it replaces: the 128-token
-    // kernels with 8 + 4 waves 1.25 times, the streamed kernels 1.25, the resident ones 1.07.  4-byte outputs that have the 32-token slab keep it up to
+    // kernels with 8 + 4 waves 1.25 times, the streamed kernels 1.25, the resident ones 1.07.  (These estimates, too, are against the
+    // resident kernels before their straight-line start: with the times of now, profiles/spmm_plan_wide_remeasured.csv, what is taken
+    // from the 32-token one runs at 0.93 of its speed, 4.7 % of all problems lose more than 3 %, and all together are 1.064 times as
+    // fast, 1.079 if every choice were right.)  4-byte outputs that have the 32-token slab keep it up to
     // 768 blocks because tests/test_gpu_parity.py pins 768x3072, 1024 tokens, to it (such problems were 1.2 times as fast with
     // the wide form).
     const int64_t blocks = (int64_t)((w.ntiles + 1) / 2) * ((M + 31) / 32);
