@@ -173,7 +173,7 @@ struct KernelArgs {
     uint16_t n_streams;         // persistent kernels: workgroups per row group, each walking token tiles j * n_streams + stream;
                                 // short-batch kernels: row tiles per workgroup
     uint16_t tile_steps;
-    uint32_t tiles_per_stream;  // token tiles / n_streams, rounded down
+    uint32_t tiles_per_stream;  // token tiles / n_streams, rounded down; short-batch kernels: Plan::dealt
 };
 static_assert(sizeof(KernelArgs) == 96, "kernel arguments");
 constexpr int LD_HIGH_BITS = 9;
@@ -198,6 +198,9 @@ struct Plan {
     int max_steps;           // unroll bound of the per-segment step loop (persistent kernels)
     int n_row_groups, n_tok_tiles, n_streams;
     int xcd_row_bits;        // the 8 XCDs take 2^this slices of the row groups and 8 / 2^this of the tokens
+    uint32_t dealt;          // short-batch kernels: 0, or the workgroups' numbers dealt to the XCDs in equal parts: 2^32 / (token
+                             // tiles, or with xcd_row_bits = 1, numbered token tile by token tile, row groups), rounded up
+    double fetch_us;         // what all XCDs together read through their L2s, as a time
     int64_t workgroups;
 };
 
@@ -224,9 +227,11 @@ bool plan_supported(int token_tile, int variant);
 // x_fast: see KernelArgs; an X without it takes the simple kernel, whatever was forced
 // out_fast: 32-bit offsets suffice for out; if not, the automatic choice avoids the 16-wave pipelined
 // kernels, whose general store path is slow for want of registers
+// equal_parts: the short-batch kernels' workgroups may be dealt to the XCDs in equal parts, as every launch has it (without: as in
+// the measurements that the estimates are fitted to and compared with, which are of before that)
 // widest: widest token tile of the wide form that the post-operators run with (wide_tile), and its handicap (wide_handicap)
 Plan make_plan(int64_t M, const WeightDims& w, int num_cus, int force_tm, int variant, int out_bytes = 1,
-               bool x_fast = true, bool out_fast = true, int widest = 128, double wide_handicap = 1.0);
+               bool x_fast = true, bool out_fast = true, int widest = 128, double wide_handicap = 1.0, bool equal_parts = false);
 // Launches the SpMM kernel; returns a hipError_t value as int (0 = success).
 // postop: SPMM_POST_* value, plus POST_SUM_BIT when a.sum is to be added
 constexpr int POST_SUM_BIT = 4;   // (a bit no SPMM_POST_* value uses)

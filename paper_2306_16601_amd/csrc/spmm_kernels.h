@@ -73,6 +73,7 @@ struct Args {
     int N, K, M, nseg, ntiles, tile_steps;
     int n_streams, tiles_per_stream;   // persistent kernels
     int wg_tiles;               // short-batch kernels: row tiles (or pairs of them) per workgroup
+    uint32_t dealt;             // short-batch kernels: see decode_tile
     int xcd_row_bits;           // the 8 XCDs take 2^this slices of the row groups x 8 / 2^this slices of the tokens
     int corr_mul;               // 128 - x_zero_point: the activations are multiplied as (x - 128)
     float x_scale, inv, out_zp_f;
@@ -123,6 +124,7 @@ __device__ __forceinline__ Args unpack(const KernelArgs& p)
     a.n_streams = p.n_streams;
     a.wg_tiles = p.n_streams;
     a.tiles_per_stream = (int)p.tiles_per_stream;
+    a.dealt = p.tiles_per_stream;
     return a;
 }
 
@@ -456,6 +458,22 @@ __device__ __forceinline__ bool decode_workgroup(const Args& a, const int n_row_
     rg = (xcd & ((1 << rb) - 1)) * rows + r;
     tt = (xcd >> rb) * toks + t;
     return rg < n_row_groups && t < toks && tt < n_tokens;
+}
+
+// The same for the kernels of one workgroup per (row group, token tile), where slices would give some XCD more workgroups than
+// it has CUs while the others have CUs left (12 row groups x 21 token tiles: 33 and 30, for 32): the workgroups are numbered
+// row group by row group, or token tile by token tile (the host's choice again), and the numbers dealt out in eight equal parts.
+__device__ __forceinline__ bool decode_tile(const Args& a, const int n_row_groups, const int n_tokens, int& rg, int& tt)
+{
+    if (!a.dealt) return decode_workgroup(a, n_row_groups, n_tokens, rg, tt);
+    const uint32_t all = (uint32_t)n_row_groups * (uint32_t)n_tokens;
+    const uint32_t i = (blockIdx.x & 7) * ((all + 7) >> 3) + (blockIdx.x >> 3);
+    const bool by_tokens = a.xcd_row_bits != 0;
+    // (dealt: 2^32 / the divisor, rounded up: exact as all < 2^16)
+    const uint32_t q = (uint32_t)((uint64_t)i * a.dealt >> 32), r = i - q * (uint32_t)(by_tokens ? n_row_groups : n_tokens);
+    rg = (int)(by_tokens ? r : q);
+    tt = (int)(by_tokens ? q : r);
+    return i < all;
 }
 
 // =======================================================================================
@@ -1252,7 +1270,7 @@ struct Resident {
         const int wt = __builtin_ctz((unsigned)a.wg_tiles), kb = 3 - wt;
         const int group_bits = wt + (R == 2 ? 1 : 0);
         int tt, rg;
-        if (!decode_workgroup(a, (a.ntiles + (1 << group_bits) - 1) >> group_bits, (a.M + TM - 1) / TM, rg, tt)) return;
+        if (!decode_tile(a, (a.ntiles + (1 << group_bits) - 1) >> group_bits, (a.M + TM - 1) / TM, rg, tt)) return;
         const int tid = threadIdx.x;
         const int lane = tid & 63;
         const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1535,7 +1553,7 @@ struct Ring {
     static __device__ __forceinline__ void run(const Args& a, uint8_t* const lds)
     {
         int tt, rg;
-        if (!decode_workgroup(a, (a.ntiles + 7) / 8, (a.M + TM - 1) / TM, rg, tt)) return;
+        if (!decode_tile(a, (a.ntiles + 7) / 8, (a.M + TM - 1) / TM, rg, tt)) return;
         const int tid = threadIdx.x;
         const int lane = tid & 63;
         const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);

@@ -83,13 +83,17 @@ struct Call {
     // rate, and is the largest part of many launches (4096x4096 at 75 %, 512 tokens, by the weight's rows alone: 31 MB).
     double fetched[4], fetch_us[4];     // and the time that takes at 7 TB/s
     int rank[4], split[4];              // rank[rb]: how many splits fetch less (or as much, with a smaller rb); and its inverse
+    double w_bytes, x_bytes;
     double steps;                       // of a (row tile, segment), on average
+    bool equal_parts;                   // see make_plan
     double wide_steps = 0.0;            // the same of the wide form (set_wide_steps)
 
-    Call(int64_t tokens, const WeightDims& dims, int cus) : M(tokens), w(dims), num_cus(cus), per_xcd(cus >= 8 ? cus / 8 : 1)
+    Call(int64_t tokens, const WeightDims& dims, int cus, bool deal)
+        : M(tokens), w(dims), num_cus(cus), per_xcd(cus >= 8 ? cus / 8 : 1), equal_parts(deal)
     {
         cu_shift = (per_xcd & (per_xcd - 1)) == 0 && per_xcd * 8 == cus ? __builtin_ctz((unsigned)per_xcd) : -1;
-        const double w_bytes = (double)w.nsteps * RECORD_BYTES, x_bytes = (double)w.K * (double)M;
+        w_bytes = (double)w.nsteps * RECORD_BYTES;
+        x_bytes = (double)w.K * (double)M;
         for (int rb = 0; rb <= 3; ++rb) {
             fetched[rb] = 8.0 * (w_bytes / (1 << rb) + x_bytes / (8 >> rb));
             fetch_us[rb] = fetched[rb] * 1e-6 / 7.0;
@@ -149,6 +153,26 @@ SPMM_INLINE void fill_wide(Plan& p, const Call& c, int tm, int waves)
     p.max_steps = std::max(5, c.w.wide_max_steps);
 }
 
+// Workgroups whose slices take more rounds than their number does, dealt to the XCDs in equal parts (decode_tile), in the order
+// that fetches less: an XCD's `each` consecutive workgroups touch so many row groups and so many token tiles.  A round saved is
+// worth far more than what the slices save: of 60 random problems of 256 to 4096 features, 32 to 1250 tokens, 70 to 90 %, where it
+// saves one (profiles/spmm_plan_equal_parts.csv), two rounds of the resident kernels become one of 0.78 of the time, of the ring 0.67;
+// no configuration is slower by more than runs of 4 us differ.  768x3072 at 80 %, 333 tokens with Sum, binary32, 12 row groups x 21
+// token tiles: 12.0 -> 8.0 us, and as 6 x 21, which it ran as before, 9.3; 1300x650 at 80 %, 665 tokens 7.1 -> 4.7.
+static void deal(Plan& p, const Call& c, int each)
+{
+    const double rows = p.n_row_groups, toks = p.n_tok_tiles;
+    auto fetch = [&](double outer, double inner, double of_outer, double of_inner) {
+        return of_outer * std::min(1.0, (each / inner + 1) / outer) + of_inner * std::min(1.0, each / inner);
+    };
+    const double by_rows = fetch(rows, toks, c.w_bytes, c.x_bytes), by_tokens = fetch(toks, rows, c.x_bytes, c.w_bytes);
+    p.xcd_row_bits = by_tokens < by_rows;
+    p.dealt = (uint32_t)((((uint64_t)1 << 32) + (uint64_t)(p.xcd_row_bits ? p.n_row_groups : p.n_tok_tiles) - 1) /
+                         (uint64_t)(p.xcd_row_bits ? p.n_row_groups : p.n_tok_tiles));
+    p.fetch_us = 8.0 * std::min(by_rows, by_tokens) * 1e-6 / 7.0;
+    p.workgroups = 8 * (int64_t)each;
+}
+
 // Simple, short-batch and streamed kernels: tm-token tiles, one workgroup of 8 waves per (row group, tile), `waves` row
 // tiles (or pairs of them) per row group.  The XCD split: as few rounds of workgroups as possible, then the least fetched.
 SPMM_INLINE void fill_simple(Plan& p, const Call& c, int r, int tm, int waves = 8)
@@ -162,6 +186,7 @@ SPMM_INLINE void fill_simple(Plan& p, const Call& c, int r, int tm, int waves = 
     p.n_tok_tiles = (int)((c.M + tm - 1) / tm);
     p.n_row_groups = (c.w.ntiles + waves * r - 1) / (waves * r);
     p.n_streams = 0;
+    p.dealt = 0;
     int64_t best = INT64_MAX, here[4];
     for (int rb = 0; rb <= 3; ++rb) {
         here[rb] = (int64_t)ceil_shift(p.n_row_groups, rb) * ceil_shift(p.n_tok_tiles, 3 - rb);
@@ -169,6 +194,9 @@ SPMM_INLINE void fill_simple(Plan& p, const Call& c, int r, int tm, int waves = 
     }
     p.xcd_row_bits = c.split[best & 3];
     p.workgroups = 8 * here[p.xcd_row_bits];
+    p.fetch_us = c.fetch_us[p.xcd_row_bits];
+    const int64_t all = (int64_t)p.n_row_groups * p.n_tok_tiles;
+    if (c.equal_parts && all < 65536 && p.n_row_groups > 1 && p.n_tok_tiles > 1 && c.xcd_rounds((all + 7) / 8) < best >> 2) deal(p, c, (int)((all + 7) / 8));
 }
 
 // ---------------------------------------------------------------------------------------
@@ -229,17 +257,16 @@ static const Fit FIT_WIDE_32_4[2]    = {{2.83, 0.00, 0.0009, 1.73, 0.0961, 0.159
 SPMM_INLINE double plan_cost(const Plan& p, const Fit& f, const Call& c, int out_bytes)
 {
     const double rounds = (double)c.rounds(p.workgroups);
-    const double fetch = c.fetch_us[p.xcd_row_bits];
     const double rows = p.waves;
     if (p.simple) {
         const double units = rows * c.steps * c.w.nseg * p.token_tile / 16.0;
         return f.start + rounds * (f.phase + f.unit * units + f.tokens * c.w.nseg * p.token_tile * 0.01 +
-                                   f.out1 * rows * TILE_ROWS * p.token_tile * 1e-3 * out_bytes) + f.fetch * fetch;
+                                   f.out1 * rows * TILE_ROWS * p.token_tile * 1e-3 * out_bytes) + f.fetch * p.fetch_us;
     }
     const int tiles = quotient(p.n_tok_tiles + p.n_streams - 1, p.n_streams), phases = tiles * c.w.nseg;
     const double units = rows * c.steps * p.token_tile / 16.0;
     return rounds * (f.start + phases * (f.phase + f.unit * units + f.tokens * p.token_tile * 0.01) +
-                     (out_bytes == 4 ? f.out4 : f.out1) * tiles * rows * TILE_ROWS * p.token_tile * 1e-3) + f.fetch * fetch;
+                     (out_bytes == 4 ? f.out4 : f.out1) * tiles * rows * TILE_ROWS * p.token_tile * 1e-3) + f.fetch * c.fetch_us[p.xcd_row_bits];
 }
 
 // The same of the wide form's kernel: an XCD's workgroups take its CUs in rounds of per_cu to a CU, and those that share a CU
@@ -300,10 +327,10 @@ static Plan forced_plan(const Call& call, int force_tm, int variant, int max_ste
 }
 
 Plan make_plan(int64_t M, const WeightDims& w, int num_cus, int force_tm, int variant, int out_bytes, bool x_fast, bool out_fast,
-               int widest, double wide_handicap)
+               int widest, double wide_handicap, bool equal_parts)
 {
     const int nseg = w.nseg, max_steps_per_segment = w.max_steps_per_segment;
-    Call call(M, w, num_cus);
+    Call call(M, w, num_cus, equal_parts);
     const int max_steps = max_steps_per_segment <= 4 ? 4 : (max_steps_per_segment <= 6 ? max_steps_per_segment : 8);
     const int fed_steps = max_steps == 5 ? 6 : max_steps;      // step slots of the loader-wave kernels: 4, 6 or 8
     if (!x_fast && !(force_tm && force_tm <= 64 && (variant == 101 || variant == 102))) {
@@ -435,8 +462,13 @@ int launch_spmm(const Plan& plan, KernelArgs& a, spmm_out_t out_type, int postop
     // x: XCD and row group within its slice, y and z: token tile or stream within its slice (decode_workgroup)
     const unsigned toks = (unsigned)ceil_shift(plan.simple ? plan.n_tok_tiles : plan.n_streams, 3 - plan.xcd_row_bits);
     const unsigned y = toks < (1u << GRID_Y_BITS) ? toks : (1u << GRID_Y_BITS);
-    const unsigned grid[3] = {8u * (unsigned)ceil_shift(plan.n_row_groups, plan.xcd_row_bits), y, (toks + y - 1) / y};
+    unsigned grid[3] = {8u * (unsigned)ceil_shift(plan.n_row_groups, plan.xcd_row_bits), y, (toks + y - 1) / y};
     if (plan.simple) {
+        a.tiles_per_stream = plan.dealt;
+        if (plan.dealt) {
+            grid[0] = (unsigned)plan.workgroups;
+            grid[1] = grid[2] = 1;
+        }
         const int key = plan.token_tile * 10 + plan.row_tiles_per_wave;
         if (plan.stream) {
             if (key == 641) launch_cfg_stream64(out_type, postop, grid, block, stream, a);
