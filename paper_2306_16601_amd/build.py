@@ -19,7 +19,7 @@ NATIVE = os.path.join(HERE, "_native_call.so")      # CPython entry points of th
 NATIVE_SOURCE = os.path.join(CSRC, "native_call.c")
 OBJDIR = os.path.join(HERE, "_build")
 
-HOST_SOURCES = ["api.cpp", "pack.cpp", "spmm_plan.hip", "spmm_peak.hip"]
+HOST_SOURCES = ["api.cpp", "pack.cpp", "spmm_pack.hip", "spmm_plan.hip", "spmm_peak.hip"]
 # (token tile, waves, step slots) of the pipelined kernel
 PIPELINED = [(128, 16, 4), (128, 16, 5), (128, 16, 6), (128, 8, 4), (128, 8, 6), (128, 8, 8),
              (96, 16, 4), (96, 16, 5), (96, 16, 6)]

@@ -81,6 +81,11 @@ hipError_t upload_forms(spmm_handle* h)
     return e;
 }
 
+// From so many elements on, the device makes its forms itself (DevicePack).  Pack on the host and so, us: 256x256 at 80 % 59 and 90,
+// 512x512 259 and 225, 1024x1024 500 and 290, 4096x4096 6100 and 1760.  The line is where the scratch memory on the device, as large
+// as the weight and a quarter more, is worth it for sure: below it a pack needs no more memory there than the forms.
+constexpr int64_t DEVICE_PACK_MIN = (int64_t)1 << 20;
+
 bool aligned(const void* p, size_t a) { return (reinterpret_cast<uintptr_t>(p) % a) == 0; }
 
 // (gelu_f32: GELU in binary32, not in a table; sum: with an operand of Sum; aligned_rows: of the activations)
@@ -114,7 +119,14 @@ static spmm_status_t pack_common(const int8_t* W_host, int64_t N, int64_t K, int
     try {
         h = new spmm_handle();
         spmm::Team team;
-        spmm::bsr_from_dense(W_host, N, K, ldw, block, h->bsr, team);
+        spmm::DevicePack pack;
+        bool there = false;
+        if (to_device && !reorder && ldw == K && N * K >= DEVICE_PACK_MIN) {
+            e = hipGetDevice(&h->device);
+            there = e == hipSuccess && pack.reserve(N, K, block);
+        }
+        const spmm::Beside beside = {[&] { pack.begin(W_host); }, [&] { e = (hipError_t)pack.finish(h->hl, h->forms, &h->d_weight); }};
+        spmm::bsr_from_dense(W_host, N, K, ldw, block, h->bsr, team, there ? &beside : nullptr);
         h->nnz_blocks = (int64_t)h->bsr.index.size();
         spmm::Bsr reordered;
         if (reorder) {
@@ -123,16 +135,21 @@ static spmm_status_t pack_common(const int8_t* W_host, int64_t N, int64_t K, int
         }
         const spmm::Bsr& ordered = reorder ? reordered : h->bsr;
         if (to_device) {
-            e = hipGetDevice(&h->device);
+            if (!there) e = hipGetDevice(&h->device);
             int cus = 0;
             if (e == hipSuccess && hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, h->device) == hipSuccess && cus > 0)
                 h->num_cus = cus;
             spmm::DeviceForms& f = h->forms;
-            // (the first form is on its way while the other threads pack the second)
-            spmm::forms_from_bsr(ordered, h->hl, f, team, [&] {
-                if (e == hipSuccess && !f.together) e = upload(&h->d_weight, f.bytes.get(), f.size);
-            });
-            if (e == hipSuccess) e = upload_forms(h);
+            if (there) {
+                h->wide = h->d_weight + f.size;
+                h->device_bytes = f.size + f.wide_size;
+            } else {
+                // (the first form is on its way while the other threads pack the second)
+                spmm::forms_from_bsr(ordered, h->hl, f, team, [&] {
+                    if (e == hipSuccess && !f.together) e = upload(&h->d_weight, f.bytes.get(), f.size);
+                });
+                if (e == hipSuccess) e = upload_forms(h);
+            }
             h->on_device = true;
         } else {
             spmm::layout_from_bsr(ordered, spmm::SEGMENT_ROWS, h->hl, team);
@@ -200,7 +217,19 @@ spmm_status_t spmm_layout_export(const spmm_handle_t* h, uint8_t* vals_host, uin
 {
     if (!h) return SPMM_E_ARG;
     const spmm::HostLayout& hl = h->hl;
-    if (h->on_device) spmm::export_steps(hl, h->forms, vals_host, idx_host);
+    if (h->on_device && h->forms.bytes) {
+        spmm::export_steps(hl, h->forms, vals_host, idx_host);
+    } else if (h->on_device && (vals_host || idx_host)) {
+        // (made on the device: the host keeps no copy, and what was made there is what this makes)
+        try {
+            spmm::HostLayout steps;
+            spmm::layout_from_bsr(h->bsr, spmm::SEGMENT_ROWS, steps);
+            if (vals_host) std::copy(steps.vals.begin(), steps.vals.end(), vals_host);
+            if (idx_host) std::copy(steps.idx.begin(), steps.idx.end(), idx_host);
+        } catch (...) {
+            return SPMM_E_ALLOC;
+        }
+    }
     if (vals_host && !hl.vals.empty()) std::memcpy(vals_host, hl.vals.data(), hl.vals.size());
     if (idx_host && !hl.idx.empty()) std::memcpy(idx_host, hl.idx.data(), hl.idx.size() * sizeof(uint32_t));
     if (seg_ptr_host) std::memcpy(seg_ptr_host, hl.seg_ptr.data(), hl.seg_ptr.size() * sizeof(int32_t));

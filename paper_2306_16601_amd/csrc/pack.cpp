@@ -31,9 +31,33 @@ inline uint64_t nonzero_bytes(uint64_t v)
     return (high >> 7) * 0x0102040810204080ull >> 56;
 }
 
-// The blocks of block-row br, at most K of them, to index / vals (4 bytes per block, as one dword); returns how many
-int64_t blocks_of_row(const int8_t* W, int64_t N, int64_t K, int64_t ldw, spmm_block_t block, int64_t br, int32_t* index,
-                      uint32_t* vals)
+// how many blocks block-row br has
+int64_t count_blocks_of_row(const int8_t* W, int64_t N, int64_t K, int64_t ldw, spmm_block_t block, int64_t br)
+{
+    int64_t n = 0;
+    if (block == SPMM_BLOCK_N4K1) {
+        const int rows = (int)std::min<int64_t>(4, N - br * 4);
+        const int8_t* r[4];
+        for (int i = 0; i < 4; ++i) r[i] = W + (br * 4 + std::min(i, rows - 1)) * ldw;     // (missing rows: the last one again)
+        const int8_t *const r0 = r[0], *const r1 = r[1], *const r2 = r[2], *const r3 = r[3];
+        for (int64_t k0 = 0; k0 < K; k0 += 128) {       // (in bytes, which the compiler takes 16 at a time)
+            uint8_t some = 0;
+            for (int64_t k = k0; k < std::min(K, k0 + 128); ++k) some = (uint8_t)(some + ((r0[k] | r1[k] | r2[k] | r3[k]) != 0));
+            n += some;
+        }
+    } else {
+        const int8_t* const r = W + br * ldw;
+        for (int64_t c = 0; c * 4 < K; ++c) {
+            uint32_t v = 0;
+            std::memcpy(&v, r + 4 * c, (size_t)std::min<int64_t>(4, K - 4 * c));
+            n += v != 0;
+        }
+    }
+    return n;
+}
+
+// The blocks of block-row br to index / vals (4 bytes per block)
+void blocks_of_row(const int8_t* W, int64_t N, int64_t K, int64_t ldw, spmm_block_t block, int64_t br, int32_t* index, int8_t* vals)
 {
     int64_t n = 0;
     if (block == SPMM_BLOCK_N4K1) {
@@ -42,9 +66,10 @@ int64_t blocks_of_row(const int8_t* W, int64_t N, int64_t K, int64_t ldw, spmm_b
         for (int i = 0; i < 4; ++i) r[i] = W + (br * 4 + std::min(i, rows - 1)) * ldw;     // (missing rows: the last one again)
         const uint32_t keep = rows == 4 ? 0xffffffffu : (1u << (8 * rows)) - 1u;
         auto add = [&](int64_t k) {
+            const uint32_t v = ((uint32_t)(uint8_t)r[0][k] | (uint32_t)(uint8_t)r[1][k] << 8 | (uint32_t)(uint8_t)r[2][k] << 16 |
+                                (uint32_t)(uint8_t)r[3][k] << 24) & keep;
             index[n] = (int32_t)k;
-            vals[n++] = ((uint32_t)(uint8_t)r[0][k] | (uint32_t)(uint8_t)r[1][k] << 8 | (uint32_t)(uint8_t)r[2][k] << 16 |
-                         (uint32_t)(uint8_t)r[3][k] << 24) & keep;
+            std::memcpy(vals + 4 * n++, &v, 4);
         };
         int64_t k = 0;
         for (; k + 64 <= K; k += 64) {      // 64 positions at a time: few mispredicted loop ends
@@ -64,11 +89,10 @@ int64_t blocks_of_row(const int8_t* W, int64_t N, int64_t K, int64_t ldw, spmm_b
             std::memcpy(&v, r + 4 * c, (size_t)std::min<int64_t>(4, K - 4 * c));
             if (v) {
                 index[n] = (int32_t)c;
-                vals[n++] = v;
+                std::memcpy(vals + 4 * n++, &v, 4);
             }
         }
     }
-    return n;
 }
 
 }  // namespace
@@ -79,53 +103,31 @@ void bsr_from_dense(const int8_t* W, int64_t N, int64_t K, int64_t ldw, spmm_blo
     bsr_from_dense(W, N, K, ldw, block, out, team);
 }
 
-void bsr_from_dense(const int8_t* W, int64_t N, int64_t K, int64_t ldw, spmm_block_t block, Bsr& out, Team& team)
+// Two passes over the weight: how many blocks there are, and the blocks, to where they stay.  (In one, with pieces put together
+// afterwards, every block was written twice, to new pages both times: 1024x4096 at 80 %, 220 to 270 us, now 180.)
+void bsr_from_dense(const int8_t* W, int64_t N, int64_t K, int64_t ldw, spmm_block_t block, Bsr& out, Team& team, const Beside* beside)
 {
     out.N = N;
     out.K = K;
     out.block = block;
     out.block_rows = (block == SPMM_BLOCK_N4K1) ? (N + 3) / 4 : N;
     out.row_ptr.assign((size_t)out.block_rows + 1, 0);
-    // pieces of block-rows, which are then put together
-    struct Piece { std::unique_ptr<int32_t[]> index; std::unique_ptr<uint32_t[]> vals; int64_t count = 0, at = 0; };
     const int64_t rows_per_block_row = (block == SPMM_BLOCK_N4K1) ? 4 : 1;
-    const int64_t piece = std::max<int64_t>(1, 65536 / (K * rows_per_block_row)), most = (block == SPMM_BLOCK_N4K1) ? K : (K + 3) / 4;
-    std::vector<Piece> pieces((size_t)((out.block_rows + piece - 1) / piece));
+    const int64_t piece = std::max<int64_t>(1, 65536 / (K * rows_per_block_row));
     team.run(out.block_rows, piece, [&](int64_t begin, int64_t end) {
-        Piece& p = pieces[(size_t)(begin / piece)];
-        int64_t room = std::max<int64_t>(most, (end - begin) * most / 3);
-        p.index.reset(new int32_t[(size_t)room]);
-        p.vals.reset(new uint32_t[(size_t)room]);
+        for (int64_t br = begin; br < end; ++br) out.row_ptr[(size_t)br + 1] = count_blocks_of_row(W, N, K, ldw, block, br);
+    }, [&] { if (beside) beside->first(); });
+    for (int64_t br = 0; br < out.block_rows; ++br) out.row_ptr[(size_t)br + 1] += out.row_ptr[(size_t)br];
+    out.index.resize((size_t)out.row_ptr.back());
+    out.vals.resize((size_t)out.row_ptr.back() * 4);
+    auto fill = [&](int64_t begin, int64_t end) {
         for (int64_t br = begin; br < end; ++br) {
-            if (p.count + most > room) {
-                room = std::min(std::max(2 * room, p.count + most), (end - begin) * most);
-                std::unique_ptr<int32_t[]> index(new int32_t[(size_t)room]);
-                std::unique_ptr<uint32_t[]> vals(new uint32_t[(size_t)room]);
-                std::memcpy(index.get(), p.index.get(), (size_t)p.count * 4);
-                std::memcpy(vals.get(), p.vals.get(), (size_t)p.count * 4);
-                p.index.swap(index);
-                p.vals.swap(vals);
-            }
-            p.count += blocks_of_row(W, N, K, ldw, block, br, p.index.get() + p.count, p.vals.get() + p.count);
-            out.row_ptr[(size_t)br + 1] = p.count;              // within the piece, for now
+            const size_t at = (size_t)out.row_ptr[(size_t)br];
+            blocks_of_row(W, N, K, ldw, block, br, out.index.data() + at, out.vals.data() + 4 * at);
         }
-    });
-    int64_t total = 0;
-    for (Piece& p : pieces) {
-        p.at = total;
-        total += p.count;
-    }
-    out.index.resize((size_t)total);
-    out.vals.resize((size_t)total * 4);
-    team.run((int64_t)pieces.size(), 1, [&](int64_t begin, int64_t end) {
-        for (int64_t i = begin; i < end; ++i) {
-            const Piece& p = pieces[(size_t)i];
-            for (int64_t br = i * piece; br < std::min(out.block_rows, (i + 1) * piece); ++br) out.row_ptr[(size_t)br + 1] += p.at;
-            if (!p.count) continue;
-            std::memcpy(&out.index[(size_t)p.at], p.index.get(), (size_t)p.count * 4);
-            std::memcpy(&out.vals[(size_t)p.at * 4], p.vals.get(), (size_t)p.count * 4);
-        }
-    });
+    };
+    if (beside) team.finish(out.block_rows, piece, fill, beside->last);
+    else team.run(out.block_rows, piece, fill);
 }
 
 void bsr_to_dense(const Bsr& b, int8_t* W, int64_t ldw)
@@ -453,22 +455,22 @@ void arrange_tile(const Lists& l, int64_t tile, uint8_t* vals, int64_t val_strid
     }
 }
 
-// dimensions and bounds of the row tiles
-void layout_dims(const Lists& l, HostLayout& out)
+// dimensions and bounds of the row tiles, from the steps of every (row tile, segment)
+void layout_dims(int nseg, int ntiles, const int32_t* steps, HostLayout& out)
 {
     out.kc = SEGMENT_ROWS;
-    out.nseg = l.nseg;
-    out.ntiles = l.ntiles;
+    out.nseg = nseg;
+    out.ntiles = ntiles;
     out.max_steps_per_tile = 0;
     out.max_steps_per_segment = 0;
-    out.seg_ptr.assign((size_t)l.ntiles * l.nseg + 1, 0);
-    for (int64_t tile = 0; tile < l.ntiles; ++tile) {
+    out.seg_ptr.assign((size_t)ntiles * nseg + 1, 0);
+    for (int64_t tile = 0; tile < ntiles; ++tile) {
         int steps_this_tile = 0;
-        for (int seg = 0; seg < l.nseg; ++seg) {
-            const size_t i = (size_t)(tile * l.nseg + seg);
-            steps_this_tile += l.steps[i];
-            out.max_steps_per_segment = std::max(out.max_steps_per_segment, l.steps[i]);
-            out.seg_ptr[i + 1] = out.seg_ptr[i] + l.steps[i];
+        for (int seg = 0; seg < nseg; ++seg) {
+            const size_t i = (size_t)(tile * nseg + seg);
+            steps_this_tile += steps[i];
+            out.max_steps_per_segment = std::max(out.max_steps_per_segment, steps[i]);
+            out.seg_ptr[i + 1] = out.seg_ptr[i] + steps[i];
         }
         out.max_steps_per_tile = std::max(out.max_steps_per_tile, steps_this_tile);
     }
@@ -488,7 +490,7 @@ void layout_from_bsr(const Bsr& b, int kc, HostLayout& out, Team& team)
     (void)kc;                                               // SEGMENT_ROWS
     out.rowsum.assign((size_t)((b.N + TILE_ROWS - 1) / TILE_ROWS) * TILE_ROWS, 0);
     const Lists l(b, out.rowsum.data(), team);
-    layout_dims(l, out);
+    layout_dims(l.nseg, l.ntiles, l.steps.data(), out);
     out.vals.assign((size_t)out.nsteps * STEP_VAL_BYTES, 0);
     out.idx.assign((size_t)out.nsteps * STEP_IDX_DWORDS, 0);
     team.finish(l.ntiles, 2 * l.grain, [&](int64_t begin, int64_t end) {
@@ -806,28 +808,36 @@ void write_wide_tile(const Lists& l, int64_t t, const WideSegment* segments, uin
 struct WideDims {
     std::vector<int64_t> first;     // record of every tile
     int64_t records = 0;
-    explicit WideDims(const Lists& l, const std::vector<int32_t>& steps, DeviceForms& f) : first((size_t)l.nt + 1, 0)
+    WideDims(int nseg, int64_t nt, const int32_t* steps, DeviceForms& f) : first((size_t)nt + 1, 0)
     {
         f.wide_max_steps = 0;
         int most = 0;
-        for (int64_t t = 0; t < l.nt; ++t) {
+        for (int64_t t = 0; t < nt; ++t) {
             int all = 0;
-            for (int seg = 0; seg < l.nseg; ++seg) {
-                all += steps[(size_t)(t * l.nseg + seg)];
-                f.wide_max_steps = std::max(f.wide_max_steps, steps[(size_t)(t * l.nseg + seg)]);
+            for (int seg = 0; seg < nseg; ++seg) {
+                all += steps[(size_t)(t * nseg + seg)];
+                f.wide_max_steps = std::max(f.wide_max_steps, steps[(size_t)(t * nseg + seg)]);
             }
             most = std::max(most, all);
             first[(size_t)t + 1] = first[(size_t)t] + all;
         }
         f.wide_max_steps = std::max(1, f.wide_max_steps);
         f.wide_nsteps = first.back();
-        f.wide_tile_steps = l.nt * most <= f.wide_nsteps + f.wide_nsteps / 2 ? most : 0;
+        f.wide_tile_steps = nt * most <= f.wide_nsteps + f.wide_nsteps / 2 ? most : 0;
         if (f.wide_tile_steps)
-            for (int64_t t = 0; t <= l.nt; ++t) first[(size_t)t] = t * most;
+            for (int64_t t = 0; t <= nt; ++t) first[(size_t)t] = t * most;
         records = std::max<int64_t>(1, first.back());
-        f.wide_size = wide_records_offset(l.nt, l.nseg) + records * WIDE_RECORD_BYTES;
+        f.wide_size = wide_records_offset(nt, nseg) + records * WIDE_RECORD_BYTES;
     }
 };
+
+// and those of the row tiles
+void narrow_dims(const HostLayout& hl, DeviceForms& f)
+{
+    f.tile_steps = (int64_t)hl.ntiles * hl.max_steps_per_tile <= hl.nsteps + hl.nsteps / 2 ? hl.max_steps_per_tile : 0;
+    const int64_t records = std::max<int64_t>(1, f.tile_steps ? (int64_t)hl.ntiles * f.tile_steps : hl.nsteps);
+    f.size = (records_offset(hl.ntiles, hl.nseg) + records * RECORD_BYTES + 127) & ~(int64_t)127;
+}
 
 }  // namespace
 
@@ -835,12 +845,10 @@ void forms_from_bsr(const Bsr& b, HostLayout& hl, DeviceForms& f, Team& team, co
 {
     hl.rowsum.assign((size_t)((b.N + TILE_ROWS - 1) / TILE_ROWS) * TILE_ROWS, 0);
     Lists l(b, hl.rowsum.data(), team);
-    layout_dims(l, hl);
+    layout_dims(l.nseg, l.ntiles, l.steps.data(), hl);
     const int64_t nt16 = l.ntiles, ns = l.nseg;
-    f.tile_steps = nt16 * hl.max_steps_per_tile <= hl.nsteps + hl.nsteps / 2 ? hl.max_steps_per_tile : 0;
-    const int64_t records = std::max<int64_t>(1, f.tile_steps ? nt16 * f.tile_steps : hl.nsteps);
-    f.size = (records_offset(nt16, ns) + records * RECORD_BYTES + 127) & ~(int64_t)127;
-    WideDims dims(l, l.wide_steps, f);
+    narrow_dims(hl, f);
+    WideDims dims(l.nseg, l.nt, l.wide_steps.data(), f);
     f.together = f.size + f.wide_size <= 256 * 1024;
     f.bytes.reset(new uint8_t[(size_t)(f.size + (f.together ? f.wide_size : 0))]);
     // The wide form is not needed to run the weight: without memory for it there is none.
@@ -918,7 +926,7 @@ void forms_from_bsr(const Bsr& b, HostLayout& hl, DeviceForms& f, Team& team, co
         const std::vector<int64_t> was_at = dims.first;
         const std::unique_ptr<uint8_t[]> old = std::move(f.wide);
         const uint8_t* const from = f.together ? f.bytes.get() + f.size : old.get();
-        dims = WideDims(l, l.wide_steps, f);
+        dims = WideDims(l.nseg, l.nt, l.wide_steps.data(), f);
         wide_memory([&] { f.wide.reset(new uint8_t[(size_t)f.wide_size]); });
         f.together = false;
         Team again;
@@ -942,6 +950,42 @@ void forms_from_bsr(const Bsr& b, HostLayout& hl, DeviceForms& f, Team& team, co
     std::memset(form + sums, 0, (size_t)wide_bounds_offset(l.nt) - sums);
     std::memset(form + wide_end, 0, (size_t)wide_records_offset(l.nt, ns) - wide_end);
     if (!f.wide_nsteps) std::memset(form + wide_records_offset(l.nt, ns), 0, WIDE_RECORD_BYTES);
+}
+
+void dims_from_steps(int64_t N, int64_t K, const int32_t* steps, const int32_t* wide_steps, const int32_t* sums, HostLayout& hl,
+                     DeviceForms& f, std::vector<uint8_t>& heads, int64_t& head)
+{
+    const int64_t ns = (K + SEGMENT_ROWS - 1) / SEGMENT_ROWS, nt16 = (N + TILE_ROWS - 1) / TILE_ROWS, nt = (nt16 + 1) / 2;
+    hl.rowsum.assign((size_t)(nt16 * TILE_ROWS), 0);
+    for (int64_t t = 0; t < nt; ++t)
+        for (int64_t g = 0; g < ns; ++g)
+            for (int64_t r = t * WIDE_ROWS; r < std::min((t + 1) * WIDE_ROWS, nt16 * TILE_ROWS); ++r)
+                hl.rowsum[(size_t)r] += sums[(t * ns + g) * WIDE_ROWS + r - t * WIDE_ROWS];
+    layout_dims((int)ns, (int)nt16, steps, hl);
+    narrow_dims(hl, f);
+    head = records_offset(nt16, ns) + (hl.nsteps ? 0 : RECORD_BYTES);
+    heads.assign((size_t)head, 0);
+    const size_t rowsums = hl.rowsum.size() * 4;
+    std::memcpy(heads.data(), hl.rowsum.data(), rowsums);
+    int32_t* bounds = (int32_t*)(heads.data() + bounds_offset(nt16));
+    for (int64_t t = 0; t < nt16; ++t) {
+        const int64_t first = hl.seg_ptr[(size_t)(t * ns)], at = f.tile_steps ? t * f.tile_steps : first;
+        for (int64_t g = 0; g <= ns; ++g) *bounds++ = (int32_t)(hl.seg_ptr[(size_t)(t * ns + g)] - first + at);
+    }
+    f.together = false;
+    if (std::any_of(wide_steps, wide_steps + nt * ns, [](int32_t s) { return s < 0; })) {
+        f.drop_wide();
+        return;
+    }
+    const WideDims dims((int)ns, nt, wide_steps, f);
+    heads.resize((size_t)(head + wide_records_offset(nt, ns) + (f.wide_nsteps ? 0 : WIDE_RECORD_BYTES)), 0);
+    std::memcpy(heads.data() + head, hl.rowsum.data(), rowsums);
+    bounds = (int32_t*)(heads.data() + head + wide_bounds_offset(nt));
+    for (int64_t t = 0; t < nt; ++t) {
+        *bounds = (int32_t)dims.first[(size_t)t];
+        for (int64_t g = 0; g < ns; ++g, ++bounds) bounds[1] = bounds[0] + wide_steps[t * ns + g];
+        ++bounds;
+    }
 }
 
 }  // namespace spmm

@@ -72,7 +72,9 @@ struct Bsr {
 
 class Team;     // (threads of one call, team.h)
 void bsr_from_dense(const int8_t* W, int64_t N, int64_t K, int64_t ldw, spmm_block_t block, Bsr& out);
-void bsr_from_dense(const int8_t* W, int64_t N, int64_t K, int64_t ldw, spmm_block_t block, Bsr& out, Team& team);
+// beside the first pass, and beside the last one, the calling thread runs these two (nothing else is shared with the team then)
+struct Beside { std::function<void()> first, last; };
+void bsr_from_dense(const int8_t* W, int64_t N, int64_t K, int64_t ldw, spmm_block_t block, Bsr& out, Team& team, const Beside* beside = nullptr);
 void bsr_to_dense(const Bsr& b, int8_t* W, int64_t ldw);
 void layout_from_bsr(const Bsr& b, int kc, HostLayout& out);
 void layout_from_bsr(const Bsr& b, int kc, HostLayout& out, Team& team);
@@ -152,6 +154,31 @@ struct DeviceForms {
 // both forms, and of the layout all but the steps, which the first form holds; first_form is called when that one is whole, and
 // the other threads work on the second meanwhile
 void forms_from_bsr(const Bsr& b, HostLayout& hl, DeviceForms& f, Team& team, const std::function<void()>& first_form);
+// What the device's numbers of steps come to (steps of every (row tile, segment), of every (32 rows, segment), below 0 if there
+// are too many, and the sums of 32 rows of every (32 rows, segment)): all of the layout but the steps, the forms' dimensions, and
+// what stands in front of their records, the first form's `head` bytes, then the wide one's.
+void dims_from_steps(int64_t N, int64_t K, const int32_t* steps, const int32_t* wide_steps, const int32_t* sums, HostLayout& hl,
+                     DeviceForms& f, std::vector<uint8_t>& heads, int64_t& head);
+// Both forms made on the device, in one allocation, from a weight whose rows lie back to back (spmm_pack.hip).  `reserve` (false:
+// no memory for it there, the host packs instead), `begin` sends the weight and starts, `finish` allocates the forms and returns a
+// hipError_t when they are there for every stream.
+class DevicePack {
+public:
+    DevicePack() = default;
+    ~DevicePack();
+    DevicePack(const DevicePack&) = delete;
+    DevicePack& operator=(const DevicePack&) = delete;
+    bool reserve(int64_t N, int64_t K, spmm_block_t block);
+    void begin(const int8_t* W);
+    int finish(HostLayout& hl, DeviceForms& f, uint8_t** weight);
+
+private:
+    void give_back();
+    uint8_t* scratch_ = nullptr;
+    int64_t N_ = 0, K_ = 0, nseg_ = 0, ntiles_ = 0, nt_ = 0, info_at_ = 0, slots_at_ = 0, wide_slots_at_ = 0, heads_at_ = 0;
+    int error_ = 0;
+    bool n4_ = false;
+};
 // those steps as HostLayout has them (either may be null)
 void export_steps(const HostLayout& hl, const DeviceForms& f, uint8_t* vals, uint32_t* idx);
 

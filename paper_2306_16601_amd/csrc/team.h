@@ -38,6 +38,9 @@ public:
     template <typename F>
     void run(int64_t n, int64_t piece, const F& f) { run(n, piece, f, [] {}, false); }
 
+    template <typename F, typename O>
+    void run(int64_t n, int64_t piece, const F& f, const O& own) { run(n, piece, f, own, false); }
+
     // the last pass: the threads end when nothing is left of it, instead of being woken for that
     template <typename F>
     void finish(int64_t n, int64_t piece, const F& f) { run(n, piece, f, [] {}, true); }

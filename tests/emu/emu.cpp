@@ -227,6 +227,16 @@ int readfirstlane(int v)
     wave_sync(w, "readfirstlane (collect)");
     return r;
 }
+uint64_t ballot(bool v)
+{
+    Wave& w = my_wave();
+    w.iv[cur()->linear & 63] = v;
+    wave_sync(w, "ballot (deposit)");
+    uint64_t r = 0;
+    for (int i = 0; i < 64; ++i) r |= (uint64_t)(w.iv[i] != 0) << i;
+    wave_sync(w, "ballot (collect)");
+    return r;
+}
 int readlane(int v, int src)
 {
     Wave& w = my_wave();

@@ -59,6 +59,7 @@ unsigned count_up(unsigned* p, unsigned v, int order);
 typedef unsigned v2u_t __attribute__((ext_vector_type(2)));
 v2u_t permlane_swap(unsigned a, unsigned b, int rows);
 int readlane(int v, int lane);
+uint64_t ballot(bool v);
 void launch(dim3 grid, dim3 block, const std::function<void()>& fn);
 void* dev_alloc(size_t bytes);
 void dev_free(void* p);
@@ -74,6 +75,7 @@ extern thread_local int last_error;     // as the runtime keeps it: of the last 
 
 #define __builtin_amdgcn_readfirstlane(v) emu::readfirstlane((int)(v))
 #define __builtin_amdgcn_readlane(v, l) emu::readlane((int)(v), (int)(l))
+#define __builtin_amdgcn_ballot_w64(v) emu::ballot(v)
 #define __builtin_amdgcn_ds_read_tr8_b64_v2i32(p) emu::tr8((const void*)(uintptr_t)(p))
 #define __builtin_amdgcn_mfma_i32_16x16x64_i8(a, b, c, x, y, z) emu::mfma_i8_16x16x64((a), (b), (c))
 #define __builtin_amdgcn_smfmac_i32_32x32x64_i8(a, b, c, sel, x, y) emu::smfmac_i8_32x32x64((a), (b), (c), (sel))
@@ -167,6 +169,7 @@ static inline hipError_t hipMalloc(void** p, size_t n)
 static inline hipError_t hipFree(void* p) { emu::dev_free(p); return hipSuccess; }
 static inline hipError_t hipMemset(void* p, int v, size_t n) { memset(p, v, n); return hipSuccess; }
 static inline hipError_t hipMemcpy(void* d, const void* s, size_t n, int) { memcpy(d, s, n); return hipSuccess; }
+static inline hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
 static inline hipError_t hipGetDevice(int* d) { *d = 0; return hipSuccess; }
 static inline hipError_t hipDeviceGetAttribute(int* v, int, int)
 {

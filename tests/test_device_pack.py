@@ -1,0 +1,84 @@
+"""Large weights' device forms are made on the device: the same bytes as the host's, and what a pack does when memory is short."""
+import os
+import subprocess
+import sys
+
+import numpy as np
+import pytest
+
+import paper_2306_16601_amd as sp
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+sys.path.insert(0, HERE)
+sys.path.insert(0, os.path.join(HERE, "emu"))
+import build_emu  # noqa: E402
+from test_short_memory import pack_and_run  # noqa: E402
+
+emulated = pytest.mark.skipif(not build_emu.available(), reason="no host clang++ for the emulation build")
+
+
+@pytest.fixture(scope="module")
+def driver(tmp_path_factory):
+    """The packer's two sources and the emulation, without the product kernels."""
+    out, csrc = tmp_path_factory.mktemp("device_pack"), os.path.join(ROOT, "paper_2306_16601_amd", "csrc")
+    subprocess.run([build_emu.CXX, "-std=c++17", "-O1", "-g", "-w", "-I", os.path.join(HERE, "emu", "include"), "-I", os.path.join(ROOT, "include"),
+                    "-I", csrc, "-x", "c++", os.path.join(HERE, "emu", "device_pack.cpp"), os.path.join(csrc, "spmm_pack.hip"),
+                    os.path.join(csrc, "pack.cpp"), os.path.join(HERE, "emu", "emu.cpp"), "-lpthread", "-o", str(out / "driver")], check=True)
+    return str(out / "driver")
+
+
+# percent of the blocks kept; the wide form: made without a step more than the lists ask for, with more, with left-over k and
+# exchanges (n1k4 at 20 %), not at all (too many steps)
+@emulated
+@pytest.mark.parametrize("N,K,percent,block,jitter", [
+    (1, 1, 100, "n4k1", 0), (33, 513, 30, "n4k1", 0), (64, 512, 20, "n4k1", 20), (95, 1100, 10, "n4k1", 5), (130, 1537, 30, "n4k1", 0),
+    (32, 511, 100, "n4k1", 0), (50, 700, 0, "n4k1", 0), (48, 640, 0, "n4k1", 2), (17, 5000, 25, "n4k1", 0), (31, 600, 45, "n4k1", 0),
+    (96, 512, 10, "n1k4", 0), (47, 777, 20, "n1k4", 10), (64, 1024, 25, "n1k4", 0), (33, 515, 40, "n1k4", 0), (70, 514, 2, "n1k4", 2)])
+def test_the_device_makes_the_bytes_that_the_host_does(driver, N, K, percent, block, jitter):
+    r = subprocess.run([driver, str(N), str(K), str(percent), block, str(jitter)], capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0 and r.stdout.startswith("ok"), (r.returncode, r.stdout[-300:], r.stderr[-1000:])
+
+
+@emulated
+@pytest.mark.parametrize("failing,expected", [(0b1, "both"), (0b10, "first"), (0b11, "first"), (0b110, "none")])
+def test_short_memory_on_the_device(failing, expected):
+    """Without memory for the scratch the host packs (its two allocations follow); without memory for both forms there is the
+    first."""
+    res = pack_and_run(1024, 1040, failing)
+    if failing == 0b11:         # (of the host's allocations the first one fails)
+        expected = "none"
+    assert res["left"] == 0
+    if expected == "none":
+        assert "allocation failed" in res["error"]
+        return
+    assert "error" not in res and res["match"] and res["unpacked"]
+    assert ("smfmac" in res["kernel"]) == (expected == "both") and (res["device_bytes"] == res["both"]) == (expected == "both")
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("N,K,density,block", [(1024, 1024, 0.2, "n4k1"), (1033, 1021, 0.1, "n4k1"), (257, 4096, 0.3, "n4k1"), (1024, 1025, 0.1, "n1k4"),
+                                               (1100, 1000, 0.0, "n4k1")])
+def test_a_weight_packed_on_the_device_runs(N, K, density, block):
+    """Exact accumulators over both forms, and the weight handed back; rows that do not lie back to back take the host's way."""
+    import torch
+    rng = np.random.default_rng(N + K)
+    keep = rng.random((-(-N // 4), K) if block == "n4k1" else (N, -(-K // 4))) < density
+    keep = np.repeat(keep, 4, axis=0)[:N] if block == "n4k1" else np.repeat(keep, 4, axis=1)[:, :K]
+    W = np.where(keep, rng.integers(-128, 128, (N, K)), 0).astype(np.int8)
+    X = rng.integers(0, 256, (K, 70), dtype=np.uint8)
+    strided = np.zeros((N, K + 3), dtype=np.int8)
+    strided[:, :K] = W
+    x, ref = torch.from_numpy(X).cuda(), W.astype(np.int64) @ X.astype(np.int64)
+    for weight in (W, strided[:, :K]):
+        h = sp.spmm_pack(weight, block)
+        try:
+            assert np.array_equal(sp.spmm_unpack(h), W)
+            variants = [(0, 0), (16, 101), (32, 101), (64, 104)] + ([(32, 134), (64, 134)] if density else [])
+            for tuning in variants:
+                sp.spmm_set_tuning(h, *tuning)
+                out = torch.full((N, 70), -1, dtype=torch.int32, device="cuda")
+                sp.spmm_run(h, x, 70, 70, sp.make_epilogue(None, 1.0, 0, None, "none", "s32"), out, 70, torch.cuda.current_stream().cuda_stream)
+                assert np.array_equal(out.cpu().numpy(), ref), tuning
+        finally:
+            sp.spmm_destroy(h)
