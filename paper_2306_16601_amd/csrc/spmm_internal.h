@@ -254,11 +254,12 @@ bool plan_supported(int token_tile, int variant);
 // x_fast: see KernelArgs; an X without it takes the simple kernel, whatever was forced
 // out_fast: 32-bit offsets suffice for out; if not, the automatic choice avoids the 16-wave pipelined
 // kernels, whose general store path is slow for want of registers
-// equal_parts: the short-batch kernels' workgroups may be dealt to the XCDs in equal parts, as every launch has it (without: as in
-// the measurements that the estimates are fitted to and compared with, which are of before that)
+// as_they_are: the resident kernels by estimates of their own, and the short-batch kernels' workgroups dealt to the XCDs in equal parts
+// where that saves a round, as every launch has it (without: as in the measurements that the other estimates are fitted to and
+// compared with, which are of before that)
 // widest: widest token tile of the wide form that the post-operators run with (wide_tile), and its handicap (wide_handicap)
 Plan make_plan(int64_t M, const WeightDims& w, int num_cus, int force_tm, int variant, int out_bytes = 1,
-               bool x_fast = true, bool out_fast = true, int widest = 128, double wide_handicap = 1.0, bool equal_parts = false);
+               bool x_fast = true, bool out_fast = true, int widest = 128, double wide_handicap = 1.0, bool as_they_are = false);
 // Launches the SpMM kernel; returns a hipError_t value as int (0 = success).
 // postop: SPMM_POST_* value, plus POST_SUM_BIT when a.sum is to be added
 constexpr int POST_SUM_BIT = 4;   // (a bit no SPMM_POST_* value uses)
