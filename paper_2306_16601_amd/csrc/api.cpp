@@ -127,6 +127,10 @@ static spmm_status_t pack_common(const int8_t* W_host, int64_t N, int64_t K, int
         }
         const spmm::Beside beside = {[&] { pack.begin(W_host); }, [&] { e = (hipError_t)pack.finish(h->hl, h->forms, &h->d_weight); }};
         spmm::bsr_from_dense(W_host, N, K, ldw, block, h->bsr, team, there ? &beside : nullptr);
+        if (there && e == hipErrorOutOfMemory) {
+            there = false;
+            e = hipSuccess;
+        }
         h->nnz_blocks = (int64_t)h->bsr.index.size();
         spmm::Bsr reordered;
         if (reorder) {

@@ -160,8 +160,9 @@ void forms_from_bsr(const Bsr& b, HostLayout& hl, DeviceForms& f, Team& team, co
 void dims_from_steps(int64_t N, int64_t K, const int32_t* steps, const int32_t* wide_steps, const int32_t* sums, HostLayout& hl,
                      DeviceForms& f, std::vector<uint8_t>& heads, int64_t& head);
 // Both forms made on the device, in one allocation, from a weight whose rows lie back to back (spmm_pack.hip).  `reserve` (false:
-// no memory for it there, the host packs instead), `begin` sends the weight and starts, `finish` allocates the forms and returns a
-// hipError_t when they are there for every stream.
+// no memory for it there, the host packs instead), `begin` sends the weight and starts, `finish` allocates the forms, gives what was
+// reserved back, and returns a hipError_t when they are there for every stream (out of memory: the host packs instead, which may
+// fit without what was reserved).
 class DevicePack {
 public:
     DevicePack() = default;

@@ -508,12 +508,6 @@ int DevicePack::finish(HostLayout& hl, DeviceForms& f, uint8_t** weight)
         int64_t head = 0;
         dims_from_steps(N_, K_, info.get(), info.get() + ntiles_ * nseg_, info.get() + (ntiles_ + nt_) * nseg_, hl, f, heads, head);
         e = hipMalloc((void**)weight, (size_t)(f.size + f.wide_size));
-        if (e == hipErrorOutOfMemory && f.wide_size) {      // (a weight runs without the wide form)
-            (void)hipGetLastError();
-            f.drop_wide();
-            heads.resize((size_t)head);
-            e = hipMalloc((void**)weight, (size_t)f.size);
-        }
         if (e != hipSuccess) *weight = nullptr;
         if (e == hipSuccess) e = hipMemcpy(scratch_ + heads_at_, heads.data(), heads.size(), hipMemcpyHostToDevice);
         if (e == hipSuccess) {

@@ -41,13 +41,11 @@ def test_the_device_makes_the_bytes_that_the_host_does(driver, N, K, percent, bl
 
 
 @emulated
-@pytest.mark.parametrize("failing,expected", [(0b1, "both"), (0b10, "first"), (0b11, "first"), (0b110, "none")])
+@pytest.mark.parametrize("failing,expected", [(0b1, "both"), (0b10, "both"), (0b1010, "first"), (0b11, "none"), (0b110, "none")])
 def test_short_memory_on_the_device(failing, expected):
-    """Without memory for the scratch the host packs (its two allocations follow); without memory for both forms there is the
-    first."""
+    """The device allocates its scratch, then both forms; where either does not fit, the host packs, which allocates the first form,
+    then the wide one.  Without memory for that one the weight has only the first."""
     res = pack_and_run(1024, 1040, failing)
-    if failing == 0b11:         # (of the host's allocations the first one fails)
-        expected = "none"
     assert res["left"] == 0
     if expected == "none":
         assert "allocation failed" in res["error"]
