@@ -1,11 +1,12 @@
 """Builds tests/emu/_build/libspmm4x1_emu.so: the library's own sources compiled for the host
-against the emulation shim in include/hip/hip_runtime.h (see there), with three textual changes:
+against the emulation shim in include/hip/hip_runtime.h (see there), with four textual changes:
   * the empty inline-assembly statements that pin a value to a vector register become no-ops;
   * where the lanes of a wave exchange data through LDS without a barrier (the transpose of 1-byte
     outputs, which relies on a wave's LDS operations completing in order), the emulated wave is
     brought into step before and after the read, because its lanes run one after the other here;
   * counting up in LDS, by which one wave hands memory to another, goes through a function that
-    checks for the release before it.
+    checks for the release before it;
+  * a kernel is launched as a function of its argument's type, not by its address.
 Test infrastructure only; nothing in the product path imports or loads it."""
 from __future__ import annotations
 
@@ -58,6 +59,7 @@ def build(force: bool = False) -> str:
         s = s.replace('const v4i v = *(const v4i*)(lds + raddr);',
                       'emu::wave_barrier(); const v4i v = *(const v4i*)(lds + raddr); emu::wave_barrier();')
         s = s.replace('__atomic_fetch_add(', 'emu::count_up(')
+        s = s.replace('hipLaunchKernel((const void*)kernel, ', 'hipLaunchKernel(kernel, ')
         code = re.sub(r'//.*', '', s)
         if re.search(r'\basm\b', code):
             raise RuntimeError("inline assembly in %s that the emulation build does not know" % f)

@@ -14,6 +14,7 @@
 #include <cstring>
 #include <algorithm>
 #include <functional>
+#include <type_traits>
 
 #define __global__
 #define __device__
@@ -185,3 +186,11 @@ static inline hipError_t hipGetLastError()
 }
 #define hipLaunchKernelGGL(kernel, grid, block, shmem, stream, ...) \
     emu::launch((grid), (block), [=]() { kernel(__VA_ARGS__); })
+// (the kernel as a function and not as an address: build_emu.py)
+template <typename A>
+static inline hipError_t hipLaunchKernel(void (*kernel)(A), dim3 grid, dim3 block, void** args, size_t, hipStream_t)
+{
+    const typename std::remove_const<A>::type a = *(const A*)args[0];
+    emu::launch(grid, block, [=]() { kernel(a); });
+    return hipSuccess;
+}
