@@ -448,6 +448,14 @@ __global__ void __launch_bounds__(THREADS) spmm_pack_records(const PackArgs a)
     }
 }
 
+// By its address, which returns the launch's own error: the one that the runtime keeps may be of any earlier call that failed, and
+// stays for whoever asks for it.
+hipError_t launch(void (*kernel)(PackArgs), int64_t nt, int64_t nseg, const PackArgs& a)
+{
+    const void* args[] = {&a};
+    return hipLaunchKernel((const void*)kernel, dim3((unsigned)nt, (unsigned)nseg), dim3(THREADS), (void**)args, 0, nullptr);
+}
+
 constexpr int64_t up(int64_t bytes) { return (bytes + 255) & ~(int64_t)255; }
 
 }  // namespace
@@ -493,8 +501,7 @@ void DevicePack::begin(const int8_t* W)
     a.nseg = (int)nseg_;
     a.ntiles = (int)ntiles_;
     a.n4 = n4_;
-    hipLaunchKernelGGL(spmm_pack_lists, dim3((unsigned)nt_, (unsigned)nseg_), dim3(THREADS), 0, nullptr, a);
-    error_ = hipGetLastError();
+    error_ = launch(spmm_pack_lists, nt_, nseg_, a);
 }
 
 int DevicePack::finish(HostLayout& hl, DeviceForms& f, uint8_t** weight)
@@ -527,8 +534,7 @@ int DevicePack::finish(HostLayout& hl, DeviceForms& f, uint8_t** weight)
             a.tile_steps = f.tile_steps;
             a.wide_tile_steps = f.wide_tile_steps;
             a.n4 = n4_;
-            hipLaunchKernelGGL(spmm_pack_records, dim3((unsigned)nt_, (unsigned)nseg_), dim3(THREADS), 0, nullptr, a);
-            e = hipGetLastError();
+            e = launch(spmm_pack_records, nt_, nseg_, a);
             if (e == hipSuccess) e = hipStreamSynchronize(nullptr);        // (the weight is there for every stream when the call returns)
         }
     }

@@ -398,6 +398,8 @@ struct Install { Install() {
 extern "C" int spmm_measure_peak(int, double*) { return 2; /* SPMM_E_UNSUPPORTED */ }
 extern "C" void* emu_alloc(size_t bytes) { return emu::dev_alloc(bytes); }
 extern "C" void emu_fail_mallocs(unsigned which) { emu::failing_mallocs = which; }
+extern "C" void emu_leave_error(int e) { emu::last_error = e; }
+extern "C" int emu_error_left() { return emu::last_error; }
 extern "C" long emu_products() { return emu::products; }
 extern "C" long emu_allocations() { return (long)emu::allocs.size(); }
 extern "C" void emu_free(void* p) { emu::dev_free(p); }

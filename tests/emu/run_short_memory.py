@@ -1,6 +1,7 @@
 """Packs a weight with the host-emulated library while device memory is short, and runs it.  Called as a subprocess by
 tests/test_short_memory.py; prints one JSON line.
-usage: python run_short_memory.py N K failing (bit i: the i-th device allocation of the pack fails)"""
+usage: python run_short_memory.py N K failing [pending] (bit i: the i-th device allocation of the pack fails; pending: the error
+that some earlier call left for whoever asks next)"""
 import ctypes
 import json
 import os
@@ -15,7 +16,7 @@ sys.path.insert(0, HERE)
 
 
 def main():
-    N, K, failing = (int(v) for v in sys.argv[1:4])
+    N, K, failing, pending = (int(v) for v in (sys.argv[1:] + ["0"])[:4])
     os.environ["EMU_CUS"] = "4"
     import build_emu
     import paper_2306_16601_amd.binding as b
@@ -36,12 +37,14 @@ def main():
     sp.spmm_destroy(whole)
     before = L.emu_allocations()
     L.emu_fail_mallocs(failing)
+    L.emu_leave_error(pending)
     try:
         h = sp.spmm_pack(W)
     except Exception as e:
         print(json.dumps({"error": str(e), "left": L.emu_allocations() - before}))
         return
     L.emu_fail_mallocs(0)
+    error_left = L.emu_error_left()
     sp.spmm_set_tuning(h, 32, 134)
     kernel = sp.spmm_kernel_variant(h, M, "s32", "none")
     sp.spmm_run(h, x, M, M, sp.make_epilogue(None, 1.0, 0, None, "none", "s32"), out, M, None)
@@ -51,7 +54,7 @@ def main():
     unpacked = bool(np.array_equal(sp.spmm_unpack(h), W))
     device_bytes = sp.spmm_info(h)[4]
     sp.spmm_destroy(h)
-    print(json.dumps({"match": match, "unpacked": unpacked, "kernel": kernel, "device_bytes": device_bytes, "both": both,
+    print(json.dumps({"match": match, "unpacked": unpacked, "kernel": kernel, "device_bytes": device_bytes, "both": both, "error_left": error_left,
                       "left": L.emu_allocations() - before}))
 
 

@@ -20,8 +20,9 @@ emulated = pytest.mark.skipif(not build_emu.available(), reason="no host clang++
 
 @pytest.fixture(scope="module")
 def driver(tmp_path_factory):
-    """The packer's two sources and the emulation, without the product kernels."""
-    out, csrc = tmp_path_factory.mktemp("device_pack"), os.path.join(ROOT, "paper_2306_16601_amd", "csrc")
+    """The packer's two sources, as the emulation changes them, and the emulation, without the product kernels."""
+    build_emu.build()
+    out, csrc = tmp_path_factory.mktemp("device_pack"), os.path.join(build_emu.OUT, "src")
     subprocess.run([build_emu.CXX, "-std=c++17", "-O1", "-g", "-w", "-I", os.path.join(HERE, "emu", "include"), "-I", os.path.join(ROOT, "include"),
                     "-I", csrc, "-x", "c++", os.path.join(HERE, "emu", "device_pack.cpp"), os.path.join(csrc, "spmm_pack.hip"),
                     os.path.join(csrc, "pack.cpp"), os.path.join(HERE, "emu", "emu.cpp"), "-lpthread", "-o", str(out / "driver")], check=True)
@@ -52,6 +53,14 @@ def test_short_memory_on_the_device(failing, expected):
         return
     assert "error" not in res and res["match"] and res["unpacked"]
     assert ("smfmac" in res["kernel"]) == (expected == "both") and (res["device_bytes"] == res["both"]) == (expected == "both")
+
+
+@emulated
+@pytest.mark.parametrize("N,K", [(1024, 1040), (64, 600)])        # forms made by the device, by the host
+def test_an_error_left_by_an_earlier_call_is_not_the_pack_s(N, K):
+    """600: the runtime's answer to a query of an event that is not over, say.  The pack neither takes it for its own nor takes it away."""
+    res = pack_and_run(N, K, 0, pending=600)
+    assert "error" not in res and res["match"] and res["unpacked"] and res["device_bytes"] == res["both"] and res["error_left"] == 600, res
 
 
 @pytest.mark.gpu
