@@ -539,7 +539,11 @@ int DevicePack::finish(HostLayout& hl, DeviceForms& f, uint8_t** weight)
         }
     }
     give_back();
-    if (e != hipSuccess) (void)hipGetLastError();
+    if (e != hipSuccess) {
+        if (*weight) (void)hipFree(*weight);        // (the host may pack instead, into an allocation of its own)
+        *weight = nullptr;
+        (void)hipGetLastError();
+    }
     return e;
 }
 

@@ -340,7 +340,7 @@ void launch(dim3 grid, dim3 block, const std::function<void()>& fn)
 static std::mutex alloc_mu;
 struct Alloc { void* base; size_t total; };
 static std::vector<std::pair<void*, Alloc>> allocs;
-unsigned failing_mallocs = 0;
+unsigned failing_mallocs = 0, failing_copies = 0;
 thread_local int last_error = 0;
 void* dev_alloc(size_t bytes)
 {
@@ -398,6 +398,7 @@ struct Install { Install() {
 extern "C" int spmm_measure_peak(int, double*) { return 2; /* SPMM_E_UNSUPPORTED */ }
 extern "C" void* emu_alloc(size_t bytes) { return emu::dev_alloc(bytes); }
 extern "C" void emu_fail_mallocs(unsigned which) { emu::failing_mallocs = which; }
+extern "C" void emu_fail_copies(unsigned which) { emu::failing_copies = which; }
 extern "C" void emu_leave_error(int e) { emu::last_error = e; }
 extern "C" int emu_error_left() { return emu::last_error; }
 extern "C" long emu_products() { return emu::products; }

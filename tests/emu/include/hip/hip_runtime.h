@@ -65,6 +65,7 @@ void launch(dim3 grid, dim3 block, const std::function<void()>& fn);
 void* dev_alloc(size_t bytes);
 void dev_free(void* p);
 extern unsigned failing_mallocs;        // bit i: the i-th hipMalloc from here on finds no memory
+extern unsigned failing_copies;         // bit i: the i-th hipMemcpy does not (for what it copies through)
 extern thread_local int last_error;     // as the runtime keeps it: of the last call that failed, until it is asked for
 }  // namespace emu
 
@@ -169,7 +170,14 @@ static inline hipError_t hipMalloc(void** p, size_t n)
 }
 static inline hipError_t hipFree(void* p) { emu::dev_free(p); return hipSuccess; }
 static inline hipError_t hipMemset(void* p, int v, size_t n) { memset(p, v, n); return hipSuccess; }
-static inline hipError_t hipMemcpy(void* d, const void* s, size_t n, int) { memcpy(d, s, n); return hipSuccess; }
+static inline hipError_t hipMemcpy(void* d, const void* s, size_t n, int)
+{
+    const bool fails = emu::failing_copies & 1;
+    emu::failing_copies >>= 1;
+    if (fails) return emu::last_error = hipErrorOutOfMemory;
+    memcpy(d, s, n);
+    return hipSuccess;
+}
 static inline hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
 static inline hipError_t hipGetDevice(int* d) { *d = 0; return hipSuccess; }
 static inline hipError_t hipDeviceGetAttribute(int* v, int, int)

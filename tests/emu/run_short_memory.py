@@ -1,7 +1,7 @@
 """Packs a weight with the host-emulated library while device memory is short, and runs it.  Called as a subprocess by
 tests/test_short_memory.py; prints one JSON line.
-usage: python run_short_memory.py N K failing [pending] (bit i: the i-th device allocation of the pack fails; pending: the error
-that some earlier call left for whoever asks next)"""
+usage: python run_short_memory.py N K failing [pending] [copies] (bit i: the i-th device allocation of the pack fails; pending: the
+error that some earlier call left for whoever asks next; bit i: the i-th copy finds no memory)"""
 import ctypes
 import json
 import os
@@ -16,7 +16,7 @@ sys.path.insert(0, HERE)
 
 
 def main():
-    N, K, failing, pending = (int(v) for v in (sys.argv[1:] + ["0"])[:4])
+    N, K, failing, pending, copies = (int(v) for v in (sys.argv[1:] + ["0", "0"])[:5])
     os.environ["EMU_CUS"] = "4"
     import build_emu
     import paper_2306_16601_amd.binding as b
@@ -37,6 +37,7 @@ def main():
     sp.spmm_destroy(whole)
     before = L.emu_allocations()
     L.emu_fail_mallocs(failing)
+    L.emu_fail_copies(copies)
     L.emu_leave_error(pending)
     try:
         h = sp.spmm_pack(W)

@@ -56,6 +56,14 @@ def test_short_memory_on_the_device(failing, expected):
 
 
 @emulated
+@pytest.mark.parametrize("copies", [0b1, 0b10, 0b100])           # of the weight, of the numbers of steps, of what stands before the records
+def test_a_copy_without_memory_leaves_nothing_behind(copies):
+    """The host packs then, into an allocation of its own."""
+    res = pack_and_run(1024, 1040, 0, copies=copies)
+    assert "error" not in res and res["match"] and res["unpacked"] and res["device_bytes"] == res["both"] and res["left"] == 0, res
+
+
+@emulated
 @pytest.mark.parametrize("N,K", [(1024, 1040), (64, 600)])        # forms made by the device, by the host
 def test_an_error_left_by_an_earlier_call_is_not_the_pack_s(N, K):
     """600: the runtime's answer to a query of an event that is not over, say.  The pack neither takes it for its own nor takes it away."""

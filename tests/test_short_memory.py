@@ -16,9 +16,9 @@ import build_emu  # noqa: E402
 CXX = shutil.which("clang++") or "/opt/rocm/llvm/bin/clang++"
 
 
-def pack_and_run(N, K, failing, pending=0):
+def pack_and_run(N, K, failing, pending=0, copies=0):
     build_emu.build()
-    r = subprocess.run([sys.executable, os.path.join(HERE, "emu", "run_short_memory.py"), str(N), str(K), str(failing), str(pending)],
+    r = subprocess.run([sys.executable, os.path.join(HERE, "emu", "run_short_memory.py"), str(N), str(K), str(failing), str(pending), str(copies)],
                        capture_output=True, text=True, timeout=300)
     assert r.returncode == 0, r.stderr[-2000:]
     return json.loads(r.stdout.strip().splitlines()[-1])
