@@ -29,8 +29,7 @@ public:
             pass_.fetch_add(1);
         }
         work_.notify_all();
-        for (int i = 0; i < most_; ++i)         // (a thread starts two others before it can end)
-            if (threads_[i].joinable()) threads_[i].join();
+        join();
     }
     Team(const Team&) = delete;
     Team& operator=(const Team&) = delete;
@@ -41,7 +40,9 @@ public:
     template <typename F, typename O>
     void run(int64_t n, int64_t piece, const F& f, const O& own) { run(n, piece, f, own, false); }
 
-    // the last pass: the threads end when nothing is left of it, instead of being woken for that
+    // the last pass: the threads end when nothing is left of it, instead of being woken for that (a pass after it starts them anew:
+    // where the device turns out to have no memory for what it was to pack, the host's passes follow; 4096x4096 at 70 %, 6.6 ms
+    // instead of 39 by the calling thread alone)
     template <typename F>
     void finish(int64_t n, int64_t piece, const F& f) { run(n, piece, f, [] {}, true); }
     template <typename F, typename O>
@@ -57,6 +58,11 @@ private:
             for (int64_t i = 0; i < pieces; ++i) f(i * piece, std::min(n, (i + 1) * piece));
             return;
         }
+        if (over_) {
+            join();
+            started_ = false;
+        }
+        over_ = last;
         const std::function<void(int64_t)> call = [&](int64_t i) { f(i * piece, std::min(n, (i + 1) * piece)); };
         {
             const std::lock_guard<std::mutex> lock(mutex_);
@@ -88,6 +94,11 @@ private:
         if (failed) std::rethrow_exception(failed);
     }
 
+    void join()
+    {
+        for (int i = 0; i < most_; ++i)         // (a thread starts two others before it can end)
+            if (threads_[i].joinable()) threads_[i].join();
+    }
     // a piece, if one is left
     bool work()
     {
@@ -132,7 +143,7 @@ private:
     }
 
     int most_;                  // threads besides the caller's
-    bool started_ = false;
+    bool started_ = false, over_ = false;       // over_: by `finish`
     std::atomic<bool> end_{false};
     std::thread threads_[7];
     std::mutex mutex_;
