@@ -462,9 +462,11 @@ constexpr int64_t up(int64_t bytes) { return (bytes + 255) & ~(int64_t)255; }
 
 DevicePack::~DevicePack() { give_back(); }
 
+// (hipFree waits for all streams of the device, also for those that the default stream does not wait for: 45 ms of a program's other
+// work were in the pack.  In the default stream's order the memory goes back when that stream is done, as the pool keeps none of it.)
 void DevicePack::give_back()
 {
-    if (scratch_) (void)hipFree(scratch_);
+    if (scratch_) (void)hipFreeAsync(scratch_, nullptr);
     scratch_ = nullptr;
 }
 
@@ -481,7 +483,7 @@ bool DevicePack::reserve(int64_t N, int64_t K, spmm_block_t block)
     wide_slots_at_ = slots_at_ + up(ntiles_ * nseg_ * SEGMENT_ROWS * 2);
     heads_at_ = wide_slots_at_ + up(nt_ * nseg_ * SEGMENT_ROWS * 2);
     const int64_t size = heads_at_ + records_offset(ntiles_, nseg_) + RECORD_BYTES + wide_records_offset(nt_, nseg_) + WIDE_RECORD_BYTES;
-    if (hipMalloc((void**)&scratch_, (size_t)size) == hipSuccess) return true;
+    if (hipMallocAsync((void**)&scratch_, (size_t)size, nullptr) == hipSuccess) return true;
     scratch_ = nullptr;
     (void)hipGetLastError();
     return false;

@@ -169,6 +169,8 @@ static inline hipError_t hipMalloc(void** p, size_t n)
     return *p ? hipSuccess : hipErrorOutOfMemory;
 }
 static inline hipError_t hipFree(void* p) { emu::dev_free(p); return hipSuccess; }
+static inline hipError_t hipMallocAsync(void** p, size_t n, hipStream_t) { return hipMalloc(p, n); }
+static inline hipError_t hipFreeAsync(void* p, hipStream_t) { return hipFree(p); }
 static inline hipError_t hipMemset(void* p, int v, size_t n) { memset(p, v, n); return hipSuccess; }
 static inline hipError_t hipMemcpy(void* d, const void* s, size_t n, int)
 {

@@ -97,3 +97,27 @@ def test_a_weight_packed_on_the_device_runs(N, K, density, block):
                 assert np.array_equal(out.cpu().numpy(), ref), tuning
         finally:
             sp.spmm_destroy(h)
+
+
+@pytest.mark.gpu
+def test_a_pack_does_not_wait_for_other_streams():
+    """A model's next weight is packed beside work that is under way on streams of its own."""
+    import torch
+    W = np.where(np.random.default_rng(1).random((1024, 1024)) < 0.2, 3, 0).astype(np.int8)
+    a, b = torch.zeros((2, 8192, 8192), dtype=torch.bfloat16, device="cuda")
+    other = torch.cuda.Stream()
+    with torch.cuda.stream(other):
+        torch.mm(a, a, out=b)
+    sp.spmm_destroy(sp.spmm_pack(W))
+    torch.cuda.synchronize()
+    with torch.cuda.stream(other):
+        for _ in range(200):            # (150 ms; a pack takes 0.2)
+            torch.mm(a, a, out=b)
+    end = other.record_event()
+    h = sp.spmm_pack(W)
+    under_way = not end.query()
+    torch.cuda.synchronize()
+    try:
+        assert under_way and np.array_equal(sp.spmm_unpack(h), W)
+    finally:
+        sp.spmm_destroy(h)
