@@ -46,12 +46,22 @@ int64_t count_blocks_of_row(const int8_t* W, int64_t N, int64_t K, int64_t ldw, 
             n += some;
         }
     } else {
+        // (whole blocks on their own: with the length of the last one in question at every block, the canonical form of 256x256
+        // at 80 % took 159 us instead of 22, and 102 in a single pass)
         const int8_t* const r = W + br * ldw;
-        for (int64_t c = 0; c * 4 < K; ++c) {
-            uint32_t v = 0;
-            std::memcpy(&v, r + 4 * c, (size_t)std::min<int64_t>(4, K - 4 * c));
-            n += v != 0;
+        const int64_t whole = K / 4;
+        for (int64_t c0 = 0; c0 < whole; c0 += 1024) {
+            uint32_t some = 0;
+            for (int64_t c = c0; c < std::min(whole, c0 + 1024); ++c) {
+                uint32_t v;
+                std::memcpy(&v, r + 4 * c, 4);
+                some += v != 0;
+            }
+            n += some;
         }
+        uint32_t v = 0;
+        std::memcpy(&v, r + 4 * whole, (size_t)(K - 4 * whole));
+        n += v != 0;
     }
     return n;
 }
@@ -84,14 +94,20 @@ void blocks_of_row(const int8_t* W, int64_t N, int64_t K, int64_t ldw, spmm_bloc
             if (r[0][k] | r[1][k] | r[2][k] | r[3][k]) add(k);
     } else {
         const int8_t* r = W + br * ldw;
-        for (int64_t c = 0; c * 4 < K; ++c) {
-            uint32_t v = 0;
-            std::memcpy(&v, r + 4 * c, (size_t)std::min<int64_t>(4, K - 4 * c));
-            if (v) {
-                index[n] = (int32_t)c;
-                std::memcpy(vals + 4 * n++, &v, 4);
-            }
+        const int64_t whole = K / 4;
+        auto add = [&](int64_t c, uint32_t v) {
+            if (!v) return;
+            index[n] = (int32_t)c;
+            std::memcpy(vals + 4 * n++, &v, 4);
+        };
+        uint32_t v;
+        for (int64_t c = 0; c < whole; ++c) {
+            std::memcpy(&v, r + 4 * c, 4);
+            add(c, v);
         }
+        v = 0;
+        std::memcpy(&v, r + 4 * whole, (size_t)(K - 4 * whole));
+        add(whole, v);
     }
 }
 

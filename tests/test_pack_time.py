@@ -106,3 +106,70 @@ def test_a_weight_of_two_pieces_starts_one_thread(tmp_path):
     for line in run(tmp_path, THREADS).splitlines():
         pieces, threads = (int(v) for v in line.split())
         assert 1 <= threads <= min(pieces, 8), (pieces, threads)
+
+
+CANONICAL = r"""
+#include <chrono>
+#include <cstdint>
+#include <cstdio>
+#include <cstring>
+#include <vector>
+#include "spmm_internal.h"
+#include "team.h"
+using namespace spmm;
+
+// the blocks of a weight in one pass, to memory that is there
+static int64_t one_pass(const int8_t* W, int64_t N, int64_t K, int32_t* index, int8_t* vals)
+{
+    int64_t n = 0;
+    for (int64_t row = 0; row < N; ++row)
+        for (int64_t c = 0; c * 4 < K; ++c) {
+            uint32_t v = 0;
+            std::memcpy(&v, W + row * K + 4 * c, (size_t)(K - 4 * c < 4 ? K - 4 * c : 4));
+            if (v) {
+                index[n] = (int32_t)c;
+                std::memcpy(vals + 4 * n++, &v, 4);
+            }
+        }
+    return n;
+}
+
+int main()
+{
+    const int64_t N = 256, K = 256;
+    std::vector<int8_t> W((size_t)(N * K), 0);
+    uint32_t seed = 777;
+    for (int64_t block = 0; block < N * K / 4; ++block) {
+        seed = seed * 1664525u + 1013904223u;
+        if ((seed >> 8) % 100 < 20)
+            for (int64_t j = 0; j < 4; ++j) W[(size_t)(4 * block + j)] = (int8_t)(1 + (seed >> 9) % 127);
+    }
+    std::vector<int32_t> index((size_t)(N * K / 4));
+    std::vector<int8_t> vals((size_t)(N * K));
+    double best[2] = {1e9, 1e9};
+    for (int round = 0; round < 200; ++round)
+        for (int i = 0; i < 2; ++i) {
+            const auto t = std::chrono::steady_clock::now();
+            int64_t n = 0;
+            if (i) {
+                Team team;
+                Bsr b;
+                bsr_from_dense(W.data(), N, K, K, SPMM_BLOCK_N1K4, b, team);
+                n = (int64_t)b.index.size();
+            } else {
+                n = one_pass(W.data(), N, K, index.data(), vals.data());
+            }
+            const double us = std::chrono::duration<double>(std::chrono::steady_clock::now() - t).count() * 1e6;
+            if (us < best[i]) best[i] = us;
+            if (n < N * K / 4 / 6) return 1;
+        }
+    std::printf("%f %f\n", best[0], best[1]);
+}
+"""
+
+
+def test_1x4_blocks_counted_and_listed_cost_little_more_than_listed(tmp_path):
+    """The canonical form in its two passes takes 1.3 times as long as one pass over the weight that lists the same blocks (9 times,
+    when the length of the last one was in question at every block, in both passes)."""
+    once, counted = (float(v) for v in run(tmp_path, CANONICAL).split())
+    assert counted < 3 * once, (counted, once)
