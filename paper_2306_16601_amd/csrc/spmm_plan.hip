@@ -155,10 +155,13 @@ SPMM_INLINE void fill_wide(Plan& p, const Call& c, int tm, int waves)
 
 // Workgroups whose slices take more rounds than their number does, dealt to the XCDs in equal parts (decode_tile), in the order
 // that fetches less: an XCD's `each` consecutive workgroups touch so many row groups and so many token tiles.  A round saved is
-// worth far more than what the slices save: of 60 random problems of 256 to 4096 features, 32 to 1250 tokens, 70 to 90 %, where it
-// saves one (profiles/spmm_plan_equal_parts.csv), two rounds of the resident kernels become one of 0.78 of the time, of the ring 0.67;
-// no configuration is slower by more than runs of 4 us differ.  768x3072 at 80 %, 333 tokens with Sum, binary32, 12 row groups x 21
-// token tiles: 12.0 -> 8.0 us, and as 6 x 21, which it ran as before, 9.3; 1300x650 at 80 %, 665 tokens 7.1 -> 4.7.
+// worth more than what the slices save: of 67 random problems of 256 to 4096 features, 32 to 1250 tokens, 70 to 90 %, where it
+// saves one (profiles/spmm_plan_equal_parts.csv), no kernel is slower; two rounds of the resident kernels become one of 0.76 of the
+// time (with one K segment, where two workgroups share a CU, 0.89), two of the ring one of 0.66, three and more 0.85.  What the plan
+// then chooses takes 0.957 of the time that its choice by slices takes: 24 are more than 3 % faster, two slower, as the estimates
+// favour a dealt slab by more than it gains (1300x2600 at 80 %, 346 tokens 8.0 -> 8.7; 2304x4096 at 85 %, 217 tokens 9.7 -> 10.2).
+// 768x3072 at 80 %, 333 tokens with Sum, binary32, 12 row groups x 21 token tiles: 12.2 -> 8.1 us, and as 6 x 21, which it ran as
+// before, 9.2; 1300x650 at 80 %, 665 tokens 5.6 -> 4.8.
 static void deal(Plan& p, const Call& c, int each)
 {
     const double rows = p.n_row_groups, toks = p.n_tok_tiles;

@@ -1,5 +1,7 @@
 """Short batches whose workgroups are dealt to the XCDs in equal parts, where slices of the row groups and of the tokens would give
-some XCD a round of workgroups more: every number is dealt once, in both orders, by both bodies of the short-batch kernels."""
+some XCD a round of workgroups more: every number is dealt once, in both orders, by both bodies of the short-batch kernels, and the
+measured times bear the rule out."""
+import csv
 import os
 import sys
 
@@ -38,6 +40,28 @@ def test_one_round_of_workgroups(N, K, M, tuning, workgroups):
         assert -(-N // here[1]) * -(-M // here[0]) <= workgroups
     finally:
         sp.spmm_destroy(h)
+
+
+@pytest.mark.parametrize("us", ["us", "graph"])        # launches back to back, and replayed from a graph
+def test_dealing_gains_wherever_it_saves_a_round(us):
+    """What a comment in spmm_plan.hip says of profiles/spmm_plan_equal_parts.csv."""
+    table = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "profiles", "spmm_plan_equal_parts.csv")
+    rows = list(csv.DictReader(line for line in open(table) if not line.startswith("#")))
+
+    def ratios(which):
+        return np.array([float(r[us + "_equal"]) / float(r[us + "_slices"]) for r in rows if which(r)])
+
+    def one_segment(r):
+        return int(r["problem"].split()[0].split("x")[1]) <= 512
+
+    forced, two = ratios(lambda r: r["configuration"] != "auto"), [r for r in rows if r["rounds_slices"] == "2"]
+    assert len(forced) >= 100 and forced.max() < 1
+    for ring, alone, most in ((False, False, 0.77), (False, True, 0.90), (True, False, 0.67)):
+        of = ratios(lambda r: r in two and r["configuration"].endswith("/104") == ring and (one_segment(r) or not alone))
+        assert len(of) >= 8 and np.exp(np.log(of).mean()) <= most
+    automatic = ratios(lambda r: r["configuration"] == "auto")
+    assert len(automatic) >= 60 and np.exp(np.log(automatic).mean()) <= 0.965
+    assert (automatic > 1.03).sum() <= 2 and automatic.max() <= 1.09
 
 
 # (8 CUs, one to an XCD: any grid that its slices do not divide)
