@@ -212,8 +212,8 @@ SPMM_INLINE void fill_simple(Plan& p, const Call& c, int r, int tm, int waves = 
 // SLAB) have since become up to 1.3 times faster: a second set of fits is of them as they are, 1500 times on average for each,
 // within 9 to 16 %, and is what launches are planned by.  Of 800 problems that it was not fitted to
 // (profiles/spmm_plan_resident_measurements.csv: 256 to 4096 features, 16 to 6144 tokens, every type, layout and orientation) the
-// choices by the first set take 1.032 of the fastest configuration's time, over 1.1 in 12.8 %, those by the second 1.013 and 2.8 %;
-// 136 changed, 11 of all are more than 3 % slower, and together all are 1.019 times as fast (tests/test_plan_resident.py).
+// choices by the first set take 1.032 of the fastest configuration's time, over 1.1 in 11.9 %, those by the second 1.014 and 2.6 %;
+// 140 changed, 10 of all are more than 3 % slower, and together all are 1.018 times as fast (tests/test_plan_resident.py).
 // 1024x256 at 80 %, 1024 tokens, u8 with GELU: the ring with 32-token tiles, 4.26 us, becomes the resident kernel, 3.61.
 // A launch is a start, rounds of workgroups on the CUs, and in a round: phases (a K segment of a token tile) with
 // their matrix instructions and the staging of their activations, and the tiles' post-operators; what has to
