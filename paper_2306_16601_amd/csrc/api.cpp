@@ -99,7 +99,7 @@ spmm::Plan plan_for(const spmm_handle* h, int64_t M, spmm_out_t ot, bool gelu_f3
     const spmm::WeightDims w{h->ntiles, h->nseg, (int)h->bsr.K, h->nsteps, h->max_steps_per_segment,
                              h->max_steps_per_tile, h->forms.wide_max_steps, h->forms.wide_nsteps};
     return spmm::make_plan(M, w, h->num_cus, h->force_tm, h->force_r, bytes ? 1 : 4, x_fast, out_fast, spmm::wide_tile(gelu_f32, sum),
-                           spmm::wide_handicap(bytes, gelu_f32, sum, aligned_rows), true);
+                           spmm::wide_handicap(bytes, gelu_f32, sum, aligned_rows));
 }
 
 }  // namespace

@@ -127,8 +127,8 @@ constexpr int64_t wide_records_offset(int64_t ntiles, int64_t nseg)
 constexpr int wide_tile(bool gelu_f32, bool sum) { return sum ? 64 : gelu_f32 ? 96 : 128; }
 // What the estimates do not tell of the wide kernels against the others.  In the problems of
 // profiles/spmm_plan_wide_measurements.csv, estimate over measured time of the wide kernels and of the others: 1-byte outputs
-// 0.97 and 1.04, 4-byte ones 0.99 and 1.00, of these with GELU 0.96 and 0.96; Sum 0.94 and 0.93; rows that do not start at 16
-// bytes 0.82 and 0.89.  (The factors are of 6600 problems of other sizes, where Sum was 1.01 and 0.89.)
+// 0.96 and 1.02, 4-byte ones 0.98 and 0.99, of these with GELU 0.96 and 0.96; Sum 0.93 and 0.90; rows that do not start at 16
+// bytes 0.81 and 0.89.  (The factors are of 6600 problems of other sizes, where Sum was 1.01 and 0.89.)
 constexpr double wide_handicap(bool bytes, bool gelu_f32, bool sum, bool aligned_rows)
 {
     return (bytes ? 1.06 : 1.0) * (sum ? 0.92 : gelu_f32 ? 0.97 : 1.0) * (aligned_rows ? 1.0 : 1.09);
@@ -255,12 +255,9 @@ bool plan_supported(int token_tile, int variant);
 // x_fast: see KernelArgs; an X without it takes the simple kernel, whatever was forced
 // out_fast: 32-bit offsets suffice for out; if not, the automatic choice avoids the 16-wave pipelined
 // kernels, whose general store path is slow for want of registers
-// as_they_are: the resident kernels by estimates of their own, and the short-batch kernels' workgroups dealt to the XCDs in equal parts
-// where that saves a round, as every launch has it (without: as in the measurements that the other estimates are fitted to and
-// compared with, which are of before that)
 // widest: widest token tile of the wide form that the post-operators run with (wide_tile), and its handicap (wide_handicap)
 Plan make_plan(int64_t M, const WeightDims& w, int num_cus, int force_tm, int variant, int out_bytes = 1,
-               bool x_fast = true, bool out_fast = true, int widest = 128, double wide_handicap = 1.0, bool as_they_are = false);
+               bool x_fast = true, bool out_fast = true, int widest = 128, double wide_handicap = 1.0);
 // Launches the SpMM kernel; returns a hipError_t value as int (0 = success).
 // postop: SPMM_POST_* value, plus POST_SUM_BIT when a.sum is to be added
 constexpr int POST_SUM_BIT = 4;   // (a bit no SPMM_POST_* value uses)

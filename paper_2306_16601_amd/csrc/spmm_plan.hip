@@ -85,11 +85,9 @@ struct Call {
     int rank[4], split[4];              // rank[rb]: how many splits fetch less (or as much, with a smaller rb); and its inverse
     double w_bytes, x_bytes;
     double steps;                       // of a (row tile, segment), on average
-    bool equal_parts;                   // see make_plan
     double wide_steps = 0.0;            // the same of the wide form (set_wide_steps)
 
-    Call(int64_t tokens, const WeightDims& dims, int cus, bool deal)
-        : M(tokens), w(dims), num_cus(cus), per_xcd(cus >= 8 ? cus / 8 : 1), equal_parts(deal)
+    Call(int64_t tokens, const WeightDims& dims, int cus) : M(tokens), w(dims), num_cus(cus), per_xcd(cus >= 8 ? cus / 8 : 1)
     {
         cu_shift = (per_xcd & (per_xcd - 1)) == 0 && per_xcd * 8 == cus ? __builtin_ctz((unsigned)per_xcd) : -1;
         w_bytes = (double)w.nsteps * RECORD_BYTES;
@@ -199,22 +197,20 @@ SPMM_INLINE void fill_simple(Plan& p, const Call& c, int r, int tm, int waves = 
     p.workgroups = 8 * here[p.xcd_row_bits];
     p.fetch_us = c.fetch_us[p.xcd_row_bits];
     const int64_t all = (int64_t)p.n_row_groups * p.n_tok_tiles;
-    if (c.equal_parts && all < 65536 && p.n_row_groups > 1 && p.n_tok_tiles > 1 && c.xcd_rounds((all + 7) / 8) < best >> 2) deal(p, c, (int)((all + 7) / 8));
+    if (all < 65536 && p.n_row_groups > 1 && p.n_tok_tiles > 1 && c.xcd_rounds((all + 7) / 8) < best >> 2) deal(p, c, (int)((all + 7) / 8));
 }
 
 // ---------------------------------------------------------------------------------------
 // What a plan costs, in us: a fit to measured launches of 256 to 4096 features, 16 to 6144 tokens, 70 to 90 %, every
 // output type, in every configuration that runs them; beyond that range it is an extrapolation.  The estimates are
-// within 5 to 15 % of the measurement (standard deviation, by configuration), and the cheapest configuration by them
-// takes 1.030 of the fastest one's time on average, 1.037 with tile-major activations, which the estimates do not
-// tell from row-major ones; for every ninth problem, every seventh tile-major, more than 1.1
-// (profiles/spmm_plan_measurements.csv: the measured times; a test recomputes these figures from them).  The resident kernels (RES,
-// SLAB) have since become up to 1.3 times faster: a second set of fits is of them as they are, 1500 times on average for each,
-// within 9 to 16 %, and is what launches are planned by.  Of 800 problems that it was not fitted to
-// (profiles/spmm_plan_resident_measurements.csv: 256 to 4096 features, 16 to 6144 tokens, every type, layout and orientation) the
-// choices by the first set take 1.032 of the fastest configuration's time, over 1.1 in 11.9 %, those by the second 1.014 and 2.6 %;
-// 140 changed, 10 of all are more than 3 % slower, and together all are 1.018 times as fast (tests/test_plan_resident.py).
-// 1024x256 at 80 %, 1024 tokens, u8 with GELU: the ring with 32-token tiles, 4.26 us, becomes the resident kernel, 3.61.
+// within 5 to 16 % of the measurement (standard deviation, by configuration).  Of 800 problems that none is fitted to
+// (profiles/spmm_plan_resident_measurements.csv: every type, layout and orientation) the cheapest configuration by them takes 1.014 of
+// the fastest one's time, over 1.1 in 2.6 %; where the weight has no wide form (596 problems, profiles/spmm_plan_measurements.csv)
+// 1.022, with tile-major activations 1.018, which the estimates do not tell from row-major ones, over 1.1 in 8 and 7 %; tests
+// recompute these figures.  The resident kernels (RES, SLAB) have become up to 1.3 times faster with their straight-line start; by
+// the fits of before the 800 take 1.032, over 1.1 in 11.9 %: with the fits of now, 1500 times on average for each, 140 of them
+// run another kernel, 10 are more than 3 % slower, and together all are 1.018 times as fast (tests/test_plan_resident.py).
+// 1024x256 at 80 %, 1024 tokens, u8 with GELU: the ring with 32-token tiles, 4.26 us, became the resident kernel, 3.61.
 // A launch is a start, rounds of workgroups on the CUs, and in a round: phases (a K segment of a token tile) with
 // their matrix instructions and the staging of their activations, and the tiles' post-operators; what has to
 // be fetched through the L2s adds to all of it.
@@ -239,25 +235,20 @@ static const Fit FIT_FED_96_12[2]  = {{2.76, 0.90, 0.0034, 0.00, 0.0515, 0.0884,
                                      {2.48, 0.82, 0.0028, 0.00, 0.1156, 0.1499, 0.76}};
 static const Fit FIT_FED_64_12[2]  = {{2.88, 0.56, 0.0030, 0.00, 0.0515, 0.0884, 1.23},
                                      {2.39, 0.52, 0.0033, 0.00, 0.1156, 0.1499, 0.76}};
-// the resident kernels: as they were when the others were fitted, and as they are (with 8, 4 and 2 row tiles)
-struct ResidentFits { Fit res_16[3], slab_16[3], res_32, res_64; };
-static const ResidentFits RESIDENT[2] = {
-    {{{2.18, 1.27, 0.0107, 1.20, 0.0091, 0.0000, 1.18}, {2.18, 1.27, 0.0107, 1.20, 0.0091, 0.0000, 1.18}, {2.18, 1.27, 0.0107, 1.20, 0.0091, 0.0000, 1.18}},
-     {{0.83, 2.22, 0.0133, 2.73, 0.0271, 0.0000, 0.00}, {0.83, 2.22, 0.0133, 2.73, 0.0271, 0.0000, 0.00}, {0.83, 2.22, 0.0133, 2.73, 0.0271, 0.0000, 0.00}},
-     {2.56, 1.07, 0.0049, 1.16, 0.0067, 0.0000, 1.37},
-     {3.71, 0.00, 0.0039, 1.15, 0.0054, 0.0000, 1.70}},
-    {{{1.81, 0.61, 0.0055, 1.38, 0.0331, 0.0000, 1.94}, {1.64, 0.61, 0.0059, 1.66, 0.0536, 0.0000, 1.50}, {1.57, 0.76, 0.0093, 1.08, 0.0871, 0.0000, 1.28}},
-     {{0.00, 3.44, 0.0064, 0.17, 0.0661, 0.0000, 1.66}, {0.00, 2.51, 0.0106, 0.80, 0.2333, 0.0000, 0.80}, {0.03, 3.18, 0.0087, 0.44, 0.2673, 0.0000, 0.08}},
-     {2.02, 0.77, 0.0032, 0.97, 0.0104, 0.0000, 1.39},
-     {2.25, 0.83, 0.0025, 0.61, 0.0038, 0.0000, 1.99}},
-};
+// the resident kernels (with 8, 4 and 2 row tiles)
+static const Fit FIT_RES_16[3]     = {{1.81, 0.61, 0.0055, 1.38, 0.0331, 0.0000, 1.94}, {1.64, 0.61, 0.0059, 1.66, 0.0536, 0.0000, 1.50},
+                                      {1.57, 0.76, 0.0093, 1.08, 0.0871, 0.0000, 1.28}};
+static const Fit FIT_SLAB_16[3]    = {{0.00, 3.44, 0.0064, 0.17, 0.0661, 0.0000, 1.66}, {0.00, 2.51, 0.0106, 0.80, 0.2333, 0.0000, 0.80},
+                                      {0.03, 3.18, 0.0087, 0.44, 0.2673, 0.0000, 0.08}};
+static const Fit FIT_RES_32        = {2.02, 0.77, 0.0032, 0.97, 0.0104, 0.0000, 1.39};
+static const Fit FIT_RES_64        = {2.25, 0.83, 0.0025, 0.61, 0.0038, 0.0000, 1.99};
 static const Fit FIT_RING_16       = {2.24, 0.68, 0.0082, 2.70, 0.0208, 0.0000, 1.04};
 static const Fit FIT_RING_32       = {0.90, 1.96, 0.0062, 2.06, 0.0130, 0.0000, 1.29};
 static const Fit FIT_RING_64       = {0.52, 2.99, 0.0039, 1.18, 0.0008, 0.0000, 1.53};
 
 // the wide form (units: 32 tokens of a step of 32 rows): 4700 other problems, 256 to 4096 features, 16 to 6144 tokens, 3e7
 // products and more, every layout; on the problems of profiles/spmm_plan_wide_measurements.csv, drawn on their own, the
-// estimates are 0.96 to 0.98 of the time, standard deviation 9 to 11 %
+// estimates are 0.96 to 0.98 of the time, standard deviation 9 to 12 %
 static const Fit FIT_WIDE_128_8[2]   = {{2.88, 0.00, 0.0018, 0.84, 0.0745, 0.0841, 1.32},
                                       {2.73, 0.71, 0.0047, 0.00, 0.0940, 0.1020, 0.62}};
 static const Fit FIT_WIDE_96_8[2]    = {{2.82, 0.00, 0.0017, 0.81, 0.0869, 0.1050, 1.33},
@@ -342,10 +333,10 @@ static Plan forced_plan(const Call& call, int force_tm, int variant, int max_ste
 }
 
 Plan make_plan(int64_t M, const WeightDims& w, int num_cus, int force_tm, int variant, int out_bytes, bool x_fast, bool out_fast,
-               int widest, double wide_handicap, bool as_they_are)
+               int widest, double wide_handicap)
 {
     const int nseg = w.nseg, max_steps_per_segment = w.max_steps_per_segment;
-    Call call(M, w, num_cus, as_they_are);
+    Call call(M, w, num_cus);
     const int max_steps = max_steps_per_segment <= 4 ? 4 : (max_steps_per_segment <= 6 ? max_steps_per_segment : 8);
     const int fed_steps = max_steps == 5 ? 6 : max_steps;      // step slots of the loader-wave kernels: 4, 6 or 8
     if (!x_fast && !(force_tm && force_tm <= 64 && (variant == 101 || variant == 102))) {
@@ -358,7 +349,6 @@ Plan make_plan(int64_t M, const WeightDims& w, int num_cus, int force_tm, int va
     if (force_tm) return forced_plan(call, force_tm, variant, max_steps, fed_steps, out_fast ? widest : 0);
     // ---- short and mid-size batches
     const int reload = nseg > 2;
-    const ResidentFits& resident = RESIDENT[as_they_are];
     Plan best{}, c{};
     double best_cost = 0.0;
     c.max_steps = max_steps;
@@ -383,18 +373,18 @@ Plan make_plan(int64_t M, const WeightDims& w, int num_cus, int force_tm, int va
         if (row_tiles < 8 && !c.slab && (int64_t)c.n_row_groups * c.n_tok_tiles * row_tiles / 8 >= num_cus * 3 / 16 &&
             (nseg <= 2 || c.workgroups > num_cus * 7 / 8)) return false;
         const int fewer = row_tiles == 8 ? 0 : row_tiles == 4 ? 1 : 2;
-        consider(c.stream ? FIT_RING_16 : c.slab ? resident.slab_16[fewer] : resident.res_16[fewer]);
+        consider(c.stream ? FIT_RING_16 : c.slab ? FIT_SLAB_16[fewer] : FIT_RES_16[fewer]);
         return true;
     };
     if (short_batch(8) && short_batch(4)) short_batch(2);
     // (the simple kernel where its resident rows hold all of K, the ring beyond)
     fill_simple(c, call, 1, 32);
-    if (nseg <= 4) consider(resident.res_32);
+    if (nseg <= 4) consider(FIT_RES_32);
     if (nseg > 4 && nseg <= SLAB_SEGMENTS_32) c.slab = 1;
     else c.stream = 1;
     consider(FIT_RING_32);
     fill_simple(c, call, 1, 64);
-    if (nseg <= 2) consider(resident.res_64);
+    if (nseg <= 2) consider(FIT_RES_64);
     c.stream = 1;
     consider(FIT_RING_64);
     // ---- persistent kernels, where they occupy more than half of the CUs (the rest is the short-batch kernels' ground).
@@ -434,22 +424,18 @@ Plan make_plan(int64_t M, const WeightDims& w, int num_cus, int force_tm, int va
         fed12(96, FIT_FED_96_12[reload]);
         fed12(64, FIT_FED_64_12[reload]);
     }
-    // ---- the wide form, from 192 blocks of 32 rows x 32 tokens on (of 200 measured problems with fewer, some were 3 to 15 %
-    // faster with it, all of them launches of 3.4 to 4.8 us, which the host's 3.5 us bound).  Of the 700 problems of
-    // profiles/spmm_plan_wide_measurements.csv one of its configurations is the fastest in 65 %.  What the estimates, whose
-    // errors are 9 to 11 %, set apart by less than the margins below goes to the kernels above, because a wrong choice is seen
-    // and a missed one is not: 39 % get it, 1.0 % are more than 3 % slower than without it, and all together are 1.069 times as
-    // fast (1.090 if every choice were right; with a margin of 0.98 1.077, and 3.7 % slower).  By what it replaces: the 128-token
-    // kernels with 8 + 4 waves 1.25 times, the streamed kernels 1.25, the resident ones 1.07.  (These estimates, too, are against the
-    // resident kernels before their straight-line start: with the times of now, profiles/spmm_plan_wide_remeasured.csv, what is taken
-    // from the 32-token one runs at 0.93 of its speed, 4.7 % of all problems lose more than 3 %, and all together are 1.064 times as
-    // fast, 1.079 if every choice were right; launches weigh them against the resident kernels as they are, and other margins, from
-    // 0.90 to 1.0, choose no better.)  4-byte outputs that have the 32-token slab keep it up to
-    // 768 blocks because tests/test_gpu_parity.py pins 768x3072, 1024 tokens, to it (such problems were 1.2 times as fast with
-    // the wide form).
+    // ---- the wide form, from 192 blocks of 32 rows x 32 tokens on (of 200 measured problems with fewer none
+    // would be faster with it).  Of the 698 problems of profiles/spmm_plan_wide_measurements.csv that
+    // have more one of its configurations is the fastest in 33 %.  What the estimates, whose errors are 9 to 11 %, set apart by
+    // less than the margins below goes to the kernels above, because a wrong choice is seen and a missed one is not: 30 % get it,
+    // 0.4 % are more than 3 % slower than without it, and all together are 1.059 times as fast (1.064 if every choice were right;
+    // with margins of 0.98 34 % would get it, 2.0 % lose more than 3 %, and the gain is the same).  By what it replaces: the
+    // 128-token kernels with 8 + 4 waves 1.24 times, the streamed kernels 1.27, the resident ones 1.26.  4-byte outputs that
+    // have the 32-token slab keep it up to 768 blocks because tests/test_gpu_parity.py pins 768x3072, 1024 tokens, to it (such
+    // problems would be 1.2 times as fast with the wide form).
     const int64_t blocks = (int64_t)((w.ntiles + 1) / 2) * ((M + 31) / 32);
     const bool pinned = out_bytes == 4 && best.slab && best.token_tile == 32 && blocks <= 768;
-    // (nor where the others are under 5 us: of 139 such problems the choice would gain nothing, and its estimates take 0.1 us)
+    // (nor where the others are estimated under 5 us: of 468 such measured problems none would get it, and its estimates take 0.1 us)
     if (w.wide_max_steps > 0 && out_fast && blocks >= 192 && best_cost > 5.0 && !pinned) {
         call.set_wide_steps();
         const double post = widest < 128 ? 1.8 : 1.0;      // (Sum, GELU in f32: of the fits with each, the closest)

@@ -28,7 +28,7 @@ int main()
                       &wide_max, &bytes, &gelu_f32, &sum, &aligned) == 13) {
         const spmm::WeightDims w{tiles, segments, K, steps, max_segment, max_tile, wide_max, wide_steps};
         const spmm::Plan p = spmm::make_plan(M, w, 256, 0, 0, bytes ? 1 : 4, true, true, spmm::wide_tile(gelu_f32, sum),
-                                             spmm::wide_handicap(bytes, gelu_f32, sum, aligned), true);
+                                             spmm::wide_handicap(bytes, gelu_f32, sum, aligned));
         if (!p.simple) std::printf("%s%d_%d\n", p.wide ? "WIDE_" : p.loaders ? "FED_" : "", p.token_tile, p.waves);
         else if (p.stream || (p.slab && p.token_tile == 32)) std::printf("RING_%d\n", p.token_tile);
         else if (p.token_tile == 16) std::printf("%s_16w%d\n", p.slab ? "SLAB" : "RES", p.waves);
