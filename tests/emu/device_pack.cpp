@@ -1,7 +1,12 @@
-// Driver of tests/test_device_pack.py: the forms that the device makes (its kernels on the CPU, see include/hip/hip_runtime.h)
-// against the host's, byte for byte.  usage: device_pack N K percent n4k1|n1k4 jitter
+// Of tests/test_device_pack.py: the forms that the device makes, read back, against the host's, byte for byte.  Two builds of it: a
+// driver with the kernels on the CPU (see include/hip/hip_runtime.h), usage: device_pack N K percent n4k1|n1k4 jitter; and a shared
+// object beside the product library, which is called where there is a GPU.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
 #include <vector>
 
 #include "spmm_internal.h"
@@ -9,12 +14,9 @@
 
 using namespace spmm;
 
-int main(int argc, char** argv)
+// 0: the same bytes
+extern "C" int device_pack_bytes(int64_t N, int64_t K, int percent, int n4, int jitter, int64_t* wide_size, int64_t* nsteps)
 {
-    if (argc != 6) return 2;
-    const int64_t N = atoll(argv[1]), K = atoll(argv[2]);
-    const int percent = atoi(argv[3]), jitter = atoi(argv[5]);
-    const bool n4 = argv[4][1] == '4';
     uint32_t seed = 12345u + (uint32_t)(N * 31 + K);
     auto random = [&](uint32_t n) { return (uint32_t)((uint64_t)(seed = seed * 1664525u + 1013904223u) * n >> 32); };
     std::vector<int8_t> W((size_t)(N * K), 0);
@@ -43,8 +45,22 @@ int main(int argc, char** argv)
         hl.max_steps_per_segment != hl2.max_steps_per_segment || hl.nseg != hl2.nseg || hl.ntiles != hl2.ntiles || hl.kc != hl2.kc) return 5;
     if (f.size != f2.size || f.wide_size != f2.wide_size || f.tile_steps != f2.tile_steps || f.wide_tile_steps != f2.wide_tile_steps ||
         f.wide_max_steps != f2.wide_max_steps || f.wide_nsteps != f2.wide_nsteps) return 6;
-    if (std::memcmp(weight, f.bytes.get(), (size_t)f.size)) return 7;
-    if (f.wide_size && std::memcmp(weight + f2.size, f.wide_bytes(), (size_t)f.wide_size)) return 8;
+    std::vector<uint8_t> back((size_t)(f2.size + f2.wide_size));
+    const hipError_t e = hipMemcpy(back.data(), weight, back.size(), hipMemcpyDeviceToHost);
     (void)hipFree(weight);
-    std::printf("ok %lld %lld\n", (long long)f.wide_size, (long long)hl.nsteps);
+    if (e != hipSuccess) return 9;
+    if (std::memcmp(back.data(), f.bytes.get(), (size_t)f.size)) return 7;
+    if (f.wide_size && std::memcmp(back.data() + f2.size, f.wide_bytes(), (size_t)f.wide_size)) return 8;
+    *wide_size = f.wide_size;
+    *nsteps = hl.nsteps;
+    return 0;
+}
+
+int main(int argc, char** argv)
+{
+    if (argc != 6) return 2;
+    int64_t wide_size = 0, nsteps = 0;
+    const int rc = device_pack_bytes(atoll(argv[1]), atoll(argv[2]), atoi(argv[3]), argv[4][1] == '4', atoi(argv[5]), &wide_size, &nsteps);
+    if (!rc) std::printf("ok %lld %lld\n", (long long)wide_size, (long long)nsteps);
+    return rc;
 }

@@ -1,5 +1,7 @@
 """Large weights' device forms are made on the device: the same bytes as the host's, and what a pack does when memory is short."""
+import ctypes
 import os
+import shutil
 import subprocess
 import sys
 
@@ -31,14 +33,39 @@ def driver(tmp_path_factory):
 
 # percent of the blocks kept; the wide form: made without a step more than the lists ask for, with more, with left-over k and
 # exchanges (n1k4 at 20 %), not at all (too many steps)
-@emulated
-@pytest.mark.parametrize("N,K,percent,block,jitter", [
+CASES = [
     (1, 1, 100, "n4k1", 0), (33, 513, 30, "n4k1", 0), (64, 512, 20, "n4k1", 20), (95, 1100, 10, "n4k1", 5), (130, 1537, 30, "n4k1", 0),
     (32, 511, 100, "n4k1", 0), (50, 700, 0, "n4k1", 0), (48, 640, 0, "n4k1", 2), (17, 5000, 25, "n4k1", 0), (31, 600, 45, "n4k1", 0),
-    (96, 512, 10, "n1k4", 0), (47, 777, 20, "n1k4", 10), (64, 1024, 25, "n1k4", 0), (33, 515, 40, "n1k4", 0), (70, 514, 2, "n1k4", 2)])
+    (96, 512, 10, "n1k4", 0), (47, 777, 20, "n1k4", 10), (64, 1024, 25, "n1k4", 0), (33, 515, 40, "n1k4", 0), (70, 514, 2, "n1k4", 2)]
+
+
+@emulated
+@pytest.mark.parametrize("N,K,percent,block,jitter", CASES)
 def test_the_device_makes_the_bytes_that_the_host_does(driver, N, K, percent, block, jitter):
     r = subprocess.run([driver, str(N), str(K), str(percent), block, str(jitter)], capture_output=True, text=True, timeout=300)
     assert r.returncode == 0 and r.stdout.startswith("ok"), (r.returncode, r.stdout[-300:], r.stderr[-1000:])
+
+
+@pytest.fixture(scope="module")
+def bytes_on_the_device(tmp_path_factory):
+    """The same comparison beside the product library, whose kernels make the forms on the GPU."""
+    cxx, out, product = shutil.which("g++") or build_emu.CXX, str(tmp_path_factory.mktemp("device_pack") / "bytes.so"), sp.binding.LIB_PATH
+    sp.lib()
+    subprocess.run([cxx, "-std=c++17", "-O1", "-w", "-shared", "-fPIC", "-pthread", "-D__HIP_PLATFORM_AMD__", "-I", os.path.join(ROOT, "include"), "-I",
+                    os.path.join(ROOT, "paper_2306_16601_amd", "csrc"), "-I", "/opt/rocm/include", os.path.join(HERE, "emu", "device_pack.cpp"),
+                    product, "-Wl,--allow-shlib-undefined", "-Wl,-rpath," + os.path.dirname(product), "-o", out], check=True)
+    return ctypes.CDLL(out).device_pack_bytes
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("N,K,percent,block,jitter", CASES + [(1024, 4096, 20, "n4k1", 0), (1033, 1021, 30, "n4k1", 20), (1100, 1000, 0, "n4k1", 0),
+                                                              (1024, 1025, 10, "n1k4", 5), (2000, 700, 25, "n1k4", 10), (70000, 16, 30, "n4k1", 0)])
+def test_the_gpu_makes_the_bytes_that_the_host_does(bytes_on_the_device, N, K, percent, block, jitter):
+    import torch
+    torch.cuda.init()
+    wide_size, steps = ctypes.c_int64(-1), ctypes.c_int64(-1)
+    rc = bytes_on_the_device(ctypes.c_int64(N), ctypes.c_int64(K), percent, block == "n4k1", jitter, ctypes.byref(wide_size), ctypes.byref(steps))
+    assert rc == 0 and wide_size.value >= 0 and steps.value >= 0, rc
 
 
 @emulated
