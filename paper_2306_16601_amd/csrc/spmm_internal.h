@@ -174,7 +174,7 @@ public:
     int finish(HostLayout& hl, DeviceForms& f, uint8_t** weight);
 
 private:
-    void give_back();
+    int give_back();
     uint8_t* scratch_ = nullptr;
     int64_t N_ = 0, K_ = 0, nseg_ = 0, ntiles_ = 0, nt_ = 0, info_at_ = 0, slots_at_ = 0, wide_slots_at_ = 0, heads_at_ = 0;
     int error_ = 0;

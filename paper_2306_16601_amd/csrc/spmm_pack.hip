@@ -460,14 +460,17 @@ constexpr int64_t up(int64_t bytes) { return (bytes + 255) & ~(int64_t)255; }
 
 }  // namespace
 
-DevicePack::~DevicePack() { give_back(); }
+DevicePack::~DevicePack() { (void)give_back(); }
 
 // (hipFree waits for all streams of the device, also for those that the default stream does not wait for: 45 ms of a program's other
-// work were in the pack.  In the default stream's order the memory goes back when that stream is done, as the pool keeps none of it.)
-void DevicePack::give_back()
+// work were in the pack.  Freed in the default stream's order the memory goes back when that stream has been waited for: until then
+// the pool keeps it, as large as the weight.)
+int DevicePack::give_back()
 {
-    if (scratch_) (void)hipFreeAsync(scratch_, nullptr);
+    if (!scratch_) return hipSuccess;
+    (void)hipFreeAsync(scratch_, nullptr);
     scratch_ = nullptr;
+    return hipStreamSynchronize(nullptr);
 }
 
 bool DevicePack::reserve(int64_t N, int64_t K, spmm_block_t block)
@@ -537,10 +540,10 @@ int DevicePack::finish(HostLayout& hl, DeviceForms& f, uint8_t** weight)
             a.wide_tile_steps = f.wide_tile_steps;
             a.n4 = n4_;
             e = launch(spmm_pack_records, nt_, nseg_, a);
-            if (e == hipSuccess) e = hipStreamSynchronize(nullptr);        // (the weight is there for every stream when the call returns)
         }
     }
-    give_back();
+    const hipError_t done = (hipError_t)give_back();        // (and the weight is there for every stream when the call returns)
+    if (e == hipSuccess) e = done;
     if (e != hipSuccess) {
         if (*weight) (void)hipFree(*weight);        // (the host may pack instead, into an allocation of its own)
         *weight = nullptr;

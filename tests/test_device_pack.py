@@ -148,3 +148,18 @@ def test_a_pack_does_not_wait_for_other_streams():
         assert under_way and np.array_equal(sp.spmm_unpack(h), W)
     finally:
         sp.spmm_destroy(h)
+
+
+@pytest.mark.gpu
+def test_a_pack_keeps_no_scratch():
+    """What is gone from the device's free memory when the call returns are the forms (in pages of up to 2 MB, an allocation each)."""
+    import torch
+    W = np.where(np.random.default_rng(2).random((4096, 4096)) < 0.05, 5, 0).astype(np.int8)
+    sp.spmm_destroy(sp.spmm_pack(W))
+    torch.cuda.synchronize()
+    before = torch.cuda.mem_get_info()[0]
+    h = sp.spmm_pack(W)
+    try:
+        assert before - torch.cuda.mem_get_info()[0] <= sp.spmm_info(h)[4] + 4 * 2 ** 20
+    finally:
+        sp.spmm_destroy(h)
