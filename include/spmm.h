@@ -104,7 +104,7 @@ typedef struct {
  * 1.9 at most); SPMM_E_ALLOC is for the first.
  * The call uses the default stream and has waited for it, and for no other, when it returns.  From 2^20 elements on (rows back
  * to back, no reordering) the forms are made on the device, which takes about N * (K + 101 * ceil(K / 512) + 9) bytes there until
- * the call returns; where they cannot be had, the host makes them, in two to three times the time.
+ * the call returns; where they cannot be had, the host makes them, which takes two to four times as long.
  * Errors: SPMM_E_ARG, SPMM_E_UNSUPPORTED, SPMM_E_ALLOC, SPMM_E_DEVICE. */
 spmm_status_t spmm_pack(const int8_t *W_host, int64_t N, int64_t K, int64_t ldw,
                         spmm_block_t block, spmm_handle_t **out_handle);
@@ -165,7 +165,9 @@ spmm_status_t spmm_layout_dims(const spmm_handle_t *h, int32_t *tile_rows, int32
  *                                           order chosen for LDS banking; padding slots
  *                                           have zero weights and a valid row index
  *   seg_ptr int32 [n_tiles*n_segments + 1] first step of (tile, segment), CSR style
- *   rowsum  int32 [n_tiles*tile_rows]      sum over k of each (padded) row of W */
+ *   rowsum  int32 [n_tiles*tile_rows]      sum over k of each (padded) row of W
+ * No HIP call is made: vals and idx of a weight whose forms the device made (spmm_pack) are made again on the host.
+ * Errors: SPMM_E_ARG, SPMM_E_ALLOC. */
 spmm_status_t spmm_layout_export(const spmm_handle_t *h, uint8_t *vals_host, uint32_t *idx_host,
                                  int32_t *seg_ptr_host, int32_t *rowsum_host);
 

@@ -82,8 +82,10 @@ hipError_t upload_forms(spmm_handle* h)
 }
 
 // From so many elements on, the device makes its forms itself (DevicePack).  Pack on the host and so, us: 256x256 at 80 % 59 and 90,
-// 512x512 259 and 225, 1024x1024 500 and 290, 4096x4096 6100 and 1760.  The line is where the scratch memory on the device, as large
-// as the weight and a quarter more, is worth it for sure: below it a pack needs no more memory there than the forms.
+// 512x512 259 and 225, 1024x1024 340 and 200, 4096x4096 3600 and 980.  The line is where the scratch memory on the device is worth it
+// for sure: below it a pack needs no more memory there than the forms.  (N * (K + 101 * ceil(K / 512) + 9) bytes: 1.2 times the
+// weight where K fills its segments; slots are kept for 512 k however few there are, so 2.7 times with K = 64, where both forms
+// are 2.0 times, and 111 with K = 1, 99 times; 16384x64 at 80 % 500 and 260 us, 65536x16 1200 and 370, 2^20 x 1 14.8 and 6.2 ms.)
 constexpr int64_t DEVICE_PACK_MIN = (int64_t)1 << 20;
 
 bool aligned(const void* p, size_t a) { return (reinterpret_cast<uintptr_t>(p) % a) == 0; }

@@ -5,9 +5,9 @@
 // weight is on the device in a fifth of the time in which 8 threads make the forms of it, and a workgroup per (32 rows, 512 k)
 // needs nothing else.  So the canonical form is made by the host's threads while the weight is on its way and its lists are dealt
 // to slots (spmm_pack_lists); the numbers of steps come back, which say where every record goes, and they are written there
-// (spmm_pack_records).  1024x4096 at 80 %, packed, unpacked and released: 1233 -> 604 us; the pack alone 1570 -> 690 in a program of
-// its own, of which the copy 135, the lists 45 (one wave's chain of 450 slots, at 0.1 us each), the records 17; 4096x4096 at 70 %
-// 6100 -> 1760.
+// (spmm_pack_records).  1024x4096 at 80 %: the pack 800 to 870 -> 350 us, of which the copy 135, the lists 45 (one wave's chain of 450
+// slots, at 0.1 us each), the records 17; packed, unpacked and released 1.22 to 1.36 -> 0.58 to 0.63 ms (machines differ);
+// 4096x4096 at 70 % 3.6 -> 0.98 ms, 1x4 blocks of 4096x1024 at 90 % 1.37 -> 0.39.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
