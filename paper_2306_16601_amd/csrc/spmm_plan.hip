@@ -156,8 +156,12 @@ SPMM_INLINE void fill_wide(Plan& p, const Call& c, int tm, int waves)
 // worth more than what the slices save: of 67 random problems of 256 to 4096 features, 32 to 1250 tokens, 70 to 90 %, where it
 // saves one (profiles/spmm_plan_equal_parts.csv), no kernel is slower; two rounds of the resident kernels become one of 0.76 of the
 // time (with one K segment, where two workgroups share a CU, 0.89), two of the ring one of 0.66, three and more 0.85.  What the plan
-// then chooses takes 0.957 of the time that its choice by slices takes: 24 are more than 3 % faster, two slower, as the estimates
-// favour a dealt slab by more than it gains (1300x2600 at 80 %, 346 tokens 8.0 -> 8.7; 2304x4096 at 85 %, 217 tokens 9.7 -> 10.2).
+// then chooses takes 0.957 of the time that its choice by slices takes: 24 are more than 3 % faster, two slower.  Those two go from the
+// wide form to a dealt slab (1300x2600 at 80 %, 346 tokens 8.0 -> 8.7), and the estimates of both are 10 to 60 % off there: of 113
+// further problems of five to eight segments whose choice dealing changes (profiles/spmm_plan_equal_parts_slabs.csv) the choices take
+// 0.93 of the time, 71 more than 3 % less, ten more than 3 % longer (2656x4096 at 70 %, 188 tokens, int32 10.1 -> 11.6, the others to
+// 6 %).  Nothing that the plan knows tells those ten apart: without dealing from the wide form to slabs 30 would lose 6 % on average
+// to save four of them, without dealing workgroups of 2 row tiles 33 would lose 3 % to save five.
 // 768x3072 at 80 %, 333 tokens with Sum, binary32, 12 row groups x 21 token tiles: 12.2 -> 8.1 us, and as 6 x 21, which it ran as
 // before, 9.2; 1300x650 at 80 %, 665 tokens 5.6 -> 4.8.
 static void deal(Plan& p, const Call& c, int each)
