@@ -102,9 +102,10 @@ typedef struct {
  * 80 %: 3.1 + 2.8 MB; 4096x4096 at 70 %: 16.5 + 12.6 MB).  Where memory for the second cannot be had, the weight is
  * packed without it: same results, the batches that would take it 1.2 times slower in the median (of 275 measured,
  * 1.9 at most); SPMM_E_ALLOC is for the first.
- * The call uses the default stream and has waited for it, and for no other, when it returns.  From 2^20 elements on (rows back
- * to back, no reordering) the forms are made on the device, which takes about N * (K + 101 * ceil(K / 512) + 9) bytes there until
- * the call returns; where they cannot be had, the host makes them, which takes two to four times as long.
+ * The call uses the default stream and has waited for it when it returns, and so for streams that the default stream waits
+ * for, but for none made with hipStreamNonBlocking.  From 2^20 elements on (rows back to back, no reordering) the forms are made
+ * on the device, which takes about N * (K + 101 * ceil(K / 512) + 9) bytes there until the call returns; where they cannot be
+ * had, the host makes them, which takes two to four times as long.
  * Errors: SPMM_E_ARG, SPMM_E_UNSUPPORTED, SPMM_E_ALLOC, SPMM_E_DEVICE. */
 spmm_status_t spmm_pack(const int8_t *W_host, int64_t N, int64_t K, int64_t ldw,
                         spmm_block_t block, spmm_handle_t **out_handle);
