@@ -464,7 +464,8 @@ DevicePack::~DevicePack() { (void)give_back(); }
 
 // (hipFree waits for all streams of the device, also for those that the default stream does not wait for: 45 ms of a program's other
 // work were in the pack.  Freed in the default stream's order the memory goes back when that stream has been waited for: until then
-// the pool keeps it, as large as the weight.)
+// the pool keeps it, as large as the weight.  This takes up to 10 us more than hipFree: packed, unpacked and released, 1024x1024 at 80 %
+// 285 -> 295 us, 1024x4096 562 -> 567.)
 int DevicePack::give_back()
 {
     if (!scratch_) return hipSuccess;
